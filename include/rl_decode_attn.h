@@ -70,14 +70,16 @@ typedef enum { RLDA_F32 = 0, RLDA_BF16 = 1, RLDA_BF16_KV8 = 2 } rlda_dtype;
 
 /* Kernel selection. */
 typedef enum {
-  RLDA_ALGO_AUTO = 0,      /* shared-prefix MFMA path when the shape allows it, else SIMPLE.  The fast path
-                              takes bf16 q (bf16 or e4m3 K/V), d = 128, Hq/Hkv <= 16, G * Hq/Hkv <= 256,
-                              scale > 0 and, for a paged store, pages of at least 32 rows.  Everything
-                              else -- fp32, d = 64, other head ratios or scales, smaller pages -- runs on
-                              SIMPLE, which is an order of magnitude slower on large batches (1.04 ms
-                              against 0.11 ms on the 7B-shaped benchmark): rl_decode_attn_plan tells which
-                              one a descriptor gets. */
-  RLDA_ALGO_SIMPLE = 1,    /* one wavefront per (sequence, query head), no sharing, no split */
+  RLDA_ALGO_AUTO = 0,      /* shared-prefix MFMA path when the shape allows it: bf16 q (bf16 or e4m3 K/V), d = 128,
+                              Hq/Hkv <= 16, G * Hq/Hkv <= 256, scale > 0 and, for a paged store, pages of at
+                              least 32 rows.  Everything else -- fp32, d = 64, other head ratios or scales,
+                              smaller pages -- is planned as SIMPLE (no sharing across sequences, no scratch);
+                              under AUTO it then runs in a one-launch form of it on the matrix cores, one
+                              workgroup per (sequence, KV head), with 32-bit softmax weights as ever.  The same
+                              form takes batches of the shared-prefix path that are too small to fill the chip;
+                              their workspace is asked for and checked all the same. */
+  RLDA_ALGO_SIMPLE = 1,    /* one wavefront per (sequence, query head), no sharing, no split, no matrix cores: the
+                              plain reference on the GPU (forced, or where the stores are not 16-byte aligned) */
   RLDA_ALGO_SHARED = 2     /* force the shared-prefix path; RLDA_ERR_UNSUPPORTED if not possible */
 } rlda_algo;
 
@@ -105,7 +107,7 @@ typedef struct {
   int32_t  Hq, Hkv, d;         /* query heads, KV heads (Hq % Hkv == 0), head dim (64 or 128)    */
   int32_t  Lp_cap, Ls_cap;     /* row capacity of the prefix / suffix KV buffers (>= 0)          */
   float    scale;              /* multiplies <q,k> before the softmax; any finite value (the shared-prefix
-                                  path takes scale > 0 only, other values run on RLDA_ALGO_SIMPLE)    */
+                                  path takes scale > 0 only, other values are planned as RLDA_ALGO_SIMPLE) */
   const void*    q;            /* [B, Hq, d]                                                     */
   const void*    k_prefix;     /* [P, Hkv, Lp_cap, d]   (may be NULL if Lp_cap == 0)             */
   const void*    v_prefix;     /* [P, Hkv, Lp_cap, d]                                            */

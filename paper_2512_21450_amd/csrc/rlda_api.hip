@@ -132,7 +132,8 @@ int enqueue_tree(const rlda_tree_desc* desc, void* hip_stream) {
   const size_t need = rlda::shared_workspace_bytes(pb);
   if (!pb.workspace || pb.workspace_bytes < need) return RLDA_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(pb.workspace) & 255u) return RLDA_ERR_WORKSPACE;
-  const hipError_t e = rlda::launch_shared(pb, static_cast<hipStream_t>(hip_stream), nullptr);
+  const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  const hipError_t e = rlda::unit_preferred(pb) ? rlda::launch_unit(pb, false, stream) : rlda::launch_shared(pb, stream, nullptr);
   g_last_hip_error = e;
   return e == hipSuccess ? RLDA_OK : RLDA_ERR_LAUNCH;
 }
@@ -159,11 +160,18 @@ int enqueue(const Problem& pb, void* hip_stream, void* mid_event) {
     const size_t need = rlda::shared_workspace_bytes(pb);
     if (need > 0 && (!pb.workspace || pb.workspace_bytes < need)) return RLDA_ERR_WORKSPACE;
     if (need > 0 && (reinterpret_cast<uintptr_t>(pb.workspace) & 255u)) return RLDA_ERR_WORKSPACE;
-    e = rlda::launch_shared(pb, stream, static_cast<hipEvent_t>(mid_event));
+    if (pb.algo != RLDA_ALGO_AUTO || !rlda::unit_preferred(pb)) {
+      e = rlda::launch_shared(pb, stream, static_cast<hipEvent_t>(mid_event));
+      g_last_hip_error = e;
+      return e == hipSuccess ? RLDA_OK : RLDA_ERR_LAUNCH;
+    }
+    e = rlda::launch_unit(pb, false, stream);
+  } else if (pb.algo == RLDA_ALGO_AUTO && rlda::unit_supported(pb)) {
+    e = rlda::launch_unit(pb, true, stream);
   } else {
     e = rlda::launch_simple(pb, stream);
-    if (e == hipSuccess && mid_event) e = hipEventRecord(static_cast<hipEvent_t>(mid_event), stream);
   }
+  if (e == hipSuccess && mid_event) e = hipEventRecord(static_cast<hipEvent_t>(mid_event), stream);
   g_last_hip_error = e;
   return e == hipSuccess ? RLDA_OK : RLDA_ERR_LAUNCH;
 }

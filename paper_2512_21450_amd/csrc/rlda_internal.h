@@ -64,6 +64,12 @@ size_t shared_workspace_bytes(const Problem& pb);
 // `mid`, if not null, is recorded between the partial kernel and the combine kernel
 hipError_t launch_shared(const Problem& pb, hipStream_t stream, hipEvent_t mid);
 
+// ---- one workgroup per (sequence, KV head): all dtypes, d in {64, 128}, tree levels, pages of any size, any finite scale.
+// `exact`: softmax weights enter the value contraction with 24 bits, else (d = 128 only) with 16
+bool unit_supported(const Problem& pb);
+bool unit_preferred(const Problem& pb);          // a problem of the shared-prefix path that runs faster here
+hipError_t launch_unit(const Problem& pb, bool exact, hipStream_t stream);
+
 // ---- causal prefill attention over each prompt (bf16, d = 128, Hq/Hkv <= 16)
 bool prefill_supported(int dtype, int Hq, int Hkv, int d);
 hipError_t launch_prefill(const void* q, const void* k, const void* v, const int32_t* lens, float* out, float* lse,

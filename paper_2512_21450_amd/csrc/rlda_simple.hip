@@ -10,6 +10,7 @@
 // key n, the tile's max and sum are reduced across the wavefront (online
 // softmax), and for the value contraction lane c owns output columns c, c+64.
 #include "rlda_internal.h"
+#include "rlda_unit.h"
 
 namespace rlda {
 namespace {

@@ -1,0 +1,499 @@
+// Decode attention with one workgroup per unit: all keys of one (sequence, KV head) against its Hq/Hkv query rows,
+// one launch, no scratch.  Two uses:
+//   * what the shared-prefix kernels do not take (fp32 stores, d = 64, wider head ratios, scales that are not
+//     positive, pages under 32 rows).  Softmax weights and sums are held in 32 bits (EXACT below);
+//   * batches so small that two dependent launches cost more than reading the prefix once per sequence
+//     (unit_preferred).  Weights then enter the value contraction with 16 bits (the shared-prefix kernels: 8).
+//
+// The NW wavefronts of a workgroup take the unit's 32-key tiles in turn (tile t goes to wavefront t % NW) and keep
+// an online-softmax state each; the states meet in LDS at the end.  Tiles are numbered segment by segment (shared
+// levels, then the own suffix), so the order of additions depends on the lengths only.
+//
+// What bounds it: memory round trips.  A wavefront has the next tile on the way in registers while it computes on the
+// present one, which goes through its private part of LDS.  (K straight into the registers of the matrix operand, 16
+// rows to an instruction, saved that trip but took the address unit four times as long as whole rows do: 1.05 us per
+// 64 KB and compute unit.)
+// Samples of one prompt sit on one die, side by side in dispatch order, so that the prefix a group shares comes from
+// memory once and from that die's L2 for the other samples.
+//
+// Tile math as in the shared-prefix kernels: S^T = K Q^T, so that a lane's accumulators (one query row, 4 keys per
+// 16-key half) are the operand of O^T += V^T P^T.  A weight is split into two bf16 pieces, EXACT: three (24 bits),
+// each contracted with V on the matrix cores; fp32 stores use the fp32 matrix instruction.
+#pragma once
+
+#include "rlda_internal.h"
+#include "rlda_sched.h"
+
+#include <math.h>
+
+#include <mutex>
+#include <type_traits>
+
+namespace rlda {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int MAX_SEG = RLDA_MAX_TREE_LEVELS + 1;
+// keys shared by `group` consecutive sequences: stores [n, Hkv, cap, d], lens [n]
+struct Segment { const char* k; const char* v; const int32_t* lens; int group, cap; };
+
+struct UnitParams {
+  const char* q;
+  float* out; float* lse;
+  Segment seg[MAX_SEG];            // shared levels, then the own suffix (group 1), at index n_seg - 1
+  int n_seg;
+  int B, G, Hq, Hkv, r, RB;        // r = Hq / Hkv query rows in RB blocks of 16
+  int groups8;                     // (prompt, KV head) groups rounded up to the dies, 0: units in plain order
+  float c, c_lo;                   // |scale| * log2(e) and what its rounding left; 1 and 0 when the scale is 0
+  uint32_t qsign, qmask;           // q bits: & qmask (0 when the scale is 0), ^ qsign (a negative scale), per 16-bit half or word
+  const int32_t* table;            // paged suffix: [B, max_pages] page ids, else null
+  int page_shift, max_pages, n_pages;
+  const uint8_t* active;
+  const float* kscale; const float* vscale;
+};
+
+enum Kind { KV_BF16, KV_F8, KV_F32 };
+
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+#define RLDA_LDS(T, p) ((__attribute__((address_space(3))) T*)(p))
+// max without the quieting of operands that fmaxf needs (no score is NaN here, or the result is NaN either way)
+__device__ __forceinline__ float max_raw(float a, float b) {
+  uint32_t inf = 0x7f800000u;
+  asm("" : "+s"(inf));
+  return __builtin_amdgcn_fmed3f(a, b, __uint_as_float(inf));
+}
+// maximum over the four lanes (l, l ^ 16, l ^ 32, l ^ 48) that share a query row
+__device__ __forceinline__ float row_max(float t) {
+  typedef unsigned int u32p __attribute__((ext_vector_type(2)));
+  const u32p a = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+  t = max_raw(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const u32p b = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+  return max_raw(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ u32x2 e4m3x4_to_bf16(uint32_t w) {            // exact
+  const bf16x2 lo = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, false);
+  const bf16x2 hi = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, true);
+  return u32x2{*reinterpret_cast<const uint32_t*>(&lo), *reinterpret_cast<const uint32_t*>(&hi)};
+}
+__device__ __forceinline__ void e4m3x16_to_bf16(const u32x4& w, u32x4& lo, u32x4& hi) {
+  const u32x2 a = e4m3x4_to_bf16(w[0]), b = e4m3x4_to_bf16(w[1]), c = e4m3x4_to_bf16(w[2]), d = e4m3x4_to_bf16(w[3]);
+  lo = u32x4{a[0], a[1], b[0], b[1]};
+  hi = u32x4{c[0], c[1], d[0], d[1]};
+}
+__device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) { return *reinterpret_cast<const bf16x8*>(&v); }
+
+// Layout of one store type and head dimension.
+template <int KIND, int D>
+struct Lay {
+  static constexpr int EB = KIND == KV_F32 ? 4 : (KIND == KV_F8 ? 1 : 2);   // bytes per stored element
+  static constexpr int ROWB = D * EB;                  // a K/V row in the store
+  static constexpr int LB = KIND == KV_F32 ? 4 : 2;    // bytes per element in LDS (e4m3 is widened on the way)
+  static constexpr int LROWB = D * LB;
+  static constexpr int TILE = TK * LROWB;              // one K or V tile in LDS
+  static constexpr int NF = LROWB / 64;                // 16-byte fragments per lane of a row of q or K
+  static constexpr int CPR = ROWB / 16;                // 16-byte chunks of a store row
+  static constexpr int RPI = 64 / CPR;                 // tile rows per load instruction
+  static constexpr int NL = TK / RPI;                  // load instructions per tile
+  // xor pattern of the 16-byte chunks of K row `row` in LDS: a wavefront reads one chunk of 16 rows
+  __device__ static __forceinline__ int kswz(int row) { return LROWB == 128 ? (row >> 1) & 7 : row & 15; }
+  // the same for V: the transposing reads take 4 rows x 2 adjacent chunks
+  // per 16 lanes, the fp32 reads 4 rows (4 apart) x 64 bytes per wavefront; either then touches every bank once
+  __device__ static __forceinline__ int vswz(int row) {
+    if (KIND == KV_F32) return ((row >> 2) & 3) << 2;
+    return D == 128 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
+  }
+};
+
+// NSEG: segments per sequence (2, or MAX_SEG for a tree); ROWS: pages of fewer rows than a tile, every row is looked up
+template <int KIND, int D, bool EXACT, int NW, int NSEG, bool ROWS>
+__global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) unit_kernel(const UnitParams P) {
+  using L_ = Lay<KIND, D>;
+  constexpr int CT = D / 16;                           // 16-column tiles of O
+  constexpr int QE = KIND == KV_F32 ? 4 : 2;           // bytes per q element
+  constexpr int NQ = L_::NF;                           // 16-byte q fragments per lane
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ float wm[NW][16], wl[NW][16];
+  const int tid = threadIdx.x, lane = tid & 63, wv = uni(tid >> 6), m16 = lane & 15, g = lane >> 4;
+
+  // ---- which unit: sequence b, KV head j, row block rb
+  int b, j, rb;
+  if (P.groups8 > 0) {
+    const int xcd = blockIdx.x & 7, s = blockIdx.x >> 3, per = P.G * P.RB;
+    const int grp = (s / per) * 8 + xcd, in = s % per;
+    const int p = grp / P.Hkv;
+    j = grp - p * P.Hkv; b = p * P.G + in / P.RB; rb = in % P.RB;
+    if (b >= P.B) return;                              // groups are rounded up to the eight dies
+  } else {
+    const int u = blockIdx.x / P.RB;
+    rb = blockIdx.x - u * P.RB; b = u / P.Hkv; j = u - b * P.Hkv;
+  }
+  const int nr = min(16, P.r - 16 * rb), h0 = j * P.r + 16 * rb;
+  const bool live = !P.active || P.active[b] != 0;
+
+  // ---- tiles of the segments
+  int len[NSEG], first[NSEG], T = 0;
+#pragma unroll
+  for (int s = 0; s < NSEG; ++s) {
+    len[s] = 0; first[s] = T;
+    if (NSEG == 2 || s < P.n_seg) {
+      len[s] = live ? clampi(P.seg[s].lens[b / P.seg[s].group], 0, P.seg[s].cap) : 0;
+      T += ceil_div(len[s], TK);
+    }
+  }
+
+  struct Tile { const char* k; const char* v; int n0, last; };            // n0: 0, or (ROWS, suffix) the tile's first key + 1
+  auto tile_of = [&](int t) {
+    Tile x{nullptr, nullptr, 0, 0};
+#pragma unroll
+    for (int s = 0; s < NSEG; ++s) {
+      const bool own = NSEG == 2 ? s == 1 : s == P.n_seg - 1;
+      if ((NSEG == 2 || s < P.n_seg) && t >= first[s] && len[s] > 0) {
+        const int n0 = (t - first[s]) * TK;
+        size_t row = ((size_t)(b / P.seg[s].group) * P.Hkv + j) * P.seg[s].cap + n0;
+        x.last = min(TK, len[s] - n0) - 1;
+        x.n0 = 0;
+        if (own && P.table) {
+          if constexpr (ROWS) {
+            row = 0; x.n0 = n0 + 1;
+          } else {                                     // a tile lies in one page
+            const int pg = uni(clampi(P.table[(size_t)b * P.max_pages + (n0 >> P.page_shift)], 0, P.n_pages - 1));
+            row = (((size_t)pg * P.Hkv + j) << P.page_shift) + (n0 & ((1 << P.page_shift) - 1));
+          }
+        }
+        x.k = P.seg[s].k + row * L_::ROWB;
+        x.v = P.seg[s].v + row * L_::ROWB;
+      }
+    }
+    return x;
+  };
+  // address of byte `byte` of tile row `i`; rows past the length re-read the last real row
+  auto row_at = [&](const Tile& x, const char* base, int i, int byte) -> const char* {
+    const int n = min(i, x.last);
+    if constexpr (ROWS) {
+      if (x.n0 > 0) {
+        const int key = x.n0 - 1 + n;
+        const int pg = clampi(P.table[(size_t)b * P.max_pages + (key >> P.page_shift)], 0, P.n_pages - 1);
+        return base + ((((size_t)pg * P.Hkv + j) << P.page_shift) + (key & ((1 << P.page_shift) - 1))) * L_::ROWB + byte;
+      }
+    }
+    return base + (uint32_t)(n * L_::ROWB + byte);     // uniform base, 32-bit offset
+  };
+
+  char* const kst = lds + wv * 2 * L_::TILE;           // this wavefront's K tile and V tile in LDS
+  char* const vst = kst + L_::TILE;
+  const int lrow = lane / L_::CPR, chunk = lane % L_::CPR;
+  u32x4 kr[L_::NL], vr[L_::NL];
+  auto load = [&](const Tile& x, const char* base, u32x4 (&r)[L_::NL]) {     // every instruction takes whole rows
+#pragma unroll
+    for (int i = 0; i < L_::NL; ++i) r[i] = *reinterpret_cast<const u32x4*>(row_at(x, base, L_::RPI * i + lrow, 16 * chunk));
+  };
+  auto store = [&](char* st, const u32x4 (&r)[L_::NL], auto swz) {
+#pragma unroll
+    for (int i = 0; i < L_::NL; ++i) {
+      const int row = L_::RPI * i + lrow;
+      char* const dst = st + row * L_::LROWB;
+      if constexpr (KIND == KV_F8) {
+        u32x4 a, d;
+        e4m3x16_to_bf16(r[i], a, d);
+        *RLDA_LDS(u32x4, dst + (((2 * chunk) ^ swz(row)) << 4)) = a;
+        *RLDA_LDS(u32x4, dst + (((2 * chunk + 1) ^ swz(row)) << 4)) = d;
+      } else {
+        *RLDA_LDS(u32x4, dst + ((chunk ^ swz(row)) << 4)) = r[i];
+      }
+    }
+  };
+
+  const float ks = KIND == KV_F8 && P.kscale ? P.kscale[j] : 1.f;
+  const float c = P.c * ks;
+  const float c_lo = fmaf(P.c, ks, -c) + P.c_lo * ks;  // EXACT: a score up to 40 would feel the rounding of c
+  const float vfac = KIND == KV_F8 && P.vscale ? P.vscale[j] : 1.f;
+
+  f32x4 O[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) O[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+
+  Tile cur;
+  u32x4 qr[NQ];
+  auto step = [&](auto more, int t) {                  // more: tile t + NW follows
+    constexpr bool MORE = decltype(more)::value;
+    store(kst, kr, L_::kswz);
+    Tile nxt = cur;
+    if constexpr (MORE) { nxt = tile_of(t + NW); load(nxt, nxt.k, kr); }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+
+    // ---- scores of this lane's row (m16) for keys 4 g + x and 16 + 4 g + x
+    f32x4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < L_::NF; ++i) {
+      const int off = m16 * L_::LROWB + (((4 * i + g) ^ L_::kswz(m16)) << 4);     // the pattern repeats after 16 rows
+      const u32x4 k0 = *RLDA_LDS(const u32x4, kst + off), k1 = *RLDA_LDS(const u32x4, kst + off + 16 * L_::LROWB);
+      if constexpr (KIND != KV_F32) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(k0), as_bf16x8(qr[i]), s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(k1), as_bf16x8(qr[i]), s1, 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k0[x]), __uint_as_float(qr[i][x]), s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k1[x]), __uint_as_float(qr[i][x]), s1, 0, 0, 0);
+        }
+      }
+    }
+    const int nvalid = cur.last + 1;
+
+    // ---- online softmax in base 2; the factor c > 0 goes into the exponent's fma, and a row's reference maximum
+    // moves only when a tile exceeds it by 2^8 (fp32 holds the larger sums without loss)
+    float sv[8];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      sv[x] = 4 * g + x < nvalid ? s0[x] : -INFINITY;
+      sv[4 + x] = 16 + 4 * g + x < nvalid ? s1[x] : -INFINITY;
+    }
+    float tm = max_raw(max_raw(max_raw(sv[0], sv[1]), max_raw(sv[2], sv[3])),
+                       max_raw(max_raw(sv[4], sv[5]), max_raw(sv[6], sv[7])));
+    tm = row_max(tm);
+    const float mn = max_raw(m, tm * c);
+    if (__any(mn > m + 8.f)) {                         // a wavefront's first tile: -inf + 8 = -inf
+      const float al = __builtin_amdgcn_exp2f(m - mn);
+      l *= al;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) O[ct] *= al;
+      m = mn;
+    }
+    float p[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      const float e = fmaf(sv[x], c, -m);
+      p[x] = __builtin_amdgcn_exp2f(EXACT && sv[x] != -INFINITY ? fmaf(sv[x], c_lo, e) : e);
+      l += p[x];
+    }
+
+    store(vst, vr, L_::vswz);
+    if constexpr (MORE) load(nxt, nxt.v, vr);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+
+    // ---- O^T += V^T P^T
+    if constexpr (KIND == KV_F32) {
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int row = 4 * g + x;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          const int off = (((4 * ct + (m16 >> 2)) ^ L_::vswz(row)) << 4) + 4 * (m16 & 3);
+          const float v0 = *RLDA_LDS(const float, vst + row * L_::LROWB + off);
+          const float v1 = *RLDA_LDS(const float, vst + (row + 16) * L_::LROWB + off);   // the pattern repeats after 16 rows
+          O[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(v0, p[x], O[ct], 0, 0, 0);
+          O[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(v1, p[4 + x], O[ct], 0, 0, 0);
+        }
+      }
+    } else {
+      constexpr int NP = EXACT ? 3 : 2;                // bf16 pieces of a weight
+      bf16x8 pb[NP];
+      float rest[8];
+#pragma unroll
+      for (int x = 0; x < 8; ++x) rest[x] = p[x];
+#pragma unroll
+      for (int k = 0; k < NP; ++k)
+#pragma unroll
+        for (int x = 0; x < 8; x += 2) {
+          const bf16x2 pr = __builtin_convertvector(f32x2{rest[x], rest[x + 1]}, bf16x2);
+          pb[k][x] = pr[0]; pb[k][x + 1] = pr[1];
+          if (k + 1 < NP) {                            // exact: what the piece leaves has fewer bits
+            rest[x] -= static_cast<float>(pr[0]);
+            rest[x + 1] -= static_cast<float>(pr[1]);
+          }
+        }
+      // a 16-lane group addresses rows 4 g .. 4 g + 3, columns 16 ct .. 16 ct + 15, and a lane receives its column of them
+      const int vrow = 4 * g + (m16 >> 2);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const int off = (((2 * ct + ((m16 & 3) >> 1)) ^ L_::vswz(vrow)) << 4) + ((m16 & 1) << 3);
+        union { s16x4 h[2]; bf16x8 v; } vt;
+        vt.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(RLDA_LDS(s16x4, vst + vrow * L_::LROWB + off));
+        vt.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(RLDA_LDS(s16x4, vst + (vrow + 16) * L_::LROWB + off));
+#pragma unroll
+        for (int k = NP - 1; k >= 0; --k) O[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt.v, pb[k], O[ct], 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");   // LDS serves a wavefront in order: the stage may be rewritten
+    __builtin_amdgcn_wave_barrier();
+    cur = nxt;
+  };
+  if (wv < T) {
+    const char* qp = P.q + ((size_t)b * P.Hq + h0 + min(m16, nr - 1)) * D * QE;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) qr[i] = *reinterpret_cast<const u32x4*>(qp + 64 * i + 16 * g);   // chunk 4 i + g, as K
+    cur = tile_of(wv);
+    load(cur, cur.k, kr);
+    load(cur, cur.v, vr);
+    const uint32_t qm = m16 < nr ? P.qmask : 0u, qs = m16 < nr ? P.qsign : 0u;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) qr[i] = (qr[i] & qm) ^ qs;
+    // the last step is a copy of its own: the waits of the others then count exactly the loads that follow
+    int t = wv;
+    for (; t + NW < T; t += NW) step(std::true_type{}, t);
+    step(std::false_type{}, t);
+  }
+
+  // ---- merge: every wavefront leaves its rows (O against its own maximum) in its V stage
+  l += __shfl_xor(l, 16, 64); l += __shfl_xor(l, 32, 64);
+  constexpr int OC = D / 4;                            // 16-byte chunks of an O row
+  constexpr int OROWB = D * 4;
+  constexpr int OSTRIDE = 2 * L_::TILE;
+  static_assert(16 * OROWB <= OSTRIDE, "a wavefront's O rows fit its stage");
+  if (m16 < nr) {
+    char* o = lds + wv * OSTRIDE + m16 * OROWB;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) *RLDA_LDS(f32x4, o + (((4 * ct + g) ^ m16) << 4)) = O[ct];
+  }
+  if (g == 0) { wm[wv][m16] = m; wl[wv][m16] = l; }
+  __syncthreads();
+  const int nw = min(NW, T);                           // wavefronts that had a tile
+  for (int it = tid; it < nr * OC; it += 64 * NW) {
+    const int row = it / OC, ch = it % OC;
+    float M = -INFINITY;
+    for (int w = 0; w < nw; ++w) M = fmaxf(M, wm[w][row]);
+    float L = 0.f;
+    f32x4 acc{0.f, 0.f, 0.f, 0.f};
+    for (int w = 0; w < nw; ++w) {
+      const float a = __builtin_amdgcn_exp2f(wm[w][row] - M);
+      L = fmaf(a, wl[w][row], L);
+      const f32x4 o = *RLDA_LDS(const f32x4, lds + w * OSTRIDE + row * OROWB + ((ch ^ row) << 4));
+#pragma unroll
+      for (int x = 0; x < 4; ++x) acc[x] = fmaf(a, o[x], acc[x]);
+    }
+    const size_t orow = (size_t)b * P.Hq + h0 + row;
+    const float inv = T > 0 ? vfac / L : 0.f;
+    *reinterpret_cast<f32x4*>(P.out + orow * D + 4 * ch) = acc * inv;
+    if (P.lse && ch == 0) P.lse[orow] = T > 0 ? (M + __builtin_amdgcn_logf(L)) * 0.69314718055994531f : -INFINITY;
+  }
+}
+
+template <int KIND, int D, bool EXACT, int NW, int NSEG = 2, bool ROWS = false>
+hipError_t launch(const UnitParams& P, int64_t blocks, hipStream_t stream) {
+  constexpr int lds = NW * 2 * Lay<KIND, D>::TILE;
+  // once per device: more than 64 KB of LDS in total needs an opt-in
+  static std::mutex mu;
+  static bool done[64] = {};
+  if (lds + 4096 > 65536) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(mu);
+    if (dev < 0 || dev >= 64 || !done[dev]) {
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(unit_kernel<KIND, D, EXACT, NW, NSEG, ROWS>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if (e != hipSuccess) return e;
+      if (dev >= 0 && dev < 64) done[dev] = true;
+    }
+  }
+  hipLaunchKernelGGL((unit_kernel<KIND, D, EXACT, NW, NSEG, ROWS>), dim3((unsigned)blocks), dim3(64 * NW), lds, stream, P);
+  return hipGetLastError();
+}
+
+// the form of one store type and head dimension: pages of fewer rows than a tile, a tree, or two segments
+template <int KIND, int D, bool EXACT>
+hipError_t launch_form(const UnitParams& P, int nw, int64_t blocks, hipStream_t stream) {
+  constexpr int WIDE = KIND == KV_F32 && D == 128 ? 4 : 8;   // two fp32 tiles of 128 columns take half a SIMD's registers
+  if (P.table && P.page_shift < 5) {                          // never EXACT = false: the shared-prefix path refuses these
+    if constexpr (EXACT) return launch<KIND, D, EXACT, WIDE, 2, true>(P, blocks, stream);
+    return hipErrorInvalidValue;
+  }
+  if (P.n_seg != 2) {
+    if constexpr (KIND == KV_BF16 && D == 128 && !EXACT) return launch<KIND, D, EXACT, WIDE, MAX_SEG>(P, blocks, stream);
+    return hipErrorInvalidValue;
+  }
+  return nw == 4 ? launch<KIND, D, EXACT, 4>(P, blocks, stream) : launch<KIND, D, EXACT, WIDE>(P, blocks, stream);
+}
+
+}  // namespace
+
+// stores, q and outputs start on 16 bytes (the loads are that wide), lengths fit the 32-bit tile arithmetic
+bool unit_supported(const Problem& pb) {
+  if (!(pb.scale - pb.scale == 0.f)) return false;                     // an infinite or NaN factor: the simple kernel's result
+  uintptr_t a = reinterpret_cast<uintptr_t>(pb.q) | reinterpret_cast<uintptr_t>(pb.out) |
+                reinterpret_cast<uintptr_t>(pb.k_suffix) | reinterpret_cast<uintptr_t>(pb.v_suffix);
+  int64_t cap = pb.Ls_cap;
+  if (pb.n_levels > 0) {
+    for (int l = 0; l < pb.n_levels; ++l) {
+      a |= reinterpret_cast<uintptr_t>(pb.levels[l].k) | reinterpret_cast<uintptr_t>(pb.levels[l].v);
+      cap += pb.levels[l].cap;
+    }
+  } else {
+    a |= reinterpret_cast<uintptr_t>(pb.k_prefix) | reinterpret_cast<uintptr_t>(pb.v_prefix);
+    cap += pb.Lp_cap;
+  }
+  if ((a & 15u) || cap > (int64_t)1 << 30) return false;
+  const int64_t rb = ceil_div(pb.Hq / pb.Hkv, 16);
+  return (n_sequences(pb) * pb.Hkv + 8 * (int64_t)max_group(pb)) * rb < (int64_t)1 << 31;
+}
+
+// Where one launch beats the shared-prefix path's two.  The lengths live on the device, so the line is drawn on the
+// capacities: it has to hold when every unit is full (shorter ones favour the single launch further).  Measured with
+// 128 columns in bf16, prefix full and suffixes uniform, us per call here / shared-prefix path, by units x keys:
+//   128 x 964 (8 prompts x 8, 2 KV heads)  11.7 / 18.8      512 x 1024  22.5 / 27.9     1024 x 512   24.5 / 27.4
+//   128 x 3072  22.7 / 25.5                                 512 x 1536  30.6 / 29.9     1024 x 1024  47.4 / 41.6
+//   128 x 5440  55.4 / 50.0                                 256 x 3072  30.6 / 31.5
+// A unit is one workgroup's work from end to end, hence the bound on its own keys.
+constexpr int64_t UNIT_KEYS = 589824, UNIT_LEN = 4096;
+bool unit_preferred(const Problem& pb) {
+  int64_t cap = pb.Ls_cap;
+  if (pb.n_levels > 0) {
+    for (int l = 0; l < pb.n_levels; ++l) cap += pb.levels[l].cap;
+  } else {
+    cap += pb.Lp_cap;
+  }
+  return cap <= UNIT_LEN && n_sequences(pb) * pb.Hkv * cap <= UNIT_KEYS && unit_supported(pb);
+}
+
+hipError_t launch_unit(const Problem& pb, bool exact, hipStream_t stream) {
+  UnitParams P{};
+  P.q = static_cast<const char*>(pb.q); P.out = pb.out; P.lse = pb.lse;
+  int n = 0;
+  if (pb.n_levels > 0) {
+    for (; n < pb.n_levels; ++n) {
+      const Problem::Level& lv = pb.levels[n];
+      P.seg[n] = Segment{static_cast<const char*>(lv.k), static_cast<const char*>(lv.v), lv.lens, lv.group, lv.cap};
+    }
+  } else {
+    P.seg[n++] = Segment{static_cast<const char*>(pb.k_prefix), static_cast<const char*>(pb.v_prefix), pb.prefix_lens, pb.G, pb.Lp_cap};
+  }
+  P.seg[n++] = Segment{static_cast<const char*>(pb.k_suffix), static_cast<const char*>(pb.v_suffix), pb.suffix_lens, 1, pb.Ls_cap};
+  P.n_seg = n;
+  P.B = (int)n_sequences(pb); P.G = max_group(pb); P.Hq = pb.Hq; P.Hkv = pb.Hkv;
+  P.r = pb.Hq / pb.Hkv; P.RB = ceil_div(P.r, 16);
+  const double c = pb.scale == 0.f ? 1.0 : fabs((double)pb.scale) * 1.4426950408889634;
+  P.c = (float)c; P.c_lo = (float)(c - (double)P.c);
+  P.qmask = pb.scale == 0.f ? 0u : 0xffffffffu;
+  P.qsign = pb.scale < 0.f ? (pb.dtype == RLDA_F32 ? 0x80000000u : 0x80008000u) : 0u;
+  P.table = pb.block_table; P.page_shift = pb.page_shift; P.max_pages = pb.max_pages; P.n_pages = pb.n_pages;
+  P.active = pb.seq_active; P.kscale = pb.k_scale; P.vscale = pb.v_scale;
+  // fewer than two groups a die: plain order, so that neighbours spread over the dies
+  const int64_t groups = (int64_t)(P.B / P.G) * P.Hkv;
+  P.groups8 = groups >= 16 && P.G > 1 ? (int)((groups + 7) / 8) : 0;
+  const int64_t blocks = P.groups8 > 0 ? (int64_t)P.groups8 * 8 * P.G * P.RB : (int64_t)P.B * P.Hkv * P.RB;
+  if (blocks == 0) return hipSuccess;
+  // eight wavefronts while every workgroup has a compute unit to itself (128 units x 964 keys: 11.7 us, 12.7 with four),
+  // four when they queue: two workgroups then share a compute unit and one starts under the other's end (512 x 1024:
+  // 22.5 us, 24.7 with eight)
+  const int nw = blocks > N_CU ? 4 : 8;
+  if (pb.dtype == RLDA_F32)
+    return pb.d == 64 ? launch_form<KV_F32, 64, true>(P, nw, blocks, stream) : launch_form<KV_F32, 128, true>(P, nw, blocks, stream);
+  if (pb.dtype == RLDA_BF16_KV8) {
+    if (pb.d == 64) return launch_form<KV_F8, 64, true>(P, nw, blocks, stream);
+    return exact ? launch_form<KV_F8, 128, true>(P, nw, blocks, stream) : launch_form<KV_F8, 128, false>(P, nw, blocks, stream);
+  }
+  if (pb.d == 64) return launch_form<KV_BF16, 64, true>(P, nw, blocks, stream);
+  return exact ? launch_form<KV_BF16, 128, true>(P, nw, blocks, stream) : launch_form<KV_BF16, 128, false>(P, nw, blocks, stream);
+}
+
+}  // namespace rlda
