@@ -367,18 +367,36 @@ int64_t rl_decode_attn_debug_partition_on(int32_t compute_units, int32_t P, int3
     }
     ++np;
   };
-  for (int p = 0; p < P; ++p)                    // the combine kernel's enumeration
+  // the combine kernels' enumerations: part by part, and (the 32-lane form) place by place; they have to agree
+  std::vector<int> walked, asked;
+  for (int p = 0; p < P; ++p)
     for (int j = 0; j < HkvP; ++j)
       for (int side = 0; side < SM; ++side)
         for_each_prefix_part(sc, X.data(), HkvP, p, j, side, [&](int rank) {
+          walked.push_back(rank);
           const int c = share_pair(sc, rank / 2, side);
           put_part(0, p, unit_j(j, side), wg_grid_index(sc, c, rank % 2), -1, (p * HkvP + j + rank) * SM + side);
         });
   for (int b = 0; b < B; ++b)
     for (int j = 0; j < Hkv; ++j)
       for_each_suffix_part(sc, X.data() + P, cumP, Hkv, b, j, [&](int rank, int v) {
+        walked.push_back(WG_WAVES * rank + v);
         put_part(1, b, j, wg_grid_index(sc, rank / 2, rank % 2), v, b * Hkv + j + WG_WAVES * rank + v);
       });
+  for (int p = 0; p < P; ++p)
+    for (int j = 0; j < HkvP; ++j)
+      for (int side = 0; side < SM; ++side) {
+        const PartLine l = prefix_parts(sc, X.data(), HkvP, p, j);
+        for (int k = 0, rank; k < l.n; ++k)
+          if (prefix_part(sc, l, side, k, rank)) asked.push_back(rank);
+      }
+  for (int b = 0; b < B; ++b)
+    for (int j = 0; j < Hkv; ++j) {
+      const PartLine l = suffix_parts(sc, X.data() + P, cumP, Hkv, b, j);
+      for (int k = 0, rank, v; k < l.n; ++k)
+        if (suffix_part(sc, l, k, rank, v)) asked.push_back(WG_WAVES * rank + v);
+    }
+  if (walked != asked) return RLDA_ERR_INVALID;
   *n_parts = np;
   return nr;
 }

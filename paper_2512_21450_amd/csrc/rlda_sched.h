@@ -279,4 +279,52 @@ __host__ __device__ inline void for_each_suffix_part(const Sched& s, const int* 
   }
 }
 
+// The partials of one unit, as places on the line that may hold one: place k < n of a prefix unit is workgroup A (in a
+// prefix-heavy batch: A or B) of a share, place k of a suffix unit is one wavefront of a pair, 8 to a pair, both in line
+// order.  The same partials as for_each_prefix_part / for_each_suffix_part enumerate, but a place tells by itself whether
+// it holds one, so that the lanes of a row can ask side by side.
+struct PartLine { int first, n, is, ie; };       // first share or pair, places, the unit's tiles [is, ie) on its line
+
+// unit (p, j) of the prefix line; Xp = scan over prompts
+__host__ __device__ inline PartLine prefix_parts(const Sched& s, const int* Xp, int Hkv, int p, int j) {
+  const int T = Xp[p + 1] - Xp[p];
+  PartLine l{0, 0, Xp[p] * Hkv + j * T, 0};
+  l.ie = l.is + T;
+  if (T > 0) {
+    l.first = prefix_tile_share(s, l.is);
+    l.n = (prefix_tile_share(s, l.ie - 1) - l.first + 1) << (s.heavy ? 1 : 0);
+  }
+  return l;
+}
+// place k, for row half `side` (0 unless dual): whether it holds a partial, and the workgroup's prefix rank
+__host__ __device__ inline bool prefix_part(const Sched& s, const PartLine& l, int side, int k, int& rank) {
+  const int q = l.first + (s.heavy ? k >> 1 : k), is_b = s.heavy ? k & 1 : 0;
+  int lo, mid, hi;                               // with fewer tiles than shares some hold nothing
+  pair_prefix_range(s, share_pair(s, q, side), lo, mid, hi);
+  const int a = is_b ? mid : lo, e = is_b ? hi : mid;
+  rank = 2 * q + is_b;
+  return (a > l.is ? a : l.is) < (e < l.ie ? e : l.ie);
+}
+// unit (b, j) of the suffix line; Xs = scan over sequences, xs0 = its value at sequence 0 (so Xs may continue Xp)
+__host__ __device__ inline PartLine suffix_parts(const Sched& s, const int* Xs, int xs0, int Hkv, int b, int j) {
+  const int T = Xs[b + 1] - Xs[b];
+  PartLine l{0, 0, (Xs[b] - xs0) * Hkv + j * T, 0};
+  l.ie = l.is + T;
+  if (T > 0) {
+    l.first = suffix_tile_pair(s, l.is);
+    l.n = (suffix_tile_pair(s, l.ie - 1) - l.first + 1) * (2 * WG_WAVES);
+  }
+  return l;
+}
+// place k: whether it holds a partial, the workgroup's suffix rank and the wavefront
+__host__ __device__ inline bool suffix_part(const Sched& s, const PartLine& l, int k, int& rank, int& v) {
+  const int c = l.first + k / (2 * WG_WAVES), is_b = (k / WG_WAVES) & 1;
+  v = k % WG_WAVES;
+  rank = 2 * c + is_b;
+  int lo, mid, hi, a, e;
+  pair_suffix_range(s, c, lo, mid, hi);
+  wave_suffix_range(is_b ? mid : lo, is_b ? hi : mid, v, a, e);
+  return (a > l.is ? a : l.is) < (e < l.ie ? e : l.ie);
+}
+
 }  // namespace rlda

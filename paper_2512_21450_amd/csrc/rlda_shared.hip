@@ -841,6 +841,57 @@ __global__ void __launch_bounds__(NTHREADS, 2) partial_kernel(const SharedParams
   }
 }
 
+// ---- the partials of one row, for the 32 lanes that combine it
+// A row's partials stand on their lines in places that may or may not hold one (PartLine).  Every lane looks at one
+// place at a time, 32 in parallel, and the places that hold one are packed in line order: lane k of the row receives
+// the k-th partial as 2 * (row index in its partial array) + [suffix], up to 32 per batch.  Every lane walking all of
+// them in turn took, of whole calls on 128-column bf16 heads: 1 x 8 sequences, 1 KV head, 1344 + 0..4096 keys 202 us
+// (now 35), 4 x 8 with 2 KV heads 60 us (36), 16 prompts x 8 of the 7B shape 42 us (40).
+template <bool TREE>
+struct RowParts {
+  static constexpr int W = 32, NL = TREE ? MAX_LEVELS : 1;
+  PartLine pre[NL], suf;
+  int pslot[NL], prow[NL], sslot;                            // slot of place 0 (prefix: its unit's rank 0); row inside a slot
+  int total, pos;                                           // places; the first one that is not packed yet
+
+  __device__ __forceinline__ int id_at(const SharedParams& P, const Sched& sc, int side, int hi_, int k) const {
+    int rank, v;                                             // -1: no partial there
+    PartLine l = pre[0];
+    int slot = pslot[0], row = prow[0];
+#pragma unroll
+    for (int i = 1; i < NL; ++i) {
+      const bool past = k >= l.n;
+      k -= past ? l.n : 0;
+      l.first = past ? pre[i].first : l.first; l.n = past ? pre[i].n : l.n;
+      l.is = past ? pre[i].is : l.is; l.ie = past ? pre[i].ie : l.ie;
+      slot = past ? pslot[i] : slot; row = past ? prow[i] : row;
+    }
+    if (k < l.n) return prefix_part(sc, l, side, k, rank) ? 2 * (((slot + rank) * P.SM + side) * P.RS + row) : -1;
+    k -= l.n;
+    return k < suf.n && suffix_part(sc, suf, k, rank, v) ? 2 * ((sslot + k) * P.r + hi_) + 1 : -1;
+  }
+  // the next batch: this lane's partial in `mine` (-1: none); returns their number
+  __device__ __forceinline__ int next(const SharedParams& P, const Sched& sc, int side, int hi_, int sub, int& mine) {
+    const int row0 = threadIdx.x & 63 & ~(W - 1);
+    int n = 0;
+    mine = -1;
+    while (pos < total) {
+      const int id = id_at(P, sc, side, hi_, pos + sub);
+      const uint32_t has = (uint32_t)(__ballot(id >= 0) >> row0);
+      const int cnt = __popc(has);
+      if (n + cnt > W) break;                                // packed with the next batch (cnt <= W)
+      // a permutation of the row's lanes: places with a partial to n, n + 1, ..., the others behind them, round the end
+      const int below = __popc(has & ((1u << sub) - 1u));
+      const int to = (n + (id >= 0 ? below : cnt + sub - below)) & (W - 1);
+      const int got = __builtin_amdgcn_ds_permute(4 * (row0 + to), id);
+      if (got >= 0) mine = got;                              // only lanes n .. n + cnt - 1 receive one
+      n += cnt;
+      pos += W;
+    }
+    return n;
+  }
+};
+
 // ---- combine: 32 lanes per (sequence, head) row.  Lane k of the row first owns part k: all lse
 // values of the row and the first sixteen parts' values are requested in one round trip (rows of a
 // small batch are cut into that many parts, and every further round trip shows in its step time); the lse
@@ -867,32 +918,33 @@ __global__ void __launch_bounds__(256) combine_kernel(const SharedParams P) {
 
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   float M = -INFINITY, Z = 0.f;                             // running max and sum over batches of 32 parts
-  for (int base = 0;; base += 32) {
-    // part `base + sub` of this row, as 2 * (row index in its partial array) + [suffix]
-    int n = 0, mine = -1;
-    if constexpr (TREE) {                                   // the row's segment on every level, in level order
+  RowParts<TREE> rp;
+  rp.pos = 0; rp.total = 0;
+  if constexpr (TREE) {                                     // the row's segment on every level, in level order
 #pragma unroll
-      for (int l = 0; l < MAX_LEVELS; ++l) {
-        if (l < P.n_lev) {
-          const int e = P.lev[l].first + b / P.lev[l].G, erow = (b % P.lev[l].G) * P.r + hi_;
-          for_each_prefix_part(sc, X, P.Hkv, e, j, 0, [&](int c) {
-            if (n == base + sub) mine = 2 * ((e * P.Hkv + j + c) * P.RS + erow);
-            ++n;
-          });
-        }
+    for (int l = 0; l < MAX_LEVELS; ++l) {
+      rp.pre[l] = PartLine{0, 0, 0, 0}; rp.pslot[l] = 0; rp.prow[l] = 0;
+      if (l < P.n_lev) {
+        const int e = P.lev[l].first + b / P.lev[l].G;
+        rp.pre[l] = prefix_parts(sc, X, P.Hkv, e, j);
+        rp.pslot[l] = e * P.Hkv + j;
+        rp.prow[l] = (b % P.lev[l].G) * P.r + hi_;
       }
-    } else {
-      for_each_prefix_part(sc, X, P.HkvP, p, jp, side, [&](int c) {
-        if (n == base + sub) mine = 2 * (((p * P.HkvP + jp + c) * P.SM + side) * P.RS + prow);
-        ++n;
-      });
+      rp.total += rp.pre[l].n;
     }
-    for_each_suffix_part(sc, X + P.P, cumP, P.Hkv, b, j, [&](int rank, int v) {
-      if (n == base + sub) mine = 2 * ((b * P.Hkv + j + WG_WAVES * rank + v) * P.r + hi_) + 1;
-      ++n;
-    });
-    const int cnt = min(n - base, 32);
-    if (cnt <= 0) break;
+  } else {
+    rp.pre[0] = prefix_parts(sc, X, P.HkvP, p, jp);
+    rp.pslot[0] = p * P.HkvP + jp;
+    rp.prow[0] = prow;
+    rp.total = rp.pre[0].n;
+  }
+  rp.suf = suffix_parts(sc, X + P.P, cumP, P.Hkv, b, j);
+  rp.sslot = b * P.Hkv + j + 2 * WG_WAVES * rp.suf.first;   // places of a pair: WG_WAVES * rank + wavefront in turn
+  rp.total += rp.suf.n;
+  for (;;) {
+    int mine;
+    const int cnt = rp.next(P, sc, TREE ? 0 : side, hi_, sub, mine);
+    if (cnt == 0) break;
     // the first FIRST parts' values are requested together with the lse values (one round trip)
     constexpr int FIRST = 16, NEXT = 8;
     f16x4 v8[FIRST];
@@ -939,7 +991,7 @@ __global__ void __launch_bounds__(256) combine_kernel(const SharedParams P) {
         acc.z = fmaf(wk[u], (float)v[u][2], acc.z); acc.w = fmaf(wk[u], (float)v[u][3], acc.w);
       }
     }
-    if (n - base <= 32) break;
+    if (rp.pos >= rp.total) break;
   }
   const float inv = Z > 0.f ? 1.f / Z : 0.f;
   *reinterpret_cast<float4*>(P.out + (size_t)row * D + c4) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
