@@ -438,21 +438,18 @@ bool unit_supported(const Problem& pb) {
 }
 
 // Where one launch beats the shared-prefix path's two.  The lengths live on the device, so the line is drawn on the
-// capacities: it has to hold when every unit is full (shorter ones favour the single launch further).  Measured with
-// 128 columns in bf16, prefix full and suffixes uniform, us per call here / shared-prefix path, by units x keys:
-//   128 x 964 (8 prompts x 8, 2 KV heads)  11.7 / 18.8      512 x 1024  22.5 / 27.9     1024 x 512   24.5 / 27.4
-//   128 x 3072  22.7 / 25.5                                 512 x 1536  30.6 / 29.9     1024 x 1024  47.4 / 41.6
-//   128 x 5440  55.4 / 50.0                                 256 x 3072  30.6 / 31.5
-// A unit is one workgroup's work from end to end, hence the bound on its own keys.
-constexpr int64_t UNIT_KEYS = 589824, UNIT_LEN = 4096;
+// capacities and has to hold when they are full; shorter sequences favour the single launch further.  A unit is one
+// workgroup's work from end to end and reads the shared levels once per sequence, so both paths were timed by units x
+// (prefix + suffix) keys, suffixes full, bf16, us per call here / shared-prefix path:
+//    64 x (1024 + 512)  14.6 / 14.2   128 x (512 + 2048)  34.5 / 37.2   256 x (1024 + 512)  20.2 / 25.9
+//    64 x (1536 + 512)  17.4 / 16.4   128 x (16 + 4000)   53.4 / 53.7   512 x (512 + 512)   34.8 / 38.4
+//    64 x (16 + 4000)   46.0 / 36.7  1024 x (512 + 16)    22.8 / 23.3  1024 x (16 + 512)    53.1 / 56.4
+// and on e4m3 stores 64 x (1024 + 1024) 18.0 / 14.4, 1024 x (512 + 16) 22.9 / 21.7.
 bool unit_preferred(const Problem& pb) {
-  int64_t cap = pb.Ls_cap;
-  if (pb.n_levels > 0) {
-    for (int l = 0; l < pb.n_levels; ++l) cap += pb.levels[l].cap;
-  } else {
-    cap += pb.Lp_cap;
-  }
-  return cap <= UNIT_LEN && n_sequences(pb) * pb.Hkv * cap <= UNIT_KEYS && unit_supported(pb);
+  int64_t shared = pb.Lp_cap;
+  for (int l = 0; l < pb.n_levels; ++l) shared += pb.levels[l].cap;
+  return pb.Ls_cap <= 2048 && 3 * shared + pb.Ls_cap <= 3600 &&
+         n_sequences(pb) * pb.Hkv * (shared + pb.Ls_cap) <= (int64_t)1 << 19 && unit_supported(pb);
 }
 
 hipError_t launch_unit(const Problem& pb, bool exact, hipStream_t stream) {
