@@ -1104,7 +1104,7 @@ __global__ void __launch_bounds__(256, 8) combine16_kernel(const SharedParams P)
 // 16-row blocks, one per wavefront, and share every K/V tile through LDS exactly as the G * r rows
 // of a decode group do in prefix_stream; a lane's row sees the keys below its own limit
 // (position + 1).  No key split: a workgroup walks all tiles up to its last position, so rows are
-// normalised and written directly.  All blocks of one (prompt, KV head) run on one XCD, one unit
+// normalised and written directly.  With many units all blocks of one (prompt, KV head) run on one XCD, one unit
 // after the other, from the end of the prompt (most tiles) to its start: workgroups are dealt to
 // the eight XCDs round-robin, so workgroup i belongs to XCD i % 8 and is the (i / 8)-th of its XCD;
 // with the units of an XCD laid out one after the other along that sequence, the 64 or so
@@ -1114,17 +1114,38 @@ struct PrefillParams {
   const char* q; const char* k; const char* v; const int32_t* lens;
   float* out; float* lse;
   int P, Hq, Hkv, r, Lp_cap, QB, nqb;
+  int spread;                                               // the blocks of a unit go to all XCDs
   float c;
 };
+constexpr int N_XCD = 8;
+// Whole units per XCD leave XCDs without work where their number is no multiple of eight and there
+// are few rounds of them: with the four units of a 28/4-head prompt half the chip stood still.  There
+// the blocks are dealt out one by one, the last block of every unit first, so that the long ones
+// start first and a round of short ones ends the pass.  Measured, whole units / spread, us:
+// 1 x 4096 tokens of 28/4 heads (4 units) 321 / 174, 1 x 1500 of 16/2 (2) 60.3 / 31.5, 6 x 512 of
+// 16/2 (12) 24.2 / 20.4, 3 x 2000 of 28/4 (12) 173 / 140, 7 ragged up to 4096 of 28/4 (28) 529 / 424,
+// 30 ragged up to 500 of 12/2 (60) 37.7 / 35.6; above, the working set of an XCD (every unit's K/V)
+// outgrows its L2 and the few empty places no longer cost that much: 41 x 700 of 16/2 (82) 153 / 165,
+// 50 of 12/2 (100) 54.5 / 56.1, 33 x 1500 of 28/4 (132) 358 / 375.
+inline bool prefill_spread(int units) { return units % N_XCD != 0 && units < 8 * N_XCD; }
+__device__ __forceinline__ void prefill_place(const PrefillParams& P, int b, int& pj, int& qb) {
+  if (P.spread) {
+    const int units = P.P * P.Hkv;
+    pj = b % units; qb = P.nqb - 1 - b / units;
+  } else {
+    const int xcd = b % N_XCD, seq = b / N_XCD;
+    pj = (seq / P.nqb) * N_XCD + xcd; qb = P.nqb - 1 - seq % P.nqb;
+  }
+}
 
 template <int NTP>                                          // 16-row blocks per wavefront: the workgroup holds 64 * NTP rows
 __global__ void __launch_bounds__(NTHREADS, 2) prefill_kernel(const PrefillParams P) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, m16 = lane & 15, g = lane >> 4;
-  constexpr int N_XCD = 8, WROWS = 16 * NTP;                // rows per wavefront
+  constexpr int WROWS = 16 * NTP;                           // rows per wavefront
   const int units = P.P * P.Hkv;
-  const int xcd = blockIdx.x % N_XCD, seq = blockIdx.x / N_XCD;
-  const int pj = (seq / P.nqb) * N_XCD + xcd, qb = P.nqb - 1 - seq % P.nqb;
+  int pj, qb;
+  prefill_place(P, blockIdx.x, pj, qb);
   if (pj >= units) return;                                  // the last round of units may not fill all XCDs
   const int p = pj / P.Hkv, j = pj % P.Hkv;
   const int L = clampi(P.lens[p], 0, P.Lp_cap), a = qb * P.QB;
@@ -1310,10 +1331,10 @@ template <int NTP>
 __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillParams P) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, m16 = lane & 15, g = lane >> 4;
-  constexpr int N_XCD = 8, WROWS = 16 * NTP;
+  constexpr int WROWS = 16 * NTP;
   const int units = P.P * P.Hkv;
-  const int xcd = blockIdx.x % N_XCD, seq = blockIdx.x / N_XCD;
-  const int pj = (seq / P.nqb) * N_XCD + xcd, qb = P.nqb - 1 - seq % P.nqb;
+  int pj, qb;
+  prefill_place(P, blockIdx.x, pj, qb);
   if (pj >= units) return;
   const int p = pj / P.Hkv, j = pj % P.Hkv;
   const int L = clampi(P.lens[p], 0, P.Lp_cap), a = qb * P.QB;
@@ -1666,6 +1687,7 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   const bool two = units8 * ceil_div(Lp_cap, (2 * rows1) / P.r) >= 4 * N_WG && scale > 0.f;   // its softmax needs scale > 0
   P.QB = ((two ? 2 : 1) * rows1) / P.r;                     // query positions per workgroup
   P.nqb = ceil_div(Lp_cap, P.QB);
+  P.spread = prefill_spread(P_ * Hkv);
   typedef void (*kern_t)(const PrefillParams);
   const kern_t kern = two ? prefill2_kernel<2> : (scale > 0.f ? prefill2_kernel<1> : prefill_kernel<1>);
   {
@@ -1683,7 +1705,7 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
       if (dev >= 0 && dev < 64) done[dev] = true;
     }
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)(units8 * P.nqb)), dim3(NTHREADS), LDS_BYTES, stream, P);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((P.spread ? (int64_t)P_ * Hkv : units8) * P.nqb)), dim3(NTHREADS), LDS_BYTES, stream, P);
   return hipGetLastError();
 }
 
