@@ -202,6 +202,7 @@ __device__ __forceinline__ void init_state(WaveState<NT>& st) {
 //     against the stale maximum, are at most 2^RESCALE_GAP, and the 32 accumulator registers of a
 //     row block are left alone;
 //   * the sum of the bf16-rounded weights is a two-element dot product per register pair.
+// prefill2_kernel leaves the maxima out after the first tile (FIXED, see there).
 constexpr float RESCALE_GAP = 8.f;
 __device__ __forceinline__ float max_raw(float a, float b) {
   uint32_t inf = 0x7f800000u;
@@ -209,15 +210,21 @@ __device__ __forceinline__ float max_raw(float a, float b) {
   return __builtin_amdgcn_fmed3f(a, b, __uint_as_float(inf));
 }
 template <int NT, bool MASK>
-__device__ __forceinline__ void softmax_max(const f32x4 (&s0)[NT], const f32x4 (&s1)[NT], const int (&nvalid)[NT],
-                                            const WaveState<NT>& st, float c, int g, float (&sv)[NT][8], float (&m_new)[NT]) {
+__device__ __forceinline__ void mask_scores(const f32x4 (&s0)[NT], const f32x4 (&s1)[NT], const int (&nvalid)[NT], int g, float (&sv)[NT][8]) {
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
+  for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       sv[nt][x] = (!MASK || 4 * g + x < nvalid[nt]) ? s0[nt][x] : -INFINITY;
       sv[nt][4 + x] = (!MASK || 16 + 4 * g + x < nvalid[nt]) ? s1[nt][x] : -INFINITY;
     }
+}
+template <int NT, bool MASK>
+__device__ __forceinline__ void softmax_max(const f32x4 (&s0)[NT], const f32x4 (&s1)[NT], const int (&nvalid)[NT],
+                                            const WaveState<NT>& st, float c, int g, float (&sv)[NT][8], float (&m_new)[NT]) {
+  mask_scores<NT, MASK>(s0, s1, nvalid, g, sv);
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
     float tmax = max_raw(max_raw(max_raw(sv[nt][0], sv[nt][1]), max_raw(sv[nt][2], sv[nt][3])),
                          max_raw(max_raw(sv[nt][4], sv[nt][5]), max_raw(sv[nt][6], sv[nt][7])));
     {
@@ -232,11 +239,12 @@ __device__ __forceinline__ void softmax_max(const f32x4 (&s0)[NT], const f32x4 (
     m_new[nt] = max_raw(st.m[nt], tmax * c);
   }
 }
-template <int NT>
+// FIXED: against the maximum the state holds, whatever m_new says
+template <int NT, bool FIXED = false>
 __device__ __forceinline__ void softmax_weights(const float (&sv)[NT][8], const float (&m_new)[NT], WaveState<NT>& st, bf16x8 (&pb)[NT], float c) {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    if (__any(m_new[nt] > st.m[nt] + RESCALE_GAP)) {         // first tile: -inf + gap = -inf
+    if (!FIXED && __any(m_new[nt] > st.m[nt] + RESCALE_GAP)) {   // first tile: -inf + gap = -inf
       const float alpha = __builtin_amdgcn_exp2f(st.m[nt] - m_new[nt]);
       st.l[nt] *= alpha;
       st.lr[nt] *= alpha;
@@ -1263,6 +1271,14 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill_kernel(const PrefillParam
 // one tile's second product and the next tile's first product is one uninterrupted run for the other
 // wavefront of the SIMD to put its softmax under.  Wavefront w moves the K (even w) or V (odd w) half
 // of tile w / 2 of a round.
+//
+// At 128 rows a tile costs a wavefront about as many cycles of vector ALU (softmax) as of matrix unit, so what the
+// softmax does beside the exponentials counts.  Row maxima are an eighth of it and put a chain (maxima, two lane
+// swaps, a branch over the rescaling) in front of every tile's weights.  They are taken of a row's first tile
+// only: softmax is the same for any reference, and sums and accumulators are in fp32, whose range holds any score
+// up to 2^32 above the reference with the same relative precision.  A workgroup in which that did not hold for
+// every row starts over with the reference following the maximum.  Measured, with the loads' addresses cut as
+// described there: 32 prompts of 1280 tokens of 28/4 heads 524 -> 486 us, 4 of 4096 537 -> 481 us (1 Pflop/s).
 template <int OFF>
 __device__ __forceinline__ bf16x8 lds_rd128_asm(uint32_t addr) {
   bf16x8 v;
@@ -1330,6 +1346,7 @@ __device__ __forceinline__ void value_products(const s16x4 (&v)[8][2], const bf1
 template <int NTP>
 __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillParams P) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ int again[WG_WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, m16 = lane & 15, g = lane >> 4;
   constexpr int WROWS = 16 * NTP;
   const int units = P.P * P.Hkv;
@@ -1340,20 +1357,18 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
   const int L = clampi(P.lens[p], 0, P.Lp_cap), a = qb * P.QB;
   if (a >= L) return;
   const int nq = min(P.QB, L - a), n_keys = a + nq, n_tiles = ceil_div(n_keys, TK), nrows = nq * P.r;
-  bool ok[NTP];
-  int pos[NTP], h[NTP], limit[NTP];
+  int limit[NTP];
   bf16x8 qf[NTP][4];
 #pragma unroll
   for (int nt = 0; nt < NTP; ++nt) {
     const int row = WROWS * wv + 16 * nt + m16;
-    ok[nt] = row < nrows;
-    pos[nt] = a + (ok[nt] ? row / P.r : 0);
-    h[nt] = j * P.r + (ok[nt] ? row % P.r : 0);
-    limit[nt] = pos[nt] + 1;
-    const char* qp = P.q + (((size_t)p * P.Lp_cap + pos[nt]) * P.Hq + h[nt]) * ROWB + 16 * g;
+    const bool ok = row < nrows;
+    const int pos = a + (ok ? row / P.r : 0), h = j * P.r + (ok ? row % P.r : 0);
+    limit[nt] = pos + 1;
+    const char* qp = P.q + (((size_t)p * P.Lp_cap + pos) * P.Hq + h) * ROWB + 16 * g;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      const u32x4 v = ok[nt] ? ldg16(qp + 64 * ks) : u32x4{0, 0, 0, 0};
+      const u32x4 v = ok ? ldg16(qp + 64 * ks) : u32x4{0, 0, 0, 0};
       qf[nt][ks] = *reinterpret_cast<const bf16x8*>(&v);
     }
   }
@@ -1367,51 +1382,70 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
   const int vrow = 4 * g + (m16 >> 2);
 #pragma unroll
   for (int ct = 0; ct < 8; ++ct) va[ct] = l0 + v_off(vrow, 2 * ct + ((m16 & 3) >> 1)) + ((m16 & 1) << 3);
-  // this wavefront's share of a round's loads: eight instructions of four rows.  Instruction i puts tile row
-  // 4 i + lane / 16 into LDS; the store's row is clamped to the last real key (a partial last tile re-reads it;
-  // those keys are masked), and the 16-byte chunk a lane fetches is its LDS chunk xor the row's pattern.
+  // This wavefront's share of a round's loads: eight instructions of four rows (a tile's 4 i + lane / 16).  The
+  // 16-byte chunk a lane fetches is its LDS chunk xor the row's pattern, which repeats after 16 rows: four lane
+  // offsets serve a whole tile on top of a uniform address, and the instruction's immediate counts on both sides
+  // because four rows are 1 KB in either.  A partial last tile clamps every row to the last real key (re-read;
+  // those keys are masked).  Without the empty asm the compiler carries the addresses of all four unrolled stages in
+  // registers, and at 128 rows per workgroup spills (126 of them; 248 registers and no spill with it).  Measured on
+  // 32 prompts of 1280 tokens, 28/4 heads: an address per row and load 496 us, the four offsets 486.
   const int kind = uni(wv & 1), sub = uni(wv >> 1), lrow = lane >> 4, chunk = lane & 15;
   const char* gb = (kind ? P.v : P.k) + (size_t)(p * P.Hkv + j) * P.Lp_cap * ROWB;      // uniform
-  const int cx = kind ? chunk ^ (lrow << 1) : chunk ^ lrow;                              // V: (row & 7) << 1, K: row & 15
-  auto issue = [&](int round) {
-    const int t = 2 * round + sub;
-    if (t >= n_tiles) return;
-    const int key0 = t * TK;
-    char* dst = lds + uni((2 * (round & 1) + sub) * STAGE_B + kind * TILE_B);
+  uint32_t vo[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int ci = kind ? ((4 * i) & 4) << 1 : (4 * i) & 12;
-      const uint32_t off = (uint32_t)min(key0 + 4 * i + lrow, n_keys - 1) * ROWB + ((cx ^ ci) << 4);
-      RLDA_G2L(gb + off, dst + i * 1024, 0);
+  for (int i = 0; i < 4; ++i) vo[i] = lrow * ROWB + ((chunk ^ (kind ? lrow << 1 ^ (i & 1) << 3 : lrow ^ i << 2)) << 4);   // V: (row & 7) << 1, K: row & 15
+  auto issue = [&](int round) {
+    int t = 2 * round + sub;
+    if (t >= n_tiles) return;
+    char* dst = lds + uni((2 * (round & 1) + sub) * STAGE_B + kind * TILE_B);
+    asm volatile("" : "+s"(t));
+    if ((t + 1) * TK <= n_keys) {
+      uint32_t o[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { o[i] = vo[i]; asm volatile("" : "+v"(o[i])); }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const char* src = gb + (size_t)t * TILE_B + u * (TILE_B / 2);
+        asm volatile("" : "+s"(src));
+        RLDA_G2L(src + o[0], dst + u * (TILE_B / 2), 0);
+        RLDA_G2L(src + o[1], dst + u * (TILE_B / 2), 1024);
+        RLDA_G2L(src + o[2], dst + u * (TILE_B / 2), 2048);
+        RLDA_G2L(src + o[3], dst + u * (TILE_B / 2), 3072);
+      }
+    } else {
+      int lr = lrow;
+      asm volatile("" : "+v"(lr));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t off = (uint32_t)min(t * TK + 4 * i + lr, n_keys - 1) * ROWB + (vo[i & 3] & (ROWB - 1));
+        RLDA_G2L(gb + off, dst + i * 1024, 0);
+      }
     }
   };
   WaveState<NTP> st;
-  init_state(st);
   f32x4 s0[NTP], s1[NTP];
   bf16x8 pb[NTP], kf[4][2];
   s16x4 vf[8][2];
-  issue(0);
-  issue(1);
-  wait_vmem();
-  __builtin_amdgcn_s_barrier();
-  if (wave_has_rows) {
-    read_k_frags<0>(ka, kf);
-    wait_k_frags(kf);
-    score_products<NTP>(kf, qf, s0, s1);
-  }
   // one tile; STAGE = t % 4 is a compile-time constant of the unrolled body
-  auto tile = [&](auto stage_c, int t) {
+  auto tile = [&](auto fixed_c, auto stage_c, int t) {
     constexpr int STAGE = decltype(stage_c)::value;
+    constexpr bool FIXED = decltype(fixed_c)::value;
     const int key0 = t * TK;
     if (wave_has_rows) {
       float sv[NTP][8], m_new[NTP];
       int nv[NTP];
 #pragma unroll
-      for (int nt = 0; nt < NTP; ++nt) nv[nt] = limit[nt] - key0;
-      if (key0 + TK <= wave_first + 1) softmax_max<NTP, false>(s0, s1, nv, st, P.c, g, sv, m_new);   // wholly in every row's past
-      else                             softmax_max<NTP, true>(s0, s1, nv, st, P.c, g, sv, m_new);
+      for (int nt = 0; nt < NTP; ++nt) { nv[nt] = limit[nt] - key0; m_new[nt] = st.m[nt]; }
+      const bool past = key0 + TK <= wave_first + 1;        // wholly in every row's past
+      if constexpr (FIXED) {
+        if (past) mask_scores<NTP, false>(s0, s1, nv, g, sv);
+        else      mask_scores<NTP, true>(s0, s1, nv, g, sv);
+      } else {
+        if (past) softmax_max<NTP, false>(s0, s1, nv, st, P.c, g, sv, m_new);
+        else      softmax_max<NTP, true>(s0, s1, nv, st, P.c, g, sv, m_new);
+      }
       read_v_frags<STAGE>(va, vf);
-      softmax_weights<NTP>(sv, m_new, st, pb, P.c);
+      softmax_weights<NTP, FIXED>(sv, m_new, st, pb, P.c);
       wait_v_frags(vf);
     }
     if ((STAGE & 1) || t == n_tiles - 1) {                  // the round's last tile: every fragment of the round is in registers
@@ -1428,21 +1462,62 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
       }
     }
   };
-  for (int t0 = 0; t0 < n_tiles; t0 += 4) {
-    tile(std::integral_constant<int, 0>{}, t0);
-    if (t0 + 1 < n_tiles) tile(std::integral_constant<int, 1>{}, t0 + 1);
-    if (t0 + 2 < n_tiles) tile(std::integral_constant<int, 2>{}, t0 + 2);
-    if (t0 + 3 < n_tiles) tile(std::integral_constant<int, 3>{}, t0 + 3);
+  // all tiles once; FIXED: with the maxima of the rows' first tile as the reference all along
+  auto pass = [&](auto fixed) {
+    init_state(st);
+    issue(0);
+    issue(1);
+    wait_vmem();
+    __builtin_amdgcn_s_barrier();
+    if (wave_has_rows) {
+      read_k_frags<0>(ka, kf);
+      wait_k_frags(kf);
+      score_products<NTP>(kf, qf, s0, s1);
+      if constexpr (decltype(fixed)::value) {               // every row sees key 0, so these are finite
+        float sv[NTP][8], m_new[NTP];
+        softmax_max<NTP, true>(s0, s1, limit, st, P.c, g, sv, m_new);
+#pragma unroll
+        for (int nt = 0; nt < NTP; ++nt) st.m[nt] = m_new[nt];
+      }
+    }
+    for (int t0 = 0; t0 < n_tiles; t0 += 4) {
+      tile(fixed, std::integral_constant<int, 0>{}, t0);
+      if (t0 + 1 < n_tiles) tile(fixed, std::integral_constant<int, 1>{}, t0 + 1);
+      if (t0 + 2 < n_tiles) tile(fixed, std::integral_constant<int, 2>{}, t0 + 2);
+      if (t0 + 3 < n_tiles) tile(fixed, std::integral_constant<int, 3>{}, t0 + 3);
+    }
+  };
+  pass(std::true_type{});
+  // Did it hold?  Sums below 2^32 and finite accumulators say that no weight came near the end of the range; while
+  // the sums stay below 2^RESCALE_GAP no weight is larger than the online softmax lets them be, and the accumulators
+  // need no look.  If one row of the workgroup fails (NaN fails as well), the tiles, which are shared, are walked again.
+  bool bad = false;
+  if (wave_has_rows) {
+    bool small = true;
+#pragma unroll
+    for (int nt = 0; nt < NTP; ++nt) { bad = bad || !(st.l[nt] < 0x1p32f); small = small && st.l[nt] < __builtin_exp2f(RESCALE_GAP); }
+    if (!__all(small))
+#pragma unroll
+      for (int nt = 0; nt < NTP; ++nt)
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct)
+#pragma unroll
+          for (int x = 0; x < 4; ++x) bad = bad || !(__builtin_fabsf(st.O[nt][ct][x]) < INFINITY);
   }
+  bad = __any(bad);
+  if (lane == 0) again[wv] = bad;
+  lds_barrier();
+  if (uni(again[0] | again[1] | again[2] | again[3])) pass(std::false_type{});
   // normalise and write the rows
 #pragma unroll
   for (int nt = 0; nt < NTP; ++nt) {
+    const int row = WROWS * wv + 16 * nt + m16, pos = limit[nt] - 1;
     float l = st.l[nt], lr = st.lr[nt];
     l += __shfl_xor(l, 16, 64);   l += __shfl_xor(l, 32, 64);
     lr += __shfl_xor(lr, 16, 64); lr += __shfl_xor(lr, 32, 64);
-    if (ok[nt]) {
+    if (row < nrows) {
       const float inv = 1.f / lr;
-      const size_t orow = ((size_t)p * P.Lp_cap + pos[nt]) * P.Hq + h[nt];
+      const size_t orow = ((size_t)p * P.Lp_cap + pos) * P.Hq + j * P.r + row - (pos - a) * P.r;
       float* o = P.out + orow * D + 4 * g;
 #pragma unroll
       for (int ct = 0; ct < 8; ++ct) {
@@ -1677,14 +1752,18 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   P.lens = lens; P.out = out; P.lse = lse;
   P.P = P_; P.Hq = Hq; P.Hkv = Hkv; P.r = Hq / Hkv; P.Lp_cap = Lp_cap;
   P.c = scale * 1.4426950408889634f;
-  // Two 16-row blocks per wavefront (128 rows per workgroup) amortise every LDS read, barrier and
-  // tile over twice the matrix work (measured with the register-staged kernel: 440 -> 514 Tflop/s on
-  // 32 prompts of 1280 tokens; prefill2_kernel, which they run on: 592, then 688 with its leaner softmax);
-  // small problems keep one block so that there are enough workgroups for 256 compute units.  The
+  // Two 16-row blocks per wavefront (128 rows per workgroup) amortise every LDS read, barrier and tile over
+  // twice the matrix work, but halve the workgroups and are longer to start and end.  They need a full round of
+  // workgroups, two per compute unit (below: 1 x 4000 tokens of 16/2 heads, 500 workgroups, 90 us with one block,
+  // 99 with two; 1 x 2500, 314, 47 / 61; 8 x 1000 of 8/8, 512, 43 / 39), and either that each has some tiles to walk
+  // (workgroups x length: 10 ragged up to 600 of 16/2, 456k, 20.3 / 21.7; 64 ragged up to 130 of 8/8, 133k,
+  // 17.1 / 21.2; 30 ragged up to 500 of 12/2, 720k, 34.2 / 30.6; 3 x 1100 of 28/4, 818k, 48.1 / 41.2; 4 x 900 of
+  // 56/8, 93 / 79) or that there are many (100 ragged up to 200 of 16/4, 2800 workgroups, 51.6 / 47.3).  The
   // register-staged kernel is what scales that are not positive run on.
   const int rows1 = 16 * WG_WAVES;
   const int64_t units8 = (int64_t)8 * ceil_div(P_ * Hkv, 8);              // eight XCDs, whole rounds of units
-  const bool two = units8 * ceil_div(Lp_cap, (2 * rows1) / P.r) >= 4 * N_WG && scale > 0.f;   // its softmax needs scale > 0
+  const int64_t wgs = (int64_t)P_ * Hkv * ceil_div(Lp_cap, (2 * rows1) / P.r);
+  const bool two = scale > 0.f && (wgs >= 4 * N_WG || (wgs >= N_WG && wgs * Lp_cap >= 600 * 1024));
   P.QB = ((two ? 2 : 1) * rows1) / P.r;                     // query positions per workgroup
   P.nqb = ceil_div(Lp_cap, P.QB);
   P.spread = prefill_spread(P_ * Hkv);
