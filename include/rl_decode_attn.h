@@ -330,6 +330,18 @@ int rl_lse_combine(const float* o_parts, const float* lse_parts, int32_t n_parts
                    int64_t n_rows, int32_t d, float* out, float* lse, void* hip_stream);
 
 /*
+ * Testing and measuring hook, pure host code: the kernels a call with this descriptor runs on, on a device with
+ * `compute_units` compute units (256: a whole MI355X): RLDA_ALGO_SIMPLE, RLDA_ALGO_SHARED (the streaming kernel and
+ * its combine) or RLDA_ROUTE_UNIT (one launch, one workgroup per sequence and KV head), or a negative RLDA_ERR_* code.
+ * Unlike the plan queries this tells what RLDA_ALGO_AUTO picks among kernels that need the same plan and workspace; it
+ * reads the alignment of the tensor pointers and is nothing that a program should keep results of.
+ */
+#define RLDA_ROUTE_UNIT 3
+int rl_decode_attn_debug_route(int32_t compute_units, const rlda_desc* desc);
+int rl_decode_attn_paged_debug_route(int32_t compute_units, const rlda_paged_desc* desc);
+int rl_decode_attn_tree_debug_route(int32_t compute_units, const rlda_tree_desc* desc);
+
+/*
  * Testing hook, pure host code: the static work partition the shared-prefix
  * path uses for the given lengths (HOST arrays prefix_lens [P], suffix_lens
  * [P*G]; rows_per_kv_group = G * Hq / Hkv, at most 256).  A KV group with more

@@ -131,6 +131,21 @@ _lib.rl_lse_combine.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32
                                 ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
 
 
+RLDA_ROUTE_UNIT = 3
+for _name, _ptr in (("rl_decode_attn_debug_route", _dp), ("rl_decode_attn_paged_debug_route", _pp),
+                    ("rl_decode_attn_tree_debug_route", _tp)):
+    getattr(_lib, _name).restype = ctypes.c_int
+    getattr(_lib, _name).argtypes = [ctypes.c_int32, _ptr]
+
+
+def rl_decode_attn_debug_route(desc, compute_units: int = 256) -> int:
+    """The kernels a call with this (contiguous, paged or tree) descriptor runs on: RLDA_ALGO_SIMPLE, RLDA_ALGO_SHARED,
+    RLDA_ROUTE_UNIT or a negative code."""
+    fn = {rlda_desc: _lib.rl_decode_attn_debug_route, rlda_paged_desc: _lib.rl_decode_attn_paged_debug_route,
+          rlda_tree_desc: _lib.rl_decode_attn_tree_debug_route}[type(desc)]
+    return fn(compute_units, ctypes.byref(desc))
+
+
 class RldaError(RuntimeError):
     def __init__(self, code: int):
         self.code = code

@@ -118,6 +118,28 @@ int check_tree(const Problem& pb) {
   return RLDA_OK;
 }
 
+// The kernels a valid, non-empty problem runs on, on a device with `pairs` workgroup pairs.  One launch takes the small
+// batches of the shared-prefix path and what that path does not take; an explicit algo never changes its kernels.
+enum Route { ROUTE_SIMPLE = RLDA_ALGO_SIMPLE, ROUTE_SHARED = RLDA_ALGO_SHARED, ROUTE_UNIT = RLDA_ROUTE_UNIT };
+Route route(const Problem& pb, int planned, int pairs) {
+  const bool tree = pb.n_levels > 0;                         // has no algo field: chosen as under AUTO
+  if (planned == RLDA_ALGO_SHARED)
+    return (tree || pb.algo == RLDA_ALGO_AUTO) && rlda::unit_preferred(pb, pairs) ? ROUTE_UNIT : ROUTE_SHARED;
+  return pb.algo == RLDA_ALGO_AUTO && rlda::unit_supported(pb) ? ROUTE_UNIT : ROUTE_SIMPLE;
+}
+
+hipError_t launch(const Problem& pb, int planned, hipStream_t stream, hipEvent_t mid) {
+  int pairs = 0;
+  hipError_t e = rlda::device_pairs(pairs);
+  if (e != hipSuccess) return e;
+  switch (route(pb, planned, pairs)) {
+    case ROUTE_SHARED: return rlda::launch_shared(pb, stream, mid);
+    case ROUTE_UNIT: e = rlda::launch_unit(pb, planned == RLDA_ALGO_SIMPLE, pairs, stream); break;
+    default: e = rlda::launch_simple(pb, stream);
+  }
+  return e == hipSuccess && mid ? hipEventRecord(mid, stream) : e;
+}
+
 int enqueue_tree(const rlda_tree_desc* desc, void* hip_stream) {
   Problem pb;
   int rc = to_problem(desc, pb);
@@ -132,8 +154,7 @@ int enqueue_tree(const rlda_tree_desc* desc, void* hip_stream) {
   const size_t need = rlda::shared_workspace_bytes(pb);
   if (!pb.workspace || pb.workspace_bytes < need) return RLDA_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(pb.workspace) & 255u) return RLDA_ERR_WORKSPACE;
-  const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const hipError_t e = rlda::unit_preferred(pb) ? rlda::launch_unit(pb, false, stream) : rlda::launch_shared(pb, stream, nullptr);
+  const hipError_t e = launch(pb, RLDA_ALGO_SHARED, static_cast<hipStream_t>(hip_stream), nullptr);
   g_last_hip_error = e;
   return e == hipSuccess ? RLDA_OK : RLDA_ERR_LAUNCH;
 }
@@ -154,24 +175,12 @@ int enqueue(const Problem& pb, void* hip_stream, void* mid_event) {
   const int rc = check_pointers(pb);
   if (rc != RLDA_OK) return rc;
   if ((int64_t)pb.P * pb.G == 0) return RLDA_OK;
-  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  hipError_t e;
   if (pl == RLDA_ALGO_SHARED) {
     const size_t need = rlda::shared_workspace_bytes(pb);
     if (need > 0 && (!pb.workspace || pb.workspace_bytes < need)) return RLDA_ERR_WORKSPACE;
     if (need > 0 && (reinterpret_cast<uintptr_t>(pb.workspace) & 255u)) return RLDA_ERR_WORKSPACE;
-    if (pb.algo != RLDA_ALGO_AUTO || !rlda::unit_preferred(pb)) {
-      e = rlda::launch_shared(pb, stream, static_cast<hipEvent_t>(mid_event));
-      g_last_hip_error = e;
-      return e == hipSuccess ? RLDA_OK : RLDA_ERR_LAUNCH;
-    }
-    e = rlda::launch_unit(pb, false, stream);
-  } else if (pb.algo == RLDA_ALGO_AUTO && rlda::unit_supported(pb)) {
-    e = rlda::launch_unit(pb, true, stream);
-  } else {
-    e = rlda::launch_simple(pb, stream);
   }
-  if (e == hipSuccess && mid_event) e = hipEventRecord(static_cast<hipEvent_t>(mid_event), stream);
+  const hipError_t e = launch(pb, pl, static_cast<hipStream_t>(hip_stream), static_cast<hipEvent_t>(mid_event));
   g_last_hip_error = e;
   return e == hipSuccess ? RLDA_OK : RLDA_ERR_LAUNCH;
 }
@@ -291,6 +300,31 @@ int rl_lse_combine(const float* o_parts, const float* lse_parts, int32_t n_parts
                                             static_cast<hipStream_t>(hip_stream));
   g_last_hip_error = e;
   return e == hipSuccess ? RLDA_OK : RLDA_ERR_LAUNCH;
+}
+
+namespace {
+int route_of(int rc, const Problem& pb, int planned, int32_t compute_units) {
+  if (rc != RLDA_OK) return rc;
+  if (planned < 0) return planned;
+  return compute_units < 1 ? RLDA_ERR_INVALID : (int)route(pb, planned, rlda::pairs_for(compute_units));
+}
+}  // namespace
+
+int rl_decode_attn_debug_route(int32_t compute_units, const rlda_desc* desc) {
+  Problem pb;
+  const int rc = to_problem(desc, pb);
+  return route_of(rc, pb, rc == RLDA_OK ? plan(pb) : rc, compute_units);
+}
+int rl_decode_attn_paged_debug_route(int32_t compute_units, const rlda_paged_desc* desc) {
+  Problem pb;
+  const int rc = to_problem(desc, pb);
+  return route_of(rc, pb, rc == RLDA_OK ? plan(pb) : rc, compute_units);
+}
+int rl_decode_attn_tree_debug_route(int32_t compute_units, const rlda_tree_desc* desc) {
+  Problem pb;
+  const int rc = to_problem(desc, pb);
+  const int rt = rc == RLDA_OK ? check_tree(pb) : rc;
+  return route_of(rc, pb, rt == RLDA_OK ? (int)RLDA_ALGO_SHARED : rt, compute_units);
 }
 
 int32_t rl_decode_attn_debug_pairs(int32_t compute_units) {

@@ -61,14 +61,17 @@ hipError_t launch_simple(const Problem& pb, hipStream_t stream);
 // ---- shared-prefix MFMA path (bf16 or bf16 with e4m3 K/V, d = 128)
 bool   shared_supported(const Problem& pb);
 size_t shared_workspace_bytes(const Problem& pb);
+// workgroup pairs of the current device: pairs_for its compute-unit count, looked up once per device
+hipError_t device_pairs(int& pairs);
 // `mid`, if not null, is recorded between the partial kernel and the combine kernel
 hipError_t launch_shared(const Problem& pb, hipStream_t stream, hipEvent_t mid);
 
 // ---- one workgroup per (sequence, KV head): all dtypes, d in {64, 128}, tree levels, pages of any size, any finite scale.
 // `exact`: softmax weights enter the value contraction with 24 bits, else (d = 128 only) with 16
+// `pairs`: workgroup pairs of the device at hand (device_pairs), which stand for its compute units
 bool unit_supported(const Problem& pb);
-bool unit_preferred(const Problem& pb);          // a problem of the shared-prefix path that runs faster here
-hipError_t launch_unit(const Problem& pb, bool exact, hipStream_t stream);
+bool unit_preferred(const Problem& pb, int pairs);   // a problem of the shared-prefix path that runs faster here
+hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t stream);
 
 // ---- causal prefill attention over each prompt (bf16, d = 128, Hq/Hkv <= 16)
 bool prefill_supported(int dtype, int Hq, int Hkv, int d);

@@ -1617,6 +1617,23 @@ size_t shared_workspace_bytes(const Problem& ds) {
   return layout(np < ds.P ? prompt_range(ds, 0, np) : ds).total;
 }
 
+hipError_t device_pairs(int& n) {
+  static std::mutex mu;
+  static int pairs[64] = {};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  std::lock_guard<std::mutex> lock(mu);
+  if (dev >= 0 && dev < 64 && pairs[dev] != 0) { n = pairs[dev]; return hipSuccess; }
+  int cus = 0;
+  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  if (cus < 1) return hipErrorInvalidDevice;
+  n = pairs_for(cus);
+  if (dev >= 0 && dev < 64) pairs[dev] = n;
+  return hipSuccess;
+}
+
 hipError_t launch_shared(const Problem& whole, hipStream_t stream, hipEvent_t mid) {
   // more prompts and sequences than one launch takes: whole prompts at a time, one after the other on the stream
   // (they share the workspace)
@@ -1658,24 +1675,9 @@ hipError_t launch_shared(const Problem& whole, hipStream_t stream, hipEvent_t mi
     }
   }
 
-  // workgroup pairs: by the compute-unit count of the device, looked up once
   {
-    static std::mutex mu;
-    static int pairs[64] = {};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = device_pairs(P.n_cu);
     if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lock(mu);
-    if (dev < 0 || dev >= 64 || pairs[dev] == 0) {
-      int cus = 0;
-      e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-      if (e != hipSuccess) return e;
-      if (cus < 1) return hipErrorInvalidDevice;
-      P.n_cu = pairs_for(cus);
-      if (dev >= 0 && dev < 64) pairs[dev] = P.n_cu;
-    } else {
-      P.n_cu = pairs[dev];
-    }
   }
   // row halves of the KV group, and wavefronts per prefix tile (NRB 16-row blocks, a power of two)
   P.SM = side_parts(P.R, P.n_cu);

@@ -444,15 +444,16 @@ bool unit_supported(const Problem& pb) {
 //    64 x (1024 + 512)  14.6 / 14.2   128 x (512 + 2048)  34.5 / 37.2   256 x (1024 + 512)  20.2 / 25.9
 //    64 x (1536 + 512)  17.4 / 16.4   128 x (16 + 4000)   53.4 / 53.7   512 x (512 + 512)   34.8 / 38.4
 //    64 x (16 + 4000)   46.0 / 36.7  1024 x (512 + 16)    22.8 / 23.3  1024 x (16 + 512)    53.1 / 56.4
-// and on e4m3 stores 64 x (1024 + 1024) 18.0 / 14.4, 1024 x (512 + 16) 22.9 / 21.7.
-bool unit_preferred(const Problem& pb) {
+// and on e4m3 stores 64 x (1024 + 1024) 18.0 / 14.4, 1024 x (512 + 16) 22.9 / 21.7.  All on 256 compute units; the
+// number of units that fills the chip follows the device's, as the other path does (2048 keys per workgroup pair).
+bool unit_preferred(const Problem& pb, int pairs) {
   int64_t shared = pb.Lp_cap;
   for (int l = 0; l < pb.n_levels; ++l) shared += pb.levels[l].cap;
   return pb.Ls_cap <= 2048 && 3 * shared + pb.Ls_cap <= 3600 &&
-         n_sequences(pb) * pb.Hkv * (shared + pb.Ls_cap) <= (int64_t)1 << 19 && unit_supported(pb);
+         n_sequences(pb) * pb.Hkv * (shared + pb.Ls_cap) <= (int64_t)2048 * pairs && unit_supported(pb);
 }
 
-hipError_t launch_unit(const Problem& pb, bool exact, hipStream_t stream) {
+hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t stream) {
   UnitParams P{};
   P.q = static_cast<const char*>(pb.q); P.out = pb.out; P.lse = pb.lse;
   int n = 0;
@@ -482,7 +483,7 @@ hipError_t launch_unit(const Problem& pb, bool exact, hipStream_t stream) {
   // eight wavefronts while every workgroup has a compute unit to itself (128 units x 964 keys: 11.7 us, 12.7 with four),
   // four when they queue: two workgroups then share a compute unit and one starts under the other's end (512 x 1024:
   // 22.5 us, 24.7 with eight)
-  const int nw = blocks > N_CU ? 4 : 8;
+  const int nw = blocks > pairs ? 4 : 8;
   if (pb.dtype == RLDA_F32)
     return pb.d == 64 ? launch_form<KV_F32, 64, true>(P, nw, blocks, stream) : launch_form<KV_F32, 128, true>(P, nw, blocks, stream);
   if (pb.dtype == RLDA_BF16_KV8) {

@@ -1,0 +1,43 @@
+"""Which kernels a call runs on, by the host-side rule alone (no GPU): rl_decode_attn_debug_route."""
+import pytest
+
+from paper_2512_21450_amd import binding as B
+
+UNIT, SIMPLE, SHARED = B.RLDA_ROUTE_UNIT, B.RLDA_ALGO_SIMPLE, B.RLDA_ALGO_SHARED
+
+
+def desc(dtype=B.RLDA_BF16, P=8, G=8, Hq=16, Hkv=2, d=128, Lp=452, Ls=512, scale=0.1, **kw):
+    return B.make_desc(dtype, P, G, Hq, Hkv, d, Lp, Ls, scale, **kw)
+
+
+def test_an_explicit_algo_keeps_its_kernels():
+    assert B.rl_decode_attn_debug_route(desc()) == UNIT
+    assert B.rl_decode_attn_debug_route(desc(algo=SHARED)) == SHARED
+    assert B.rl_decode_attn_debug_route(desc(algo=SIMPLE)) == SIMPLE
+    assert B.rl_decode_attn_debug_route(desc(d=64)) == UNIT
+    assert B.rl_decode_attn_debug_route(desc(d=64, algo=SIMPLE)) == SIMPLE
+
+
+def test_errors_are_those_of_the_plan():
+    assert B.rl_decode_attn_debug_route(desc(d=96)) == B.RLDA_ERR_UNSUPPORTED
+    assert B.rl_decode_attn_debug_route(desc(d=64, algo=SHARED)) == B.RLDA_ERR_UNSUPPORTED
+    assert B.rl_decode_attn_debug_route(desc(), 0) == B.RLDA_ERR_INVALID
+    ds = B.make_tree_desc(B.RLDA_F32, 8, 16, 2, 128, 64, 0.1, [(None, None, None, 4, 64)])
+    assert B.rl_decode_attn_debug_route(ds) == B.RLDA_ERR_UNSUPPORTED
+
+
+def test_pointers_off_sixteen_bytes_and_factors_that_are_not_finite_stay_on_the_simple_kernel():
+    assert B.rl_decode_attn_debug_route(desc(d=64, k_suffix=1 << 20)) == UNIT
+    assert B.rl_decode_attn_debug_route(desc(d=64, k_suffix=(1 << 20) + 2)) == SIMPLE
+    assert B.rl_decode_attn_debug_route(desc(k_suffix=(1 << 20) + 2)) == SHARED
+    for s in (float("inf"), float("-inf"), float("nan")):
+        assert B.rl_decode_attn_debug_route(desc(d=64, scale=s)) == SIMPLE
+
+
+@pytest.mark.parametrize("cus,units", [(256, 512), (128, 256), (64, 128), (32, 64)])
+def test_how_many_units_fill_the_chip_follows_the_device(cus, units):
+    """1024 keys a unit: 2048 keys per workgroup pair are two units per pair, on a partition as on the whole device."""
+    tree = lambda n: B.make_tree_desc(B.RLDA_BF16, n, 8, 1, 128, 512, 0.1, [(None, None, None, 1, 512)])
+    for n, want in ((units, UNIT), (units + 1, SHARED)):
+        assert B.rl_decode_attn_debug_route(desc(P=n, G=1, Hq=8, Hkv=1, Lp=512, Ls=512), cus) == want
+        assert B.rl_decode_attn_debug_route(tree(n), cus) == want
