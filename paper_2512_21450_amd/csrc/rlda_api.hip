@@ -125,7 +125,7 @@ Route route(const Problem& pb, int planned, int pairs) {
   const bool tree = pb.n_levels > 0;                         // has no algo field: chosen as under AUTO
   if (planned == RLDA_ALGO_SHARED)
     return (tree || pb.algo == RLDA_ALGO_AUTO) && rlda::unit_preferred(pb, pairs) ? ROUTE_UNIT : ROUTE_SHARED;
-  return pb.algo == RLDA_ALGO_AUTO && rlda::unit_supported(pb) ? ROUTE_UNIT : ROUTE_SIMPLE;
+  return pb.algo == RLDA_ALGO_AUTO && rlda::unit_supported(pb, pairs) ? ROUTE_UNIT : ROUTE_SIMPLE;
 }
 
 hipError_t launch(const Problem& pb, int planned, hipStream_t stream, hipEvent_t mid) {

@@ -400,10 +400,34 @@ hipError_t launch(const UnitParams& P, int64_t blocks, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// two fp32 tiles of 128 columns take half a SIMD's registers
+constexpr int wide_waves(bool f32, int d) { return f32 && d == 128 ? 4 : 8; }
+
+// Grid of a problem (n_sequences > 0).
+struct UnitGrid {
+  int groups8;                     // as in UnitParams
+  int64_t blocks;
+  int nw;                          // wavefronts of a workgroup
+};
+UnitGrid unit_grid(const Problem& pb, int pairs) {
+  const int64_t B = n_sequences(pb), G = max_group(pb), rb = ceil_div(pb.Hq / pb.Hkv, 16);
+  UnitGrid u;
+  // fewer than two groups a die: plain order, so that neighbours spread over the dies
+  const int64_t groups = B / G * pb.Hkv;
+  u.groups8 = groups >= 16 && G > 1 ? (int)((groups + 7) / 8) : 0;
+  u.blocks = u.groups8 > 0 ? u.groups8 * 8 * G * rb : B * pb.Hkv * rb;
+  // eight wavefronts while every workgroup has a compute unit to itself (128 units x 964 keys: 11.7 us, 12.7 with four),
+  // four when they queue: two workgroups then share a compute unit and one starts under the other's end (512 x 1024:
+  // 22.5 us, 24.7 with eight).  Trees and pages of fewer rows than a tile have the wide form only.
+  const bool one_form = (pb.block_table && pb.page_shift < 5) || pb.n_levels > 1;
+  u.nw = u.blocks > pairs && !one_form ? 4 : wide_waves(pb.dtype == RLDA_F32, pb.d);
+  return u;
+}
+
 // the form of one store type and head dimension: pages of fewer rows than a tile, a tree, or two segments
 template <int KIND, int D, bool EXACT>
 hipError_t launch_form(const UnitParams& P, int nw, int64_t blocks, hipStream_t stream) {
-  constexpr int WIDE = KIND == KV_F32 && D == 128 ? 4 : 8;   // two fp32 tiles of 128 columns take half a SIMD's registers
+  constexpr int WIDE = wide_waves(KIND == KV_F32, D);
   if (P.table && P.page_shift < 5) {                          // never EXACT = false: the shared-prefix path refuses these
     if constexpr (EXACT) return launch<KIND, D, EXACT, WIDE, 2, true>(P, blocks, stream);
     return hipErrorInvalidValue;
@@ -417,8 +441,9 @@ hipError_t launch_form(const UnitParams& P, int nw, int64_t blocks, hipStream_t 
 
 }  // namespace
 
-// stores, q and outputs start on 16 bytes (the loads are that wide), lengths fit the 32-bit tile arithmetic
-bool unit_supported(const Problem& pb) {
+// stores, q and outputs start on 16 bytes (the loads are that wide), lengths fit the 32-bit tile arithmetic, and the
+// launch its limit of 2^32 threads (the simple kernel spends 64 threads on a row and takes the calls beyond)
+bool unit_supported(const Problem& pb, int pairs) {
   if (!(pb.scale - pb.scale == 0.f)) return false;                     // an infinite or NaN factor: the simple kernel's result
   uintptr_t a = reinterpret_cast<uintptr_t>(pb.q) | reinterpret_cast<uintptr_t>(pb.out) |
                 reinterpret_cast<uintptr_t>(pb.k_suffix) | reinterpret_cast<uintptr_t>(pb.v_suffix);
@@ -433,8 +458,9 @@ bool unit_supported(const Problem& pb) {
     cap += pb.Lp_cap;
   }
   if ((a & 15u) || cap > (int64_t)1 << 30) return false;
-  const int64_t rb = ceil_div(pb.Hq / pb.Hkv, 16);
-  return (n_sequences(pb) * pb.Hkv + 8 * (int64_t)max_group(pb)) * rb < (int64_t)1 << 31;
+  if (n_sequences(pb) == 0) return true;
+  const UnitGrid u = unit_grid(pb, pairs);
+  return u.blocks * 64 * u.nw < (int64_t)1 << 32;
 }
 
 // Where one launch beats the shared-prefix path's two.  The lengths live on the device, so the line is drawn on the
@@ -450,7 +476,7 @@ bool unit_preferred(const Problem& pb, int pairs) {
   int64_t shared = pb.Lp_cap;
   for (int l = 0; l < pb.n_levels; ++l) shared += pb.levels[l].cap;
   return pb.Ls_cap <= 2048 && 3 * shared + pb.Ls_cap <= 3600 &&
-         n_sequences(pb) * pb.Hkv * (shared + pb.Ls_cap) <= (int64_t)2048 * pairs && unit_supported(pb);
+         n_sequences(pb) * pb.Hkv * (shared + pb.Ls_cap) <= (int64_t)2048 * pairs && unit_supported(pb, pairs);
 }
 
 hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t stream) {
@@ -475,15 +501,11 @@ hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t str
   P.qsign = pb.scale < 0.f ? (pb.dtype == RLDA_F32 ? 0x80000000u : 0x80008000u) : 0u;
   P.table = pb.block_table; P.page_shift = pb.page_shift; P.max_pages = pb.max_pages; P.n_pages = pb.n_pages;
   P.active = pb.seq_active; P.kscale = pb.k_scale; P.vscale = pb.v_scale;
-  // fewer than two groups a die: plain order, so that neighbours spread over the dies
-  const int64_t groups = (int64_t)(P.B / P.G) * P.Hkv;
-  P.groups8 = groups >= 16 && P.G > 1 ? (int)((groups + 7) / 8) : 0;
-  const int64_t blocks = P.groups8 > 0 ? (int64_t)P.groups8 * 8 * P.G * P.RB : (int64_t)P.B * P.Hkv * P.RB;
-  if (blocks == 0) return hipSuccess;
-  // eight wavefronts while every workgroup has a compute unit to itself (128 units x 964 keys: 11.7 us, 12.7 with four),
-  // four when they queue: two workgroups then share a compute unit and one starts under the other's end (512 x 1024:
-  // 22.5 us, 24.7 with eight)
-  const int nw = blocks > pairs ? 4 : 8;
+  if (P.B == 0) return hipSuccess;
+  const UnitGrid grid = unit_grid(pb, pairs);
+  P.groups8 = grid.groups8;
+  const int64_t blocks = grid.blocks;
+  const int nw = grid.nw;
   if (pb.dtype == RLDA_F32)
     return pb.d == 64 ? launch_form<KV_F32, 64, true>(P, nw, blocks, stream) : launch_form<KV_F32, 128, true>(P, nw, blocks, stream);
   if (pb.dtype == RLDA_BF16_KV8) {

@@ -41,3 +41,16 @@ def test_how_many_units_fill_the_chip_follows_the_device(cus, units):
     for n, want in ((units, UNIT), (units + 1, SHARED)):
         assert B.rl_decode_attn_debug_route(desc(P=n, G=1, Hq=8, Hkv=1, Lp=512, Ls=512), cus) == want
         assert B.rl_decode_attn_debug_route(tree(n), cus) == want
+
+
+def test_a_launch_holds_less_than_two_to_the_32_threads():
+    """What one launch cannot hold stays on the simple kernel, which spends fewer threads on a row.  One query head per KV
+    head, one-row stores: 256 threads a sequence, 512 with pages of fewer rows than a tile."""
+    one = lambda n, G=1, **kw: B.rl_decode_attn_debug_route(desc(P=n, G=G, Hq=1, Hkv=1, d=64, Lp=1, Ls=1, **kw))
+    assert [one((1 << 24) + k) for k in (-1, 0, 1)] == [UNIT, SIMPLE, SIMPLE]
+    assert [one((1 << 22) + k, 4) for k in (-8, -7, 0)] == [UNIT, SIMPLE, SIMPLE]     # groups rounded up to the eight dies
+    assert one((1 << 23) + 1, algo=SIMPLE) == SIMPLE and one(1 << 30) == SIMPLE
+    ds = B.make_paged_desc(B.RLDA_BF16, 1 << 23, 1, 1, 1, 64, 1, 1, 1, 1, 0.1, block_table=1 << 20)
+    assert B.rl_decode_attn_debug_route(ds) == SIMPLE
+    ds.P -= 1
+    assert B.rl_decode_attn_debug_route(ds) == UNIT
