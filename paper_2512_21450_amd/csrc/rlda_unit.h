@@ -24,6 +24,7 @@
 #include "rlda_internal.h"
 #include "rlda_sched.h"
 
+#include <float.h>
 #include <math.h>
 
 #include <mutex>
@@ -51,8 +52,8 @@ struct UnitParams {
   int n_seg;
   int B, G, Hq, Hkv, r, RB;        // r = Hq / Hkv query rows in RB blocks of 16
   int groups8;                     // (prompt, KV head) groups rounded up to the dies, 0: units in plain order
-  float c, c_lo;                   // |scale| * log2(e) and what its rounding left; 1 and 0 when the scale is 0
-  uint32_t qsign, qmask;           // q bits: & qmask (0 when the scale is 0), ^ qsign (a negative scale), per 16-bit half or word
+  float scale, c, c_lo;            // and |scale| * log2(e) with what its rounding left; 1 and 0 when the scale is 0
+  uint32_t qsign, qmask;           // q bits: & qmask (0 when the scale is 0), ^ qsign (for a negative factor), per 16-bit half or word
   const int32_t* table;            // paged suffix: [B, max_pages] page ids, else null
   int page_shift, max_pages, n_pages;
   const uint8_t* active;
@@ -210,15 +211,19 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     }
   };
 
-  const float ks = KIND == KV_F8 && P.kscale ? P.kscale[j] : 1.f;
-  const float c = P.c * ks;
-  const float c_lo = fmaf(P.c, ks, -c) + P.c_lo * ks;  // EXACT: a score up to 40 would feel the rounding of c
+  // The factor of the exponents meets differences of products only, so that the size of the scores costs a weight
+  // nothing, and is kept positive and finite (a difference of 0 or -inf times it has to stay).  EXACT: its rounding, the
+  // same for all keys, would show in lse.
+  const float ks = KIND == KV_F8 && P.kscale ? P.kscale[j] : 1.f, kabs = fabsf(ks);
+  float c = P.c * kabs, c_lo = fmaf(P.c, kabs, -c) + P.c_lo * kabs;
+  if (c < FLT_MIN) { c = FLT_MIN; c_lo = 0.f; }
+  if (c > FLT_MAX) { c = FLT_MAX; c_lo = 0.f; }
   const float vfac = KIND == KV_F8 && P.vscale ? P.vscale[j] : 1.f;
 
   f32x4 O[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) O[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l = 0.f;                        // m: a product q . k, not yet times the scale
 
   Tile cur;
   u32x4 qr[NQ];
@@ -231,7 +236,8 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     __builtin_amdgcn_wave_barrier();
 
     // ---- scores of this lane's row (m16) for keys 4 g + x and 16 + 4 g + x
-    f32x4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f};
+    // (fp32: two sums each, half as long a chain of roundings and of waits)
+    f32x4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f}, s2{0.f, 0.f, 0.f, 0.f}, s3{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < L_::NF; ++i) {
       const int off = m16 * L_::LROWB + (((4 * i + g) ^ L_::kswz(m16)) << 4);     // the pattern repeats after 16 rows
@@ -242,15 +248,18 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
       } else {
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-          s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k0[x]), __uint_as_float(qr[i][x]), s0, 0, 0, 0);
-          s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k1[x]), __uint_as_float(qr[i][x]), s1, 0, 0, 0);
+          f32x4& a = i & 1 ? s2 : s0;
+          f32x4& d = i & 1 ? s3 : s1;
+          a = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k0[x]), __uint_as_float(qr[i][x]), a, 0, 0, 0);
+          d = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k1[x]), __uint_as_float(qr[i][x]), d, 0, 0, 0);
         }
       }
     }
+    if constexpr (KIND == KV_F32) { s0 += s2; s1 += s3; }
     const int nvalid = cur.last + 1;
 
-    // ---- online softmax in base 2; the factor c > 0 goes into the exponent's fma, and a row's reference maximum
-    // moves only when a tile exceeds it by 2^8 (fp32 holds the larger sums without loss)
+    // ---- online softmax in base 2; a row's reference maximum moves only when a tile exceeds it by a factor of 2^8
+    // in the weights (fp32 holds the larger sums without loss)
     float sv[8];
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
@@ -260,9 +269,9 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     float tm = max_raw(max_raw(max_raw(sv[0], sv[1]), max_raw(sv[2], sv[3])),
                        max_raw(max_raw(sv[4], sv[5]), max_raw(sv[6], sv[7])));
     tm = row_max(tm);
-    const float mn = max_raw(m, tm * c);
-    if (__any(mn > m + 8.f)) {                         // a wavefront's first tile: -inf + 8 = -inf
-      const float al = __builtin_amdgcn_exp2f(m - mn);
+    const float mn = max_raw(m, tm);
+    if (__any((mn - m) * c > 8.f)) {                   // a wavefront's first tile: m = -inf
+      const float al = __builtin_amdgcn_exp2f((m - mn) * c);
       l *= al;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) O[ct] *= al;
@@ -271,10 +280,10 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     float p[8];
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
-      const float e = fmaf(sv[x], c, -m);
-      p[x] = __builtin_amdgcn_exp2f(EXACT && sv[x] != -INFINITY ? fmaf(sv[x], c_lo, e) : e);
-      l += p[x];
+      const float dx = sv[x] - m, e = dx * c;
+      p[x] = __builtin_amdgcn_exp2f(EXACT && sv[x] != -INFINITY ? fmaf(dx, c_lo, e) : e);
     }
+    l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
 
     store(vst, vr, L_::vswz);
     if constexpr (MORE) load(nxt, nxt.v, vr);
@@ -335,7 +344,8 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     cur = tile_of(wv);
     load(cur, cur.k, kr);
     load(cur, cur.v, vr);
-    const uint32_t qm = m16 < nr ? P.qmask : 0u, qs = m16 < nr ? P.qsign : 0u;
+    const uint32_t qm = m16 < nr ? P.qmask : 0u;
+    const uint32_t qs = m16 < nr && (P.scale < 0.f) != (ks < 0.f) ? P.qsign : 0u;
 #pragma unroll
     for (int i = 0; i < NQ; ++i) qr[i] = (qr[i] & qm) ^ qs;
     // the last step is a copy of its own: the waits of the others then count exactly the loads that follow
@@ -365,7 +375,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     float L = 0.f;
     f32x4 acc{0.f, 0.f, 0.f, 0.f};
     for (int w = 0; w < nw; ++w) {
-      const float a = __builtin_amdgcn_exp2f(wm[w][row] - M);
+      const float a = __builtin_amdgcn_exp2f((wm[w][row] - M) * c);
       L = fmaf(a, wl[w][row], L);
       const f32x4 o = *RLDA_LDS(const f32x4, lds + w * OSTRIDE + row * OROWB + ((ch ^ row) << 4));
 #pragma unroll
@@ -374,7 +384,11 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     const size_t orow = (size_t)b * P.Hq + h0 + row;
     const float inv = T > 0 ? vfac / L : 0.f;
     *reinterpret_cast<f32x4*>(P.out + orow * D + 4 * ch) = acc * inv;
-    if (P.lse && ch == 0) P.lse[orow] = T > 0 ? (M + __builtin_amdgcn_logf(L)) * 0.69314718055994531f : -INFINITY;
+    if (P.lse && ch == 0) {
+      const float f = fabsf(P.scale) * kabs, f_lo = f <= FLT_MAX ? fmaf(fabsf(P.scale), kabs, -f) : 0.f;
+      const float log_l = __builtin_amdgcn_logf(L) * 0.69314718055994531f;
+      P.lse[orow] = T > 0 ? fmaf(M, f, fmaf(M, f_lo, log_l)) : -INFINITY;
+    }
   }
 }
 
@@ -495,10 +509,11 @@ hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t str
   P.n_seg = n;
   P.B = (int)n_sequences(pb); P.G = max_group(pb); P.Hq = pb.Hq; P.Hkv = pb.Hkv;
   P.r = pb.Hq / pb.Hkv; P.RB = ceil_div(P.r, 16);
+  P.scale = pb.scale;
   const double c = pb.scale == 0.f ? 1.0 : fabs((double)pb.scale) * 1.4426950408889634;
-  P.c = (float)c; P.c_lo = (float)(c - (double)P.c);
+  P.c = (float)c; P.c_lo = P.c <= FLT_MAX ? (float)(c - (double)P.c) : 0.f;
   P.qmask = pb.scale == 0.f ? 0u : 0xffffffffu;
-  P.qsign = pb.scale < 0.f ? (pb.dtype == RLDA_F32 ? 0x80000000u : 0x80008000u) : 0u;
+  P.qsign = pb.dtype == RLDA_F32 ? 0x80000000u : 0x80008000u;
   P.table = pb.block_table; P.page_shift = pb.page_shift; P.max_pages = pb.max_pages; P.n_pages = pb.n_pages;
   P.active = pb.seq_active; P.kscale = pb.k_scale; P.vscale = pb.v_scale;
   if (P.B == 0) return hipSuccess;
