@@ -78,6 +78,8 @@ __device__ __forceinline__ float row_max(float t) {
   const u32p b = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
   return max_raw(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
+// a reference to subtract: products may be -inf (infinite keys, or an overflow), and a row may have met no other yet
+__device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
 __device__ __forceinline__ u32x2 e4m3x4_to_bf16(uint32_t w) {            // exact
   const bf16x2 lo = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, false);
   const bf16x2 hi = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, true);
@@ -271,16 +273,17 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     tm = row_max(tm);
     const float mn = max_raw(m, tm);
     if (__any((mn - m) * c > 8.f)) {                   // a wavefront's first tile: m = -inf
-      const float al = __builtin_amdgcn_exp2f((m - mn) * c);
+      const float al = __builtin_amdgcn_exp2f((m - finite_ref(mn)) * c);
       l *= al;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) O[ct] *= al;
       m = mn;
     }
     float p[8];
+    const float ref = finite_ref(m);
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
-      const float dx = sv[x] - m, e = dx * c;
+      const float dx = sv[x] - ref, e = dx * c;
       p[x] = __builtin_amdgcn_exp2f(EXACT && sv[x] != -INFINITY ? fmaf(dx, c_lo, e) : e);
     }
     l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
@@ -387,7 +390,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     if (P.lse && ch == 0) {
       const float f = fabsf(P.scale) * kabs, f_lo = f <= FLT_MAX ? fmaf(fabsf(P.scale), kabs, -f) : 0.f;
       const float log_l = __builtin_amdgcn_logf(L) * 0.69314718055994531f;
-      P.lse[orow] = T > 0 ? fmaf(M, f, fmaf(M, f_lo, log_l)) : -INFINITY;
+      P.lse[orow] = L > 0.f ? fmaf(M, f, fmaf(M, f_lo, log_l)) : -INFINITY;   // no key, or none that is a number
     }
   }
 }
