@@ -384,6 +384,28 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
 #pragma unroll
       for (int x = 0; x < 4; ++x) acc[x] = fmaf(a, o[x], acc[x]);
     }
+    // An infinite value gives an infinite result; but split weights leave pieces of 0 or below zero, and rows past the
+    // length repeat the last one at weight 0, and either makes it NaN.  Such columns are the sum of what is not finite.
+    if constexpr (KIND != KV_F8) {                     // e4m3 has no infinity
+      const bool off = !(fabsf(acc[0]) + fabsf(acc[1]) + fabsf(acc[2]) + fabsf(acc[3]) < INFINITY);
+      if (off && L < INFINITY) {
+        f32x4 odd{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < T; ++t) {
+          const Tile x = tile_of(t);
+          for (int i = 0; i <= x.last; ++i) {
+            const char* src = row_at(x, x.v, i, 4 * ch * L_::EB);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const float v = KIND == KV_F32 ? reinterpret_cast<const float*>(src)[k]
+                                             : __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(src)[k] << 16);
+              if (!(fabsf(v) < INFINITY)) odd[k] += v;
+            }
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] = odd[k] == 0.f ? acc[k] : odd[k];
+      }
+    }
     const size_t orow = (size_t)b * P.Hq + h0 + row;
     const float inv = T > 0 ? vfac / L : 0.f;
     *reinterpret_cast<f32x4*>(P.out + orow * D + 4 * ch) = acc * inv;
