@@ -214,12 +214,17 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   };
 
   // The factor of the exponents meets differences of products only, so that the size of the scores costs a weight
-  // nothing, and is kept positive and finite (a difference of 0 or -inf times it has to stay).  EXACT: its rounding, the
-  // same for all keys, would show in lse.
+  // nothing, and is kept positive and finite (a difference of 0 or -inf times it has to stay).  EXACT: what its rounding
+  // left, the same for all keys, would show in lse; that part is positive too, for the same reason.
   const float ks = KIND == KV_F8 && P.kscale ? P.kscale[j] : 1.f, kabs = fabsf(ks);
   float c = P.c * kabs, c_lo = fmaf(P.c, kabs, -c) + P.c_lo * kabs;
   if (c < FLT_MIN) { c = FLT_MIN; c_lo = 0.f; }
   if (c > FLT_MAX) { c = FLT_MAX; c_lo = 0.f; }
+  if (EXACT) {
+    const float below = __uint_as_float(__float_as_uint(c) - 1);
+    if (!(c_lo > 0.f) && c > FLT_MIN) { c_lo += c - below; c = below; }
+    c_lo = max_raw(c_lo, FLT_MIN);
+  }
   const float vfac = KIND == KV_F8 && P.vscale ? P.vscale[j] : 1.f;
 
   f32x4 O[CT];
@@ -284,7 +289,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
       const float dx = sv[x] - ref, e = dx * c;
-      p[x] = __builtin_amdgcn_exp2f(EXACT && sv[x] != -INFINITY ? fmaf(dx, c_lo, e) : e);
+      p[x] = __builtin_amdgcn_exp2f(EXACT ? fmaf(dx, c_lo, e) : e);
     }
     l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
 
@@ -371,6 +376,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   if (g == 0) { wm[wv][m16] = m; wl[wv][m16] = l; }
   __syncthreads();
   const int nw = min(NW, T);                           // wavefronts that had a tile
+  bool odd = false;                                    // a column that is not finite where the row's weights are
   for (int it = tid; it < nr * OC; it += 64 * NW) {
     const int row = it / OC, ch = it % OC;
     float M = -INFINITY;
@@ -384,35 +390,44 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
 #pragma unroll
       for (int x = 0; x < 4; ++x) acc[x] = fmaf(a, o[x], acc[x]);
     }
-    // An infinite value gives an infinite result; but split weights leave pieces of 0 or below zero, and rows past the
-    // length repeat the last one at weight 0, and either makes it NaN.  Such columns are the sum of what is not finite.
-    if constexpr (KIND != KV_F8) {                     // e4m3 has no infinity
-      const bool off = !(fabsf(acc[0]) + fabsf(acc[1]) + fabsf(acc[2]) + fabsf(acc[3]) < INFINITY);
-      if (off && L < INFINITY) {
-        f32x4 odd{0.f, 0.f, 0.f, 0.f};
-        for (int t = 0; t < T; ++t) {
-          const Tile x = tile_of(t);
-          for (int i = 0; i <= x.last; ++i) {
-            const char* src = row_at(x, x.v, i, 4 * ch * L_::EB);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const float v = KIND == KV_F32 ? reinterpret_cast<const float*>(src)[k]
-                                             : __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(src)[k] << 16);
-              if (!(fabsf(v) < INFINITY)) odd[k] += v;
-            }
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[k] = odd[k] == 0.f ? acc[k] : odd[k];
-      }
-    }
     const size_t orow = (size_t)b * P.Hq + h0 + row;
     const float inv = T > 0 ? vfac / L : 0.f;
-    *reinterpret_cast<f32x4*>(P.out + orow * D + 4 * ch) = acc * inv;
+    acc *= inv;
+    odd = odd || (L < INFINITY && !(fabsf(acc[0]) + fabsf(acc[1]) + fabsf(acc[2]) + fabsf(acc[3]) < INFINITY));
+    *reinterpret_cast<f32x4*>(P.out + orow * D + 4 * ch) = acc;
     if (P.lse && ch == 0) {
       const float f = fabsf(P.scale) * kabs, f_lo = f <= FLT_MAX ? fmaf(fabsf(P.scale), kabs, -f) : 0.f;
       const float log_l = __builtin_amdgcn_logf(L) * 0.69314718055994531f;
       P.lse[orow] = L > 0.f ? fmaf(M, f, fmaf(M, f_lo, log_l)) : -INFINITY;   // no key, or none that is a number
+    }
+  }
+  // An infinite value gives an infinite result; but split weights leave pieces of 0 or below zero, and rows past the
+  // length repeat the last one at weight 0, and either makes it NaN.  Such columns are the sum of what is not finite.
+  // (In a loop of its own: inside the one above it cost 0.3 us of 9 without being entered.)
+  if constexpr (KIND != KV_F8) {                       // e4m3 has no infinity
+    if (!odd) return;
+    for (int it = tid; it < nr * OC; it += 64 * NW) {
+      const int row = it / OC, ch = it % OC;
+      float L = 0.f;
+      for (int w = 0; w < nw; ++w) L += wl[w][row];
+      if (!(L < INFINITY)) continue;                   // a score that is not a number: the row is none
+      f32x4 sum{0.f, 0.f, 0.f, 0.f};
+      for (int t = 0; t < T; ++t) {
+        const Tile x = tile_of(t);
+        for (int i = 0; i <= x.last; ++i) {
+          const char* src = row_at(x, x.v, i, 4 * ch * L_::EB);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float v = KIND == KV_F32 ? reinterpret_cast<const float*>(src)[k]
+                                           : __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(src)[k] << 16);
+            if (!(fabsf(v) < INFINITY)) sum[k] += v;
+          }
+        }
+      }
+      float* const o = P.out + ((size_t)b * P.Hq + h0 + row) * D + 4 * ch;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (sum[k] != 0.f) o[k] = sum[k];
     }
   }
 }
