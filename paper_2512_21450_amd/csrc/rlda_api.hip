@@ -119,13 +119,13 @@ int check_tree(const Problem& pb) {
 }
 
 // The kernels a valid, non-empty problem runs on, on a device with `pairs` workgroup pairs.  One launch takes the small
-// batches of the shared-prefix path and what that path does not take; an explicit algo never changes its kernels.
+// batches of the shared-prefix path and most of what that path does not take; an explicit algo never changes its kernels.
 enum Route { ROUTE_SIMPLE = RLDA_ALGO_SIMPLE, ROUTE_SHARED = RLDA_ALGO_SHARED, ROUTE_UNIT = RLDA_ROUTE_UNIT };
 Route route(const Problem& pb, int planned, int pairs) {
   const bool tree = pb.n_levels > 0;                         // has no algo field: chosen as under AUTO
   if (planned == RLDA_ALGO_SHARED)
     return (tree || pb.algo == RLDA_ALGO_AUTO) && rlda::unit_preferred(pb, pairs) ? ROUTE_UNIT : ROUTE_SHARED;
-  return pb.algo == RLDA_ALGO_AUTO && rlda::unit_supported(pb, pairs) ? ROUTE_UNIT : ROUTE_SIMPLE;
+  return pb.algo == RLDA_ALGO_AUTO && rlda::unit_supported(pb, pairs) && rlda::unit_pays(pb, pairs) ? ROUTE_UNIT : ROUTE_SIMPLE;
 }
 
 hipError_t launch(const Problem& pb, int planned, hipStream_t stream, hipEvent_t mid) {

@@ -70,6 +70,7 @@ hipError_t launch_shared(const Problem& pb, hipStream_t stream, hipEvent_t mid);
 // `exact`: softmax weights enter the value contraction with 24 bits, else (d = 128 only) with 16
 // `pairs`: workgroup pairs of the device at hand (device_pairs), which stand for its compute units
 bool unit_supported(const Problem& pb, int pairs);
+bool unit_pays(const Problem& pb, int pairs);        // and runs faster here than on the simple kernel
 bool unit_preferred(const Problem& pb, int pairs);   // a problem of the shared-prefix path that runs faster here
 hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t stream);
 

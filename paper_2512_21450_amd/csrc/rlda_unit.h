@@ -457,24 +457,49 @@ hipError_t launch(const UnitParams& P, int64_t blocks, hipStream_t stream) {
 // two fp32 tiles of 128 columns take half a SIMD's registers
 constexpr int wide_waves(bool f32, int d) { return f32 && d == 128 ? 4 : 8; }
 
+// pages of fewer rows than a tile: every row is looked up
+bool row_lookup(const Problem& pb) { return pb.block_table && pb.page_shift < 5; }
+int64_t shared_cap(const Problem& pb) {
+  int64_t n = pb.Lp_cap;
+  for (int l = 0; l < pb.n_levels; ++l) n += pb.levels[l].cap;
+  return n;
+}
+
 // Grid of a problem (n_sequences > 0).
 struct UnitGrid {
   int groups8;                     // as in UnitParams
   int64_t blocks;
   int nw;                          // wavefronts of a workgroup
 };
-UnitGrid unit_grid(const Problem& pb, int pairs) {
-  const int64_t B = n_sequences(pb), G = max_group(pb), rb = ceil_div(pb.Hq / pb.Hkv, 16);
+// How many wavefronts a unit gets.  Eight while every workgroup has a compute unit to itself (128 units x 964 keys: 11.7 us,
+// 12.7 with four).  When workgroups queue, what counts is how many units are on their way at once: a workgroup holds the
+// LDS of all its wavefronts from the first length it reads to the last row it writes, so the more of them there are and
+// the shorter they are, the fewer wavefronts each may take.  Measured, us with 8 / 4 / 2 / 1 wavefronts:
+//   fp32, 64 columns    512 units x 1024 keys     42 / 38 / 50 / 61     1024 x 64     19 / 14 / 10.6 / 9.8
+//                      4096 x 64                   68 / 41 / 28 / 24     4096 x 1024  280 / 253 / 265 / 283
+//   bf16, 64 columns   1024 x 256                14.3 / 12.0 / 12.5 / 13.2       16384 x 32   104 / 56 / 36 / 29
+//   fp32, 128 columns   512 x 256                   - / 25 / 23 / 31     4096 x 64      - / 108 / 62 / 49
+//   small batches (two bf16 pieces), 1024 x 128  19.8 / 14.8 / 12.6 / 13.1        8192 x 64    137 / 85 / 66 / 66
+//   pages of 16 rows, bf16, 128 columns  256 x 1024  26 / 39 / 62 / 108  4096 x 256   223 / 134 / 134 / 117
+UnitGrid unit_grid(const Problem& pb, int pairs, bool exact) {
+  const int64_t B = n_sequences(pb), G = max_group(pb), rb = ceil_div(pb.Hq / pb.Hkv, 16), keys = shared_cap(pb) + pb.Ls_cap;
   UnitGrid u;
   // fewer than two groups a die: plain order, so that neighbours spread over the dies
   const int64_t groups = B / G * pb.Hkv;
   u.groups8 = groups >= 16 && G > 1 ? (int)((groups + 7) / 8) : 0;
   u.blocks = u.groups8 > 0 ? u.groups8 * 8 * G * rb : B * pb.Hkv * rb;
-  // eight wavefronts while every workgroup has a compute unit to itself (128 units x 964 keys: 11.7 us, 12.7 with four),
-  // four when they queue: two workgroups then share a compute unit and one starts under the other's end (512 x 1024:
-  // 22.5 us, 24.7 with eight).  Trees and pages of fewer rows than a tile have the wide form only.
-  const bool one_form = (pb.block_table && pb.page_shift < 5) || pb.n_levels > 1;
-  u.nw = u.blocks > pairs && !one_form ? 4 : wide_waves(pb.dtype == RLDA_F32, pb.d);
+  const bool f32 = pb.dtype == RLDA_F32, queue = u.blocks > 2 * (int64_t)pairs, many = u.blocks > 4 * (int64_t)pairs;
+  if (u.blocks <= pairs) {
+    u.nw = wide_waves(f32, pb.d);
+  } else if (row_lookup(pb) || pb.n_levels > 1) {
+    u.nw = many ? 1 : 2;
+  } else if (f32 && pb.d == 128) {
+    u.nw = queue && keys <= 256 ? 1 : 2;
+  } else if (!queue || (exact && (keys >= 512 || (keys >= 256 && u.blocks <= 8 * (int64_t)pairs)))) {
+    u.nw = 4;
+  } else {
+    u.nw = many && (!exact || keys <= 128) ? 1 : 2;
+  }
   return u;
 }
 
@@ -482,14 +507,20 @@ UnitGrid unit_grid(const Problem& pb, int pairs) {
 template <int KIND, int D, bool EXACT>
 hipError_t launch_form(const UnitParams& P, int nw, int64_t blocks, hipStream_t stream) {
   constexpr int WIDE = wide_waves(KIND == KV_F32, D);
-  if (P.table && P.page_shift < 5) {                          // never EXACT = false: the shared-prefix path refuses these
-    if constexpr (EXACT) return launch<KIND, D, EXACT, WIDE, 2, true>(P, blocks, stream);
-    return hipErrorInvalidValue;
-  }
-  if (P.n_seg != 2) {
-    if constexpr (KIND == KV_BF16 && D == 128 && !EXACT) return launch<KIND, D, EXACT, WIDE, MAX_SEG>(P, blocks, stream);
-    return hipErrorInvalidValue;
-  }
+  if constexpr (EXACT)                                        // the shared-prefix path refuses small pages, so only here
+    if (P.table && P.page_shift < 5) {
+      if (nw == 1) return launch<KIND, D, EXACT, 1, 2, true>(P, blocks, stream);
+      if (nw == 2) return launch<KIND, D, EXACT, 2, 2, true>(P, blocks, stream);
+      return launch<KIND, D, EXACT, WIDE, 2, true>(P, blocks, stream);
+    }
+  if constexpr (KIND == KV_BF16 && D == 128 && !EXACT)        // what a tree holds
+    if (P.n_seg != 2) {
+      if (nw == 1) return launch<KIND, D, EXACT, 1, MAX_SEG>(P, blocks, stream);
+      if (nw == 2) return launch<KIND, D, EXACT, 2, MAX_SEG>(P, blocks, stream);
+      return launch<KIND, D, EXACT, WIDE, MAX_SEG>(P, blocks, stream);
+    }
+  if (nw == 1) return launch<KIND, D, EXACT, 1>(P, blocks, stream);
+  if (nw == 2) return launch<KIND, D, EXACT, 2>(P, blocks, stream);
   return nw == 4 ? launch<KIND, D, EXACT, 4>(P, blocks, stream) : launch<KIND, D, EXACT, WIDE>(P, blocks, stream);
 }
 
@@ -513,8 +544,47 @@ bool unit_supported(const Problem& pb, int pairs) {
   }
   if ((a & 15u) || cap > (int64_t)1 << 30) return false;
   if (n_sequences(pb) == 0) return true;
-  const UnitGrid u = unit_grid(pb, pairs);
-  return u.blocks * 64 * u.nw < (int64_t)1 << 32;
+  for (bool exact : {false, true}) {
+    const UnitGrid u = unit_grid(pb, pairs, exact);
+    if (u.blocks * 64 * u.nw >= (int64_t)1 << 32) return false;
+  }
+  return true;
+}
+
+// Where one wavefront per query head is faster than one workgroup per KV head, among what the shared-prefix path does not
+// take: few rows that share a KV head over few keys, so that little is shared and the tiles are mostly padding, and fp32
+// tiles whose rows are looked up one by one.  The line is drawn over r * (keys + 10), with r the heads per KV head and
+// the keys as capacities; measured, us unit / simple kernel, units x keys:
+//   fp32, 64 columns    r 1: 64 x 16 5.8 / 5.4, 64 x 24 5.7 / 6.5, 512 x 32 7.4 / 5.9, 1024 x 100 13.1 / 14.2,
+//                            4096 x 100 34 / 31, 4096 x 128 41 / 42;   r 2: 4096 x 24 21.0 / 20.1, 4096 x 48 22 / 26
+//   fp32, 128 columns   r 1: 64 x 32 7.8 / 7.0, 512 x 64 11 / 12, 1024 x 100 21 / 19, 4096 x 128 85 / 80, 4096 x 300 177 / 187;
+//                       r 2: 4096 x 24 41 / 34, 4096 x 48 43 / 49;     r 4: 4096 x 1 43 / 36, 4096 x 16 42 / 49
+//   bf16, r 1           64 columns: 1024 x 4 5.9 / 6.8, 4096 x 16 10.2 / 8.1, 4096 x 48 11.1 / 12.2;
+//                       128: 4096 x 48 18.2 / 17.1, 4096 x 100 29 / 32
+//   pages of 16 rows    bf16, 128 columns: r 1: 1024 x 64 13 / 12, 1024 x 256 25 / 28, 4096 x 1024 429 / 319;
+//                       r 2: 4096 x 64 29 / 37;                        bf16, 64 columns: as without pages
+//                       fp32, 64: r 1: 1024 x 256 29 / 26, 4096 x 1024 474 / 307;    r 4: 256 x 32 7.9 / 6.7, 4096 x 32 31 / 37
+//                       fp32, 128: r 1: 1024 x 1024 385 / 199;  r 2: 4096 x 256 389 / 250;  r 4: 4096 x 64 115 / 119
+// e4m3 bytes cost the simple kernel's vector ALU too much at any size.
+bool unit_pays(const Problem& pb, int pairs) {
+  if (pb.dtype == RLDA_BF16_KV8 || n_sequences(pb) == 0) return true;
+  const int64_t r = pb.Hq / pb.Hkv, keys = shared_cap(pb) + pb.Ls_cap, units = n_sequences(pb) * pb.Hkv;
+  const bool f32 = pb.dtype == RLDA_F32, wide = pb.d == 128;
+  const bool queue = units > pairs, many = units > 4 * (int64_t)pairs;
+  constexpr int64_t never = INT64_MAX;
+  int64_t line = 0;
+  if (row_lookup(pb) && f32 && wide) {
+    line = !queue ? 100 : (r <= 2 ? never : 200);
+  } else if (row_lookup(pb) && f32) {
+    line = queue && r == 1 ? (many ? never : 400) : 170;
+  } else if (row_lookup(pb) && wide) {
+    line = r == 1 ? (many ? never : 100) : 60;
+  } else if (f32) {
+    line = !queue ? (wide ? 45 : 30) : (r > 1 ? 70 : (wide && units > 2 * (int64_t)pairs ? 150 : (many ? 115 : 60)));
+  } else if (many && r == 1) {
+    line = wide ? 70 : 50;
+  }
+  return r * (keys + 10) > line;
 }
 
 // Where one launch beats the shared-prefix path's two.  The lengths live on the device, so the line is drawn on the
@@ -524,12 +594,12 @@ bool unit_supported(const Problem& pb, int pairs) {
 //    64 x (1024 + 512)  14.6 / 14.2   128 x (512 + 2048)  34.5 / 37.2   256 x (1024 + 512)  20.2 / 25.9
 //    64 x (1536 + 512)  17.4 / 16.4   128 x (16 + 4000)   53.4 / 53.7   512 x (512 + 512)   34.8 / 38.4
 //    64 x (16 + 4000)   46.0 / 36.7  1024 x (512 + 16)    22.8 / 23.3  1024 x (16 + 512)    53.1 / 56.4
-// and on e4m3 stores 64 x (1024 + 1024) 18.0 / 14.4, 1024 x (512 + 16) 22.9 / 21.7.  All on 256 compute units; the
+// and on e4m3 stores 64 x (1024 + 1024) 18.0 / 14.4, 1024 x (512 + 16) 22.9 / 21.7.  Units of hardly any key, which
+// wait for nothing but their turn: 16384 x (16 + 16) 58 / 70, 65536 x (1 + 1) 163 / 149.  All on 256 compute units; the
 // number of units that fills the chip follows the device's, as the other path does (2048 keys per workgroup pair).
 bool unit_preferred(const Problem& pb, int pairs) {
-  int64_t shared = pb.Lp_cap;
-  for (int l = 0; l < pb.n_levels; ++l) shared += pb.levels[l].cap;
-  return pb.Ls_cap <= 2048 && 3 * shared + pb.Ls_cap <= 3600 &&
+  const int64_t shared = shared_cap(pb);
+  return pb.Ls_cap <= 2048 && 3 * shared + pb.Ls_cap <= 3600 && n_sequences(pb) * pb.Hkv <= (int64_t)64 * pairs &&
          n_sequences(pb) * pb.Hkv * (shared + pb.Ls_cap) <= (int64_t)2048 * pairs && unit_supported(pb, pairs);
 }
 
@@ -557,7 +627,7 @@ hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t str
   P.table = pb.block_table; P.page_shift = pb.page_shift; P.max_pages = pb.max_pages; P.n_pages = pb.n_pages;
   P.active = pb.seq_active; P.kscale = pb.k_scale; P.vscale = pb.v_scale;
   if (P.B == 0) return hipSuccess;
-  const UnitGrid grid = unit_grid(pb, pairs);
+  const UnitGrid grid = unit_grid(pb, pairs, exact);
   P.groups8 = grid.groups8;
   const int64_t blocks = grid.blocks;
   const int nw = grid.nw;

@@ -1,0 +1,139 @@
+"""The one-launch decode kernel over batches of every size: a unit gets eight, four, two or one wavefronts by how many units
+there are, and batches of few rows over few keys go back to the kernels they came from.
+
+Parity with the fp64 oracle on both sides of the lines, at the tolerances of test_gpu_unit; and, with a margin of 1.4 on
+times that were 2 to 20 times as long before, that AUTO does not lose to the kernel it replaces."""
+import numpy as np
+import pytest
+
+from paper_2512_21450_amd import workloads as wl
+from tests import util
+from tests.test_gpu_unit import EXACT, LEAN, B, case, compare  # noqa: F401  (B is the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("keys", [100, 300, 600])
+@pytest.mark.parametrize("units", [260, 516, 1028, 2052])                # 256, 512, 1024, 2048 are lines
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("e4m3", 64), ("bf16", 128), ("e4m3", 128)])
+def test_numbers_of_units(B, dtype, d, units, keys):  # noqa: F811
+    if units * keys > 700_000:                                           # the oracle's time; the line lies below 512 keys
+        keys = 290
+    lean = d == 128 and dtype != "f32" and 3 * (keys // 2) + keys // 2 <= 3600 and units * keys <= 1 << 19
+    x = case(units, units // 4, 4, 4, 1, d, keys // 2, keys - keys // 2, dtype)
+    out, lse = util.gpu_run(util.to_device(x), 0.1, 4)
+    ro, rl = util.oracle(x, 0.1, 4)
+    if d == 128 and dtype != "f32" and not lean:
+        util.compare(out, lse, ro, rl, "bf16", "shared-prefix kernels")
+    else:
+        compare(out, lse, ro, rl, LEAN if lean else EXACT, (dtype, d, units, keys))
+
+
+@pytest.mark.parametrize("units", [256, 260, 1028])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128), ("e4m3", 128)])
+def test_numbers_of_units_on_small_pages(B, dtype, d, units):  # noqa: F811
+    import torch
+    x = wl.to_pages(case(units + 1, units // 4, 4, 5, 1, d, 70, 130, dtype), 16, seed=2)
+    act = (np.arange(units) % 5 != 1).astype(np.uint8)
+    out, lse = util.gpu_run_paged(util.to_device(x), 0.1, 4, active=torch.from_numpy(act).cuda())
+    ro, rl = util.oracle_paged(x, 0.1, 4, active=act)
+    compare(out, lse, ro, rl, EXACT, (dtype, d, units))
+
+
+@pytest.mark.parametrize("units", [256, 264, 1032])
+def test_numbers_of_units_in_a_tree(B, units):  # noqa: F811
+    from oracle import ref
+    levels = [(8, 66, ("uniform", 66)), (4, 33, ("uniform", 33)), (2, 40, ("const", 40))]
+    x = wl.make_tree_inputs(units, units, 3, 1, 128, levels, 70, ("uniform", 70), empty=0.1)
+    lv = [tuple(util.to_device({"k": k, "v": v, "n": n}).values()) + (g,) for k, v, n, g in x["levels"]]
+    t = util.to_device({k: x[k] for k in ("q", "k_suffix", "v_suffix", "suffix_lens")})
+    out, lse = B.rl_decode_attn_tree(t["q"], lv, t["k_suffix"], t["v_suffix"], t["suffix_lens"], 0.1)
+    ro, rl = ref.decode_attn_tree_ref(x["q"], x["levels"], x["k_suffix"], x["v_suffix"], x["suffix_lens"], 0.1)
+    compare(out, lse, ro, rl, LEAN, units)
+
+
+# ---------------------------------------------------------------- times
+def us_per_call(fn, n=10, reps=5):
+    import torch
+    fn()
+    torch.cuda.synchronize()
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(s), torch.cuda.graph(g, stream=s):
+        for _ in range(n):
+            fn()
+    t = []
+    for _ in range(reps):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record(); g.replay(); b.record()
+        torch.cuda.synchronize()
+        t.append(a.elapsed_time(b) * 1e3 / n)
+    return sorted(t)[len(t) // 2]
+
+
+def stores(B, dtype, d, seqs, Hkv, r, Lp, Ls, G=4, page=0):  # noqa: F811
+    import torch
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    rnd = lambda *s: torch.randn(*s, device="cuda").to(dt)
+    P = seqs // G
+    x = dict(q=rnd(seqs, Hkv * r, d), kp=rnd(P, Hkv, Lp, d), vp=rnd(P, Hkv, Lp, d),
+             pl=torch.full((P,), Lp, dtype=torch.int32, device="cuda"), sl=torch.full((seqs,), Ls, dtype=torch.int32, device="cuda"),
+             out=torch.empty((seqs, Hkv * r, d), device="cuda"), lse=torch.empty((seqs, Hkv * r), device="cuda"))
+    if page:
+        n = -(-Ls // page)
+        x["table"] = torch.randperm(seqs * n, device="cuda").to(torch.int32).view(seqs, n)
+        x["ks"], x["vs"] = rnd(seqs * n, Hkv, page, d), rnd(seqs * n, Hkv, page, d)
+    else:
+        x["ks"], x["vs"] = rnd(seqs, Hkv, Ls, d), rnd(seqs, Hkv, Ls, d)
+
+    def call(algo):
+        import torch as th
+        if page:
+            ds = B.paged_desc_from_tensors(x["q"], x["kp"], x["vp"], x["pl"], x["ks"], x["vs"], x["table"], x["sl"], 0.1, G,
+                                           x["out"], x["lse"], algo=algo)
+            go = B.rl_decode_attn_paged_raw
+        else:
+            ds = B.desc_from_tensors(x["q"], x["kp"], x["vp"], x["pl"], x["ks"], x["vs"], x["sl"], 0.1, G, x["out"], x["lse"],
+                                     algo=algo)
+            go = B.rl_decode_attn_raw
+            ws = th.empty(max(256, B.rl_decode_attn_workspace_bytes(ds)), dtype=th.uint8, device="cuda")
+            ds.workspace, ds.workspace_bytes = ws.data_ptr(), ws.numel()
+            ds._keep = ws
+
+        def fn():
+            assert go(ds, th.cuda.current_stream().cuda_stream) == 0
+        return fn
+    return call
+
+
+@pytest.mark.parametrize("dtype,d,seqs,r,Lp,Ls,page,other", [
+    ("f32", 64, 8192, 1, 8, 8, 0, "SIMPLE"), ("f32", 64, 2048, 4, 16, 16, 0, "SIMPLE"), ("f32", 128, 1024, 1, 16, 16, 0, "SIMPLE"),
+    ("bf16", 64, 8192, 1, 8, 8, 0, "SIMPLE"), ("bf16", 64, 512, 1, 1, 1, 0, "SIMPLE"), ("f32", 64, 512, 1, 512, 512, 16, "SIMPLE"),
+    ("bf16", 128, 512, 1, 32, 32, 16, "SIMPLE"), ("f32", 128, 256, 1, 256, 256, 16, "SIMPLE"),
+    ("bf16", 128, 2048, 4, 16, 16, 0, "SHARED"), ("bf16", 128, 2048, 1, 1, 63, 0, "SHARED")])
+def test_auto_is_not_the_slower_choice(B, dtype, d, seqs, r, Lp, Ls, page, other):  # noqa: F811
+    call = stores(B, dtype, d, seqs, 8, r, Lp, Ls, 8 if other == "SHARED" else 4, page)
+    auto, forced = us_per_call(call(B.RLDA_ALGO_AUTO)), us_per_call(call(getattr(B, "RLDA_ALGO_" + other)))
+    print(f"\nAUTO {auto:.1f} us, {other} {forced:.1f} us")
+    assert auto <= 1.4 * forced, (auto, forced)
+
+
+def test_a_tree_of_many_short_segments_is_not_slower_than_the_shared_path(B):  # noqa: F811
+    """Against the two-launch call over one level that holds as many keys."""
+    import torch
+    seqs, Hkv, r = 1024, 8, 4
+    call = stores(B, "bf16", 128, seqs, Hkv, r, 32, 16, 8)
+    rnd = lambda *s: torch.randn(*s, device="cuda").bfloat16()
+    lv = [(rnd(seqs // g, Hkv, 16, 128), rnd(seqs // g, Hkv, 16, 128), torch.full((seqs // g,), 16, dtype=torch.int32, device="cuda"), g)
+          for g in (8, 2)]
+    q, ks, vs = rnd(seqs, Hkv * r, 128), rnd(seqs, Hkv, 16, 128), rnd(seqs, Hkv, 16, 128)
+    sl = torch.full((seqs,), 16, dtype=torch.int32, device="cuda")
+    out, lse = torch.empty((seqs, Hkv * r, 128), device="cuda"), torch.empty((seqs, Hkv * r), device="cuda")
+    ds = B.tree_desc_from_tensors(q, lv, ks, vs, sl, 0.1, out, lse)
+    ws = torch.empty(max(256, B.rl_decode_attn_tree_workspace_bytes(ds)), dtype=torch.uint8, device="cuda")
+    ds.workspace, ds.workspace_bytes = ws.data_ptr(), ws.numel()
+
+    def tree():
+        assert B.rl_decode_attn_tree_raw(ds, torch.cuda.current_stream().cuda_stream) == 0
+    auto, forced = us_per_call(tree), us_per_call(call(B.RLDA_ALGO_SHARED))
+    print(f"\ntree {auto:.1f} us, two launches over one level {forced:.1f} us")
+    assert auto <= 1.4 * forced, (auto, forced)

@@ -44,13 +44,48 @@ def test_how_many_units_fill_the_chip_follows_the_device(cus, units):
 
 
 def test_a_launch_holds_less_than_two_to_the_32_threads():
-    """What one launch cannot hold stays on the simple kernel, which spends fewer threads on a row.  One query head per KV
-    head, one-row stores: 256 threads a sequence, 512 with pages of fewer rows than a tile."""
-    one = lambda n, G=1, **kw: B.rl_decode_attn_debug_route(desc(P=n, G=G, Hq=1, Hkv=1, d=64, Lp=1, Ls=1, **kw))
+    """What one launch cannot hold stays on the simple kernel, which spends 64 threads on a row.  One query head per KV head:
+    256 threads a sequence with long stores, 64 with short ones or with pages of fewer rows than a tile."""
+    one = lambda n, G=1, Ls=600, **kw: B.rl_decode_attn_debug_route(desc(P=n, G=G, Hq=1, Hkv=1, d=64, Lp=1, Ls=Ls, **kw))
     assert [one((1 << 24) + k) for k in (-1, 0, 1)] == [UNIT, SIMPLE, SIMPLE]
     assert [one((1 << 22) + k, 4) for k in (-8, -7, 0)] == [UNIT, SIMPLE, SIMPLE]     # groups rounded up to the eight dies
+    assert [one((1 << 26) + k, Ls=100) for k in (-1, 0)] == [UNIT, SIMPLE]
     assert one((1 << 23) + 1, algo=SIMPLE) == SIMPLE and one(1 << 30) == SIMPLE
-    ds = B.make_paged_desc(B.RLDA_BF16, 1 << 23, 1, 1, 1, 64, 1, 1, 1, 1, 0.1, block_table=1 << 20)
-    assert B.rl_decode_attn_debug_route(ds) == SIMPLE
-    ds.P -= 1
-    assert B.rl_decode_attn_debug_route(ds) == UNIT
+    paged = lambda n: B.rl_decode_attn_debug_route(
+        B.make_paged_desc(B.RLDA_BF16, n, 1, 1, 1, 64, 1, 8, 10, 1, 0.1, block_table=1 << 20))
+    assert [paged((1 << 26) + k) for k in (-1, 0)] == [UNIT, SIMPLE]
+
+
+# (dtype, d, units, heads per KV head, keys): on either side of the lines of the rule, on 256 compute units
+KEPT = [(0, 64, 64, 1, 24), (0, 64, 64, 2, 96), (0, 64, 1024, 1, 64), (0, 64, 4096, 1, 128), (0, 64, 4096, 4, 16),
+        (0, 128, 512, 1, 64), (0, 128, 4096, 1, 256), (0, 128, 4096, 2, 48), (1, 64, 1024, 1, 1), (1, 64, 4096, 1, 48),
+        (1, 64, 4096, 4, 1), (1, 128, 4096, 1, 64), (2, 64, 65536, 1, 1), (2, 128, 65536, 1, 16)]
+BACK = [(0, 64, 64, 1, 16), (0, 64, 4096, 1, 100), (0, 64, 4096, 2, 24), (0, 64, 16384, 4, 1), (0, 128, 4096, 1, 128),
+        (0, 128, 4096, 4, 1), (1, 64, 4096, 1, 16), (1, 64, 65536, 1, 32), (1, 128, 4096, 1, 48)]
+
+
+@pytest.mark.parametrize("want,cases", [(UNIT, KEPT), (SIMPLE, BACK)], ids=["kept", "back"])
+def test_few_rows_over_few_keys_go_to_the_simple_kernel(want, cases):
+    for dtype, d, units, r, keys in cases:
+        scale = -0.1 if d == 128 and dtype else 0.1                       # not the shared-prefix path's
+        ds = desc(dtype, units // 8, 1, 8 * r, 8, d, keys // 2, keys - keys // 2, scale)
+        assert B.rl_decode_attn_debug_route(ds) == want, (dtype, d, units, r, keys)
+
+
+@pytest.mark.parametrize("dtype,d,r,keys,units,want", [
+    (1, 128, 1, 1024, 4096, SIMPLE), (1, 128, 1, 1024, 1024, UNIT), (1, 128, 4, 32, 4096, UNIT), (1, 64, 1, 64, 4096, UNIT),
+    (0, 64, 1, 1024, 4096, SIMPLE), (0, 64, 1, 256, 1024, SIMPLE), (0, 64, 4, 64, 4096, UNIT), (0, 64, 4, 32, 256, SIMPLE),
+    (0, 128, 1, 1024, 1024, SIMPLE), (0, 128, 2, 256, 4096, SIMPLE), (0, 128, 4, 64, 4096, UNIT), (0, 128, 1, 1024, 256, UNIT),
+    (2, 128, 1, 32, 4096, UNIT)])
+def test_pages_of_fewer_rows_than_a_tile(dtype, d, r, keys, units, want):
+    ds = B.make_paged_desc(dtype, units // 8, 1, 8 * r, 8, d, keys // 2, 16, keys // 32, units * keys // 32, 0.1,
+                           block_table=1 << 20)
+    assert B.rl_decode_attn_debug_route(ds) == want
+
+
+def test_units_of_hardly_any_key_in_large_numbers_stay_on_the_shared_path():
+    tree = lambda n: B.make_tree_desc(B.RLDA_BF16, n // 8, 8, 8, 128, 1, 0.1, [(None, None, None, 1, 1)])
+    for units, want in ((16384, UNIT), (16384 + 8, SHARED)):
+        assert B.rl_decode_attn_debug_route(desc(P=units // 8, G=1, Hq=8, Hkv=8, Lp=1, Ls=1)) == want
+    for units, want in ((8192, UNIT), (16384 + 8, SHARED)):
+        assert B.rl_decode_attn_debug_route(tree(units)) == want
