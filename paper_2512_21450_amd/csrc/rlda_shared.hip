@@ -1276,9 +1276,12 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill_kernel(const PrefillParam
 // softmax does beside the exponentials counts.  Row maxima are an eighth of it and put a chain (maxima, two lane
 // swaps, a branch over the rescaling) in front of every tile's weights.  They are taken of a row's first tile
 // only: softmax is the same for any reference, and sums and accumulators are in fp32, whose range holds any score
-// up to 2^32 above the reference with the same relative precision.  A workgroup in which that did not hold for
-// every row starts over with the reference following the maximum.  Measured, with the loads' addresses cut as
-// described there: 32 prompts of 1280 tokens of 28/4 heads 524 -> 486 us, 4 of 4096 537 -> 481 us (1 Pflop/s).
+// far above the reference with the same relative precision.  After every four tiles a sum beyond 2^RESCALE_GAP moves
+// its row's reference by its logarithm, so that only a weight some 2^115 above all before it, within four tiles, leaves
+// the range (a score 80 nats above); a workgroup that met one starts over with the reference following the maximum.
+// Measured, with the loads' addresses cut as described there: 32 prompts of 1280 tokens of 28/4 heads 524 -> 486 us,
+// 4 of 4096 537 -> 485 us (1 Pflop/s).  The same 32 with the keys past the 32nd 6, 12 and 60 times as large: 543, 553
+// and 558 with the maxima of every tile, 517, 520 and 944 so (900 each before the reference followed the sums).
 template <int OFF>
 __device__ __forceinline__ bf16x8 lds_rd128_asm(uint32_t addr) {
   bf16x8 v;
@@ -1342,6 +1345,11 @@ __device__ __forceinline__ void value_products(const s16x4 (&v)[8][2], const bf1
 #define RLDA_G2L(src, dst, off)                                                                                 \
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),                        \
                                    (__attribute__((address_space(3))) void*)(dst), 16, (off), 0)
+
+__device__ __forceinline__ float sum_of_row(float v) {      // over the four lanes that share a query row
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
 
 template <int NTP>
 __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillParams P) {
@@ -1462,7 +1470,8 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
       }
     }
   };
-  // all tiles once; FIXED: with the maxima of the rows' first tile as the reference all along
+  // all tiles once; FIXED: against the maxima of the rows' first tile, moved after every four tiles to where the sums are
+  bool moved = false;
   auto pass = [&](auto fixed) {
     init_state(st);
     issue(0);
@@ -1473,7 +1482,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
       read_k_frags<0>(ka, kf);
       wait_k_frags(kf);
       score_products<NTP>(kf, qf, s0, s1);
-      if constexpr (decltype(fixed)::value) {               // every row sees key 0, so these are finite
+      if constexpr (decltype(fixed)::value) {               // every row sees key 0
         float sv[NTP][8], m_new[NTP];
         softmax_max<NTP, true>(s0, s1, limit, st, P.c, g, sv, m_new);
 #pragma unroll
@@ -1485,24 +1494,49 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
       if (t0 + 1 < n_tiles) tile(fixed, std::integral_constant<int, 1>{}, t0 + 1);
       if (t0 + 2 < n_tiles) tile(fixed, std::integral_constant<int, 2>{}, t0 + 2);
       if (t0 + 3 < n_tiles) tile(fixed, std::integral_constant<int, 3>{}, t0 + 3);
+      if constexpr (decltype(fixed)::value) {
+        bool big = false;
+#pragma unroll
+        for (int nt = 0; nt < NTP; ++nt) big = big || !(st.l[nt] < __builtin_exp2f(RESCALE_GAP));
+        if (wave_has_rows && __any(big)) {
+          moved = true;
+#pragma unroll
+          for (int nt = 0; nt < NTP; ++nt) {
+            float top = st.l[nt];                           // of the four lanes of the row
+            top = fmaxf(top, __shfl_xor(top, 16, 64));
+            top = fmaxf(top, __shfl_xor(top, 32, 64));
+            // an infinite sum stays for the check at the end, one that is not a number makes the row none
+            const float m_new = top > 2.f && top < INFINITY ? st.m[nt] + __builtin_amdgcn_logf(top) : st.m[nt];
+            const float alpha = __builtin_amdgcn_exp2f(st.m[nt] - m_new);
+            st.l[nt] *= alpha;
+            st.lr[nt] *= alpha;
+#pragma unroll
+            for (int ct = 0; ct < 8; ++ct) st.O[nt][ct] *= alpha;
+            st.m[nt] = m_new;
+          }
+        }
+      }
     }
   };
   pass(std::true_type{});
-  // Did it hold?  Sums below 2^32 and finite accumulators say that no weight came near the end of the range; while
-  // the sums stay below 2^RESCALE_GAP no weight is larger than the online softmax lets them be, and the accumulators
-  // need no look.  If one row of the workgroup fails (NaN fails as well), the tiles, which are shared, are walked again.
+  // Did it hold?  A weight that left the range of fp32 made its row's sum infinite, or (large values) an accumulator; a
+  // wavefront whose sums all stayed below 2^RESCALE_GAP has met no weight that the online softmax would not have met.
+  // If one row of the workgroup failed, the tiles, which are shared, are walked again.
   bool bad = false;
   if (wave_has_rows) {
-    bool small = true;
 #pragma unroll
-    for (int nt = 0; nt < NTP; ++nt) { bad = bad || !(st.l[nt] < 0x1p32f); small = small && st.l[nt] < __builtin_exp2f(RESCALE_GAP); }
-    if (!__all(small))
+    for (int nt = 0; nt < NTP; ++nt) bad = bad || st.l[nt] == INFINITY;
+    if (moved)
 #pragma unroll
-      for (int nt = 0; nt < NTP; ++nt)
+      for (int nt = 0; nt < NTP; ++nt) {
+        const float l = sum_of_row(st.l[nt]);
+        float zero = 0.f;                                   // of finite accumulators
 #pragma unroll
         for (int ct = 0; ct < 8; ++ct)
 #pragma unroll
-          for (int x = 0; x < 4; ++x) bad = bad || !(__builtin_fabsf(st.O[nt][ct][x]) < INFINITY);
+          for (int x = 0; x < 4; ++x) zero = fmaf(st.O[nt][ct][x], 0.f, zero);
+        bad = bad || (l < INFINITY && zero != 0.f);         // a sum that is not a number: so is the row, any way
+      }
   }
   bad = __any(bad);
   if (lane == 0) again[wv] = bad;
@@ -1512,9 +1546,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
 #pragma unroll
   for (int nt = 0; nt < NTP; ++nt) {
     const int row = WROWS * wv + 16 * nt + m16, pos = limit[nt] - 1;
-    float l = st.l[nt], lr = st.lr[nt];
-    l += __shfl_xor(l, 16, 64);   l += __shfl_xor(l, 32, 64);
-    lr += __shfl_xor(lr, 16, 64); lr += __shfl_xor(lr, 32, 64);
+    const float l = sum_of_row(st.l[nt]), lr = sum_of_row(st.lr[nt]);
     if (row < nrows) {
       const float inv = 1.f / lr;
       const size_t orow = ((size_t)p * P.Lp_cap + pos) * P.Hq + j * P.r + row - (pos - a) * P.r;

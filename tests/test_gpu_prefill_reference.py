@@ -1,9 +1,9 @@
 """Prefill where the maximum of a row's first 32 keys is a poor reference for its softmax.
 
-The kernels take the exponents against that maximum and start a workgroup over, with the reference
-following the running maximum, where a sum or an accumulator left its range.  Both ways, and rows of
-both kinds in one workgroup, against the fp64 oracle at the bar of the other prefill tests (1e-2 abs
-on out for values of unit size, 1e-3 abs on lse), for 64 and 128 rows per workgroup.
+The kernels take the exponents against that maximum, move it to the sums after every four tiles, and start
+a workgroup over, with the reference following the running maximum, where a sum or an accumulator left its
+range.  Both ways, and rows of both kinds in one workgroup, against the fp64 oracle at the bar of the other
+prefill tests (1e-2 abs on out for values of unit size, 1e-3 abs on lse), for 64 and 128 rows per workgroup.
 """
 import math
 
@@ -28,7 +28,7 @@ def set_up(kind, shape):
     P, L, Hq, Hkv = shape
     x = case(970, P, L, Hq, Hkv, lens=np.maximum(1, L - 7 * np.arange(P) % L))
     v_size = 1.0
-    if kind == "later keys somewhat larger":                 # sums beyond 2^8, far below 2^32
+    if kind == "later keys somewhat larger":                 # sums beyond 2^8, far inside the range
         x["k"][:, :, 32:] = scaled(x["k"][:, :, 32:], 6.0)
     elif kind == "later keys far larger":                    # scores tens of nats above the first tile's
         x["k"][:, :, 40:] = scaled(x["k"][:, :, 40:], 60.0)
