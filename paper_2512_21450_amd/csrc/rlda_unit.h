@@ -78,8 +78,6 @@ __device__ __forceinline__ float row_max(float t) {
   const u32p b = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
   return max_raw(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
-// a reference to subtract: products may be -inf (infinite keys, or an overflow), and a row may have met no other yet
-__device__ __forceinline__ float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
 __device__ __forceinline__ u32x2 e4m3x4_to_bf16(uint32_t w) {            // exact
   const bf16x2 lo = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, false);
   const bf16x2 hi = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, true);
@@ -230,7 +228,9 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   f32x4 O[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) O[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;                        // m: a product q . k, not yet times the scale
+  // m: a product q . k, not yet times the scale; finite from the start, because products may be -inf (infinite keys, or an
+  // overflow) and -inf less itself is not a number
+  float m = -FLT_MAX, l = 0.f;
 
   Tile cur;
   u32x4 qr[NQ];
@@ -277,18 +277,17 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
                        max_raw(max_raw(sv[4], sv[5]), max_raw(sv[6], sv[7])));
     tm = row_max(tm);
     const float mn = max_raw(m, tm);
-    if (__any((mn - m) * c > 8.f)) {                   // a wavefront's first tile: m = -inf
-      const float al = __builtin_amdgcn_exp2f((m - finite_ref(mn)) * c);
+    if (__any((mn - m) * c > 8.f || m == -FLT_MAX)) {  // or a wavefront's first tile
+      const float al = __builtin_amdgcn_exp2f((m - mn) * c);
       l *= al;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) O[ct] *= al;
       m = mn;
     }
     float p[8];
-    const float ref = finite_ref(m);
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
-      const float dx = sv[x] - ref, e = dx * c;
+      const float dx = sv[x] - m, e = dx * c;
       p[x] = __builtin_amdgcn_exp2f(EXACT ? fmaf(dx, c_lo, e) : e);
     }
     l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
@@ -403,19 +402,28 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   }
   // An infinite value gives an infinite result; but split weights leave pieces of 0 or below zero, and rows past the
   // length repeat the last one at weight 0, and either makes it NaN.  Such columns are the sum of what is not finite.
-  // (In a loop of its own: inside the one above it cost 0.3 us of 9 without being entered.)
+  // (In a loop of its own, which reads the arguments again: inside the one above, or with what the tiles used kept for it,
+  // it cost 0.3 us of 9 without being entered.)
   if constexpr (KIND != KV_F8) {                       // e4m3 has no infinity
     if (!odd) return;
+    typedef const __attribute__((address_space(4))) UnitParams* args_t;
+    args_t A = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(A));
     for (int it = tid; it < nr * OC; it += 64 * NW) {
       const int row = it / OC, ch = it % OC;
       float L = 0.f;
       for (int w = 0; w < nw; ++w) L += wl[w][row];
       if (!(L < INFINITY)) continue;                   // a score that is not a number: the row is none
       f32x4 sum{0.f, 0.f, 0.f, 0.f};
-      for (int t = 0; t < T; ++t) {
-        const Tile x = tile_of(t);
-        for (int i = 0; i <= x.last; ++i) {
-          const char* src = row_at(x, x.v, i, 4 * ch * L_::EB);
+      for (int s = 0; s < A->n_seg; ++s) {
+        const int owner = b / A->seg[s].group, cap = A->seg[s].cap, n_keys = clampi(A->seg[s].lens[owner], 0, cap);
+        for (int n = 0; n < n_keys; ++n) {
+          size_t at = ((size_t)owner * A->Hkv + j) * cap + n;
+          if (A->table && s == A->n_seg - 1) {
+            const int pg = clampi(A->table[(size_t)b * A->max_pages + (n >> A->page_shift)], 0, A->n_pages - 1);
+            at = (((size_t)pg * A->Hkv + j) << A->page_shift) + (n & ((1 << A->page_shift) - 1));
+          }
+          const char* const src = A->seg[s].v + at * L_::ROWB + 4 * ch * L_::EB;
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
             const float v = KIND == KV_F32 ? reinterpret_cast<const float*>(src)[k]
