@@ -488,7 +488,8 @@ struct UnitGrid {
 //   bf16, 64 columns   1024 x 256                14.3 / 12.0 / 12.5 / 13.2       16384 x 32   104 / 56 / 36 / 29
 //   fp32, 128 columns   512 x 256                   - / 25 / 23 / 31     4096 x 64      - / 108 / 62 / 49
 //   small batches (two bf16 pieces), 1024 x 128  19.8 / 14.8 / 12.6 / 13.1        8192 x 64    137 / 85 / 66 / 66
-//   pages of 16 rows, bf16, 128 columns  256 x 1024  26 / 39 / 62 / 108  4096 x 256   223 / 134 / 134 / 117
+//   pages of 16 rows, bf16, 128 columns  320 x 1000  38 / 44 / - / -     512 x 1000  44 / 40 / - / -   1024 x 64 34 / 21 / 13 / 14
+//                                        256 x 1024  26 / 39 / 62 / 108  4096 x 256   223 / 134 / 134 / 117
 UnitGrid unit_grid(const Problem& pb, int pairs, bool exact) {
   const int64_t B = n_sequences(pb), G = max_group(pb), rb = ceil_div(pb.Hq / pb.Hkv, 16), keys = shared_cap(pb) + pb.Ls_cap;
   UnitGrid u;
@@ -496,17 +497,20 @@ UnitGrid unit_grid(const Problem& pb, int pairs, bool exact) {
   const int64_t groups = B / G * pb.Hkv;
   u.groups8 = groups >= 16 && G > 1 ? (int)((groups + 7) / 8) : 0;
   u.blocks = u.groups8 > 0 ? u.groups8 * 8 * G * rb : B * pb.Hkv * rb;
-  const bool f32 = pb.dtype == RLDA_F32, queue = u.blocks > 2 * (int64_t)pairs, many = u.blocks > 4 * (int64_t)pairs;
-  if (u.blocks <= pairs) {
+  const bool f32 = pb.dtype == RLDA_F32, many = u.blocks > 4 * (int64_t)pairs;
+  // workgroups of four wavefronts that a compute unit's LDS holds: tiles of 64 16-bit columns are half as large
+  const int64_t fit = (pb.d == 64 && !f32 ? 4 : 2) * (int64_t)pairs;
+  // rows looked up one by one make a long chain, worth more wavefronts than the queue costs a little longer
+  if (u.blocks <= pairs || (row_lookup(pb) && keys >= 512 && 2 * u.blocks <= 3 * (int64_t)pairs)) {
     u.nw = wide_waves(f32, pb.d);
   } else if (row_lookup(pb) || pb.n_levels > 1) {
-    u.nw = many ? 1 : 2;
+    u.nw = many ? 1 : (u.blocks > 2 * (int64_t)pairs || (f32 && pb.d == 128) ? 2 : 4);
   } else if (f32 && pb.d == 128) {
-    u.nw = queue && keys <= 256 ? 1 : 2;
-  } else if (!queue || (exact && (keys >= 512 || (keys >= 256 && u.blocks <= 8 * (int64_t)pairs)))) {
+    u.nw = u.blocks > fit && keys <= 256 ? 1 : 2;
+  } else if (u.blocks <= fit || (exact && (keys >= 512 || (keys >= 256 && u.blocks <= 8 * (int64_t)pairs)))) {
     u.nw = 4;
   } else {
-    u.nw = many && (!exact || keys <= 128) ? 1 : 2;
+    u.nw = u.blocks > 2 * fit && (!exact || keys <= 128) ? 1 : 2;
   }
   return u;
 }
@@ -519,12 +523,14 @@ hipError_t launch_form(const UnitParams& P, int nw, int64_t blocks, hipStream_t 
     if (P.table && P.page_shift < 5) {
       if (nw == 1) return launch<KIND, D, EXACT, 1, 2, true>(P, blocks, stream);
       if (nw == 2) return launch<KIND, D, EXACT, 2, 2, true>(P, blocks, stream);
+      if (nw == 4) return launch<KIND, D, EXACT, 4, 2, true>(P, blocks, stream);
       return launch<KIND, D, EXACT, WIDE, 2, true>(P, blocks, stream);
     }
   if constexpr (KIND == KV_BF16 && D == 128 && !EXACT)        // what a tree holds
     if (P.n_seg != 2) {
       if (nw == 1) return launch<KIND, D, EXACT, 1, MAX_SEG>(P, blocks, stream);
       if (nw == 2) return launch<KIND, D, EXACT, 2, MAX_SEG>(P, blocks, stream);
+      if (nw == 4) return launch<KIND, D, EXACT, 4, MAX_SEG>(P, blocks, stream);
       return launch<KIND, D, EXACT, WIDE, MAX_SEG>(P, blocks, stream);
     }
   if (nw == 1) return launch<KIND, D, EXACT, 1>(P, blocks, stream);

@@ -29,18 +29,18 @@ def test_numbers_of_units(B, dtype, d, units, keys):  # noqa: F811
         compare(out, lse, ro, rl, LEAN if lean else EXACT, (dtype, d, units, keys))
 
 
-@pytest.mark.parametrize("units", [256, 260, 1028])
+@pytest.mark.parametrize("units,Ls", [(256, 130), (260, 130), (260, 460), (516, 130), (1028, 130)])
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128), ("e4m3", 128)])
-def test_numbers_of_units_on_small_pages(B, dtype, d, units):  # noqa: F811
+def test_numbers_of_units_on_small_pages(B, dtype, d, units, Ls):  # noqa: F811
     import torch
-    x = wl.to_pages(case(units + 1, units // 4, 4, 5, 1, d, 70, 130, dtype), 16, seed=2)
+    x = wl.to_pages(case(units + 1, units // 4, 4, 5, 1, d, 70, Ls, dtype), 16, seed=2)
     act = (np.arange(units) % 5 != 1).astype(np.uint8)
     out, lse = util.gpu_run_paged(util.to_device(x), 0.1, 4, active=torch.from_numpy(act).cuda())
     ro, rl = util.oracle_paged(x, 0.1, 4, active=act)
     compare(out, lse, ro, rl, EXACT, (dtype, d, units))
 
 
-@pytest.mark.parametrize("units", [256, 264, 1032])
+@pytest.mark.parametrize("units", [256, 264, 520, 1032])
 def test_numbers_of_units_in_a_tree(B, units):  # noqa: F811
     from oracle import ref
     levels = [(8, 66, ("uniform", 66)), (4, 33, ("uniform", 33)), (2, 40, ("const", 40))]
