@@ -75,11 +75,25 @@ def csrc_sha256():
     return h.hexdigest()
 
 
-def measured_traffic(workload, plan):
-    """Counter-measured HBM bytes per launch (carried over from the profile run), or None when they do
-    not describe this run."""
+# the kernel that reads the K/V stores, by what rl_decode_attn_debug_route says a call runs on; all but the first are the
+# whole call in one launch
+DECODE_KERNELS = {2: "partial_kernel", 1: "simple_kernel", 3: "unit_kernel"}
+
+
+def kernel_bytes(route, ab, w):
+    """Bytes that kernel cannot do without.  The streaming kernel of the shared-prefix path reads the K/V rows, q and the
+    lengths (out and lse are the combine kernel's; the partial results between the two are scratch, not the method's
+    bytes); the others write out and lse as well."""
+    if route == 2:
+        return ab["prefix"] + ab["suffix"] + w.B * w.Hq * w.d * w.elem_bytes + 4 * (w.P + w.B)
+    return ab["total"]
+
+
+def measured_traffic(workload, route):
+    """Counter-measured HBM bytes per launch of the streaming kernel (carried over from the profile run), or None when
+    they do not describe this run."""
     t = PMC_TRAFFIC.get(workload)
-    if not t or plan != 2 or not t["fetch_bytes"] or csrc_sha256() != PMC_TRAFFIC["csrc_sha256"]:
+    if not t or route != 2 or not t["fetch_bytes"] or csrc_sha256() != PMC_TRAFFIC["csrc_sha256"]:
         return None
     return t["fetch_bytes"] + t["write_bytes"]
 
@@ -150,9 +164,6 @@ def run_decode(args, torch, B, wl, dev, wname, steps, warmup, event_calls, full)
     live_p = live_b.reshape(w.P, w.G).any(axis=1)
     ab = wl.algorithmic_bytes(w, np.where(live_p, x["prefix_lens"], 0), np.where(live_b, x["suffix_lens"], 0),
                               kv_elem_bytes=1 if kv8 else 0)
-    # what the K/V-streaming kernel itself has to read: the K/V rows, q and the lengths (out and lse are the
-    # combine kernel's; the partial results between the two kernels are scratch, not the method's bytes)
-    kern_bytes = ab["prefix"] + ab["suffix"] + w.B * w.Hq * w.d * w.elem_bytes + 4 * (w.P + w.B)
 
     def dev_t(a):
         if a.dtype == np.uint16:
@@ -182,6 +193,8 @@ def run_decode(args, torch, B, wl, dev, wname, steps, warmup, event_calls, full)
         ds.workspace, ds.workspace_bytes = ws.data_ptr(), ws.numel()
         descs.append(ds)
     plan = B.rl_decode_attn_paged_plan(descs[0]) if paged else B.rl_decode_attn_plan(descs[0])
+    route = B.rl_decode_attn_debug_route(descs[0], torch.cuda.get_device_properties(dev).multi_processor_count)
+    kern_bytes = kernel_bytes(route, ab, w)
     stream = torch.cuda.current_stream()
     sh = stream.cuda_stream
 
@@ -203,8 +216,8 @@ def run_decode(args, torch, B, wl, dev, wname, steps, warmup, event_calls, full)
     value = int(live_b.sum()) / (ms_per_step * 1e-3)    # one query token per live sequence and step
 
     # per-call timings from HIP events on the launch stream: first the whole call (two events), then the
-    # K/V-streaming kernel alone (a third event, recorded by the library between its two kernels; recording
-    # it lengthens the step, so the whole-call figures come from the two-event loop)
+    # K/V-reading kernel alone (a third event, recorded by the library behind it; where it is all there is, the
+    # interval is the call; recording it lengthens the step, so the whole-call figures come from the two-event loop)
     n_ev = max(event_calls, 1)
     ev2 = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(n_ev)]
     for i, (a, b) in enumerate(ev2):
@@ -250,7 +263,7 @@ def run_decode(args, torch, B, wl, dev, wname, steps, warmup, event_calls, full)
     call = stats_us(call_ms)
     gbps = lambda nbytes, us: nbytes / (us * 1e-6) / 1e9
     res = {
-        "workload": w.name, "ms_per_step": ms_per_step, "value": value, "steps": steps, "plan": plan,
+        "workload": w.name, "ms_per_step": ms_per_step, "value": value, "steps": steps, "plan": plan, "kernel": DECODE_KERNELS[route],
         "algorithmic_bytes": ab, "kernel_algorithmic_bytes": kern_bytes,
         "whole_step_GBps": gbps(ab["total"], ms_per_step * 1e3),
         "whole_step_frac_of_hbm_peak": gbps(ab["total"], ms_per_step * 1e3) / HBM_PEAK_GBS,
@@ -262,7 +275,7 @@ def run_decode(args, torch, B, wl, dev, wname, steps, warmup, event_calls, full)
         "mean_suffix_len": float(x["suffix_lens"].mean()), "max_suffix_len": int(x["suffix_lens"].max()),
         "mean_prefix_len": float(x["prefix_lens"].mean()),
         "parity": {"ok": parity_ok, "max_abs_err_out": err_o, "max_abs_err_lse": err_l, "rows": len(rows)},
-        "traffic": None if paged or kv8 else measured_traffic(w.name, plan),
+        "traffic": None if paged or kv8 else measured_traffic(w.name, route),
     }
     if not full:
         del sets, base, descs, ws
@@ -415,7 +428,7 @@ def main():
                 continue
             o = run_decode(args, torch, B, wl, dev, name, min(args.steps, 100), min(args.warmup, 10),
                            min(args.event_calls, 60), full=False)
-            others[name] = {k: o[k] for k in ("ms_per_step", "value", "plan", "algorithmic_bytes", "whole_step_GBps",
+            others[name] = {k: o[k] for k in ("ms_per_step", "value", "plan", "kernel", "algorithmic_bytes", "whole_step_GBps",
                                               "whole_step_frac_of_hbm_peak", "whole_call_us_by_events",
                                               "kernel_us_by_events", "kernel_algorithmic_bytes", "kernel_frac_of_hbm_peak",
                                               "traffic", "mean_suffix_len",
@@ -434,11 +447,11 @@ def main():
         "pct_of_hbm_peak_whole_step": 100.0 * r["whole_step_frac_of_hbm_peak"],
         "whole_call_us_by_events": r["whole_call_us_by_events"],
         "algorithmic_bytes": r["algorithmic_bytes"],
-        # the dominant kernel alone: the bytes it has to read / its duration (median over the event-timed calls)
+        # the dominant kernel alone: the bytes it cannot do without / its duration (median over the event-timed calls)
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": r["traffic"],
                      "traffic_source": "rocprofv3 counters of an earlier profile run of the same sources (profiles/)",
-                     "kernel": "partial_kernel" if r["plan"] == 2 else "simple_kernel",
+                     "kernel": r["kernel"],
                      "kernel_algorithmic_bytes": r["kernel_algorithmic_bytes"],
                      "kernel_us_median": kern["median"], "kernel_us_min": kern["min"], "kernel_us_p90": kern["p90"],
                      "event_timed_calls": kern["n"],
@@ -709,7 +722,7 @@ def bench_prefill(args, torch, B, wl, dev):
                    "tensor_sets_rotated": len(sets)},
         "algorithmic_flops": flops,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": None, "kernel": "prefill_kernel",
+                     "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": None, "kernel": "prefill2_kernel",
                      "kernel_us_mean": call_us},
         "cpu_baseline": {"value": n0 / (c1 - c0), "unit": "prompt-tokens/s", "cores": 1, "kind": "oracle",
                          "sample": f"prompt 0 of {w.P} ({n0} tokens, all heads), {c1 - c0:.2f} s"},

@@ -50,3 +50,26 @@ def test_source_hash_ignores_comments_and_layout_only():
     c = 'int f(int x) { return 3 * x; } const char* s = "// kept";'
     assert bench.strip_comments(a) == bench.strip_comments(b) != bench.strip_comments(c)
     assert '"// kept"' in bench.strip_comments(a)
+
+
+def test_the_kernel_of_a_workload_is_the_one_its_calls_run_on():
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2512_21450_amd import binding as B
+    from paper_2512_21450_amd import workloads as wl
+    src = "".join(open(os.path.join(ROOT, "paper_2512_21450_amd", "csrc", f)).read()
+                  for f in ("rlda_shared.hip", "rlda_simple.hip", "rlda_unit.h"))
+    for name in bench.DECODE_KERNELS.values():
+        assert f" {name}(" in src
+    want = {"tiny": "unit_kernel", "vlm3b": "unit_kernel", "vlm7b": "partial_kernel", "agentic": "partial_kernel",
+            "highbatch": "partial_kernel"}
+    ab = {"prefix": 1000, "suffix": 100, "total": 5000}
+    for name, kernel in want.items():
+        w = wl.WORKLOADS[name]
+        dt = {"f32": B.RLDA_F32, "bf16": B.RLDA_BF16}[w.dtype]
+        route = B.rl_decode_attn_debug_route(B.make_desc(dt, w.P, w.G, w.Hq, w.Hkv, w.d, w.Lp_cap, w.Ls_cap, w.scale))
+        assert bench.DECODE_KERNELS[route] == kernel, name
+        # one launch writes out and lse too; the streaming kernel does not
+        io = w.B * w.Hq * w.d * w.elem_bytes + 4 * (w.P + w.B)
+        assert bench.kernel_bytes(route, ab, w) == (5000 if kernel == "unit_kernel" else 1100 + io)
+        assert (bench.measured_traffic(name, route) is None) or kernel == "partial_kernel"
