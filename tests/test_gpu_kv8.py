@@ -17,7 +17,7 @@ from tests import util
 
 pytestmark = pytest.mark.gpu
 
-ALGOS = {"auto": 0, "simple": 1}
+ALGOS = {"auto": 0, "simple": 1, "shared": 2}                # AUTO takes small batches in one launch: the two-launch path by name
 
 
 @pytest.fixture(scope="module")
@@ -38,7 +38,7 @@ def byte_rows():
     return np.stack(rows)                                  # [4, 128]
 
 
-@pytest.mark.parametrize("algo", ["auto", "simple"])
+@pytest.mark.parametrize("algo", ["auto", "simple", "shared"])
 @pytest.mark.parametrize("where", ["prefix", "suffix"])
 def test_every_byte_value_decodes_exactly(where, algo, B):
     import torch
@@ -86,10 +86,10 @@ CASES = [
     (2, 5, 12, 4, 128, 64, 95),        # R = 15
     (3, 1, 8, 8, 128, 50, 40),         # G = 1, r = 1
     (1, 2, 32, 2, 128, 40, 33),        # r = 16
-    (2, 4, 8, 2, 64, 77, 91),          # d = 64: simple kernel under AUTO
+    (2, 4, 8, 2, 64, 77, 91),          # d = 64: not the shared-prefix path's
     (5, 7, 6, 3, 128, 31, 1),          # one-row suffix buffers
     (2, 32, 14, 2, 128, 150, 60),      # R = 224: four row parts
-    (2, 2, 64, 2, 128, 60, 50),        # r = 32: outside the matrix-core path, simple kernel under AUTO
+    (2, 2, 64, 2, 128, 60, 50),        # r = 32: not the shared-prefix path's either
 ]
 
 
@@ -97,8 +97,10 @@ def kv8_case(seed, P, G, Hq, Hkv, d, Lp_cap, Ls_cap, **kw):
     return wl.kv_to_e4m3(util.random_case(seed, P, G, Hq, Hkv, d, Lp_cap, Ls_cap, "bf16", **kw))
 
 
-@pytest.mark.parametrize("algo", ["auto", "simple"])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "P{}G{}H{}-{}d{}Lp{}Ls{}".format(*c))
+RUNS = [(c, a) for a in ALGOS for c in CASES if a != "shared" or c[4] == 128 and c[2] // c[3] <= 16]
+
+
+@pytest.mark.parametrize("case,algo", RUNS, ids=lambda c: c if isinstance(c, str) else "P{}G{}H{}-{}d{}Lp{}Ls{}".format(*c))
 def test_reduced_sizes(case, algo, B):
     import torch
     P, G, Hq, Hkv, d, Lp_cap, Ls_cap = case
@@ -138,7 +140,7 @@ def test_empty_full_and_clamped_lengths_with_nan_padding(B):
         x["v_suffix"][b, :, int(np.clip(sl[b], 0, Ls_cap)):] = 0xFF
     x["k_prefix"][0] = 0x7F
     x["v_prefix"][0] = 0x7F
-    for algo in ("auto", "simple"):
+    for algo in ("auto", "simple", "shared"):
         t = util.to_device(x)
         out, lse = util.gpu_run(t, 0.09, G, algo=ALGOS[algo])
         ro, rl = util.oracle(x, 0.09, G)
@@ -146,8 +148,9 @@ def test_empty_full_and_clamped_lengths_with_nan_padding(B):
     assert np.isneginf(rl[0]).all() and np.isfinite(rl[1]).all()        # sequence 0: no prefix, no suffix
 
 
+@pytest.mark.parametrize("algo", ["auto", "shared"])
 @pytest.mark.parametrize("page_size", [32, 128])
-def test_paged_store_with_finished_sequences(page_size, B):
+def test_paged_store_with_finished_sequences(page_size, algo, B):
     import torch
     P, G, Hq, Hkv, d = 3, 8, 28, 4, 128
     x = kv8_case(21, P, G, Hq, Hkv, d, 150, 400)
@@ -157,15 +160,17 @@ def test_paged_store_with_finished_sequences(page_size, B):
     act[8:16] = 0                                           # a whole group finished: its prefix is skipped
     t = util.to_device(y)
     for a in (None, act):
-        out, lse = util.gpu_run_paged(t, 0.088, G, active=None if a is None else torch.from_numpy(a).cuda())
+        out, lse = util.gpu_run_paged(t, 0.088, G, active=None if a is None else torch.from_numpy(a).cuda(), algo=ALGOS[algo])
         ro, rl = util.oracle_paged(y, 0.088, G, active=a)
         util.compare(out, lse, ro, rl, "bf16", f"paged {page_size} {a is not None}")
 
 
-@pytest.mark.parametrize("G,Hq,Hkv", [(16, 16, 2), (32, 14, 2)])
-def test_paged_store_with_several_row_parts(G, Hq, Hkv, B):
+@pytest.mark.parametrize("algo", ["auto", "shared"])
+@pytest.mark.parametrize("G,Hq,Hkv", [(2, 16, 2), (4, 14, 2), (8, 16, 2), (16, 16, 2), (32, 14, 2)])
+def test_paged_store_with_several_row_parts(G, Hq, Hkv, algo, B):
     """KV groups of 128 and 224 rows (two and four row parts) on a paged e4m3 store with finished sequences:
-    the kernel variant that keeps the prefix tiles cached between the parts, in its extended e4m3 form."""
+    the kernel variant that keeps the prefix tiles cached between the parts, in its extended e4m3 form; and
+    groups of 16, 28 and 64 rows, the forms of one, two and four row blocks."""
     import torch
     P, d = 3, 128
     x = kv8_case(23 + G, P, G, Hq, Hkv, d, 170, 260)
@@ -173,17 +178,18 @@ def test_paged_store_with_several_row_parts(G, Hq, Hkv, B):
     act = (np.arange(P * G) % 4 != 2).astype(np.uint8)
     t = util.to_device(y)
     for a in (None, act):
-        out, lse = util.gpu_run_paged(t, 0.088, G, active=None if a is None else torch.from_numpy(a).cuda())
+        out, lse = util.gpu_run_paged(t, 0.088, G, active=None if a is None else torch.from_numpy(a).cuda(), algo=ALGOS[algo])
         ro, rl = util.oracle_paged(y, 0.088, G, active=a)
         util.compare(out, lse, ro, rl, "bf16", f"paged G{G} {a is not None}")
 
 
-def test_bitwise_determinism_and_store_independence(B):
+@pytest.mark.parametrize("algo", ["auto", "shared"])
+def test_bitwise_determinism_and_store_independence(B, algo):
     import torch
     x = kv8_case(31, 4, 8, 28, 4, 128, 300, 500)
     t = util.to_device(x)
-    o1, l1 = util.gpu_run(t, 0.088, 8)
-    o2, l2 = util.gpu_run(t, 0.088, 8)
+    o1, l1 = util.gpu_run(t, 0.088, 8, algo=ALGOS[algo])
+    o2, l2 = util.gpu_run(t, 0.088, 8, algo=ALGOS[algo])
     assert torch.equal(o1, o2) and torch.equal(l1, l2)
     # the same values held in a bf16 store (dequantised with power-of-two factors, hence exactly) give the same bits:
     # both stores feed identical bf16 tiles to the same arithmetic
@@ -192,7 +198,7 @@ def test_bitwise_determinism_and_store_independence(B):
     vs = np.array([0.015625, 0.0078125, 0.0078125, 0.0625], np.float32)
     x2["k_scale"], x2["v_scale"] = ks, vs
     t2 = util.to_device(x2)
-    o8, l8 = util.gpu_run(t2, 0.088, 8)
+    o8, l8 = util.gpu_run(t2, 0.088, 8, algo=ALGOS[algo])
     y = {k: v for k, v in x2.items() if k not in ("k_scale", "v_scale")}
     for name, sc in (("k", ks), ("v", vs)):
         for st in ("prefix", "suffix"):
@@ -201,7 +207,7 @@ def test_bitwise_determinism_and_store_independence(B):
             y[f"{name}_{st}"] = wl.f32_to_bf16_bits(f)
             assert np.array_equal(wl.bf16_bits_to_f32(y[f"{name}_{st}"]), f)       # exact in bf16
     ty = util.to_device(y)
-    ob, lb = util.gpu_run(ty, 0.088, 8)
+    ob, lb = util.gpu_run(ty, 0.088, 8, algo=ALGOS[algo])
     ro, rl = util.oracle(x2, 0.088, 8)
     util.compare(o8, l8, ro, rl, "bf16", "kv8 pow2")
     do = np.abs(o8.cpu().numpy() - ob.cpu().numpy()).max()

@@ -96,7 +96,7 @@ def test_page_pool_beyond_4gib(B):
         t[name] = pool
     table = y["block_table"].astype(np.int64)
     t["block_table"] = torch.from_numpy(np.where(table >= 0, n_big - 1 - table, table).astype(np.int32)).cuda()
-    for algo in (B.RLDA_ALGO_AUTO, B.RLDA_ALGO_SIMPLE):
+    for algo in (B.RLDA_ALGO_AUTO, B.RLDA_ALGO_SIMPLE, B.RLDA_ALGO_SHARED):
         out, lse = util.gpu_run_paged(t, 0.09, G, algo=algo)
         torch.cuda.synchronize()
         ro, rl = util.oracle_paged(y, 0.09, G)

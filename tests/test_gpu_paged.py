@@ -34,12 +34,14 @@ def test_full_size_configs_paged(B, name, ps):
     check(y, w.dtype, w.scale, w.G, what=f"paged {name}")
 
 
-@pytest.mark.parametrize("ps", [16, 32, 64, 128, 256, 512])     # 16 rows: shorter than a key tile, the simple kernel's
-@pytest.mark.parametrize("dtype,d,algo", [("bf16", 128, "auto"), ("bf16", 128, "simple"), ("f32", 64, "auto")])
+# 16 rows: shorter than a key tile, not the shared-prefix path's
+@pytest.mark.parametrize("ps,dtype,d,algo", [(ps,) + k for ps in (16, 32, 64, 128, 256, 512)
+                                             for k in (("bf16", 128, "auto"), ("bf16", 128, "simple"), ("bf16", 128, "shared"),
+                                                       ("f32", 64, "auto")) if ps >= 32 or k[2] != "shared"])
 def test_page_sizes_on_both_kernel_families(B, ps, dtype, d, algo):
     x = util.random_case(100 + ps, 3, 4, 8, 2, d, 150, 700, dtype)
     y = wl.to_pages(x, ps, seed=ps)
-    a = {"auto": B.RLDA_ALGO_AUTO, "simple": B.RLDA_ALGO_SIMPLE}[algo]
+    a = {"auto": B.RLDA_ALGO_AUTO, "simple": B.RLDA_ALGO_SIMPLE, "shared": B.RLDA_ALGO_SHARED}[algo]
     check(y, dtype, 0.11, 4, algo=a, what=f"page {ps} {dtype} {algo}")
 
 
@@ -57,7 +59,8 @@ def test_finished_sequences_and_finished_groups(B):
     check(y, w.dtype, w.scale, w.G, active=act, algo=B.RLDA_ALGO_SIMPLE, what="finished mix, simple kernel")
 
 
-def test_finished_sequences_may_hold_garbage(B):
+@pytest.mark.parametrize("algo", [0, 2], ids=["auto", "shared"])
+def test_finished_sequences_may_hold_garbage(B, algo):
     # a finished sequence's table row and length are never used
     x = util.random_case(7, 2, 4, 28, 4, 128, 200, 300, "bf16")
     y = wl.to_pages(x, 32, seed=7)
@@ -71,11 +74,12 @@ def test_finished_sequences_may_hold_garbage(B):
         z["suffix_lens"][b] = 1 << 30
     import torch
     t = util.to_device(z)
-    out, lse = util.gpu_run_paged(t, 0.1, 4, active=torch.from_numpy(act).cuda())
+    out, lse = util.gpu_run_paged(t, 0.1, 4, active=torch.from_numpy(act).cuda(), algo=algo)
     util.compare(out, lse, ro, rl, "bf16", "garbage rows of finished sequences")
 
 
-def test_out_of_range_page_ids_are_clamped_not_followed(B):
+@pytest.mark.parametrize("algo", [0, 2], ids=["auto", "shared"])
+def test_out_of_range_page_ids_are_clamped_not_followed(B, algo):
     # a wrong id in a used entry gives a wrong result for that sequence only, and no stray access
     x = util.random_case(8, 2, 4, 28, 4, 128, 100, 260, "bf16", slens=[260, 100, 64, 1, 0, 33, 200, 129])
     y = wl.to_pages(x, 64, seed=8, poison=False)
@@ -84,7 +88,7 @@ def test_out_of_range_page_ids_are_clamped_not_followed(B):
     z["block_table"][0, 1] = -5
     z["block_table"][6, 0] = 1_000_000
     import torch
-    out, lse = util.gpu_run_paged(util.to_device(z), 0.1, 4)
+    out, lse = util.gpu_run_paged(util.to_device(z), 0.1, 4, algo=algo)
     torch.cuda.synchronize()
     keep = [1, 2, 3, 4, 5, 7]
     util.compare(out[keep], lse[keep], ro[keep], rl[keep], "bf16", "neighbours of a bad page id")
@@ -160,7 +164,8 @@ def test_decode_loop_captured_in_a_graph(B):
         assert torch.equal(t["suffix_lens"], lens0 + steps * inc)
 
 
-def test_no_suffix_pages_at_all_and_very_large_pages(B):
+@pytest.mark.parametrize("algo", [0, 2], ids=["auto", "shared"])
+def test_no_suffix_pages_at_all_and_very_large_pages(B, algo):
     import torch
     x = util.random_case(9, 2, 4, 28, 4, 128, 130, 64, "bf16")
     t = util.to_device(x)
@@ -168,10 +173,10 @@ def test_no_suffix_pages_at_all_and_very_large_pages(B):
     empty_pool = torch.empty((0, 4, 64, 128), dtype=torch.bfloat16, device="cuda")
     table = torch.empty((8, 0), dtype=torch.int32, device="cuda")
     out, lse = B.rl_decode_attn_paged(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_lens"], empty_pool, empty_pool,
-                                      table, t["suffix_lens"], 0.1, 4)
+                                      table, t["suffix_lens"], 0.1, 4, algo=algo)
     z = dict(x); z["suffix_lens"] = np.zeros(8, np.int32)
     ro, rl = util.oracle(z, 0.1, 4)
     util.compare(out, lse, ro, rl, "bf16", "no pages")
     # one page of 1024 rows per sequence
     y = wl.to_pages(util.random_case(10, 2, 4, 28, 4, 128, 130, 900, "bf16"), 1024, seed=1)
-    check(y, "bf16", 0.1, 4, what="page 1024")
+    check(y, "bf16", 0.1, 4, what="page 1024", algo=algo)

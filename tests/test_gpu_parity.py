@@ -13,7 +13,7 @@ from tests import util
 
 pytestmark = pytest.mark.gpu
 
-ALGOS = {"auto": 0, "simple": 1}
+ALGOS = {"auto": 0, "simple": 1, "shared": 2}                # AUTO takes small batches in one launch: the two-launch path by name
 
 
 @pytest.fixture(scope="module")
@@ -92,8 +92,10 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("algo", ["auto", "simple"])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "P{}G{}H{}-{}d{}Lp{}Ls{}{}".format(*c))
+RUNS = [(c, a) for a in ALGOS for c in CASES if a != "shared" or c[4] == 128 and c[7] == "bf16"]
+
+
+@pytest.mark.parametrize("case,algo", RUNS, ids=lambda c: c if isinstance(c, str) else "P{}G{}H{}-{}d{}Lp{}Ls{}{}".format(*c))
 def test_reduced_sizes(case, algo, B):
     P, G, Hq, Hkv, d, Lp_cap, Ls_cap, dtype = case
     x = util.random_case(100 + CASES.index(case), P, G, Hq, Hkv, d, Lp_cap, Ls_cap, dtype)
@@ -101,8 +103,8 @@ def test_reduced_sizes(case, algo, B):
 
 
 # ------------------------------------------------------------------ edge cases
-@pytest.mark.parametrize("algo", ["auto", "simple"])
-@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("algo,dtype,d", [("auto", "bf16", 128), ("simple", "bf16", 128), ("shared", "bf16", 128),
+                                          ("auto", "f32", 64), ("simple", "f32", 64)])
 def test_empty_and_full_lengths(algo, dtype, d, B):
     P, G, Hq, Hkv, Lp_cap, Ls_cap = 3, 4, 8, 2, 96, 80
     plens = [0, Lp_cap, 17]
@@ -121,7 +123,7 @@ def test_empty_and_full_lengths(algo, dtype, d, B):
         check(y, 0.2, G, dtype, algo, f"lens {pl[0]},{sl[0]}", B)
 
 
-@pytest.mark.parametrize("algo", ["auto", "simple"])
+@pytest.mark.parametrize("algo", ["auto", "simple", "shared"])
 def test_rows_beyond_length_may_hold_nan_and_lengths_clamp(algo, B):
     P, G, Hq, Hkv, d, Lp_cap, Ls_cap = 2, 4, 14, 2, 128, 75, 140
     x = util.random_case(11, P, G, Hq, Hkv, d, Lp_cap, Ls_cap, "bf16")
@@ -143,7 +145,7 @@ def test_rows_beyond_length_may_hold_nan_and_lengths_clamp(algo, B):
     check(z, 0.09, G, "bf16", algo, "clamp", B)
 
 
-@pytest.mark.parametrize("algo", ["auto", "simple"])
+@pytest.mark.parametrize("algo", ["auto", "simple", "shared"])
 def test_constant_v_and_sharp_softmax(algo, B):
     P, G, Hq, Hkv, d = 2, 8, 28, 4, 128
     x = util.random_case(21, P, G, Hq, Hkv, d, 150, 210, "bf16", gain=6.0)   # scores with std ~6
@@ -160,7 +162,8 @@ def test_constant_v_and_sharp_softmax(algo, B):
     check(x, 1 / math.sqrt(d), G, "bf16", algo, "sharp", B)
 
 
-def test_sharing_is_invisible_replicated_prefix(B):
+@pytest.mark.parametrize("algo", ["auto", "shared"])
+def test_sharing_is_invisible_replicated_prefix(B, algo):
     """Shared prefix == the prefix physically copied in front of every sequence's own keys."""
     P, G, Hq, Hkv, d, Lp_cap, Ls_cap = 3, 8, 28, 4, 128, 120, 100
     x = util.random_case(31, P, G, Hq, Hkv, d, Lp_cap, Ls_cap, "bf16")
@@ -176,11 +179,11 @@ def test_sharing_is_invisible_replicated_prefix(B):
     y = dict(x, k_suffix=ks, v_suffix=vs, suffix_lens=sl, prefix_lens=np.zeros(P, np.int32))
     ro, rl = util.oracle(x, 0.1, G)
     for inp in (x, y):
-        out, lse = util.gpu_run(util.to_device(inp), 0.1, G)
+        out, lse = util.gpu_run(util.to_device(inp), 0.1, G, algo=ALGOS[algo])
         util.compare(out, lse, ro, rl, "bf16", "replicated prefix")
 
 
-@pytest.mark.parametrize("algo", ["auto", "simple"])
+@pytest.mark.parametrize("algo", ["auto", "simple", "shared"])
 def test_bitwise_determinism(algo, B):
     import torch
     w = wl.scaled(wl.WORKLOADS["agentic"], P=4, Ls_cap=1024)
@@ -202,13 +205,14 @@ def test_long_tail_load_balance_case(B):
     check(x, w.scale, w.G, "bf16", "auto", "outlier", B)
 
 
-def test_lse_null_and_caller_buffers(B):
+@pytest.mark.parametrize("algo", ["auto", "shared"])
+def test_lse_null_and_caller_buffers(B, algo):
     import torch
     x = util.random_case(41, 2, 4, 8, 2, 128, 60, 70, "bf16")
     t = util.to_device(x)
     out = torch.full((8, 8, 128), 7.0, device="cuda:0")
     ds = B.desc_from_tensors(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_lens"], t["k_suffix"], t["v_suffix"],
-                             t["suffix_lens"], 0.1, 4, out, None)
+                             t["suffix_lens"], 0.1, 4, out, None, algo=ALGOS[algo])
     need = B.rl_decode_attn_workspace_bytes(ds)
     ws = torch.empty(max(need, 1), dtype=torch.uint8, device="cuda:0")
     ds.workspace, ds.workspace_bytes = ws.data_ptr(), need
@@ -222,14 +226,15 @@ def test_lse_null_and_caller_buffers(B):
         assert B.rl_decode_attn_raw(ds, None) == B.RLDA_ERR_WORKSPACE
 
 
-def test_non_default_stream(B):
+@pytest.mark.parametrize("algo", ["auto", "shared"])
+def test_non_default_stream(B, algo):
     import torch
     x = util.random_case(43, 2, 8, 16, 2, 128, 90, 110, "bf16")
     t = util.to_device(x)
     s = torch.cuda.Stream()
     s.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(s):
-        out, lse = util.gpu_run(t, 0.1, 8, stream=s)
+        out, lse = util.gpu_run(t, 0.1, 8, stream=s, algo=ALGOS[algo])
     s.synchronize()
     ro, rl = util.oracle(x, 0.1, 8)
     util.compare(out, lse, ro, rl, "bf16", "side stream")
@@ -258,14 +263,15 @@ def test_lse_combine_against_oracle(d, B):
 
 
 def test_one_workspace_reused_across_shapes_and_steps(B):
-    """A decode loop reuses one workspace; stale partials of an earlier, larger call must not leak."""
+    """A decode loop reuses one workspace; stale partials of an earlier, larger call must not leak.  On the kernels that
+    write it: these batches are small enough for AUTO to do without."""
     import torch
     big = util.random_case(51, 4, 8, 28, 4, 128, 300, 500, "bf16")
     small = util.random_case(52, 2, 8, 28, 4, 128, 300, 500, "bf16", plens=[40, 0], slens=[3, 0, 70, 0, 0, 0, 1, 33, 0, 0, 0, 0, 0, 0, 0, 5])
     tb, tsm = util.to_device(big), util.to_device(small)
     out_b = torch.empty((32, 28, 128), dtype=torch.float32, device="cuda:0")
     ds_b = B.desc_from_tensors(tb["q"], tb["k_prefix"], tb["v_prefix"], tb["prefix_lens"], tb["k_suffix"], tb["v_suffix"],
-                               tb["suffix_lens"], 0.1, 8, out_b, None)
+                               tb["suffix_lens"], 0.1, 8, out_b, None, algo=B.RLDA_ALGO_SHARED)
     ws = torch.empty(B.rl_decode_attn_workspace_bytes(ds_b), dtype=torch.uint8, device="cuda:0")
     ws.fill_(0xFF)                                   # NaN patterns everywhere
     sh = torch.cuda.current_stream().cuda_stream
@@ -273,14 +279,17 @@ def test_one_workspace_reused_across_shapes_and_steps(B):
         out = torch.empty((P * 8, 28, 128), dtype=torch.float32, device="cuda:0")
         lse = torch.empty((P * 8, 28), dtype=torch.float32, device="cuda:0")
         ds = B.desc_from_tensors(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_lens"], t["k_suffix"], t["v_suffix"],
-                                 t["suffix_lens"], 0.1, 8, out, lse, ws)
+                                 t["suffix_lens"], 0.1, 8, out, lse, ws, B.RLDA_ALGO_SHARED)
         assert B.rl_decode_attn_workspace_bytes(ds) <= ws.numel()
+        assert util.route(ds) == B.RLDA_ALGO_SHARED
         assert B.rl_decode_attn_raw(ds, sh) == 0
         ro, rl = util.oracle(x, 0.1, 8)
         util.compare(out, lse, ro, rl, "bf16", f"reused workspace P={P}")
+        assert not bool((ws == 0xFF).all())          # the call did write it
 
 
-def test_profiled_entry_point_records_the_middle_event(B):
+@pytest.mark.parametrize("algo", ["auto", "simple", "shared"])
+def test_profiled_entry_point_records_the_middle_event(B, algo):
     import torch
     w = wl.scaled(wl.WORKLOADS["vlm7b"], P=4)
     x = wl.make_inputs(w)
@@ -288,8 +297,8 @@ def test_profiled_entry_point_records_the_middle_event(B):
     out = torch.empty((w.B, w.Hq, w.d), dtype=torch.float32, device="cuda:0")
     lse = torch.empty((w.B, w.Hq), dtype=torch.float32, device="cuda:0")
     ds = B.desc_from_tensors(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_lens"], t["k_suffix"], t["v_suffix"],
-                             t["suffix_lens"], w.scale, w.G, out, lse)
-    ws = torch.empty(B.rl_decode_attn_workspace_bytes(ds), dtype=torch.uint8, device="cuda:0")
+                             t["suffix_lens"], w.scale, w.G, out, lse, algo=ALGOS[algo])
+    ws = torch.empty(max(256, B.rl_decode_attn_workspace_bytes(ds)), dtype=torch.uint8, device="cuda:0")
     ds.workspace, ds.workspace_bytes = ws.data_ptr(), ws.numel()
     s = torch.cuda.current_stream()
     e0, em, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(3))
@@ -304,7 +313,8 @@ def test_profiled_entry_point_records_the_middle_event(B):
     util.compare(out, lse, ro, rl, "bf16", "profiled")
 
 
-def test_two_level_shared_prefix_by_composition(B):
+@pytest.mark.parametrize("algo", ["auto", "shared"])
+def test_two_level_shared_prefix_by_composition(B, algo):
     """A prefix tree (prompt shared by the group, a first turn shared by sub-groups, own suffix) needs no
     new kernel: one call per level yields (o, lse) partials over disjoint key sets and rl_lse_combine
     merges them.  Checked against the oracle on the concatenated keys."""
@@ -335,8 +345,8 @@ def test_two_level_shared_prefix_by_composition(B):
                      else torch.from_numpy(a).cuda())
     qd = dev(q)
     zero = torch.zeros(P * G, dtype=torch.int32, device="cuda")
-    o0, l0 = B.rl_decode_attn(qd, dev(k0), dev(v0), dev(len0), dev(ks), dev(vs), zero, 0.09, G)
-    o1, l1 = B.rl_decode_attn(qd, dev(k1), dev(v1), dev(len1), dev(ks), dev(vs), dev(lens), 0.09, sub)
+    o0, l0 = B.rl_decode_attn(qd, dev(k0), dev(v0), dev(len0), dev(ks), dev(vs), zero, 0.09, G, algo=ALGOS[algo])
+    o1, l1 = B.rl_decode_attn(qd, dev(k1), dev(v1), dev(len1), dev(ks), dev(vs), dev(lens), 0.09, sub, algo=ALGOS[algo])
     parts_o = torch.stack([o0.reshape(-1, d), o1.reshape(-1, d)])
     parts_l = torch.stack([l0.reshape(-1), l1.reshape(-1)])
     out, lse = B.rl_lse_combine(parts_o, parts_l)
@@ -369,9 +379,9 @@ def test_around_the_tile_count_where_half_the_workgroup_pairs_take_over(B, tiles
     pl = np.full(P, 16 * 32, np.int32)
     sl = np.full(P * G, 62 * 32, np.int32)
     sl[13] += (tiles - 2048) * 32
-    x = util.random_case(600 + tiles, P, G, Hq, Hkv, d, 16 * 32, 63 * 32, "bf16", plens=pl, slens=sl)
+    x = util.random_case(600 + tiles, P, G, Hq, Hkv, d, 16 * 32, 63 * 32, "bf16", plens=pl, slens=sl)      # forced: AUTO needs no split
     assert int((-(-x["prefix_lens"] // 32)).sum() + (-(-x["suffix_lens"] // 32)).sum()) == tiles
-    check(x, 0.09, G, "bf16", "auto", f"{tiles} tiles", B)
+    check(x, 0.09, G, "bf16", "shared", f"{tiles} tiles", B)
 
 
 @pytest.mark.parametrize("paged", [False, True])
@@ -400,7 +410,8 @@ def test_rows_with_many_parts_in_the_16_lane_combine(B, paged):
 @pytest.mark.parametrize("scale", [-0.09, 0.0])
 def test_non_positive_scale_runs_on_the_simple_kernel(B, scale):
     """The shared-prefix path takes its row maxima before scaling and therefore positive scales only; anything
-    else (anti-attention, a uniform average) is planned onto the simple kernel, with the same result."""
+    else (anti-attention, a uniform average) is planned as SIMPLE, with the same result: forced, on the simple
+    kernel, under AUTO in one launch."""
     import torch
     x = util.random_case(91, 3, 4, 8, 2, 128, 150, 90, "bf16")
     t = util.to_device(x)
@@ -408,6 +419,8 @@ def test_non_positive_scale_runs_on_the_simple_kernel(B, scale):
     ds = B.desc_from_tensors(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_lens"], t["k_suffix"], t["v_suffix"],
                              t["suffix_lens"], scale, 4, out, None)
     assert B.rl_decode_attn_plan(ds) == B.RLDA_ALGO_SIMPLE
-    check(x, scale, 4, "bf16", "auto", f"scale {scale}", B)
+    assert util.route(ds) == B.RLDA_ROUTE_UNIT
+    for algo in ("auto", "simple"):
+        check(x, scale, 4, "bf16", algo, f"scale {scale}", B)
     with pytest.raises(B.RldaError):
         util.gpu_run(t, scale, 4, algo=B.RLDA_ALGO_SHARED)

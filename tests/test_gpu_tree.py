@@ -1,6 +1,9 @@
 """rl_decode_attn_tree on the GPU against the fp64 oracle on the concatenated keys: two and three levels of
 shared segments with ragged (and empty) segments and suffixes, sharing widths down to one sequence, levels
-that do not nest, and the single-level case against rl_decode_attn bit for bit."""
+that do not nest, and the single-level case against rl_decode_attn bit for bit.
+
+The call has no algo field, and trees as small as these run in one launch.  Suffix stores of more than 2048
+rows, whatever they hold, take it to the shared-prefix kernels: every case runs on both."""
 import numpy as np
 import pytest
 
@@ -16,6 +19,22 @@ def to_dev(a):
     if a.dtype == np.uint16:
         return torch.from_numpy(a.view(np.int16)).cuda().view(torch.bfloat16)
     return torch.from_numpy(a).cuda()
+
+
+def widen(x, cap):
+    """x with suffix stores of `cap` rows (NaN behind the old ones)."""
+    y = dict(x)
+    for k in ("k_suffix", "v_suffix"):
+        wide = np.full(x[k].shape[:2] + (cap,) + x[k].shape[3:], 0x7FC0, np.uint16)
+        wide[:, :, :x[k].shape[2]] = x[k]
+        y[k] = wide
+    return y
+
+
+def tree_route(x, scale):
+    lv = [(None, None, None, g, k.shape[2]) for k, v, l, g in x["levels"]]
+    Bn, Hq, d = x["q"].shape
+    return util.route(B.make_tree_desc(B.RLDA_BF16, Bn, Hq, x["k_suffix"].shape[1], d, x["k_suffix"].shape[2], scale, lv))
 
 
 def run_tree(x, scale):
@@ -44,20 +63,27 @@ CASES = [
 ]
 
 
+@pytest.mark.parametrize("launches", [1, 2])
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
-def test_tree_against_the_oracle(case):
+def test_tree_against_the_oracle(case, launches):
     _, Bn, Hq, Hkv, levels, Ls_cap, suffix, empty = case
     x = wl.make_tree_inputs(4100 + Bn + len(levels), Bn, Hq, Hkv, 128, levels, Ls_cap, suffix, q_gain=1.5, empty=empty)
     scale = 1.0 / np.sqrt(128)
-    out, lse = run_tree(x, scale)
     ro, rl = oracle_tree(x, scale)
+    y = widen(x, 2080) if launches == 2 else x
+    if launches == 2 or case[0] != "one head per KV head, long ragged segments":       # long ones take two anyway
+        assert tree_route(y, scale) == (B.RLDA_ALGO_SHARED if launches == 2 else B.RLDA_ROUTE_UNIT)
+    out, lse = run_tree(y, scale)
     util.compare(out, lse, ro, rl, "bf16", case[0])
 
 
-def test_one_level_equals_the_shared_prefix_call_bit_for_bit():
+@pytest.mark.parametrize("launches", [1, 2])
+def test_one_level_equals_the_shared_prefix_call_bit_for_bit(launches):
     import torch
     w = wl.scaled(wl.WORKLOADS["vlm7b"], P=3, Lp_cap=333, Ls_cap=211, prefix=("uniform", 333), suffix=("uniform", 211))
     x = wl.make_inputs(w)
+    if launches == 2:
+        x = widen(x, 2080)
     t = util.to_device(x)
     o1, l1 = util.gpu_run(t, w.scale, w.G)
     o2, l2 = B.rl_decode_attn_tree(t["q"], [(t["k_prefix"], t["v_prefix"], t["prefix_lens"], w.G)], t["k_suffix"],

@@ -35,6 +35,13 @@ def gpu_run(t, scale, G, **kw):
                                   k_scale=t.get("k_scale"), v_scale=t.get("v_scale"), **kw)
 
 
+def route(ds):
+    """The kernels a call with this descriptor runs on, on the GPU at hand."""
+    import torch
+    from paper_2512_21450_amd import binding
+    return binding.rl_decode_attn_debug_route(ds, torch.cuda.get_device_properties(0).multi_processor_count)
+
+
 def compare(out, lse, ref_out, ref_lse, dtype, what=""):
     """Element-by-element against the fp64 oracle; -inf must match exactly."""
     tol_o, tol_l = TOL[dtype]
