@@ -11,7 +11,7 @@
 // one pass of the workgroup) and requests them, its values and the lengths before the angles are
 // evaluated.  Eight dependent passes of one element each took 6.5-7.3 us for 128 such sequences; now 3.1-4.0
 // (a captured decode step of append, attention and combine 48.4 -> 44.5).  Buffers that are not aligned
-// to 16 bytes take one element at a time.
+// to 16 bytes take one element at a time, and so do heads so few that a thread has one or two elements anyway.
 // Stores may hold e4m3 bytes: the appended rows are then divided by the KV head's factor and
 // rounded to the nearest e4m3 value with integer operations (ties to even, saturating).
 #include <hip/hip_runtime.h>
@@ -296,12 +296,19 @@ extern "C" int rl_kv_append_rope(const rl_kv_append_desc* d, void* hip_stream) {
   P.s0 = d->sections[0]; P.s1 = d->sections[1];
   P.kscale = d->dtype == 2 ? d->k_scale : nullptr; P.vscale = d->dtype == 2 ? d->v_scale : nullptr;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  // 16 bytes at a time where every row starts on such a line: d is a multiple of 64, so the bases decide
+  // 16 bytes at a time where every row starts on such a line (d is a multiple of 64, so the bases decide) and there is
+  // enough to do: a thread with 16 bytes rounds 8 or 16 e4m3 values one after the other, where few heads leave other
+  // threads without work.  us, 16 bytes / one element at a time, sequences x heads of 128 (64) columns:
+  //   e4m3  128 x 3/1 6.0 / 3.6, 128 x 8/2 4.55 / 4.27, 128 x 28/4 (64) 4.7 / 4.5, 256 x 16/2 4.6 / 4.9, 128 x 8/8 5.5 / 6.1,
+  //         4096 x 4/1 (64) 12.5 / 7.4, 2048 x 12/2 8.3 / 8.3, 2048 x 16/2 8.0 / 9.1
+  //   bf16  64 x 2/2 (64) 3.34 / 3.21, 128 x 3/1 3.36 / 3.40, 128 x 4/4 3.3 / 3.9;   fp32  64 x 2/2 (64) 3.22 / 3.28
+  const int64_t elements = (int64_t)(d->Hq + d->Hkv) * (d->d / 2) + (int64_t)d->Hkv * d->d;   // rotations and values
+  static constexpr int64_t few[3] = {0, 256, 1280};
   const uintptr_t bases = (uintptr_t)P.q | (uintptr_t)P.k_new | (uintptr_t)P.v_new | (uintptr_t)P.ks | (uintptr_t)P.vs;
   typedef void (*kern_t)(const Params);
   static constexpr kern_t kerns[2][3] = {
       {kv_append_rope_kernel<float, false>, kv_append_rope_kernel<uint16_t, false>, kv_append_rope_kernel<uint16_t, true>},
       {kv_append_rope_vec_kernel<float, false>, kv_append_rope_vec_kernel<uint16_t, false>, kv_append_rope_vec_kernel<uint16_t, true>}};
-  hipLaunchKernelGGL(kerns[bases % 16 == 0][d->dtype], dim3(d->B), dim3(256), 0, st, P);
+  hipLaunchKernelGGL(kerns[bases % 16 == 0 && elements > few[d->dtype]][d->dtype], dim3(d->B), dim3(256), 0, st, P);
   return hipGetLastError() == hipSuccess ? 0 : -5;
 }
