@@ -498,8 +498,9 @@ UnitGrid unit_grid(const Problem& pb, int pairs, bool exact) {
   u.groups8 = groups >= 16 && G > 1 ? (int)((groups + 7) / 8) : 0;
   u.blocks = u.groups8 > 0 ? u.groups8 * 8 * G * rb : B * pb.Hkv * rb;
   const bool f32 = pb.dtype == RLDA_F32, many = u.blocks > 4 * (int64_t)pairs;
-  // workgroups of four wavefronts that a compute unit's LDS holds: tiles of 64 16-bit columns are half as large
-  const int64_t fit = (pb.d == 64 && !f32 ? 4 : 2) * (int64_t)pairs;
+  // workgroups of four wavefronts that the compute units' LDS holds (tiles of 64 16-bit columns are half as large), and a
+  // quarter more, which follow as soon as short units end: 528 units of up to 182 keys 9.5 us with four, 10.0 with two
+  const int64_t fit = (pb.d == 64 && !f32 ? 4 : 2) * (int64_t)pairs * 5 / 4;
   // rows looked up one by one make a long chain, worth more wavefronts than the queue costs a little longer
   if (u.blocks <= pairs || (row_lookup(pb) && keys >= 512 && 2 * u.blocks <= 3 * (int64_t)pairs)) {
     u.nw = wide_waves(f32, pb.d);
@@ -515,7 +516,9 @@ UnitGrid unit_grid(const Problem& pb, int pairs, bool exact) {
   return u;
 }
 
-// the form of one store type and head dimension: pages of fewer rows than a tile, a tree, or two segments
+// The form of one store type and head dimension: pages of fewer rows than a tile, a tree, or two segments.  The fewer
+// wavefronts share a unit's tiles, the fewer of a row's large weights are a tile's own maximum, which is 1 and needs no
+// bits: few wavefronts keep all 24 of the others (16 bits: 1.7e-6 of out against 64 bits, 1.1e-6 with one tile a wavefront).
 template <int KIND, int D, bool EXACT>
 hipError_t launch_form(const UnitParams& P, int nw, int64_t blocks, hipStream_t stream) {
   constexpr int WIDE = wide_waves(KIND == KV_F32, D);
@@ -528,13 +531,13 @@ hipError_t launch_form(const UnitParams& P, int nw, int64_t blocks, hipStream_t 
     }
   if constexpr (KIND == KV_BF16 && D == 128 && !EXACT)        // what a tree holds
     if (P.n_seg != 2) {
-      if (nw == 1) return launch<KIND, D, EXACT, 1, MAX_SEG>(P, blocks, stream);
-      if (nw == 2) return launch<KIND, D, EXACT, 2, MAX_SEG>(P, blocks, stream);
-      if (nw == 4) return launch<KIND, D, EXACT, 4, MAX_SEG>(P, blocks, stream);
+      if (nw == 1) return launch<KIND, D, true, 1, MAX_SEG>(P, blocks, stream);
+      if (nw == 2) return launch<KIND, D, true, 2, MAX_SEG>(P, blocks, stream);
+      if (nw == 4) return launch<KIND, D, true, 4, MAX_SEG>(P, blocks, stream);
       return launch<KIND, D, EXACT, WIDE, MAX_SEG>(P, blocks, stream);
     }
-  if (nw == 1) return launch<KIND, D, EXACT, 1>(P, blocks, stream);
-  if (nw == 2) return launch<KIND, D, EXACT, 2>(P, blocks, stream);
+  if (nw == 1) return launch<KIND, D, true, 1>(P, blocks, stream);
+  if (nw == 2) return launch<KIND, D, true, 2>(P, blocks, stream);
   return nw == 4 ? launch<KIND, D, EXACT, 4>(P, blocks, stream) : launch<KIND, D, EXACT, WIDE>(P, blocks, stream);
 }
 
