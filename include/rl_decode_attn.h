@@ -27,17 +27,19 @@
  * caller has already appended the current token's K/V and counted it in
  * suffix_lens).  Positional rotation of q and K happens before the call.
  *
- * How it is computed: the prefix K/V of a prompt is read from HBM once and
- * reused by all G samples and all Hq/Hkv query heads of a KV group; each
- * sequence's suffix is streamed once; partial (o, lse) results of key ranges
- * are merged by a log-sum-exp combine.  The method is exact; what the result
- * carries is rounding.  fp32 inputs: fp32 rounding order only.  bf16 inputs:
- * scores and sums accumulate in fp32, the softmax weights are rounded to bf16
- * before the value contraction, and a partial result passes between the two
- * kernels as fp16 after a per-row power-of-two scaling that puts its largest
- * magnitude into [0.5, 1) (an error of at most 2^-12 of that magnitude per
- * element).  Observed against the fp64 definition on the benchmark shapes:
- * 1e-3 on out, 1e-6 on lse.
+ * How it is computed: on the shared-prefix path the prefix K/V of a prompt is
+ * read from HBM once and reused by all G samples and all Hq/Hkv query heads of
+ * a KV group; each sequence's suffix is streamed once; partial (o, lse) results
+ * of key ranges are merged by a log-sum-exp combine.  The method is exact; what
+ * the result carries is rounding.  fp32 inputs: fp32 rounding order only.  bf16
+ * inputs: scores and sums accumulate in fp32; on the shared-prefix path the
+ * softmax weights are rounded to bf16 before the value contraction, and a
+ * partial result passes between the two kernels as fp16 after a per-row
+ * power-of-two scaling that puts its largest magnitude into [0.5, 1) (an error
+ * of at most 2^-12 of that magnitude per element).  Observed against the fp64
+ * definition on the benchmark shapes: 1e-3 on out, 1e-6 on lse.  Calls that
+ * take one launch (see RLDA_ALGO_AUTO) keep 16 or 24 bits of a weight and no
+ * fp16 partials.
  */
 #ifndef RL_DECODE_ATTN_H
 #define RL_DECODE_ATTN_H
@@ -62,8 +64,8 @@ extern "C" {
  *                         store halves those bytes.  The call computes the attention of the header
  *                         comment on exactly these dequantised values (every e4m3 value is exact in
  *                         bf16, so nothing is rounded on the way in); how the bytes were produced is
- *                         the caller's business.  Both kernel families take it (d = 64 or 128; the
- *                         usual limits of RLDA_ALGO_SHARED decide which one AUTO picks).  NaN bytes
+ *                         the caller's business.  All kernels take it (d = 64 or 128; the usual
+ *                         limits of RLDA_ALGO_SHARED decide how a call is planned).  NaN bytes
  *                         may sit in rows at or beyond a length like any other garbage.
  */
 typedef enum { RLDA_F32 = 0, RLDA_BF16 = 1, RLDA_BF16_KV8 = 2 } rlda_dtype;
@@ -74,12 +76,15 @@ typedef enum {
                               Hq/Hkv <= 16, G * Hq/Hkv <= 256, scale > 0 and, for a paged store, pages of at
                               least 32 rows.  Everything else -- fp32, d = 64, other head ratios or scales,
                               smaller pages -- is planned as SIMPLE (no sharing across sequences, no scratch);
-                              under AUTO it then runs in a one-launch form of it on the matrix cores, one
-                              workgroup per (sequence, KV head), with 32-bit softmax weights as ever.  The same
-                              form takes batches of the shared-prefix path that are too small to fill the chip;
-                              their workspace is asked for and checked all the same. */
+                              under AUTO most of it then runs in a one-launch form on the matrix cores, one
+                              workgroup per (sequence, KV head), with 24-bit softmax weights; few rows over few
+                              keys stay on the simple kernel, which is faster there.  The one-launch form also
+                              takes batches of the shared-prefix path that are too small to fill the chip (16 or
+                              24 bits of a weight); their workspace is asked for and checked all the same. */
   RLDA_ALGO_SIMPLE = 1,    /* one wavefront per (sequence, query head), no sharing, no split, no matrix cores: the
-                              plain reference on the GPU (forced, or where the stores are not 16-byte aligned) */
+                              plain reference on the GPU.  Under AUTO also what the one-launch form does not take:
+                              few rows over few keys, stores that are not 16-byte aligned, a scale that is not
+                              finite, very large capacities and grids */
   RLDA_ALGO_SHARED = 2     /* force the shared-prefix path; RLDA_ERR_UNSUPPORTED if not possible */
 } rlda_algo;
 
@@ -155,9 +160,10 @@ int rl_decode_attn_profiled(const rlda_desc* desc, void* hip_stream, void* mid_e
 size_t rl_decode_attn_workspace_bytes(const rlda_desc* desc);
 
 /*
- * The kernel family rl_decode_attn would run for this descriptor:
- * RLDA_ALGO_SIMPLE or RLDA_ALGO_SHARED, or a negative RLDA_ERR_* code.
- * Pure host function.
+ * How rl_decode_attn plans this descriptor: RLDA_ALGO_SHARED (the shared-prefix
+ * path's shapes, with its workspace) or RLDA_ALGO_SIMPLE (no workspace), or a
+ * negative RLDA_ERR_* code.  Under RLDA_ALGO_AUTO either may run in one launch
+ * without that changing the plan.  Pure host function.
  */
 int rl_decode_attn_plan(const rlda_desc* desc);
 
@@ -211,8 +217,8 @@ int rl_decode_attn_version(void);
  * Key n of sequence b's suffix is row n % page_size of page
  * block_table[b, n / page_size].  A page holds all KV heads:
  * k_pages / v_pages are [n_pages, Hkv, page_size, d].  page_size is a power of
- * two (below 32 rows the call runs on RLDA_ALGO_SIMPLE).  Table entries at or beyond ceil(suffix_lens[b] / page_size) are
- * never read as page ids of live keys and may hold anything; entries that are
+ * two (below 32 rows the call is planned as RLDA_ALGO_SIMPLE).  Table entries at
+ * or beyond ceil(suffix_lens[b] / page_size) are never read as page ids of live keys and may hold anything; entries that are
  * used are clamped to [0, n_pages) (a wrong id gives a wrong result, never an
  * out-of-pool access).  suffix_lens are clamped to [0, max_pages * page_size].
  *

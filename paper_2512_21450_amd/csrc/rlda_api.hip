@@ -33,7 +33,7 @@ int to_problem(const rlda_paged_desc* ds, Problem& pb) {
   if (!ds) return RLDA_ERR_INVALID;
   if (ds->struct_size != sizeof(rlda_paged_desc)) return RLDA_ERR_STRUCT_SIZE;
   if (ds->max_pages < 0 || ds->n_pages < 0 || ds->page_size <= 0) return RLDA_ERR_INVALID;
-  if (ds->page_size & (ds->page_size - 1)) return RLDA_ERR_UNSUPPORTED;   // below 32 rows: the simple kernel only
+  if (ds->page_size & (ds->page_size - 1)) return RLDA_ERR_UNSUPPORTED;   // below 32 rows: not the shared-prefix kernels
   if ((int64_t)ds->max_pages * ds->page_size > (int64_t)1 << 30) return RLDA_ERR_UNSUPPORTED;
   if (ds->max_pages > 0 && ds->n_pages < 1) return RLDA_ERR_INVALID;
   pb = Problem{};

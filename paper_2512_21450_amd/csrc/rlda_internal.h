@@ -67,7 +67,8 @@ hipError_t device_pairs(int& pairs);
 hipError_t launch_shared(const Problem& pb, hipStream_t stream, hipEvent_t mid);
 
 // ---- one workgroup per (sequence, KV head): all dtypes, d in {64, 128}, tree levels, pages of any size, any finite scale.
-// `exact`: softmax weights enter the value contraction with 24 bits, else (d = 128 only) with 16
+// `exact`: softmax weights enter the value contraction with 24 bits; else (d = 128 only) with 16 in the forms of 8 and 4
+// wavefronts per unit (trees: 8), with 24 in the others
 // `pairs`: workgroup pairs of the device at hand (device_pairs), which stand for its compute units
 bool unit_supported(const Problem& pb, int pairs);
 bool unit_pays(const Problem& pb, int pairs);        // and runs faster here than on the simple kernel

@@ -1395,7 +1395,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
   // offsets serve a whole tile on top of a uniform address, and the instruction's immediate counts on both sides
   // because four rows are 1 KB in either.  A partial last tile clamps every row to the last real key (re-read;
   // those keys are masked).  Without the empty asm the compiler carries the addresses of all four unrolled stages in
-  // registers, and at 128 rows per workgroup spills (126 of them; 248 registers and no spill with it).  Measured on
+  // registers, and at 128 rows per workgroup spills (126 of them; 252 registers and no spill with it).  Measured on
   // 32 prompts of 1280 tokens, 28/4 heads: an address per row and load 496 us, the four offsets 486.
   const int kind = uni(wv & 1), sub = uni(wv >> 1), lrow = lane >> 4, chunk = lane & 15;
   const char* gb = (kind ? P.v : P.k) + (size_t)(p * P.Hkv + j) * P.Lp_cap * ROWB;      // uniform
@@ -1794,6 +1794,10 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   // 17.1 / 21.2; 30 ragged up to 500 of 12/2, 720k, 34.2 / 30.6; 3 x 1100 of 28/4, 818k, 48.1 / 41.2; 4 x 900 of
   // 56/8, 93 / 79) or that there are many (100 ragged up to 200 of 16/4, 2800 workgroups, 51.6 / 47.3).  The
   // register-staged kernel is what scales that are not positive run on.
+  // The host knows the capacity only.  Below four rounds two blocks lose where the prompts fill less than about half
+  // of it, one block / two: 4 x 2048 of 16/2 all filled 99 / 80 us, 60 % 46.6 / 41.3, 50 % 35.4 / 37.3, 30 %
+  // 19.9 / 25.0; 1 x 4096 of 28/4 163 / 128, 66 / 69, 51 / 59, 29.0 / 36.9; 2 x 4096 of 28/4 313 / 250, 124 / 100,
+  // 92 / 74, 42.4 / 41.8.  Both bodies in one kernel that chose by the lengths cost every call 1 to 3 us.
   const int rows1 = 16 * WG_WAVES;
   const int64_t units8 = (int64_t)8 * ceil_div(P_ * Hkv, 8);              // eight XCDs, whole rounds of units
   const int64_t wgs = (int64_t)P_ * Hkv * ceil_div(Lp_cap, (2 * rows1) / P.r);

@@ -1,8 +1,11 @@
 // Simple decode-attention kernel: one 64-lane wavefront per (sequence, query
-// head).  No prefix sharing, no key split, plain vector ALU.  It is the fp32
-// path and the unoptimised GPU reference row of the benchmark.  K/V stores may
-// also hold e4m3 bytes (decoded here with integer operations, not with the
-// hardware converter the matrix-core path uses).
+// head).  No prefix sharing, no key split, plain vector ALU.  It is the
+// unoptimised GPU reference row of the benchmark, and under RLDA_ALGO_AUTO what
+// neither the shared-prefix kernels nor the unit kernel take: few rows over few
+// keys outside the former's shapes, stores off 16-byte boundaries, scales that
+// are not finite, capacities and grids beyond the unit kernel's bounds.  K/V
+// stores may also hold e4m3 bytes (decoded here with integer operations, not
+// with the hardware converter the matrix-core path uses).
 //
 // For its (b, h) the wavefront walks the prompt prefix of prompt p = b / G and
 // then the sequence's own suffix (Sec. 3.1 of the paper: the state is the

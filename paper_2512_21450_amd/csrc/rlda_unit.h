@@ -1,13 +1,16 @@
 // Decode attention with one workgroup per unit: all keys of one (sequence, KV head) against its Hq/Hkv query rows,
 // one launch, no scratch.  Two uses:
-//   * what the shared-prefix kernels do not take (fp32 stores, d = 64, wider head ratios, scales that are not
-//     positive, pages under 32 rows).  Softmax weights and sums are held in 32 bits (EXACT below);
+//   * most of what the shared-prefix kernels do not take (fp32 stores, d = 64, wider head ratios, scales that are
+//     not positive, pages under 32 rows), but for few rows over few keys, which the simple kernel runs faster
+//     (unit_pays).  Weights enter the value contraction with 24 bits (EXACT below);
 //   * batches so small that two dependent launches cost more than reading the prefix once per sequence
-//     (unit_preferred).  Weights then enter the value contraction with 16 bits (the shared-prefix kernels: 8).
+//     (unit_preferred).  Weights then have 16 bits (the shared-prefix kernels: 8) where 8 or 4 wavefronts share a
+//     unit of two segments, or 8 one of a tree, and 24 in the forms with fewer.
 //
-// The NW wavefronts of a workgroup take the unit's 32-key tiles in turn (tile t goes to wavefront t % NW) and keep
-// an online-softmax state each; the states meet in LDS at the end.  Tiles are numbered segment by segment (shared
-// levels, then the own suffix), so the order of additions depends on the lengths only.
+// The NW = 8, 4, 2 or 1 wavefronts of a workgroup (unit_grid says how many) take the unit's 32-key tiles in turn
+// (tile t goes to wavefront t % NW) and keep an online-softmax state each; the states meet in LDS at the end.  Tiles
+// are numbered segment by segment (shared levels, then the own suffix), so the order of additions depends on the
+// lengths and NW only.
 //
 // What bounds it: memory round trips.  A wavefront has the next tile on the way in registers while it computes on the
 // present one, which goes through its private part of LDS.  (K straight into the registers of the matrix operand, 16
@@ -17,7 +20,7 @@
 // memory once and from that die's L2 for the other samples.
 //
 // Tile math as in the shared-prefix kernels: S^T = K Q^T, so that a lane's accumulators (one query row, 4 keys per
-// 16-key half) are the operand of O^T += V^T P^T.  A weight is split into two bf16 pieces, EXACT: three (24 bits),
+// 16-key half) are the operand of O^T += V^T P^T.  A weight is split into two bf16 pieces (16 bits), EXACT: three (24),
 // each contracted with V on the matrix cores; fp32 stores use the fp32 matrix instruction.
 #pragma once
 
@@ -361,7 +364,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     step(std::false_type{}, t);
   }
 
-  // ---- merge: every wavefront leaves its rows (O against its own maximum) in its V stage
+  // ---- merge: every wavefront leaves its rows (O against its own maximum) in its stages, from the K stage on
   l += __shfl_xor(l, 16, 64); l += __shfl_xor(l, 32, 64);
   constexpr int OC = D / 4;                            // 16-byte chunks of an O row
   constexpr int OROWB = D * 4;
