@@ -131,7 +131,7 @@ def test_auto_selects_the_shared_prefix_path_for_bf16_d128():
         ds = B.make_desc(B.RLDA_BF16, W.P, W.G, W.Hq, W.Hkv, W.d, W.Lp_cap, W.Ls_cap, W.scale)
         assert B.rl_decode_attn_plan(ds) == B.RLDA_ALGO_SHARED
         assert B.rl_decode_attn_workspace_bytes(ds) > 0
-    # shapes outside the MFMA path fall back to the simple kernel under AUTO
+    # shapes outside the shared-prefix path have the plan SIMPLE under AUTO
     assert B.rl_decode_attn_plan(good(d=64)) == B.RLDA_ALGO_SIMPLE
     assert B.rl_decode_attn_plan(good(Hq=64, Hkv=2)) == B.RLDA_ALGO_SIMPLE          # 32 heads per KV head
     assert B.rl_decode_attn_plan(good(Hq=64, Hkv=2, algo=B.RLDA_ALGO_SHARED)) == B.RLDA_ERR_UNSUPPORTED
@@ -169,7 +169,7 @@ def test_paged_shape_errors(kw, code):
 
 
 def test_small_pages_plan_onto_the_simple_kernel():
-    # a page shorter than a 32-key tile: the shared-prefix path cannot take it, the simple kernel resolves pages key by key
+    # a page shorter than a 32-key tile: the shared-prefix path cannot take it, the other kernels resolve pages key by key
     for ps in (1, 8, 16):
         assert B.rl_decode_attn_paged_plan(good_paged(page_size=ps)) == B.RLDA_ALGO_SIMPLE
         assert B.rl_decode_attn_paged_workspace_bytes(good_paged(page_size=ps)) == 0
