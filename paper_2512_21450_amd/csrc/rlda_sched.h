@@ -83,6 +83,21 @@ struct Sched {
   int psh;      // logarithm of the number of shares of the prefix line (cu_sh, dual: cu_sh - 1)
 };
 
+// n / d for 0 <= n < 2^31 as a multiplication: m = floor(2^k / d) + 1 with k = 31 + ceil(log2 d) (m fits 32 bits,
+// and m * d - 2^k <= d <= 2^(k - 31) makes the quotient exact).  The combine kernels split every row index three
+// times and the unit kernel its place in the grid; a 32-bit integer division costs them about ten times this.
+struct FastDiv { uint32_t m; int k; };
+inline FastDiv make_fastdiv(int d) {
+  if (d < 1) d = 1;                                          // an empty batch launches nothing; keep the host safe
+  int l = 0;
+  while ((1 << l) < d) ++l;
+  FastDiv f;
+  f.k = 31 + l;
+  f.m = (uint32_t)(((uint64_t)1 << f.k) / (uint32_t)d + 1);
+  return f;
+}
+__host__ __device__ inline int fast_div(int n, FastDiv f) { return (int)(((uint64_t)(uint32_t)n * f.m) >> f.k); }
+
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // The R = G * Hq/Hkv query rows that share a prefix tile are handled in row parts ("halves") of at

@@ -58,21 +58,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 struct TreeLevel { const char* k; const char* v; const int32_t* lens; int first, G, R, cap; };
 constexpr int MAX_LEVELS = RLDA_MAX_TREE_LEVELS;   // 4
 
-// n / d for 0 <= n < 2^31 as a multiplication: m = floor(2^k / d) + 1 with k = 31 + ceil(log2 d) (m fits 32 bits,
-// and m * d - 2^k <= d <= 2^(k - 31) makes the quotient exact).  The combine kernels split every row index three
-// times; a 32-bit integer division costs them about ten times this.
-struct FastDiv { uint32_t m; int k; };
-inline FastDiv make_fastdiv(int d) {
-  if (d < 1) d = 1;                                          // an empty batch launches nothing; keep the host safe
-  int l = 0;
-  while ((1 << l) < d) ++l;
-  FastDiv f;
-  f.k = 31 + l;
-  f.m = (uint32_t)(((uint64_t)1 << f.k) / (uint32_t)d + 1);
-  return f;
-}
-__device__ __forceinline__ int fast_div(int n, FastDiv f) { return (int)(((uint64_t)(uint32_t)n * f.m) >> f.k); }
-
 struct SharedParams {
   const char* q; const char* kp; const char* vp; const char* ks; const char* vs;
   const int32_t* plens; const int32_t* slens;

@@ -12,10 +12,18 @@
 // are numbered segment by segment (shared levels, then the own suffix), so the order of additions depends on the
 // lengths and NW only.
 //
-// What bounds it: memory round trips.  A wavefront has the next tile on the way in registers while it computes on the
-// present one, which goes through its private part of LDS.  (K straight into the registers of the matrix operand, 16
-// rows to an instruction, saved that trip but took the address unit four times as long as whole rows do: 1.05 us per
-// 64 KB and compute unit.)
+// What bounds it: the round trips before the first product, and the 64 bytes a clock that a compute unit loads (8 tiles of
+// 128 bf16 columns: 1 us).  A wavefront has the next tile on the way in registers while it computes on the present one,
+// which goes through its private part of LDS.  (K straight into the registers of the matrix operand, 16 rows to an
+// instruction, saved that trip but took the address unit four times as long as whole rows do: 1.05 us per 64 KB and
+// compute unit.)  So the start is what counts for units of few tiles: the lengths are asked for first, then q and, where
+// the first segment's capacity has room for a whole tile, the wavefront's first K tile, before the lengths are known (a
+// tile that turns out shorter is loaded again: calls whose segments are empty pay 0.3-0.5 us for it; asking for V as well
+// gained 0.2 us more and cost those 1.0-1.7); the second tile is asked for before the first has landed; the place in the
+// grid is found without divisions; and the loop holds one copy of the arithmetic, masks under a branch.  Calls captured
+// back to back, before / after, us: 64 units x 256 keys, bf16, 64 columns 5.28 / 4.60, 128 columns 6.6 / 5.9, fp32 7.8 /
+// 7.0; x 512 keys 6.75 / 6.0, 9.6 / 9.3, 12.2 / 11.6; e4m3 of 128 columns x 512 keys 8.6 / 7.7; 448 units of up to 1864
+// keys, e4m3, 64 columns 19.0 / 17.7; 512 units x 964, bf16, 64 columns 20.4 / 19.0.
 // Samples of one prompt sit on one die, side by side in dispatch order, so that the prefix a group shares comes from
 // memory once and from that die's L2 for the other samples.
 //
@@ -46,7 +54,7 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int MAX_SEG = RLDA_MAX_TREE_LEVELS + 1;
 // keys shared by `group` consecutive sequences: stores [n, Hkv, cap, d], lens [n]
-struct Segment { const char* k; const char* v; const int32_t* lens; int group, cap; };
+struct Segment { const char* k; const char* v; const int32_t* lens; int group, cap; FastDiv div; };   // div: by group
 
 struct UnitParams {
   const char* q;
@@ -54,6 +62,7 @@ struct UnitParams {
   Segment seg[MAX_SEG];            // shared levels, then the own suffix (group 1), at index n_seg - 1
   int n_seg;
   int B, G, Hq, Hkv, r, RB;        // r = Hq / Hkv query rows in RB blocks of 16
+  FastDiv div_per, div_RB, div_Hkv;   // quotients by G * RB, RB and Hkv
   int groups8;                     // (prompt, KV head) groups rounded up to the dies, 0: units in plain order
   float scale, c, c_lo;            // and |scale| * log2(e) with what its rounding left; 1 and 0 when the scale is 0
   uint32_t qsign, qmask;           // q bits: & qmask (0 when the scale is 0), ^ qsign (for a negative factor), per 16-bit half or word
@@ -130,25 +139,27 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   int b, j, rb;
   if (P.groups8 > 0) {
     const int xcd = blockIdx.x & 7, s = blockIdx.x >> 3, per = P.G * P.RB;
-    const int grp = (s / per) * 8 + xcd, in = s % per;
-    const int p = grp / P.Hkv;
-    j = grp - p * P.Hkv; b = p * P.G + in / P.RB; rb = in % P.RB;
+    const int round = fast_div(s, P.div_per), grp = round * 8 + xcd, in = s - round * per;
+    const int p = fast_div(grp, P.div_Hkv), own = fast_div(in, P.div_RB);
+    j = grp - p * P.Hkv; b = p * P.G + own; rb = in - own * P.RB;
     if (b >= P.B) return;                              // groups are rounded up to the eight dies
   } else {
-    const int u = blockIdx.x / P.RB;
-    rb = blockIdx.x - u * P.RB; b = u / P.Hkv; j = u - b * P.Hkv;
+    const int u = fast_div(blockIdx.x, P.div_RB);
+    rb = blockIdx.x - u * P.RB; b = fast_div(u, P.div_Hkv); j = u - b * P.Hkv;
   }
   const int nr = min(16, P.r - 16 * rb), h0 = j * P.r + 16 * rb;
-  const bool live = !P.active || P.active[b] != 0;
 
-  // ---- tiles of the segments
+  // ---- the segments: where they start, and their lengths, which are on their way while q and the first K tile are asked for
+  size_t at[NSEG];
   int len[NSEG], first[NSEG], T = 0;
+  const int act = P.active ? P.active[b] : 1;
 #pragma unroll
   for (int s = 0; s < NSEG; ++s) {
-    len[s] = 0; first[s] = T;
+    len[s] = 0; at[s] = 0;
     if (NSEG == 2 || s < P.n_seg) {
-      len[s] = live ? clampi(P.seg[s].lens[b / P.seg[s].group], 0, P.seg[s].cap) : 0;
-      T += ceil_div(len[s], TK);
+      const int owner = fast_div(b, P.seg[s].div);
+      at[s] = ((size_t)owner * P.Hkv + j) * P.seg[s].cap * L_::ROWB;
+      len[s] = P.seg[s].lens[owner];
     }
   }
 
@@ -160,19 +171,19 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
       const bool own = NSEG == 2 ? s == 1 : s == P.n_seg - 1;
       if ((NSEG == 2 || s < P.n_seg) && t >= first[s] && len[s] > 0) {
         const int n0 = (t - first[s]) * TK;
-        size_t row = ((size_t)(b / P.seg[s].group) * P.Hkv + j) * P.seg[s].cap + n0;
+        size_t off = at[s] + (size_t)n0 * L_::ROWB;
         x.last = min(TK, len[s] - n0) - 1;
         x.n0 = 0;
         if (own && P.table) {
           if constexpr (ROWS) {
-            row = 0; x.n0 = n0 + 1;
+            off = 0; x.n0 = n0 + 1;
           } else {                                     // a tile lies in one page
             const int pg = uni(clampi(P.table[(size_t)b * P.max_pages + (n0 >> P.page_shift)], 0, P.n_pages - 1));
-            row = (((size_t)pg * P.Hkv + j) << P.page_shift) + (n0 & ((1 << P.page_shift) - 1));
+            off = ((((size_t)pg * P.Hkv + j) << P.page_shift) + (n0 & ((1 << P.page_shift) - 1))) * L_::ROWB;
           }
         }
-        x.k = P.seg[s].k + row * L_::ROWB;
-        x.v = P.seg[s].v + row * L_::ROWB;
+        x.k = P.seg[s].k + off;
+        x.v = P.seg[s].v + off;
       }
     }
     return x;
@@ -214,6 +225,28 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     }
   };
 
+  // ---- what needs no length: q, and the wavefront's first K tile where the first segment has room for all of it
+  u32x4 qr[NQ], ka[L_::NL], va[L_::NL];
+  const char* qp = P.q + ((size_t)b * P.Hq + h0 + min(m16, nr - 1)) * D * QE;
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) qr[i] = *reinterpret_cast<const u32x4*>(qp + 64 * i + 16 * g);   // chunk 4 i + g, as K
+  const bool early = (wv + 1) * TK <= P.seg[0].cap && (NSEG == 2 || P.n_seg > 1);
+  if (early) {
+    const size_t off = at[0] + (size_t)wv * TK * L_::ROWB;
+    const Tile guess{P.seg[0].k + off, P.seg[0].v + off, 0, TK - 1};
+    load(guess, guess.k, ka);
+  }
+
+  // ---- tiles of the segments
+#pragma unroll
+  for (int s = 0; s < NSEG; ++s) {
+    first[s] = T;
+    if (NSEG == 2 || s < P.n_seg) {
+      len[s] = act != 0 ? clampi(len[s], 0, P.seg[s].cap) : 0;
+      T += ceil_div(len[s], TK);
+    }
+  }
+
   // The factor of the exponents meets differences of products only, so that the size of the scores costs a weight
   // nothing, and is kept positive and finite (a difference of 0 or -inf times it has to stay).  EXACT: what its rounding
   // left, the same for all keys, would show in lse; that part is positive too, for the same reason.
@@ -235,16 +268,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   // overflow) and -inf less itself is not a number
   float m = -FLT_MAX, l = 0.f;
 
-  Tile cur;
-  u32x4 qr[NQ];
-  auto step = [&](auto more, int t) {                  // more: tile t + NW follows
-    constexpr bool MORE = decltype(more)::value;
-    store(kst, kr, L_::kswz);
-    Tile nxt = cur;
-    if constexpr (MORE) { nxt = tile_of(t + NW); load(nxt, nxt.k, kr); }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-
+  auto step = [&](int nvalid) {                        // the tile in LDS, its first `nvalid` keys
     // ---- scores of this lane's row (m16) for keys 4 g + x and 16 + 4 g + x
     // (fp32: two sums each, half as long a chain of roundings and of waits)
     f32x4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f}, s2{0.f, 0.f, 0.f, 0.f}, s3{0.f, 0.f, 0.f, 0.f};
@@ -266,16 +290,18 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
       }
     }
     if constexpr (KIND == KV_F32) { s0 += s2; s1 += s3; }
-    const int nvalid = cur.last + 1;
 
     // ---- online softmax in base 2; a row's reference maximum moves only when a tile exceeds it by a factor of 2^8
     // in the weights (fp32 holds the larger sums without loss)
     float sv[8];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      sv[x] = 4 * g + x < nvalid ? s0[x] : -INFINITY;
-      sv[4 + x] = 16 + 4 * g + x < nvalid ? s1[x] : -INFINITY;
-    }
+    for (int x = 0; x < 4; ++x) { sv[x] = s0[x]; sv[4 + x] = s1[x]; }
+    if (nvalid < TK)                                   // (uniform)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        sv[x] = 4 * g + x < nvalid ? s0[x] : -INFINITY;
+        sv[4 + x] = 16 + 4 * g + x < nvalid ? s1[x] : -INFINITY;
+      }
     float tm = max_raw(max_raw(max_raw(sv[0], sv[1]), max_raw(sv[2], sv[3])),
                        max_raw(max_raw(sv[4], sv[5]), max_raw(sv[6], sv[7])));
     tm = row_max(tm);
@@ -294,11 +320,6 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
       p[x] = __builtin_amdgcn_exp2f(EXACT ? fmaf(dx, c_lo, e) : e);
     }
     l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-
-    store(vst, vr, L_::vswz);
-    if constexpr (MORE) load(nxt, nxt.v, vr);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
 
     // ---- O^T += V^T P^T
     if constexpr (KIND == KV_F32) {
@@ -345,23 +366,39 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");   // LDS serves a wavefront in order: the stage may be rewritten
     __builtin_amdgcn_wave_barrier();
-    cur = nxt;
   };
   if (wv < T) {
-    const char* qp = P.q + ((size_t)b * P.Hq + h0 + min(m16, nr - 1)) * D * QE;
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) qr[i] = *reinterpret_cast<const u32x4*>(qp + 64 * i + 16 * g);   // chunk 4 i + g, as K
-    cur = tile_of(wv);
-    load(cur, cur.k, kr);
-    load(cur, cur.v, vr);
+    const Tile cur = tile_of(wv);
+    if (!(early && (wv + 1) * TK <= len[0])) load(cur, cur.k, ka);
+    load(cur, cur.v, va);
     const uint32_t qm = m16 < nr ? P.qmask : 0u;
     const uint32_t qs = m16 < nr && (P.scale < 0.f) != (ks < 0.f) ? P.qsign : 0u;
+    Tile nxt = cur;
+    // the second tile is asked for before the first has landed; in branches of their own, so that the wait for the first
+    // counts the loads that follow it
+    if (wv + NW < T) {
+      nxt = tile_of(wv + NW);
+      load(nxt, nxt.k, kr); load(nxt, nxt.v, vr);
+      store(kst, ka, L_::kswz);
+      store(vst, va, L_::vswz);
+    } else {
+      store(kst, ka, L_::kswz);
+      store(vst, va, L_::vswz);
+    }
 #pragma unroll
     for (int i = 0; i < NQ; ++i) qr[i] = (qr[i] & qm) ^ qs;
-    // the last step is a copy of its own: the waits of the others then count exactly the loads that follow
-    int t = wv;
-    for (; t + NW < T; t += NW) step(std::true_type{}, t);
-    step(std::false_type{}, t);
+    int nvalid = cur.last + 1;
+    for (int t = wv;;) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      step(nvalid);
+      t += NW;
+      if (t >= T) break;
+      nvalid = nxt.last + 1;
+      store(kst, kr, L_::kswz);
+      store(vst, vr, L_::vswz);
+      if (t + NW < T) { nxt = tile_of(t + NW); load(nxt, nxt.k, kr); load(nxt, nxt.v, vr); }
+    }
   }
 
   // ---- merge: every wavefront leaves its rows (O against its own maximum) in its stages, from the K stage on
@@ -377,15 +414,16 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   }
   if (g == 0) { wm[wv][m16] = m; wl[wv][m16] = l; }
   __syncthreads();
-  const int nw = min(NW, T);                           // wavefronts that had a tile
   bool odd = false;                                    // a column that is not finite where the row's weights are
   for (int it = tid; it < nr * OC; it += 64 * NW) {
     const int row = it / OC, ch = it % OC;
-    float M = -INFINITY;
-    for (int w = 0; w < nw; ++w) M = fmaxf(M, wm[w][row]);
+    float M = wm[0][row];                              // a wavefront without a tile: the lowest maximum, and zeros
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, wm[w][row]);
     float L = 0.f;
     f32x4 acc{0.f, 0.f, 0.f, 0.f};
-    for (int w = 0; w < nw; ++w) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
       const float a = __builtin_amdgcn_exp2f((wm[w][row] - M) * c);
       L = fmaf(a, wl[w][row], L);
       const f32x4 o = *RLDA_LDS(const f32x4, lds + w * OSTRIDE + row * OROWB + ((ch ^ row) << 4));
@@ -415,7 +453,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     for (int it = tid; it < nr * OC; it += 64 * NW) {
       const int row = it / OC, ch = it % OC;
       float L = 0.f;
-      for (int w = 0; w < nw; ++w) L += wl[w][row];
+      for (int w = 0; w < NW; ++w) L += wl[w][row];
       if (!(L < INFINITY)) continue;                   // a score that is not a number: the row is none
       f32x4 sum{0.f, 0.f, 0.f, 0.f};
       for (int s = 0; s < A->n_seg; ++s) {
@@ -630,15 +668,19 @@ hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t str
   if (pb.n_levels > 0) {
     for (; n < pb.n_levels; ++n) {
       const Problem::Level& lv = pb.levels[n];
-      P.seg[n] = Segment{static_cast<const char*>(lv.k), static_cast<const char*>(lv.v), lv.lens, lv.group, lv.cap};
+      P.seg[n] = Segment{static_cast<const char*>(lv.k), static_cast<const char*>(lv.v), lv.lens, lv.group, lv.cap,
+                         make_fastdiv(lv.group)};
     }
   } else {
-    P.seg[n++] = Segment{static_cast<const char*>(pb.k_prefix), static_cast<const char*>(pb.v_prefix), pb.prefix_lens, pb.G, pb.Lp_cap};
+    P.seg[n++] = Segment{static_cast<const char*>(pb.k_prefix), static_cast<const char*>(pb.v_prefix), pb.prefix_lens, pb.G, pb.Lp_cap,
+                         make_fastdiv(pb.G)};
   }
-  P.seg[n++] = Segment{static_cast<const char*>(pb.k_suffix), static_cast<const char*>(pb.v_suffix), pb.suffix_lens, 1, pb.Ls_cap};
+  P.seg[n++] = Segment{static_cast<const char*>(pb.k_suffix), static_cast<const char*>(pb.v_suffix), pb.suffix_lens, 1, pb.Ls_cap,
+                       make_fastdiv(1)};
   P.n_seg = n;
   P.B = (int)n_sequences(pb); P.G = max_group(pb); P.Hq = pb.Hq; P.Hkv = pb.Hkv;
   P.r = pb.Hq / pb.Hkv; P.RB = ceil_div(P.r, 16);
+  P.div_per = make_fastdiv(P.G * P.RB); P.div_RB = make_fastdiv(P.RB); P.div_Hkv = make_fastdiv(P.Hkv);
   P.scale = pb.scale;
   const double c = pb.scale == 0.f ? 1.0 : fabs((double)pb.scale) * 1.4426950408889634;
   P.c = (float)c; P.c_lo = P.c <= FLT_MAX ? (float)(c - (double)P.c) : 0.f;
