@@ -150,49 +150,78 @@ __device__ __forceinline__ float token_term(const LossParams& L, float lp, float
   return flat ? 0.f : -w * ra;
 }
 
-// One workgroup per sequence.  VEC: rows are 16-byte aligned and T is handled four tokens per thread
-// and step (one 16-byte load per array); otherwise one token per thread and step.  Either way a
-// thread adds its tokens in increasing t, the 64 lanes of a wavefront are folded by a fixed
-// butterfly and the four wavefronts in order, so the sums do not depend on anything but the data.
-template <bool VEC>
+// Token pass, one workgroup per sequence.  COUNT: every workgroup adds up all lengths itself before its first token, which
+// saves the launch of policy_count_kernel in front of it (1.5 us on the device and one of the host's).  That reads 4 bytes per
+// pair of sequences, so it pays up to COUNT_MAX of them only; one launch / two, advantages and loss together, captured, us:
+// 64 sequences 12.8 / 14.4, 512 13.5 / 15.0, 1024 15.6 / 17.1, 2048 19.3 / 19.7, 4096 27.1 / 24.2, 8192 48.4 / 33.7.
+// (Workgroups that stay and take several sequences in turn read less, but longer ones hold them up: 4096 x 4096 tokens
+// 51 us against 48.)  Four tokens per thread and step: one 16-byte load per array, which the hardware wants aligned to 4
+// bytes only, so rows of any length take it (8192 x 999 tokens 35.2 -> 33.7 us, one by one before), and single elements at a
+// row's end.  A thread adds its tokens in increasing t, the 64 lanes of a wavefront are folded by a fixed butterfly and the
+// four wavefronts in order, so the sums do not depend on anything but the data.
+constexpr int COUNT_MAX = 1024;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4u __attribute__((aligned(4)));
+
+template <bool COUNT>
 __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
   __shared__ float shf[NT / 64][6];
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const long long n_tok = L.counts[0], n_seq = L.counts[1];
+  const int tid = threadIdx.x;
+  long long n_tok, n_seq;
+  if (COUNT) {
+    __shared__ long long sh[2][NT / 64];
+    long long a = 0;
+    int c = 0;
+    for (int b0 = tid; b0 < L.B; b0 += 16 * NT) {
+      int n[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) n[k] = b0 + k * NT < L.B ? L.lens[b0 + k * NT] : 0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const int m = clamp_len(n[k], L.T);
+        a += m; c += m > 0;
+      }
+    }
+    a = wave_sum(a); c = wave_sum(c);
+    if ((tid & 63) == 0) { sh[0][tid >> 6] = a; sh[1][tid >> 6] = c; }
+    __syncthreads();
+    n_tok = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
+    n_seq = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
+    if (blockIdx.x == 0 && tid == 0) { L.counts[0] = n_tok; L.counts[1] = n_seq; }
+  } else {
+    n_tok = L.counts[0]; n_seq = L.counts[1];
+  }
+  const int b = blockIdx.x;
   const int len = clamp_len(L.lens[b], L.T);
-  float w = 0.f;                                            // weight of one of this sequence's tokens in the aggregate
+  float w = 0.f;                                          // weight of one of this sequence's tokens in the aggregate
   if (len > 0) w = L.agg == RL_AGG_SEQ_MEAN ? (float)(1.0 / ((double)len * (double)n_seq)) : (float)(1.0 / (double)n_tok);
   const float A = L.adv[b];
   const size_t row = (size_t)b * L.stride;
   float sums[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (VEC) {
-    for (int t = 4 * tid; t < L.T; t += 4 * NT) {
-      float g[4] = {0.f, 0.f, 0.f, 0.f};
-      if (t < len) {                                        // the four tokens t .. t+3 exist as memory (T % 4 == 0); some may be padding
-        const float4 lp = *reinterpret_cast<const float4*>(L.lp + row + t), old = *reinterpret_cast<const float4*>(L.old + row + t);
-        const float4 kl = L.kl ? *reinterpret_cast<const float4*>(L.kl + row + t) : make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 en = L.ent ? *reinterpret_cast<const float4*>(L.ent + row + t) : make_float4(0.f, 0.f, 0.f, 0.f);
-        const float lpv[4] = {lp.x, lp.y, lp.z, lp.w}, ov[4] = {old.x, old.y, old.z, old.w};
-        const float kv[4] = {kl.x, kl.y, kl.z, kl.w}, ev[4] = {en.x, en.y, en.z, en.w};
+  for (int t = 4 * tid; t < L.T; t += 4 * NT) {
+    f32x4 g = {0.f, 0.f, 0.f, 0.f};
+    if (t + 4 <= L.T) {                                   // the four tokens exist as memory; some may be padding
+      if (t < len) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        const f32x4 lp = *reinterpret_cast<const f32x4u*>(L.lp + row + t), old = *reinterpret_cast<const f32x4u*>(L.old + row + t);
+        const f32x4 kl = L.kl ? *reinterpret_cast<const f32x4u*>(L.kl + row + t) : zero;
+        const f32x4 en = L.ent ? *reinterpret_cast<const f32x4u*>(L.ent + row + t) : zero;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-          if (t + k < len) g[k] = token_term(L, lpv[k], ov[k], kv[k], ev[k], A, w, sums);
+          if (t + k < len) g[k] = token_term(L, lp[k], old[k], kl[k], en[k], A, w, sums);
       }
-      if (L.grad) *reinterpret_cast<float4*>(L.grad + row + t) = make_float4(g[0], g[1], g[2], g[3]);
-    }
-  } else {
-    for (int t = tid; t < L.T; t += NT) {
-      float g = 0.f;
-      if (t < len)
-        g = token_term(L, L.lp[row + t], L.old[row + t], L.kl ? L.kl[row + t] : 0.f, L.ent ? L.ent[row + t] : 0.f, A, w, sums);
-      if (L.grad) L.grad[row + t] = g;
+      if (L.grad) *reinterpret_cast<f32x4u*>(L.grad + row + t) = g;
+    } else {
+      for (int k = t; k < L.T; ++k) {
+        float gk = 0.f;
+        if (k < len)
+          gk = token_term(L, L.lp[row + k], L.old[row + k], L.kl ? L.kl[row + k] : 0.f, L.ent ? L.ent[row + k] : 0.f, A, w, sums);
+        if (L.grad) L.grad[row + k] = gk;
+      }
     }
   }
 #pragma unroll
-  for (int k = 0; k < 6; ++k) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sums[k] += __shfl_xor(sums[k], o, 64);
-  }
+  for (int k = 0; k < 6; ++k) sums[k] = wave_sum(sums[k]);
   if ((tid & 63) == 0) {
 #pragma unroll
     for (int k = 0; k < 6; ++k) shf[tid >> 6][k] = sums[k];
@@ -303,14 +332,15 @@ int rl_policy_loss(const rl_policy_loss_desc* d, void* hip_stream) {
   L.B = d->B; L.T = d->T; L.form = d->form; L.agg = d->agg; L.stride = d->row_stride;
   L.lo = 1.f - d->clip_low; L.hi = 1.f + d->clip_high; L.beta_kl = d->beta_kl; L.beta_ent = d->beta_ent;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  hipLaunchKernelGGL(policy_count_kernel, dim3(1), dim3(NB), 0, st, L);
-  if (hipGetLastError() != hipSuccess) return -5;
+  const bool own = d->B > 0 && d->B <= COUNT_MAX;           // the token pass counts for itself
+  if (!own) {
+    hipLaunchKernelGGL(policy_count_kernel, dim3(1), dim3(NB), 0, st, L);
+    if (hipGetLastError() != hipSuccess) return -5;
+  }
   if (d->B > 0) {
-    auto aligned = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
-    const bool vec = d->T % 4 == 0 && d->row_stride % 4 == 0 && aligned(d->logprob) && aligned(d->old_logprob) &&
-                     aligned(d->kl) && aligned(d->entropy) && aligned(d->grad_logprob);
-    if (vec) hipLaunchKernelGGL(policy_loss_kernel<true>, dim3(d->B), dim3(NT), 0, st, L);
-    else     hipLaunchKernelGGL(policy_loss_kernel<false>, dim3(d->B), dim3(NT), 0, st, L);
+    const dim3 grid(d->B);
+    if (own) hipLaunchKernelGGL(policy_loss_kernel<true>, grid, dim3(NT), 0, st, L);
+    else     hipLaunchKernelGGL(policy_loss_kernel<false>, grid, dim3(NT), 0, st, L);
     if (hipGetLastError() != hipSuccess) return -5;
   }
   hipLaunchKernelGGL(policy_loss_reduce_kernel, dim3(1), dim3(NB), 0, st, L);
