@@ -204,8 +204,16 @@ def rl_decode_attn_static_workspace_limit() -> int:
     return _lib.rl_decode_attn_static_workspace_limit()
 
 
+def _stream_handle(stream, like) -> int:
+    """The stream a call is enqueued on: the caller's, or torch's current one on the device of tensor `like`."""
+    return stream.cuda_stream if stream is not None else torch._C._cuda_getCurrentRawStream(like.device.index)
+
+
+def _ptr(t):
+    return None if t is None or t.numel() == 0 else t.data_ptr()
+
+
 def _torch_dtype_code(t):
-    import torch
     if t.dtype == torch.float32:
         return RLDA_F32
     if t.dtype == torch.bfloat16:
@@ -215,7 +223,6 @@ def _torch_dtype_code(t):
 
 def _kv_dtype_code(q, stores, k_scale, v_scale):
     """Descriptor dtype for q and its K/V stores; e4m3 stores are uint8 (or torch.float8_e4m3fn) tensors."""
-    import torch
     code = _torch_dtype_code(q)
     kv8 = [t.dtype in (torch.uint8, torch.float8_e4m3fn) for t in stores]
     if all(kv8):
@@ -234,7 +241,6 @@ def _kv_dtype_code(q, stores, k_scale, v_scale):
 
 def _check_lens(t, n, name, like):
     """A length array as the kernels read it: int32, n entries, contiguous, on q's device."""
-    import torch
     if t.dtype != torch.int32:
         raise TypeError(f"{name} must be int32 (got {t.dtype}): the kernels read 4-byte lengths")
     if t.numel() != n or not t.is_contiguous():
@@ -245,7 +251,6 @@ def _check_lens(t, n, name, like):
 
 def _check_outputs(q, out, lse):
     """out [B, Hq, d] and lse [B, Hq] (optional) as the kernels write them: float32, contiguous, on q's device."""
-    import torch
     B, Hq, d = q.shape
     for t, shape, name in ((out, (B, Hq, d), "out"), (lse, (B, Hq), "lse")):
         if t is None:
@@ -287,13 +292,12 @@ def desc_from_tensors(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, su
     _check_lens(suffix_lens, B, "suffix_lens", q)
     _check_outputs(q, out, lse)
     code = _kv_dtype_code(q, (k_prefix, v_prefix, k_suffix, v_suffix), k_scale, v_scale)
-    ptr = lambda t: None if t is None or t.numel() == 0 else t.data_ptr()
     return make_desc(code, P, G, Hq, Hkv, d, Lp_cap, Ls_cap, float(scale), algo,
-                     q=ptr(q), k_prefix=ptr(k_prefix), v_prefix=ptr(v_prefix), prefix_lens=ptr(prefix_lens),
-                     k_suffix=ptr(k_suffix), v_suffix=ptr(v_suffix), suffix_lens=ptr(suffix_lens),
-                     out=ptr(out), lse=ptr(lse), workspace=ptr(workspace),
+                     q=_ptr(q), k_prefix=_ptr(k_prefix), v_prefix=_ptr(v_prefix), prefix_lens=_ptr(prefix_lens),
+                     k_suffix=_ptr(k_suffix), v_suffix=_ptr(v_suffix), suffix_lens=_ptr(suffix_lens),
+                     out=_ptr(out), lse=_ptr(lse), workspace=_ptr(workspace),
                      workspace_bytes=0 if workspace is None else workspace.numel() * workspace.element_size(),
-                     k_scale=ptr(k_scale), v_scale=ptr(v_scale))
+                     k_scale=_ptr(k_scale), v_scale=_ptr(v_scale))
 
 
 def rl_decode_attn(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, suffix_lens, scale, G,
@@ -303,7 +307,6 @@ def rl_decode_attn(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, suffi
     Allocates out/lse/workspace with torch when they are not passed in.  The
     call is asynchronous on ``stream`` (default: torch's current stream).
     """
-    import torch
     if not q.is_cuda:
         raise RuntimeError("rl_decode_attn needs device tensors; there is no CPU path")
     B, Hq, d = q.shape
@@ -318,8 +321,7 @@ def rl_decode_attn(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, suffi
         if need:
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
             ds.workspace, ds.workspace_bytes = workspace.data_ptr(), need
-    s = stream if stream is not None else torch.cuda.current_stream(q.device)
-    rc = _lib.rl_decode_attn(ctypes.byref(ds), ctypes.c_void_p(s.cuda_stream))
+    rc = _lib.rl_decode_attn(ctypes.byref(ds), _stream_handle(stream, q))
     if rc != RLDA_OK:
         raise RldaError(rc)
     return out, lse
@@ -328,13 +330,11 @@ def rl_decode_attn(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, suffi
 def rl_decode_attn_static(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, suffix_lens, scale, G,
                           out, lse=None, algo=RLDA_ALGO_AUTO, stream=None, k_scale=None, v_scale=None):
     """rl_decode_attn without any allocation: ``out`` (and ``lse``) are the caller's, the scratch is the library's."""
-    import torch
     if not q.is_cuda:
         raise RuntimeError("rl_decode_attn_static needs device tensors; there is no CPU path")
     ds = desc_from_tensors(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, suffix_lens, scale, G,
                            out, lse, None, algo, k_scale, v_scale)
-    s = stream if stream is not None else torch.cuda.current_stream(q.device)
-    rc = _lib.rl_decode_attn_static(ctypes.byref(ds), ctypes.c_void_p(s.cuda_stream))
+    rc = _lib.rl_decode_attn_static(ctypes.byref(ds), _stream_handle(stream, q))
     if rc != RLDA_OK:
         raise RldaError(rc)
     return out, lse
@@ -374,26 +374,24 @@ def tree_desc_from_tensors(q, levels, k_suffix, v_suffix, suffix_lens, scale, ou
         raise ValueError("inconsistent shapes")
     pairs = [(k_suffix, v_suffix, "suffix")]
     lv = []
-    ptr = lambda t: None if t is None or t.numel() == 0 else t.data_ptr()
     for i, (k, v, lens, group) in enumerate(levels):
         if group < 1 or B % group or k.shape[0] * group != B or k.shape[1] != Hkv or k.shape[3] != d:
             raise ValueError(f"level {i}: {tuple(k.shape)} stores with groups of {group} do not cover {B} sequences")
         pairs.append((k, v, f"level {i}"))
         _check_lens(lens, B // group, f"lens of level {i}", q)
-        lv.append((ptr(k), ptr(v), ptr(lens), int(group), int(k.shape[2])))
+        lv.append((_ptr(k), _ptr(v), _ptr(lens), int(group), int(k.shape[2])))
     _check_stores(q, pairs)
     _check_lens(suffix_lens, B, "suffix_lens", q)
     _check_outputs(q, out, lse)
     code = _kv_dtype_code(q, [t for k, v, _ in pairs for t in (k, v)], None, None)
-    return make_tree_desc(code, B, Hq, Hkv, d, Ls_cap, float(scale), lv, q=ptr(q), k_suffix=ptr(k_suffix),
-                          v_suffix=ptr(v_suffix), suffix_lens=ptr(suffix_lens), out=ptr(out), lse=ptr(lse),
-                          workspace=ptr(workspace),
+    return make_tree_desc(code, B, Hq, Hkv, d, Ls_cap, float(scale), lv, q=_ptr(q), k_suffix=_ptr(k_suffix),
+                          v_suffix=_ptr(v_suffix), suffix_lens=_ptr(suffix_lens), out=_ptr(out), lse=_ptr(lse),
+                          workspace=_ptr(workspace),
                           workspace_bytes=0 if workspace is None else workspace.numel() * workspace.element_size())
 
 
 def rl_decode_attn_tree(q, levels, k_suffix, v_suffix, suffix_lens, scale, out=None, lse=None, workspace=None, stream=None):
     """One decode step over a tree of shared prefix segments plus the own suffixes; returns (out, lse)."""
-    import torch
     if not q.is_cuda:
         raise RuntimeError("rl_decode_attn_tree needs device tensors; there is no CPU path")
     B, Hq, d = q.shape
@@ -406,8 +404,7 @@ def rl_decode_attn_tree(q, levels, k_suffix, v_suffix, suffix_lens, scale, out=N
         need = rl_decode_attn_tree_workspace_bytes(ds)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
         ds.workspace, ds.workspace_bytes = workspace.data_ptr(), workspace.numel()
-    s = stream if stream is not None else torch.cuda.current_stream(q.device)
-    rc = _lib.rl_decode_attn_tree(ctypes.byref(ds), ctypes.c_void_p(s.cuda_stream))
+    rc = _lib.rl_decode_attn_tree(ctypes.byref(ds), _stream_handle(stream, q))
     if rc != RLDA_OK:
         raise RldaError(rc)
     return out, lse
@@ -444,7 +441,6 @@ def paged_desc_from_tensors(q, k_prefix, v_prefix, prefix_lens, k_pages, v_pages
                             scale, G, out, lse=None, seq_active=None, workspace=None,
                             algo=RLDA_ALGO_AUTO, k_scale=None, v_scale=None) -> rlda_paged_desc:
     """Paged descriptor over torch device tensors (shapes as in the header)."""
-    import torch
     B, Hq, d = q.shape
     P, Hkv, Lp_cap, _ = k_prefix.shape
     n_pages, Hkv2, page_size, _ = k_pages.shape
@@ -462,21 +458,19 @@ def paged_desc_from_tensors(q, k_prefix, v_prefix, prefix_lens, k_pages, v_pages
     _check_lens(suffix_lens, B, "suffix_lens", q)
     _check_outputs(q, out, lse)
     code = _kv_dtype_code(q, (k_prefix, v_prefix, k_pages, v_pages), k_scale, v_scale)
-    ptr = lambda t: None if t is None or t.numel() == 0 else t.data_ptr()
     return make_paged_desc(code, P, G, Hq, Hkv, d, Lp_cap, page_size, block_table.shape[1], n_pages, float(scale),
-                           algo, q=ptr(q), k_prefix=ptr(k_prefix), v_prefix=ptr(v_prefix),
-                           prefix_lens=ptr(prefix_lens), k_pages=ptr(k_pages), v_pages=ptr(v_pages),
-                           block_table=ptr(block_table), suffix_lens=ptr(suffix_lens), seq_active=ptr(seq_active),
-                           out=ptr(out), lse=ptr(lse), workspace=ptr(workspace),
+                           algo, q=_ptr(q), k_prefix=_ptr(k_prefix), v_prefix=_ptr(v_prefix),
+                           prefix_lens=_ptr(prefix_lens), k_pages=_ptr(k_pages), v_pages=_ptr(v_pages),
+                           block_table=_ptr(block_table), suffix_lens=_ptr(suffix_lens), seq_active=_ptr(seq_active),
+                           out=_ptr(out), lse=_ptr(lse), workspace=_ptr(workspace),
                            workspace_bytes=0 if workspace is None else workspace.numel() * workspace.element_size(),
-                           k_scale=ptr(k_scale), v_scale=ptr(v_scale))
+                           k_scale=_ptr(k_scale), v_scale=_ptr(v_scale))
 
 
 def rl_decode_attn_paged(q, k_prefix, v_prefix, prefix_lens, k_pages, v_pages, block_table, suffix_lens, scale, G,
                          seq_active=None, out=None, lse=None, workspace=None, algo=RLDA_ALGO_AUTO, stream=None,
                          k_scale=None, v_scale=None):
     """One decode step over a paged suffix store; returns (out, lse).  Asynchronous on ``stream``."""
-    import torch
     if not q.is_cuda:
         raise RuntimeError("rl_decode_attn_paged needs device tensors; there is no CPU path")
     B, Hq, d = q.shape
@@ -491,8 +485,7 @@ def rl_decode_attn_paged(q, k_prefix, v_prefix, prefix_lens, k_pages, v_pages, b
         if need:
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
             ds.workspace, ds.workspace_bytes = workspace.data_ptr(), need
-    s = stream if stream is not None else torch.cuda.current_stream(q.device)
-    rc = _lib.rl_decode_attn_paged(ctypes.byref(ds), ctypes.c_void_p(s.cuda_stream), None)
+    rc = _lib.rl_decode_attn_paged(ctypes.byref(ds), _stream_handle(stream, q), None)
     if rc != RLDA_OK:
         raise RldaError(rc)
     return out, lse
@@ -500,7 +493,6 @@ def rl_decode_attn_paged(q, k_prefix, v_prefix, prefix_lens, k_pages, v_pages, b
 
 def rl_lse_combine(o_parts, lse_parts, out=None, lse=None, stream=None):
     """Merge partials o_parts [n_parts, n_rows, d], lse_parts [n_parts, n_rows] (fp32 device tensors)."""
-    import torch
     n_parts, n_rows, d = o_parts.shape
     if out is None:
         out = torch.empty((n_rows, d), dtype=torch.float32, device=o_parts.device)
@@ -555,13 +547,13 @@ def rl_token_logprob_raw(desc: rl_token_logprob_desc, stream_handle=None) -> int
 
 
 _TOKEN_OUTPUTS = ("logprob", "lse", "entropy", "ref_logprob", "kl")
+_TOKEN_OUTPUT_SET, _TOKEN_DESC_BYTES = frozenset(_TOKEN_OUTPUTS), ctypes.sizeof(rl_token_logprob_desc)
 
 
 def token_logprob_desc_from_tensors(logits, token_ids, inv_temperature=1.0, ref_logits=None, outputs=None,
                                     workspace=None) -> rl_token_logprob_desc:
     """Descriptor over torch device tensors: logits [n_rows, vocab] (a row-strided view is fine),
     token_ids [n_rows] int32, outputs: dict name -> fp32 tensor [n_rows]."""
-    import torch
     if logits.dim() != 2 or logits.stride(1) != 1:
         raise ValueError("logits must be [n_rows, vocab] with unit stride along the vocabulary")
     if token_ids.dtype != torch.int32 or not token_ids.is_contiguous():
@@ -571,22 +563,20 @@ def token_logprob_desc_from_tensors(logits, token_ids, inv_temperature=1.0, ref_
                                    or ref_logits.dtype != logits.dtype):
         raise ValueError("ref_logits must match logits in shape, strides and dtype")
     n, V = logits.shape
-    ptr = lambda t: None if t is None or t.numel() == 0 else t.data_ptr()
-    outs = {k: ptr(v) for k, v in (outputs or {}).items()}
-    unknown = set(outs) - set(_TOKEN_OUTPUTS)
+    outs = outputs or {}
+    unknown = set(outs) - _TOKEN_OUTPUT_SET
     if unknown:
         raise KeyError(f"unknown outputs {sorted(unknown)}")
-    return make_token_logprob_desc(code, n, V, logits.stride(0) if n > 1 else max(logits.stride(0), V),
-                                   float(inv_temperature), logits=ptr(logits), ref_logits=ptr(ref_logits),
-                                   token_ids=ptr(token_ids), workspace=ptr(workspace),
-                                   workspace_bytes=0 if workspace is None else workspace.numel(), **outs)
+    return rl_token_logprob_desc(_TOKEN_DESC_BYTES, code, n, logits.stride(0) if n > 1 else max(logits.stride(0), V), V,
+                                 float(inv_temperature), _ptr(logits), _ptr(ref_logits), _ptr(token_ids),
+                                 *[_ptr(outs.get(k)) for k in _TOKEN_OUTPUTS],
+                                 _ptr(workspace), 0 if workspace is None else workspace.numel())
 
 
 def rl_token_logprob(logits, token_ids, inv_temperature=1.0, ref_logits=None, want=None, workspace=None,
                      stream=None) -> dict:
     """Per-token log-prob / lse / entropy (and ref_logprob / kl with ``ref_logits``); returns a dict of
     fp32 device tensors [n_rows].  Asynchronous on ``stream``."""
-    import torch
     if not logits.is_cuda:
         raise RuntimeError("rl_token_logprob needs device tensors; there is no CPU path")
     names = want or (_TOKEN_OUTPUTS if ref_logits is not None else _TOKEN_OUTPUTS[:3])
@@ -597,8 +587,7 @@ def rl_token_logprob(logits, token_ids, inv_temperature=1.0, ref_logits=None, wa
         if need:
             workspace = torch.empty(need, dtype=torch.uint8, device=logits.device)
             ds.workspace, ds.workspace_bytes = workspace.data_ptr(), need
-    s = stream if stream is not None else torch.cuda.current_stream(logits.device)
-    rc = _lib.rl_token_logprob(ctypes.byref(ds), ctypes.c_void_p(s.cuda_stream))
+    rc = _lib.rl_token_logprob(ctypes.byref(ds), _stream_handle(stream, logits))
     if rc != RLDA_OK:
         raise RldaError(rc)
     return outs
@@ -646,7 +635,6 @@ def kv_append_desc_from_tensors(q, k_new, v_new, positions, inv_freq, sections, 
     """Descriptor over torch device tensors.  ``k_store`` / ``v_store`` are [B, Hkv, Ls_cap, d], or with
     ``block_table`` the page pools [n_pages, Hkv, page_size, d]; uint8 / float8_e4m3fn stores take e4m3
     bytes quantised with the factors ``k_scale`` / ``v_scale`` (float32 [Hkv])."""
-    import torch
     B, Hq, d = q.shape
     Hkv = k_new.shape[1]
     code = _torch_dtype_code(q)
@@ -662,10 +650,9 @@ def kv_append_desc_from_tensors(q, k_new, v_new, positions, inv_freq, sections, 
     for t in (q, k_new, v_new, positions, inv_freq, k_store, v_store, suffix_lens):
         if not t.is_contiguous():
             raise ValueError("tensors must be contiguous")
-    ptr = lambda t: None if t is None or t.numel() == 0 else t.data_ptr()
-    kw = dict(q=ptr(q), k_new=ptr(k_new), v_new=ptr(v_new), positions=ptr(positions), inv_freq=ptr(inv_freq),
-              k_store=ptr(k_store), v_store=ptr(v_store), block_table=ptr(block_table),
-              suffix_lens=ptr(suffix_lens), seq_active=ptr(seq_active), k_scale=ptr(k_scale), v_scale=ptr(v_scale))
+    kw = dict(q=_ptr(q), k_new=_ptr(k_new), v_new=_ptr(v_new), positions=_ptr(positions), inv_freq=_ptr(inv_freq),
+              k_store=_ptr(k_store), v_store=_ptr(v_store), block_table=_ptr(block_table),
+              suffix_lens=_ptr(suffix_lens), seq_active=_ptr(seq_active), k_scale=_ptr(k_scale), v_scale=_ptr(v_scale))
     if block_table is None:
         if tuple(k_store.shape[:2]) != (B, Hkv):
             raise ValueError("contiguous store must be [B, Hkv, Ls_cap, d]")
@@ -677,13 +664,11 @@ def kv_append_desc_from_tensors(q, k_new, v_new, positions, inv_freq, sections, 
 def rl_kv_append_rope(q, k_new, v_new, positions, inv_freq, sections, k_store, v_store, suffix_lens,
                       block_table=None, seq_active=None, stream=None, k_scale=None, v_scale=None) -> None:
     """Rotate q (in place) and k_new, append k / v to the store, increment suffix_lens.  Asynchronous."""
-    import torch
     if not q.is_cuda:
         raise RuntimeError("rl_kv_append_rope needs device tensors; there is no CPU path")
     ds = kv_append_desc_from_tensors(q, k_new, v_new, positions, inv_freq, sections, k_store, v_store, suffix_lens,
                                      block_table, seq_active, k_scale, v_scale)
-    s = stream if stream is not None else torch.cuda.current_stream(q.device)
-    rc = _lib.rl_kv_append_rope(ctypes.byref(ds), ctypes.c_void_p(s.cuda_stream))
+    rc = _lib.rl_kv_append_rope(ctypes.byref(ds), _stream_handle(stream, q))
     if rc != RLDA_OK:
         raise RldaError(rc)
 
@@ -723,6 +708,7 @@ class rl_policy_loss_desc(ctypes.Structure):
     ]
 
 
+_ADVANTAGE_DESC_BYTES, _LOSS_DESC_BYTES = ctypes.sizeof(rl_group_advantage_desc), ctypes.sizeof(rl_policy_loss_desc)
 _lib.rl_group_advantage.restype = ctypes.c_int
 _lib.rl_group_advantage.argtypes = [ctypes.POINTER(rl_group_advantage_desc), ctypes.c_void_p]
 _lib.rl_policy_loss.restype = ctypes.c_int
@@ -746,7 +732,6 @@ def rl_group_advantage_raw(desc: rl_group_advantage_desc, stream_handle=None) ->
 
 def rl_group_advantage(metrics, weights, G, mode=RL_ADV_GROUP_NORM, eps=1e-6, unbiased=True, stream=None):
     """metrics [M, B], weights [M] (float32 device tensors) -> (rewards [B], advantages [B]).  Asynchronous."""
-    import torch
     if not metrics.is_cuda:
         raise RuntimeError("rl_group_advantage needs device tensors; there is no CPU path")
     if metrics.dtype != torch.float32 or weights.dtype != torch.float32 or not metrics.is_contiguous():
@@ -754,12 +739,10 @@ def rl_group_advantage(metrics, weights, G, mode=RL_ADV_GROUP_NORM, eps=1e-6, un
     M, Bn = metrics.shape
     if Bn % G or weights.numel() != M:
         raise ValueError("inconsistent shapes")
-    rewards = torch.empty(Bn, dtype=torch.float32, device=metrics.device)
-    adv = torch.empty(Bn, dtype=torch.float32, device=metrics.device)
-    ds = make_group_advantage_desc(Bn // G, G, M, mode, float(eps), int(bool(unbiased)), metrics=metrics.data_ptr(),
-                                   weights=weights.data_ptr(), rewards=rewards.data_ptr(), advantages=adv.data_ptr())
-    s = stream if stream is not None else torch.cuda.current_stream(metrics.device)
-    rc = _lib.rl_group_advantage(ctypes.byref(ds), ctypes.c_void_p(s.cuda_stream))
+    rewards, adv = metrics.new_empty(Bn), metrics.new_empty(Bn)
+    ds = rl_group_advantage_desc(_ADVANTAGE_DESC_BYTES, mode, Bn // G, G, M, int(bool(unbiased)), float(eps),
+                                 metrics.data_ptr(), weights.data_ptr(), rewards.data_ptr(), adv.data_ptr())
+    rc = _lib.rl_group_advantage(ctypes.byref(ds), _stream_handle(stream, metrics))
     if rc != RLDA_OK:
         raise RldaError(rc)
     return rewards, adv
@@ -788,33 +771,30 @@ def policy_loss_desc_from_tensors(logprob, old_logprob, advantages, lens, clip_l
                                   entropy=None, grad=None, beta_kl=0.0, beta_ent=0.0, form=RL_PG_PPO_CLIP,
                                   agg=RL_AGG_TOKEN_MEAN, workspace=None) -> rl_policy_loss_desc:
     """Descriptor over torch device tensors; the [B, T] tensors may be row-strided views sharing one stride."""
-    import torch
-    Bn, T = logprob.shape
-    stride = logprob.stride(0) if Bn > 1 else max(T, 1)
+    shape, strides, f32 = logprob.shape, logprob.stride(), torch.float32
+    Bn, T = shape
+    stride = strides[0] if Bn > 1 else max(T, 1)
     for t in (logprob, old_logprob, kl, entropy, grad):
         if t is None:
             continue
-        if t.dtype != torch.float32 or tuple(t.shape) != (Bn, T) or (T > 1 and t.stride(1) != 1) or \
+        if t.dtype != f32 or t.shape != shape or (T > 1 and t.stride(1) != 1) or \
                 (Bn > 1 and t.stride(0) != stride):
             raise TypeError("the [B, T] tensors must be float32 with unit column stride and one common row stride")
-    if advantages.dtype != torch.float32 or lens.dtype != torch.int32 or stats.dtype != torch.float32 or stats.numel() < 8:
+    if advantages.dtype != f32 or lens.dtype != torch.int32 or stats.dtype != f32 or stats.numel() < 8:
         raise TypeError("advantages float32 [B], lens int32 [B], stats float32 [8]")
-    ptr = lambda t: None if t is None or t.numel() == 0 else t.data_ptr()
-    return make_policy_loss_desc(Bn, T, stride, float(clip_low), float(clip_high), float(beta_kl), float(beta_ent), form,
-                                 agg, logprob=ptr(logprob), old_logprob=ptr(old_logprob), advantages=ptr(advantages),
-                                 kl=ptr(kl), entropy=ptr(entropy), lens=ptr(lens), grad_logprob=ptr(grad),
-                                 stats=ptr(stats), workspace=ptr(workspace),
-                                 workspace_bytes=0 if workspace is None else workspace.numel() * workspace.element_size())
+    return rl_policy_loss_desc(_LOSS_DESC_BYTES, form, agg, Bn, T, stride, float(clip_low), float(clip_high), float(beta_kl),
+                               float(beta_ent), _ptr(logprob), _ptr(old_logprob), _ptr(advantages), _ptr(kl), _ptr(entropy),
+                               _ptr(lens), _ptr(grad), _ptr(stats), _ptr(workspace),
+                               0 if workspace is None else workspace.numel() * workspace.element_size())
 
 
 def rl_policy_loss(logprob, old_logprob, advantages, lens, clip_low, clip_high, kl=None, entropy=None, beta_kl=0.0,
                    beta_ent=0.0, form=RL_PG_PPO_CLIP, agg=RL_AGG_TOKEN_MEAN, want_grad=True, workspace=None, stream=None):
     """Clipped policy loss over [B, T] per-token tensors; returns (stats [8] device tensor in the order of
     POLICY_LOSS_STATS, grad_logprob [B, T] or None).  Asynchronous."""
-    import torch
     if not logprob.is_cuda:
         raise RuntimeError("rl_policy_loss needs device tensors; there is no CPU path")
-    stats = torch.empty(8, dtype=torch.float32, device=logprob.device)
+    stats = logprob.new_empty(8, dtype=torch.float32)
     grad = torch.empty_like(logprob) if want_grad else None
     ds = policy_loss_desc_from_tensors(logprob, old_logprob, advantages, lens, clip_low, clip_high, stats, kl, entropy,
                                        grad, beta_kl, beta_ent, form, agg, workspace)
@@ -822,8 +802,7 @@ def rl_policy_loss(logprob, old_logprob, advantages, lens, clip_low, clip_high, 
         need = rl_policy_loss_workspace_bytes(ds)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=logprob.device)
         ds.workspace, ds.workspace_bytes = workspace.data_ptr(), workspace.numel()
-    s = stream if stream is not None else torch.cuda.current_stream(logprob.device)
-    rc = _lib.rl_policy_loss(ctypes.byref(ds), ctypes.c_void_p(s.cuda_stream))
+    rc = _lib.rl_policy_loss(ctypes.byref(ds), _stream_handle(stream, logprob))
     if rc != RLDA_OK:
         raise RldaError(rc)
     return stats, grad
@@ -843,6 +822,7 @@ class rl_prefill_desc(ctypes.Structure):
     ]
 
 
+_PREFILL_DESC_BYTES = ctypes.sizeof(rl_prefill_desc)
 _lib.rl_prefill_attn.restype = ctypes.c_int
 _lib.rl_prefill_attn.argtypes = [ctypes.POINTER(rl_prefill_desc), ctypes.c_void_p]
 
@@ -861,7 +841,6 @@ def rl_prefill_attn_raw(desc: rl_prefill_desc, stream_handle=None) -> int:
 
 
 def prefill_desc_from_tensors(q, k, v, lens, scale, out, lse=None) -> rl_prefill_desc:
-    import torch
     P, Lc, Hq, d = q.shape
     Hkv = k.shape[1]
     if tuple(k.shape) != (P, Hkv, Lc, d) or k.shape != v.shape or tuple(out.shape) != (P, Lc, Hq, d):
@@ -874,15 +853,13 @@ def prefill_desc_from_tensors(q, k, v, lens, scale, out, lse=None) -> rl_prefill
     code = _torch_dtype_code(q)
     if _torch_dtype_code(k) != code or _torch_dtype_code(v) != code:
         raise TypeError("q/k/v dtypes differ")
-    ptr = lambda t: None if t is None or t.numel() == 0 else t.data_ptr()
-    return make_prefill_desc(code, P, Hq, Hkv, d, Lc, float(scale), q=ptr(q), k=ptr(k), v=ptr(v), lens=ptr(lens),
-                             out=ptr(out), lse=ptr(lse))
+    return rl_prefill_desc(_PREFILL_DESC_BYTES, code, P, Hq, Hkv, d, Lc, float(scale), _ptr(q), _ptr(k), _ptr(v), _ptr(lens),
+                           _ptr(out), _ptr(lse))
 
 
 def rl_prefill_attn(q, k, v, lens, scale, out=None, lse=None, stream=None):
     """Causal attention of every prompt over itself; returns (out [P, L_cap, Hq, d], lse [P, L_cap, Hq]) fp32.
     Rows at positions >= lens[p] are left as they were (zero when the outputs are allocated here)."""
-    import torch
     if not q.is_cuda:
         raise RuntimeError("rl_prefill_attn needs device tensors; there is no CPU path")
     P, Lc, Hq, d = q.shape
@@ -891,8 +868,7 @@ def rl_prefill_attn(q, k, v, lens, scale, out=None, lse=None, stream=None):
     if lse is None:
         lse = torch.zeros((P, Lc, Hq), dtype=torch.float32, device=q.device)
     ds = prefill_desc_from_tensors(q, k, v, lens, scale, out, lse)
-    s = stream if stream is not None else torch.cuda.current_stream(q.device)
-    rc = _lib.rl_prefill_attn(ctypes.byref(ds), ctypes.c_void_p(s.cuda_stream))
+    rc = _lib.rl_prefill_attn(ctypes.byref(ds), _stream_handle(stream, q))
     if rc != RLDA_OK:
         raise RldaError(rc)
     return out, lse
