@@ -194,24 +194,13 @@ __device__ __forceinline__ float max_raw(float a, float b) {
   asm("" : "+s"(inf));
   return __builtin_amdgcn_fmed3f(a, b, __uint_as_float(inf));
 }
-template <int NT, bool MASK>
-__device__ __forceinline__ void mask_scores(const f32x4 (&s0)[NT], const f32x4 (&s1)[NT], const int (&nvalid)[NT], int g, float (&sv)[NT][8]) {
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      sv[nt][x] = (!MASK || 4 * g + x < nvalid[nt]) ? s0[nt][x] : -INFINITY;
-      sv[nt][4 + x] = (!MASK || 16 + 4 * g + x < nvalid[nt]) ? s1[nt][x] : -INFINITY;
-    }
-}
-template <int NT, bool MASK>
-__device__ __forceinline__ void softmax_max(const f32x4 (&s0)[NT], const f32x4 (&s1)[NT], const int (&nvalid)[NT],
-                                            const WaveState<NT>& st, float c, int g, float (&sv)[NT][8], float (&m_new)[NT]) {
-  mask_scores<NT, MASK>(s0, s1, nvalid, g, sv);
+// `score(nt, x)`: the masked score of key 4 g + x (x < 4) or 16 + 4 g + x - 4 of row block nt.
+template <int NT, class Score>
+__device__ __forceinline__ void softmax_max(Score score, const WaveState<NT>& st, float c, float (&m_new)[NT]) {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
-    float tmax = max_raw(max_raw(max_raw(sv[nt][0], sv[nt][1]), max_raw(sv[nt][2], sv[nt][3])),
-                         max_raw(max_raw(sv[nt][4], sv[nt][5]), max_raw(sv[nt][6], sv[nt][7])));
+    float tmax = max_raw(max_raw(max_raw(score(nt, 0), score(nt, 1)), max_raw(score(nt, 2), score(nt, 3))),
+                         max_raw(max_raw(score(nt, 4), score(nt, 5)), max_raw(score(nt, 6), score(nt, 7))));
     {
       // swap(x, x) returns (x with its odd rows replaced by the even ones, x with its even rows replaced by
       // the odd ones), resp. the same for the two halves of 32 lanes: their maximum is max(x[l], x[l ^ 16 or 32])
@@ -225,8 +214,8 @@ __device__ __forceinline__ void softmax_max(const f32x4 (&s0)[NT], const f32x4 (
   }
 }
 // FIXED: against the maximum the state holds, whatever m_new says
-template <int NT, bool FIXED = false>
-__device__ __forceinline__ void softmax_weights(const float (&sv)[NT][8], const float (&m_new)[NT], WaveState<NT>& st, bf16x8 (&pb)[NT], float c) {
+template <int NT, bool FIXED = false, class Score>
+__device__ __forceinline__ void softmax_weights(Score score, const float (&m_new)[NT], WaveState<NT>& st, bf16x8 (&pb)[NT], float c) {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     if (!FIXED && __any(m_new[nt] > st.m[nt] + RESCALE_GAP)) {   // first tile: -inf + gap = -inf
@@ -241,8 +230,8 @@ __device__ __forceinline__ void softmax_weights(const float (&sv)[NT][8], const 
     float se = 0.f, sr = 0.f;
 #pragma unroll
     for (int x = 0; x < 8; x += 2) {
-      const float pe0 = __builtin_amdgcn_exp2f(fmaf(sv[nt][x], c, nm));
-      const float pe1 = __builtin_amdgcn_exp2f(fmaf(sv[nt][x + 1], c, nm));
+      const float pe0 = __builtin_amdgcn_exp2f(fmaf(score(nt, x), c, nm));
+      const float pe1 = __builtin_amdgcn_exp2f(fmaf(score(nt, x + 1), c, nm));
       const bf16x2 pr = __builtin_convertvector(f32x2{pe0, pe1}, bf16x2);
       pb[nt][x] = pr[0]; pb[nt][x + 1] = pr[1];
       se += pe0 + pe1;
@@ -278,8 +267,16 @@ __device__ __forceinline__ void compute_tile(const char* Kl, const char* Vl, con
   bf16x8 pb[NT];
   if constexpr (LEAN) {
     float sv[NT][8], m_new[NT];
-    softmax_max<NT, MASK>(s0, s1, nvalid, st, c, g, sv, m_new);
-    softmax_weights<NT>(sv, m_new, st, pb, c);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        sv[nt][x] = (!MASK || 4 * g + x < nvalid[nt]) ? s0[nt][x] : -INFINITY;
+        sv[nt][4 + x] = (!MASK || 16 + 4 * g + x < nvalid[nt]) ? s1[nt][x] : -INFINITY;
+      }
+    const auto score = [&](int nt, int x) { return sv[nt][x]; };
+    softmax_max<NT>(score, st, c, m_new);
+    softmax_weights<NT>(score, m_new, st, pb, c);
   } else {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -1107,6 +1104,7 @@ struct PrefillParams {
   const char* q; const char* k; const char* v; const int32_t* lens;
   float* out; float* lse;
   int P, Hq, Hkv, r, Lp_cap, QB, nqb;
+  FastDiv div_Hkv, div_r, div_nqb, div_units;
   int spread;                                               // the blocks of a unit go to all XCDs
   float c;
 };
@@ -1124,10 +1122,11 @@ inline bool prefill_spread(int units) { return units % N_XCD != 0 && units < 8 *
 __device__ __forceinline__ void prefill_place(const PrefillParams& P, int b, int& pj, int& qb) {
   if (P.spread) {
     const int units = P.P * P.Hkv;
-    pj = b % units; qb = P.nqb - 1 - b / units;
+    const int i = fast_div(b, P.div_units);
+    pj = b - i * units; qb = P.nqb - 1 - i;
   } else {
-    const int xcd = b % N_XCD, seq = b / N_XCD;
-    pj = (seq / P.nqb) * N_XCD + xcd; qb = P.nqb - 1 - seq % P.nqb;
+    const int xcd = b % N_XCD, seq = b / N_XCD, u = fast_div(seq, P.div_nqb);
+    pj = u * N_XCD + xcd; qb = P.nqb - 1 - (seq - u * P.nqb);
   }
 }
 
@@ -1331,6 +1330,17 @@ __device__ __forceinline__ void value_products(const s16x4 (&v)[8][2], const bf1
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),                        \
                                    (__attribute__((address_space(3))) void*)(dst), 16, (off), 0)
 
+// In place: under a branch there is then nothing to copy on either side of it (16 moves a tile before).
+template <int NT>
+__device__ __forceinline__ void mask_scores(f32x4 (&s0)[NT], f32x4 (&s1)[NT], const int (&nvalid)[NT], int g) {
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      s0[nt][x] = 4 * g + x < nvalid[nt] ? s0[nt][x] : -INFINITY;
+      s1[nt][x] = 16 + 4 * g + x < nvalid[nt] ? s1[nt][x] : -INFINITY;
+    }
+}
 __device__ __forceinline__ float sum_of_row(float v) {      // over the four lanes that share a query row
   v += __shfl_xor(v, 16, 64);
   return v + __shfl_xor(v, 32, 64);
@@ -1346,7 +1356,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
   int pj, qb;
   prefill_place(P, blockIdx.x, pj, qb);
   if (pj >= units) return;
-  const int p = pj / P.Hkv, j = pj % P.Hkv;
+  const int p = fast_div(pj, P.div_Hkv), j = pj - p * P.Hkv;
   const int L = clampi(P.lens[p], 0, P.Lp_cap), a = qb * P.QB;
   if (a >= L) return;
   const int nq = min(P.QB, L - a), n_keys = a + nq, n_tiles = ceil_div(n_keys, TK), nrows = nq * P.r;
@@ -1356,7 +1366,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
   for (int nt = 0; nt < NTP; ++nt) {
     const int row = WROWS * wv + 16 * nt + m16;
     const bool ok = row < nrows;
-    const int pos = a + (ok ? row / P.r : 0), h = j * P.r + (ok ? row % P.r : 0);
+    const int o = ok ? fast_div(row, P.div_r) : 0, pos = a + o, h = j * P.r + (ok ? row - o * P.r : 0);
     limit[nt] = pos + 1;
     const char* qp = P.q + (((size_t)p * P.Lp_cap + pos) * P.Hq + h) * ROWB + 16 * g;
 #pragma unroll
@@ -1365,7 +1375,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
       qf[nt][ks] = *reinterpret_cast<const bf16x8*>(&v);
     }
   }
-  const int wave_first = a + (WROWS * wv) / P.r;            // first position any row of this wavefront holds
+  const int wave_first = a + fast_div(WROWS * wv, P.div_r);            // first position any row of this wavefront holds
   const bool wave_has_rows = WROWS * wv < nrows;
   // LDS addresses of this lane's fragment reads inside stage 0 (the stage goes into the immediate offset)
   const uint32_t l0 = (uint32_t)(uintptr_t)RLDA_LDS(char, lds);
@@ -1425,20 +1435,19 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
     constexpr bool FIXED = decltype(fixed_c)::value;
     const int key0 = t * TK;
     if (wave_has_rows) {
-      float sv[NTP][8], m_new[NTP];
-      int nv[NTP];
+      float m_new[NTP];
+      if (key0 + TK > wave_first + 1) {                     // not wholly in every row's past
+        int nv[NTP];
 #pragma unroll
-      for (int nt = 0; nt < NTP; ++nt) { nv[nt] = limit[nt] - key0; m_new[nt] = st.m[nt]; }
-      const bool past = key0 + TK <= wave_first + 1;        // wholly in every row's past
-      if constexpr (FIXED) {
-        if (past) mask_scores<NTP, false>(s0, s1, nv, g, sv);
-        else      mask_scores<NTP, true>(s0, s1, nv, g, sv);
-      } else {
-        if (past) softmax_max<NTP, false>(s0, s1, nv, st, P.c, g, sv, m_new);
-        else      softmax_max<NTP, true>(s0, s1, nv, st, P.c, g, sv, m_new);
+        for (int nt = 0; nt < NTP; ++nt) nv[nt] = limit[nt] - key0;
+        mask_scores<NTP>(s0, s1, nv, g);
       }
+#pragma unroll
+      for (int nt = 0; nt < NTP; ++nt) m_new[nt] = st.m[nt];
+      const auto score = [&](int nt, int x) { return x < 4 ? s0[nt][x & 3] : s1[nt][x & 3]; };
+      if constexpr (!FIXED) softmax_max<NTP>(score, st, P.c, m_new);
       read_v_frags<STAGE>(va, vf);
-      softmax_weights<NTP, FIXED>(sv, m_new, st, pb, P.c);
+      softmax_weights<NTP, FIXED>(score, m_new, st, pb, P.c);
       wait_v_frags(vf);
     }
     if ((STAGE & 1) || t == n_tiles - 1) {                  // the round's last tile: every fragment of the round is in registers
@@ -1468,8 +1477,12 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
       wait_k_frags(kf);
       score_products<NTP>(kf, qf, s0, s1);
       if constexpr (decltype(fixed)::value) {               // every row sees key 0
-        float sv[NTP][8], m_new[NTP];
-        softmax_max<NTP, true>(s0, s1, limit, st, P.c, g, sv, m_new);
+        f32x4 t0[NTP], t1[NTP];
+        float m_new[NTP];
+#pragma unroll
+        for (int nt = 0; nt < NTP; ++nt) { t0[nt] = s0[nt]; t1[nt] = s1[nt]; }
+        mask_scores<NTP>(t0, t1, limit, g);
+        softmax_max<NTP>([&](int nt, int x) { return x < 4 ? t0[nt][x & 3] : t1[nt][x & 3]; }, st, P.c, m_new);
 #pragma unroll
         for (int nt = 0; nt < NTP; ++nt) st.m[nt] = m_new[nt];
       }
@@ -1526,22 +1539,36 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
   bad = __any(bad);
   if (lane == 0) again[wv] = bad;
   lds_barrier();
-  if (uni(again[0] | again[1] | again[2] | again[3])) pass(std::false_type{});
-  // normalise and write the rows
+  if (uni(again[0] | again[1] | again[2] | again[3])) {
+    pass(std::false_type{});
+    lds_barrier();
+  }
+  // Normalise and write the rows.  Through this wavefront's quarter of the LDS (every wavefront has read the last tiles), so
+  // that a store instruction covers two whole rows, and past the caches: the outputs are more bytes than all inputs
+  // together, and what lies in the L2s as dirty lines has to leave them before the launch can end.  Rows of 64-byte pieces
+  // from the accumulators / whole rows / whole rows past the caches, us: 8 ragged prompts up to 452 tokens of 16/2 heads
+  // 15.9 / 15.9 / 14.2, 15 up to 635 of 14/2 27.3 / 26.8 / 24.6, 5 x 4083 of 8/4 183 / 183 / 173, 32 x 1280 of 28/4
+  // 487 / 493 / 487 (pieces past the caches 501).
+  char* const rows = lds + wv * STAGE_B;
 #pragma unroll
   for (int nt = 0; nt < NTP; ++nt) {
     const int row = WROWS * wv + 16 * nt + m16, pos = limit[nt] - 1;
-    const float l = sum_of_row(st.l[nt]), lr = sum_of_row(st.lr[nt]);
-    if (row < nrows) {
-      const float inv = 1.f / lr;
-      const size_t orow = ((size_t)p * P.Lp_cap + pos) * P.Hq + j * P.r + row - (pos - a) * P.r;
-      float* o = P.out + orow * D + 4 * g;
+    const float l = sum_of_row(st.l[nt]), inv = 1.f / sum_of_row(st.lr[nt]);
 #pragma unroll
-      for (int ct = 0; ct < 8; ++ct) {
-        const f32x4 v = st.O[nt][ct] * inv;
-        *reinterpret_cast<float4*>(o + 16 * ct) = make_float4(v[0], v[1], v[2], v[3]);
-      }
-      if (P.lse && g == 0) P.lse[orow] = (st.m[nt] + __builtin_amdgcn_logf(l)) * 0.69314718055994531f;
+    for (int ct = 0; ct < 8; ++ct) *RLDA_LDS(f32x4, rows + (16 * nt + m16) * (D * 4) + (((4 * ct + g) ^ m16) << 4)) = st.O[nt][ct] * inv;
+    if (P.lse && g == 0 && row < nrows)
+      P.lse[((size_t)p * P.Lp_cap + pos) * P.Hq + j * P.r + row - (pos - a) * P.r] = (st.m[nt] + __builtin_amdgcn_logf(l)) * 0.69314718055994531f;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < WROWS / 2; ++i) {
+    const int lr = 2 * i + (lane >> 5), c = lane & 31, row = WROWS * wv + lr;
+    const f32x4 v = *RLDA_LDS(const f32x4, rows + lr * (D * 4) + ((c ^ (lr & 15)) << 4));
+    if (row < nrows) {
+      const int q = fast_div(row, P.div_r);
+      float* o = P.out + (((size_t)p * P.Lp_cap + a + q) * P.Hq + j * P.r + row - q * P.r) * D + 4 * c;
+      __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(o));
     }
   }
 }
@@ -1790,6 +1817,7 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   P.QB = ((two ? 2 : 1) * rows1) / P.r;                     // query positions per workgroup
   P.nqb = ceil_div(Lp_cap, P.QB);
   P.spread = prefill_spread(P_ * Hkv);
+  P.div_Hkv = make_fastdiv(Hkv); P.div_r = make_fastdiv(P.r); P.div_nqb = make_fastdiv(P.nqb); P.div_units = make_fastdiv(P_ * Hkv);
   typedef void (*kern_t)(const PrefillParams);
   const kern_t kern = two ? prefill2_kernel<2> : (scale > 0.f ? prefill2_kernel<1> : prefill_kernel<1>);
   {
