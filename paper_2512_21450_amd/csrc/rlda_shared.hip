@@ -886,6 +886,9 @@ struct RowParts {
 // values of the row and the first sixteen parts' values are requested in one round trip (rows of a
 // small batch are cut into that many parts, and every further round trip shows in its step time); the lse
 // values become weights with two 32-lane reductions; then every lane accumulates its 4 columns.  Parts are taken in line order, so the sum has one fixed order.
+// The partials are read and the rows written past the caches: each is touched once, and what they displace is what other
+// rows still need (2048 x 16 rows: 152.7 us per call before, 145 with the stores so, 140 with the loads as well; others 0 to
+// 0.5 us).
 template <bool EXT, bool TREE = false>
 __global__ void __launch_bounds__(256) combine_kernel(const SharedParams P) {
   const int row = blockIdx.x * 8 + (threadIdx.x >> 5);
@@ -894,7 +897,7 @@ __global__ void __launch_bounds__(256) combine_kernel(const SharedParams P) {
   if (row >= P.B * P.Hq) return;
   const int b = fast_div(row, P.div_Hq), h = row - b * P.Hq;
   if (EXT && P.active && P.active[b] == 0) {               // finished sequence: its prefix rows were computed, not used
-    *reinterpret_cast<float4*>(P.out + (size_t)row * D + c4) = make_float4(0.f, 0.f, 0.f, 0.f);
+    __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4*>(P.out + (size_t)row * D + c4));
     if (P.lse && c4 == 0) P.lse[row] = -INFINITY;
     return;
   }
@@ -941,7 +944,7 @@ __global__ void __launch_bounds__(256) combine_kernel(const SharedParams P) {
 #pragma unroll
     for (int u = 0; u < FIRST; ++u) {
       const int id = __shfl(mine, min(u, cnt - 1), 32);
-      v8[u] = *reinterpret_cast<const f16x4*>(reinterpret_cast<const char*>((id & 1 ? P.so : P.po) + (size_t)(id >> 1) * D) + coff);
+      v8[u] = __builtin_nontemporal_load(reinterpret_cast<const f16x4*>(reinterpret_cast<const char*>((id & 1 ? P.so : P.po) + (size_t)(id >> 1) * D) + coff));
     }
     const float2 ls = mine < 0 ? make_float2(-INFINITY, 0.f)
                                : *reinterpret_cast<const float2*>((mine & 1 ? P.sl : P.pl) + 2 * (size_t)(mine >> 1));
@@ -973,7 +976,7 @@ __global__ void __launch_bounds__(256) combine_kernel(const SharedParams P) {
         const int k = min(k0 + u, cnt - 1);
         const int id = __shfl(mine, k, 32);
         wk[u] = k0 + u < cnt ? __shfl(wsc, k, 32) : 0.f;
-        v[u] = *reinterpret_cast<const f16x4*>(reinterpret_cast<const char*>((id & 1 ? P.so : P.po) + (size_t)(id >> 1) * D) + coff);
+        v[u] = __builtin_nontemporal_load(reinterpret_cast<const f16x4*>(reinterpret_cast<const char*>((id & 1 ? P.so : P.po) + (size_t)(id >> 1) * D) + coff));
       }
 #pragma unroll
       for (int u = 0; u < NEXT; ++u) {
@@ -984,7 +987,7 @@ __global__ void __launch_bounds__(256) combine_kernel(const SharedParams P) {
     if (rp.pos >= rp.total) break;
   }
   const float inv = Z > 0.f ? 1.f / Z : 0.f;
-  *reinterpret_cast<float4*>(P.out + (size_t)row * D + c4) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+  __builtin_nontemporal_store(f32x4{acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv}, reinterpret_cast<f32x4*>(P.out + (size_t)row * D + c4));
   if (P.lse && c4 == 0) P.lse[row] = Z > 0.f ? M + __logf(Z) : -INFINITY;
 }
 
@@ -1008,8 +1011,8 @@ __global__ void __launch_bounds__(256, 8) combine16_kernel(const SharedParams P)
   const int b = fast_div(row, P.div_Hq), h = row - b * P.Hq;
   float* orow = P.out + (size_t)row * D;
   if (EXT && P.active && P.active[b] == 0) {               // finished sequence: its prefix rows were computed, not used
-    *reinterpret_cast<float4*>(orow + ca) = make_float4(0.f, 0.f, 0.f, 0.f);
-    *reinterpret_cast<float4*>(orow + cb) = make_float4(0.f, 0.f, 0.f, 0.f);
+    __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4*>(orow + ca));
+    __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4*>(orow + cb));
     if (P.lse && sub == 0) P.lse[row] = -INFINITY;
     return;
   }
@@ -1024,7 +1027,7 @@ __global__ void __launch_bounds__(256, 8) combine16_kernel(const SharedParams P)
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float M = -INFINITY, Z = 0.f;                             // running max and sum over batches of 16 parts
   auto part_values = [&](int id) {
-    return *reinterpret_cast<const f16x8*>(reinterpret_cast<const char*>((id & 1 ? P.so : P.po) + (size_t)(id >> 1) * D) + coff);
+    return __builtin_nontemporal_load(reinterpret_cast<const f16x8*>(reinterpret_cast<const char*>((id & 1 ? P.so : P.po) + (size_t)(id >> 1) * D) + coff));
   };
   for (int base = 0;; base += 16) {
     // part `base + sub` of this row, as 2 * (row index in its partial array) + [suffix]
@@ -1083,8 +1086,8 @@ __global__ void __launch_bounds__(256, 8) combine16_kernel(const SharedParams P)
     if (n - base <= 16) break;
   }
   const float inv = Z > 0.f ? 1.f / Z : 0.f;
-  *reinterpret_cast<float4*>(orow + ca) = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
-  *reinterpret_cast<float4*>(orow + cb) = make_float4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv);
+  __builtin_nontemporal_store(f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv}, reinterpret_cast<f32x4*>(orow + ca));
+  __builtin_nontemporal_store(f32x4{acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv}, reinterpret_cast<f32x4*>(orow + cb));
   if (P.lse && sub == 0) P.lse[row] = Z > 0.f ? M + __logf(Z) : -INFINITY;
 }
 
