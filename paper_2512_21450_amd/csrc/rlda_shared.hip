@@ -866,7 +866,7 @@ struct RowParts {
     int n = 0;
     mine = -1;
     while (pos < total) {
-      const int id = id_at(P, sc, side, hi_, pos + sub);
+      const int id = pos + sub < total ? id_at(P, sc, side, hi_, pos + sub) : -1;   // the places behind may be another team's
       const uint32_t has = (uint32_t)(__ballot(id >= 0) >> row0);
       const int cnt = __popc(has);
       if (n + cnt > W) break;                                // packed with the next batch (cnt <= W)
@@ -882,25 +882,23 @@ struct RowParts {
   }
 };
 
-// ---- combine: 32 lanes per (sequence, head) row.  Lane k of the row first owns part k: all lse
-// values of the row and the first sixteen parts' values are requested in one round trip (rows of a
-// small batch are cut into that many parts, and every further round trip shows in its step time); the lse
-// values become weights with two 32-lane reductions; then every lane accumulates its 4 columns.  Parts are taken in line order, so the sum has one fixed order.
-// The partials are read and the rows written past the caches: each is touched once, and what they displace is what other
-// rows still need (2048 x 16 rows: 152.7 us per call before, 145 with the stores so, 140 with the loads as well; others 0 to
-// 0.5 us).
-template <bool EXT, bool TREE = false>
-__global__ void __launch_bounds__(256) combine_kernel(const SharedParams P) {
-  const int row = blockIdx.x * 8 + (threadIdx.x >> 5);
+// ---- combine: TEAMS teams of 32 lanes per (sequence, head) row, which take even runs of its places.  Lane k of a team first
+// owns part k: all lse values of the team's parts and the first sixteen parts' values are requested in one round trip (rows
+// of a small batch are cut into many parts, and every further round trip shows in its step time); the lse values become
+// weights with two 32-lane reductions; then every lane accumulates its 4 columns.  Parts are taken in line order, and the
+// teams meet in LDS in that order, so the sum has one fixed order.  The partials are read and the rows written past the
+// caches: each is touched once, and what the read of the partials and the outputs displace is what other rows still need
+// (2048 x 16 rows: 152.7 us per call before, 145 with the stores so, 140 with the loads as well; others 0 to 0.5 us).
+template <bool EXT, bool TREE, int TEAMS>
+__global__ void __launch_bounds__(TEAMS > 8 ? 32 * TEAMS : 256) combine_kernel(const SharedParams P) {
+  const int team = (threadIdx.x >> 5) & (TEAMS - 1), rows = P.B * P.Hq;
+  const int at = TEAMS > 8 ? blockIdx.x : blockIdx.x * (8 / TEAMS) + threadIdx.x / (32 * TEAMS);
   const int sub = threadIdx.x & 31, c4 = sub * 4;
   const int coff = part_col_off(sub);                       // where this lane's 4 columns sit in a stored partial row
-  if (row >= P.B * P.Hq) return;
+  if (TEAMS == 1 && at >= rows) return;
+  const int row = min(at, rows - 1);
   const int b = fast_div(row, P.div_Hq), h = row - b * P.Hq;
-  if (EXT && P.active && P.active[b] == 0) {               // finished sequence: its prefix rows were computed, not used
-    __builtin_nontemporal_store(f32x4{0.f, 0.f, 0.f, 0.f}, reinterpret_cast<f32x4*>(P.out + (size_t)row * D + c4));
-    if (P.lse && c4 == 0) P.lse[row] = -INFINITY;
-    return;
-  }
+  const bool live = !(EXT && P.active && P.active[b] == 0); // finished sequence: its prefix rows were computed, not used
   const int p = fast_div(b, P.div_G), gs = b - p * P.G, j = fast_div(h, P.div_r), hi_ = h - j * P.r;
   const int* X = P.cum;
   const int cumP = X[P.P];
@@ -934,6 +932,12 @@ __global__ void __launch_bounds__(256) combine_kernel(const SharedParams P) {
   rp.suf = suffix_parts(sc, X + P.P, cumP, P.Hkv, b, j);
   rp.sslot = b * P.Hkv + j + 2 * WG_WAVES * rp.suf.first;   // places of a pair: WG_WAVES * rank + wavefront in turn
   rp.total += rp.suf.n;
+  if (!live) rp.total = 0;
+  if constexpr (TEAMS > 1) {                                // this team's places
+    const int per = ceil_div(rp.total, TEAMS);
+    rp.pos = team * per;
+    rp.total = min(rp.pos + per, rp.total);
+  }
   for (;;) {
     int mine;
     const int cnt = rp.next(P, sc, TREE ? 0 : side, hi_, sub, mine);
@@ -986,13 +990,34 @@ __global__ void __launch_bounds__(256) combine_kernel(const SharedParams P) {
     }
     if (rp.pos >= rp.total) break;
   }
+  if constexpr (TEAMS > 1) {                                // the teams of a row meet in LDS, merged in line order
+    constexpr int ALL = TEAMS > 8 ? TEAMS : 8;              // teams of the workgroup
+    __shared__ f32x4 tacc[ALL][32];
+    __shared__ float2 tmz[ALL];
+    const int t0 = (threadIdx.x >> 5) - team;
+    tacc[t0 + team][sub] = f32x4{acc.x, acc.y, acc.z, acc.w};
+    if (sub == 0) tmz[t0 + team] = make_float2(M, Z);
+    __syncthreads();
+    if (team > 0 || at >= rows) return;
+    float Mt = M;
+#pragma unroll
+    for (int t = 1; t < TEAMS; ++t) Mt = fmaxf(Mt, tmz[t0 + t].x);
+    f32x4 sum{0.f, 0.f, 0.f, 0.f};
+    Z = 0.f;
+#pragma unroll
+    for (int t = 0; t < TEAMS; ++t) {
+      const float2 mz = tmz[t0 + t];
+      const float w = mz.y > 0.f ? __expf(mz.x - Mt) : 0.f;  // a team without a part: M is -inf
+      Z = fmaf(w, mz.y, Z);
+      sum += tacc[t0 + t][sub] * w;
+    }
+    M = Mt;
+    acc = make_float4(sum[0], sum[1], sum[2], sum[3]);
+  }
   const float inv = Z > 0.f ? 1.f / Z : 0.f;
   __builtin_nontemporal_store(f32x4{acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv}, reinterpret_cast<f32x4*>(P.out + (size_t)row * D + c4));
   if (P.lse && c4 == 0) P.lse[row] = Z > 0.f ? M + __logf(Z) : -INFINITY;
 }
-
-// from this many prefix units (prompts x KV heads x row parts) on, rows have few enough parts for combine16_kernel
-constexpr int COMBINE16_MIN_UNITS = 128;
 
 // ---- the same with 16 lanes per row and 16 rows per workgroup, for batches of many units, whose rows
 // have few parts (a prefix unit is cut into about 1 + N_WG / units parts): half the wavefronts, so that
@@ -1576,6 +1601,42 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
   }
 }
 
+// Which form merges the partials.  A row's time is the chain of its parts: with the lines cut evenly, a prefix unit is cut
+// into about 1 + pairs / units parts and a suffix unit into 1 + 8 * pairs / units, a few times that where lengths differ.
+// The more there are, the more teams of 32 lanes share a row; few rows have many parts, so that the chip has room for them.
+// Measured, us per call with 1 / 2 / 4 / 8 / 16 / 32 teams (parts by the formula below):
+//   1 x 1  32/2 heads 1500 + 4000 keys (1152)  38.2 / 28.8 / 22.8 / 18.6 / 18.0 / 14.7
+//   1 x 8   8/1   2000 + 0..4096 (512)  37.7 / 28.3 / 22.0 / 17.0 / 14.4 / 14.6      1 x 16  8/1  4000 + 500 (384)  32.9 / 30.8 / 19.8 / 15.8 / 14.7 / 15.9
+//   2 x 4  16/4   3000 + 4096    (96)   28.3 / 24.8 / 22.2 / 19.5 / 20.1             8 x 5   7/1  1600 + 4000  (83)  32.6 / 29.1 / 25.0 / 22.3 / 23.4
+//   2 x 8  28/4   1344 + 3000    (64)   33.8 / 28.4 / 24.4 / 25.3                    4 x 8  28/4  1344 + 0..4096 (32) 35.7 / 34.1 / 30.2 / 31.5
+//   2 x 16 32/8   4000 + 1000    (24)   29.8 / 29.3 / 29.5                           8 x 8  28/4  1344 + 0..3000 (16) 39.9 / 38.1 / 39.0
+//   16 x 8 28/4   1344 + 0..4096  (8)   45.5 / 46.1 / 49.8
+// From 128 prefix units and 4 suffix units a pair on, rows have so few parts that their number counts: 16 lanes each
+// (32 / 16 lanes: 128 x 16 16/2 151 / 140, 128 x 8 16/2 85 / 80, 32 x 8 28/4 112.6 / 111.3; but 40 x 5 20/4 with answers
+// up to 3686 keys, half of them finished, 52 / 57).
+void launch_combine_rows(const SharedParams& P, bool tree, bool ext, int rows, int64_t prefix_units, hipStream_t stream) {
+  const int64_t suffix_units = (int64_t)P.B * P.Hkv;
+  if (!tree && prefix_units >= 128 && suffix_units >= 4 * (int64_t)P.n_cu) {
+    if (ext) hipLaunchKernelGGL(combine16_kernel<true>, dim3((rows + 15) / 16), dim3(256), 0, stream, P);
+    else     hipLaunchKernelGGL(combine16_kernel<false>, dim3((rows + 15) / 16), dim3(256), 0, stream, P);
+    return;
+  }
+  if (rows == 0) return;
+  const int64_t parts = P.n_cu / ((int64_t)P.P * P.HkvP) + 8 * (int64_t)P.n_cu / suffix_units;
+  const int teams = parts >= 700 ? 32 : parts >= 200 ? 16 : parts >= 68 ? 8 : parts >= 28 ? 4 : parts >= 12 ? 2 : 1;
+  typedef void (*kern_t)(const SharedParams);
+  static const kern_t kerns[3][6] = {
+      {combine_kernel<false, false, 1>, combine_kernel<false, false, 2>, combine_kernel<false, false, 4>,
+       combine_kernel<false, false, 8>, combine_kernel<false, false, 16>, combine_kernel<false, false, 32>},
+      {combine_kernel<true, false, 1>, combine_kernel<true, false, 2>, combine_kernel<true, false, 4>,
+       combine_kernel<true, false, 8>, combine_kernel<true, false, 16>, combine_kernel<true, false, 32>},
+      {combine_kernel<false, true, 1>, combine_kernel<false, true, 2>, combine_kernel<false, true, 4>,
+       combine_kernel<false, true, 8>, combine_kernel<false, true, 16>, combine_kernel<false, true, 32>}};
+  const kern_t kern = kerns[tree ? 2 : ext ? 1 : 0][31 - __builtin_clz((unsigned)teams)];
+  const int per = teams > 8 ? 1 : 8 / teams;               // rows per workgroup
+  hipLaunchKernelGGL(kern, dim3((unsigned)((rows + per - 1) / per)), dim3(teams > 8 ? 32 * teams : 256), 0, stream, P);
+}
+
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct Layout { size_t cum, pl, po, sl, so, total; };
@@ -1778,15 +1839,7 @@ hipError_t launch_shared(const Problem& whole, hipStream_t stream, hipEvent_t mi
     if (e != hipSuccess) return e;
   }
   const int rows = P.B * P.Hq;
-  if (tree) {
-    hipLaunchKernelGGL((combine_kernel<false, true>), dim3((rows + 7) / 8), dim3(256), 0, stream, P);
-  } else if ((int64_t)ds.P * P.HkvP * P.SM >= COMBINE16_MIN_UNITS) {
-    if (ext) hipLaunchKernelGGL(combine16_kernel<true>, dim3((rows + 15) / 16), dim3(256), 0, stream, P);
-    else     hipLaunchKernelGGL(combine16_kernel<false>, dim3((rows + 15) / 16), dim3(256), 0, stream, P);
-  } else {
-    if (ext) hipLaunchKernelGGL(combine_kernel<true>, dim3((rows + 7) / 8), dim3(256), 0, stream, P);
-    else     hipLaunchKernelGGL(combine_kernel<false>, dim3((rows + 7) / 8), dim3(256), 0, stream, P);
-  }
+  launch_combine_rows(P, tree, ext, rows, (int64_t)ds.P * P.HkvP * P.SM, stream);
   return hipGetLastError();
 }
 
