@@ -252,17 +252,37 @@ int check(const rl_token_logprob_desc* d) {
   return 0;
 }
 
-// Splits per row.  From about one row per compute unit upwards a row is not split (one kernel, no
-// merge pass, which costs more than a slightly uneven last wave of workgroups); fewer rows are
-// split until there is a workgroup per compute unit, but never below 8192 logits per workgroup.
-int splits_for(const rl_token_logprob_desc* d) {
-  if (d->n_rows <= 0 || d->n_rows >= 192) return 1;
-  long long s = (256 + d->n_rows - 1) / d->n_rows;
-  const long long by_size = d->vocab / 8192;
-  if (s > by_size) s = by_size;
-  if (s > MAX_SPLITS) s = MAX_SPLITS;
+// Splits per row, and the workspace they take.  Few rows are cut into workgroups of 256 threads that read 4096 logits and
+// more each, in one or a few rounds of loads; the merge of the splits is a launch of its own, 2 us.  About one row per
+// compute unit is not split: 16 wavefronts take it.  Rows of a large vocabulary between one and one and three quarters a
+// compute unit, or a little over two, would leave most compute units waiting for those with one row more.  Measured, us,
+// rows x logits, bf16 with a reference, splits as before (enough for a workgroup of 1024 threads per compute unit) / 4 / 8 / 12:
+//    16 x 32000   9.6 /  7.7 /  7.2 /  7.2     48 x 32000   9.9 /  8.2 /  8.1 /  8.4    100 x 32000  13.2 / 10.1 / 9.9 / 10.4
+//    16 x 151936 10.6 / 15.5 / 11.6 / 10.0     48 x 151936 17.7 / 17.0 / 15.0 / 14.6    100 x 151936 25.5 / 22.0 / 21.2 / 19.7
+//   192 x 32000  11.9 / 12.5 / 12.8 / 14.2    256 x 151936 33.3 / 34.9 / 35.0 / 35.4    512 x 151936 57.9 / 61.5 / 63.9 / 62.8
+//   300 x 32000  17.4 / 15.5 / 16.5 / 18.7    300 x 151936 51.9 / 41.5 / 41.4 / 41.4    400 x 151936 53.9 / 52.1 / 50.1 / 50.7
+//   400 x 32000  18.1 / 18.1 / 20.2 / 22.9    600 x 151936 78.5 / 71.4 / 70.4 / 73.7   1024 x 151936 110.6 / 113.5 / 116.8
+constexpr int64_t PER_SPLIT = 6 * sizeof(float);
+int clamp_splits(long long s, long long by_size) {
+  s = s < by_size ? s : by_size;
+  s = s < MAX_SPLITS ? s : MAX_SPLITS;
   return s < 1 ? 1 : (int)s;
 }
+int splits_for(const rl_token_logprob_desc* d) {
+  const long long n = d->n_rows, by_size = d->vocab / 4096;
+  if (n <= 0) return 1;
+  if (n < 192) return clamp_splits(12, by_size);
+  if (d->vocab >= 65536 && ((n > 256 && n <= 448) || (n > 512 && n <= 640))) return clamp_splits(8, by_size);
+  if (n > 256 && n <= 352) return clamp_splits(4, by_size);
+  return 1;
+}
+// What a caller with less workspace gets: as many splits as give every compute unit a workgroup of 1024 threads, of 8192
+// logits and more, for fewer than 192 rows; else none.
+int splits_with_less(const rl_token_logprob_desc* d) {
+  if (d->n_rows <= 0 || d->n_rows >= 192) return 1;
+  return clamp_splits((256 + d->n_rows - 1) / d->n_rows, d->vocab / 8192);
+}
+size_t bytes_for(const rl_token_logprob_desc* d, int S) { return S == 1 ? 0 : (size_t)d->n_rows * S * PER_SPLIT; }
 
 thread_local hipError_t g_last = hipSuccess;
 
@@ -272,8 +292,8 @@ extern "C" {
 
 size_t rl_token_logprob_workspace_bytes(const rl_token_logprob_desc* d) {
   if (check(d) != 0) return 0;
-  const int S = splits_for(d);
-  return S == 1 ? 0 : (size_t)d->n_rows * S * 6 * sizeof(float);
+  const int a = splits_for(d), b = splits_with_less(d);     // room for either
+  return bytes_for(d, a > b ? a : b);
 }
 
 int rl_token_logprob(const rl_token_logprob_desc* d, void* hip_stream) {
@@ -283,10 +303,14 @@ int rl_token_logprob(const rl_token_logprob_desc* d, void* hip_stream) {
   if (!d->logits || !d->token_ids) return -1;
   if (!d->ref_logits && (d->kl || d->ref_logprob)) return -1;
   if ((reinterpret_cast<uintptr_t>(d->logits) & 15u) || (reinterpret_cast<uintptr_t>(d->ref_logits) & 15u)) return -2;
-  const int S = splits_for(d);
-  const size_t need = S == 1 ? 0 : (size_t)d->n_rows * S * 6 * sizeof(float);
-  if (need > 0 && (!d->workspace || d->workspace_bytes < need || (reinterpret_cast<uintptr_t>(d->workspace) & 255u)))
-    return -3;
+  auto fits = [&](int splits) {
+    const size_t need = bytes_for(d, splits);
+    return need == 0 || (d->workspace && d->workspace_bytes >= need && !(reinterpret_cast<uintptr_t>(d->workspace) & 255u));
+  };
+  int S = splits_for(d);
+  const bool less = !fits(S);
+  if (less) S = splits_with_less(d);
+  if (!fits(S)) return -3;
   const int vn = d->dtype == 0 ? 4 : 8;
   Params P;
   P.logits = static_cast<const char*>(d->logits); P.ref = static_cast<const char*>(d->ref_logits);
@@ -300,7 +324,7 @@ int rl_token_logprob(const rl_token_logprob_desc* d, void* hip_stream) {
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const dim3 grid((unsigned)(d->n_rows * S)), fin((unsigned)d->n_rows);
   const bool ref = d->ref_logits != nullptr;
-  const bool wide = d->n_rows * S <= 512;                  // few workgroups: make each one 16 wavefronts
+  const bool wide = (S == 1 || less) && d->n_rows * S <= 512;               // few workgroups: make each one 16 wavefronts
 #define RLTL_LAUNCH(T)                                                                                      \
   do {                                                                                                      \
     if (wide) {                                                                                             \
