@@ -1374,11 +1374,18 @@ __device__ __forceinline__ float sum_of_row(float v) {      // over the four lan
   return v + __shfl_xor(v, 32, 64);
 }
 
-template <int NTP>
-__global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillParams P) {
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  __shared__ int again[WG_WAVES];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, m16 = lane & 15, g = lane >> 4;
+// TEAMS = 2 (few, long blocks, see launch_prefill): two teams of four wavefronts hold the same rows and take the rounds of two
+// tiles in turn, each in its own half of the LDS; the second takes its reference from the first, because its own tiles may lie in
+// a row's future, and its state is folded into the first's at the end.
+template <int NTP, int TEAMS>
+__global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const PrefillParams P) {
+  extern __shared__ __attribute__((aligned(16))) char lds_all[];
+  __shared__ int again[WG_WAVES * TEAMS];
+  __shared__ float first_max[WG_WAVES][16];                 // TEAMS == 2: the rows' maxima over tile 0
+  const int tid = threadIdx.x, lane = tid & 63, wv = (tid >> 6) & (WG_WAVES - 1), m16 = lane & 15, g = lane >> 4;
+  const int team = TEAMS == 1 ? 0 : uni(tid >> 8);
+  char* const lds = lds_all + team * LDS_BYTES;
+  static_assert(TEAMS == 1 || NTP == 1, "the teams of a workgroup share one row block per wavefront");
   constexpr int WROWS = 16 * NTP;
   const int units = P.P * P.Hkv;
   int pj, qb;
@@ -1426,7 +1433,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
 #pragma unroll
   for (int i = 0; i < 4; ++i) vo[i] = lrow * ROWB + ((chunk ^ (kind ? lrow << 1 ^ (i & 1) << 3 : lrow ^ i << 2)) << 4);   // V: (row & 7) << 1, K: row & 15
   auto issue = [&](int round) {
-    int t = 2 * round + sub;
+    int t = TEAMS == 1 ? 2 * round + sub : 4 * round + 2 * team + sub;
     if (t >= n_tiles) return;
     char* dst = lds + uni((2 * (round & 1) + sub) * STAGE_B + kind * TILE_B);
     asm volatile("" : "+s"(t));
@@ -1457,12 +1464,16 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
   f32x4 s0[NTP], s1[NTP];
   bf16x8 pb[NTP], kf[4][2];
   s16x4 vf[8][2];
-  // one tile; STAGE = t % 4 is a compile-time constant of the unrolled body
-  auto tile = [&](auto fixed_c, auto stage_c, int t) {
+  // The tiles of this wavefront's team: step u is tile t = u, or with two teams the pairs of tiles in turn.
+  auto tile_at = [&](int u) { return TEAMS == 1 ? u : 4 * (u >> 1) + 2 * team + (u & 1); };
+  const int steps = TEAMS == 1 ? n_tiles : 2 * ceil_div(n_tiles, 4);        // the same for both teams: they share the barriers
+  // one step; STAGE = u % 4 is a compile-time constant of the unrolled body
+  auto tile = [&](auto fixed_c, auto stage_c, int u) {
     constexpr int STAGE = decltype(stage_c)::value;
     constexpr bool FIXED = decltype(fixed_c)::value;
-    const int key0 = t * TK;
-    if (wave_has_rows) {
+    const int t = tile_at(u), key0 = t * TK;
+    const bool here = TEAMS == 1 || t < n_tiles;
+    if (wave_has_rows && here) {
       float m_new[NTP];
       if (key0 + TK > wave_first + 1) {                     // not wholly in every row's past
         int nv[NTP];
@@ -1478,15 +1489,16 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
       softmax_weights<NTP, FIXED>(score, m_new, st, pb, P.c);
       wait_v_frags(vf);
     }
-    if ((STAGE & 1) || t == n_tiles - 1) {                  // the round's last tile: every fragment of the round is in registers
+    if ((STAGE & 1) || (TEAMS == 1 && t == n_tiles - 1)) {  // the round's last tile: every fragment of the round is in registers
       wait_vmem();                                          // this wavefront's loads of the next round have landed
       __builtin_amdgcn_s_barrier();
-      issue((t >> 1) + 2);                                  // into the buffer the round just left
+      issue((u >> 1) + 2);                                  // into the buffer the round just left
     }
     if (wave_has_rows) {
-      if (t + 1 < n_tiles) read_k_frags<(STAGE + 1) & 3>(ka, kf);
-      value_products<NTP>(vf, pb, st);
-      if (t + 1 < n_tiles) {
+      const int after = tile_at(u + 1);
+      if (after < n_tiles) read_k_frags<(STAGE + 1) & 3>(ka, kf);
+      if (here) value_products<NTP>(vf, pb, st);
+      if (after < n_tiles) {
         wait_k_frags(kf);
         score_products<NTP>(kf, qf, s0, s1);
       }
@@ -1500,11 +1512,11 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
     issue(1);
     wait_vmem();
     __builtin_amdgcn_s_barrier();
-    if (wave_has_rows) {
+    if (wave_has_rows && tile_at(0) < n_tiles) {
       read_k_frags<0>(ka, kf);
       wait_k_frags(kf);
       score_products<NTP>(kf, qf, s0, s1);
-      if constexpr (decltype(fixed)::value) {               // every row sees key 0
+      if ((decltype(fixed)::value || TEAMS == 2) && team == 0) {            // every row sees key 0
         f32x4 t0[NTP], t1[NTP];
         float m_new[NTP];
 #pragma unroll
@@ -1513,13 +1525,18 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
         softmax_max<NTP>([&](int nt, int x) { return x < 4 ? t0[nt][x & 3] : t1[nt][x & 3]; }, st, P.c, m_new);
 #pragma unroll
         for (int nt = 0; nt < NTP; ++nt) st.m[nt] = m_new[nt];
+        if (TEAMS == 2 && g == 0) first_max[wv][m16] = m_new[0];
       }
     }
-    for (int t0 = 0; t0 < n_tiles; t0 += 4) {
-      tile(fixed, std::integral_constant<int, 0>{}, t0);
-      if (t0 + 1 < n_tiles) tile(fixed, std::integral_constant<int, 1>{}, t0 + 1);
-      if (t0 + 2 < n_tiles) tile(fixed, std::integral_constant<int, 2>{}, t0 + 2);
-      if (t0 + 3 < n_tiles) tile(fixed, std::integral_constant<int, 3>{}, t0 + 3);
+    if constexpr (TEAMS == 2) {                             // the other team's rows may see none of its tiles: the same reference
+      lds_barrier();
+      if (team == 1) st.m[0] = first_max[wv][m16];
+    }
+    for (int u0 = 0; u0 < steps; u0 += 4) {
+      tile(fixed, std::integral_constant<int, 0>{}, u0);
+      if (u0 + 1 < steps) tile(fixed, std::integral_constant<int, 1>{}, u0 + 1);
+      if (u0 + 2 < steps) tile(fixed, std::integral_constant<int, 2>{}, u0 + 2);
+      if (u0 + 3 < steps) tile(fixed, std::integral_constant<int, 3>{}, u0 + 3);
       if constexpr (decltype(fixed)::value) {
         bool big = false;
 #pragma unroll
@@ -1565,11 +1582,35 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill2_kernel(const PrefillPara
       }
   }
   bad = __any(bad);
-  if (lane == 0) again[wv] = bad;
+  if (lane == 0) again[WG_WAVES * team + wv] = bad;
   lds_barrier();
-  if (uni(again[0] | again[1] | again[2] | again[3])) {
+  int redo = again[0] | again[1] | again[2] | again[3];
+  if constexpr (TEAMS == 2) redo |= again[4] | again[5] | again[6] | again[7];
+  if (uni(redo)) {
     pass(std::false_type{});
     lds_barrier();
+  }
+  // Two teams: the second leaves its state in its own part of the LDS, lane by lane, and the first folds it in.
+  if constexpr (TEAMS == 2) {
+    float* const park = reinterpret_cast<float*>(lds_all + LDS_BYTES + wv * STAGE_B) + lane;
+    if (team == 1) {
+#pragma unroll
+      for (int ct = 0; ct < 8; ++ct)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) park[(4 * ct + x) * 64] = st.O[0][ct][x];
+      park[32 * 64] = st.m[0]; park[33 * 64] = st.l[0]; park[34 * 64] = st.lr[0];
+    }
+    lds_barrier();
+    if (team == 1) return;
+    const float m2 = park[32 * 64], mn = fmaxf(st.m[0], m2);
+    const float a1 = __builtin_amdgcn_exp2f(st.m[0] - mn), a2 = __builtin_amdgcn_exp2f(m2 - mn);
+#pragma unroll
+    for (int ct = 0; ct < 8; ++ct)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) st.O[0][ct][x] = st.O[0][ct][x] * a1 + park[(4 * ct + x) * 64] * a2;
+    st.l[0] = st.l[0] * a1 + park[33 * 64] * a2;
+    st.lr[0] = st.lr[0] * a1 + park[34 * 64] * a2;
+    st.m[0] = mn;
   }
   // Normalise and write the rows.  Through this wavefront's quarter of the LDS (every wavefront has read the last tiles), so
   // that a store instruction covers two whole rows, and past the caches: the outputs are more bytes than all inputs
@@ -1875,7 +1916,18 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   P.spread = prefill_spread(P_ * Hkv);
   P.div_Hkv = make_fastdiv(Hkv); P.div_r = make_fastdiv(P.r); P.div_nqb = make_fastdiv(P.nqb); P.div_units = make_fastdiv(P_ * Hkv);
   typedef void (*kern_t)(const PrefillParams);
-  const kern_t kern = two ? prefill2_kernel<2> : (scale > 0.f ? prefill2_kernel<1> : prefill_kernel<1>);
+  // Workgroups that all find a place at once end with the longest one's chain of tiles; where it is long, two teams of four
+  // wavefronts share its tiles, at one workgroup per compute unit.  Measured, us, one team / two (blocks): 1 x 2048 tokens of
+  // 8/2 heads (256) 34.5 / 26.8, 2 x 2048 (512) 39.1 / 33.1, 4 x 3890 of 2/2 (488) 68.2 / 53.7, 5 x 1280 of 4/1 (400) 26.2 / 22.4,
+  // 1 x 700 of 28/4 (312) 15.8 / 14.0, 2 x 397 of 10/2 (136) 10.6 / 10.2; not 1 x 1280 of 28/4 (572) 26.5 / 30.8, 3 x 211 of
+  // 16/4 (168) 7.8 / 8.0.
+  int pairs = 0;
+  {
+    const hipError_t e = device_pairs(pairs);
+    if (e != hipSuccess) return e;
+  }
+  const bool teams = !two && scale > 0.f && (int64_t)P_ * Hkv * P.nqb <= 2 * (int64_t)pairs && Lp_cap >= 640;
+  const kern_t kern = two ? prefill2_kernel<2, 1> : (teams ? prefill2_kernel<1, 2> : (scale > 0.f ? prefill2_kernel<1, 1> : prefill_kernel<1>));
   {
     static std::mutex mu;
     static bool done[64] = {};
@@ -1884,14 +1936,17 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(mu);
     if (dev < 0 || dev >= 64 || !done[dev]) {
-      for (const kern_t kf : {static_cast<kern_t>(prefill_kernel<1>), static_cast<kern_t>(prefill2_kernel<2>), static_cast<kern_t>(prefill2_kernel<1>)}) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(kf), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+      for (const kern_t kf : {static_cast<kern_t>(prefill_kernel<1>), static_cast<kern_t>(prefill2_kernel<2, 1>),
+                              static_cast<kern_t>(prefill2_kernel<1, 1>), static_cast<kern_t>(prefill2_kernel<1, 2>)}) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(kf), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kf == static_cast<kern_t>(prefill2_kernel<1, 2>) ? 2 * LDS_BYTES : LDS_BYTES);
         if (e != hipSuccess) return e;
       }
       if (dev >= 0 && dev < 64) done[dev] = true;
     }
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)((P.spread ? (int64_t)P_ * Hkv : units8) * P.nqb)), dim3(NTHREADS), LDS_BYTES, stream, P);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((P.spread ? (int64_t)P_ * Hkv : units8) * P.nqb)), dim3(teams ? 2 * NTHREADS : NTHREADS),
+                     teams ? 2 * LDS_BYTES : LDS_BYTES, stream, P);
   return hipGetLastError();
 }
 

@@ -1,0 +1,43 @@
+"""The prefill of few, long blocks: two teams of wavefronts share a block's tiles.  Numbers of tiles around multiples of the
+four that the teams take in turn (blocks whose second team has no tile, one, or only tiles in the future of some rows), both
+sides of the rule's lines (640 rows of capacity, two blocks a compute unit), scores that move the reference and scores that
+make a workgroup start over; against the fp64 oracle at the bar of the other prefill tests."""
+import math
+
+import numpy as np
+import pytest
+
+from tests.test_gpu_prefill import B, case, check, run  # noqa: F401  (B is the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(1, 1), (7, 1), (8, 1), (6, 2)])
+@pytest.mark.parametrize("cap", [639, 640, 700])
+def test_numbers_of_tiles(B, Hq, Hkv, cap):  # noqa: F811
+    lens = [1, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 160, 193, 257, 0, cap]
+    for i in range(0, len(lens), 4):                               # few prompts, so that all blocks find a place at once
+        x = case(cap + i + Hq, 4, cap, Hq, Hkv, lens=lens[i:i + 4])
+        check(B, x, 1.0 / math.sqrt(128), (Hq, Hkv, cap, lens[i:i + 4]))
+
+
+@pytest.mark.parametrize("cap", [2048, 2056])                      # 512 and 514 blocks of eight positions
+def test_both_sides_of_two_blocks_a_compute_unit(B, cap):  # noqa: F811
+    check(B, case(cap, 2, cap, 8, 1, lens=[300, 555]), 1.0 / math.sqrt(128), cap)
+
+
+@pytest.mark.parametrize("gain", [6.0, 60.0])
+@pytest.mark.parametrize("first", [32, 64, 100])
+def test_growing_scores(B, gain, first):  # noqa: F811
+    """Keys past the first ones `gain` times as large: the reference follows the sums, or the workgroup starts over."""
+    x = case(int(gain) + first, 1, 700, 8, 1, lens=[530])
+    k = (x["k"].astype(np.uint32) << 16).view(np.float32).copy()
+    k[:, :, first:] *= gain
+    x["k"] = (k.view(np.uint32) >> 16).astype(np.uint16)
+    check(B, x, 1.0 / math.sqrt(128), (gain, first))
+
+
+def test_run_to_run(B):  # noqa: F811
+    x = case(5, 1, 900, 8, 2, lens=[871])
+    a, b = run(B, x, 0.1), run(B, x, 0.1)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
