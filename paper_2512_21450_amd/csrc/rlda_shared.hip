@@ -846,7 +846,8 @@ __global__ void __launch_bounds__(NTHREADS, 2) partial_kernel(const SharedParams
 // place at a time, 32 in parallel, and the places that hold one are packed in line order: lane k of the row receives
 // the k-th partial as 2 * (row index in its partial array) + [suffix], up to 32 per batch.  Every lane walking all of
 // them in turn took, of whole calls on 128-column bf16 heads: 1 x 8 sequences, 1 KV head, 1344 + 0..4096 keys 202 us
-// (now 35), 4 x 8 with 2 KV heads 60 us (36), 16 prompts x 8 of the 7B shape 42 us (40).
+// (35 side by side, 14.5 with
+// the teams of launch_combine_rows), 4 x 8 with 2 KV heads 60 us (36), 16 prompts x 8 of the 7B shape 42 us (40).
 template <bool TREE>
 struct RowParts {
   static constexpr int W = 32, NL = TREE ? MAX_LEVELS : 1;
@@ -1916,7 +1917,8 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   // The host knows the capacity only.  Below four rounds two blocks lose where the prompts fill less than about half
   // of it, one block / two: 4 x 2048 of 16/2 all filled 99 / 80 us, 60 % 46.6 / 41.3, 50 % 35.4 / 37.3, 30 %
   // 19.9 / 25.0; 1 x 4096 of 28/4 163 / 128, 66 / 69, 51 / 59, 29.0 / 36.9; 2 x 4096 of 28/4 313 / 250, 124 / 100,
-  // 92 / 74, 42.4 / 41.8.  Both bodies in one kernel that chose by the lengths cost every call 1 to 3 us.
+  // 92 / 74, 42.4 / 41.8.  Both bodies in one kernel that chose by the lengths cost every call 1 to 3 us.  (All before rows
+  // were stored whole and past the caches, which took 2 to 15 % off either side.)
   const int rows1 = 16 * WG_WAVES;
   const int64_t units8 = (int64_t)8 * ceil_div(P_ * Hkv, 8);              // eight XCDs, whole rounds of units
   const int64_t wgs = (int64_t)P_ * Hkv * ceil_div(Lp_cap, (2 * rows1) / P.r);

@@ -655,6 +655,9 @@ bool unit_pays(const Problem& pb, int pairs) {
 // and on e4m3 stores 64 x (1024 + 1024) 18.0 / 14.4, 1024 x (512 + 16) 22.9 / 21.7.  Units of hardly any key, which
 // wait for nothing but their turn: 16384 x (16 + 16) 58 / 70, 65536 x (1 + 1) 163 / 149.  All on 256 compute units; the
 // number of units that fills the chip follows the device's, as the other path does (2048 keys per workgroup pair).
+// Since rows of many parts are merged by several teams of lanes, up to 32 units of 1500 keys and more run faster over there
+// (16 x (1024 + 512) 13.4 / 12.8, 32 x (512 + 2048) half full 19.4 / 16.1), but with weights of 8 bits where this kernel keeps
+// 16, so the line stands.
 bool unit_preferred(const Problem& pb, int pairs) {
   const int64_t shared = shared_cap(pb);
   return pb.Ls_cap <= 2048 && 3 * shared + pb.Ls_cap <= 3600 && n_sequences(pb) * pb.Hkv <= (int64_t)64 * pairs &&
