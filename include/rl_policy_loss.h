@@ -29,7 +29,8 @@
  *                      grad_logprob[b,t] = d loss / d logprob[b,t] = - weight_t * (rho_t A if the unclipped branch is
  *                              the minimum, else 0); 0 on padding.  (KL_t and H_t are inputs: their dependence on the
  *                              logits is the caller's autograd business.)
- * Tokens t >= lens[b] are padding and never read.  Arithmetic is fp32, the batch sums are accumulated per
+ * Tokens t >= lens[b] are padding and never used (a load of four tokens may reach past lens[b], inside the row).
+ * Arithmetic is fp32, the batch sums are accumulated per
  * sequence in fp32 in a fixed order and across sequences in fp64 in a fixed order: results are
  * bit-reproducible from call to call.
  */
