@@ -55,7 +55,7 @@ typedef struct {
   float* entropy;
   float* ref_logprob;        /* needs ref_logits */
   float* kl;                 /* needs ref_logits */
-  void*  workspace;          /* device scratch, 256-byte aligned, >= rl_token_logprob_workspace_bytes */
+  void*  workspace;          /* device scratch, 256-byte aligned (see rl_token_logprob_workspace_bytes) */
   size_t workspace_bytes;
 } rl_token_logprob_desc;
 
@@ -66,11 +66,17 @@ typedef struct {
  * (NULL logits/token_ids with rows > 0, ref outputs without ref_logits,
  * negative sizes), -2 unsupported (dtype, stride not a multiple of the vector
  * width or < vocab, misaligned base), -3 workspace, -4 struct_size, -5 HIP
- * error.  Results are bit-reproducible from call to call.
+ * error.  Results are bit-reproducible from call to call with the same
+ * workspace_bytes (which may decide into how many parts a row is cut).
  */
 int rl_token_logprob(const rl_token_logprob_desc* desc, void* hip_stream);
 
-/* Bytes of workspace the call needs (0 if none or if the descriptor is invalid).  Pure host code. */
+/*
+ * Bytes of workspace with which the call runs fastest (0 if none or if the descriptor is invalid).  Pure host code; looks at
+ * n_rows, vocab, dtype and whether ref_logits is NULL.  With less, or a misaligned or no workspace, 192 rows and more run
+ * without any.  Fewer rows are cut into fewer parts, down to min(ceil(256 / n_rows), vocab / 8192, 64) of them, which take 24
+ * bytes a part and row; where that is 1 part, none is needed.  Below that the call returns -3.
+ */
 size_t rl_token_logprob_workspace_bytes(const rl_token_logprob_desc* desc);
 
 #ifdef __cplusplus

@@ -252,32 +252,54 @@ int check(const rl_token_logprob_desc* d) {
   return 0;
 }
 
-// Splits per row, and the workspace they take.  Few rows are cut into workgroups of 256 threads that read 4096 logits and
-// more each, in one or a few rounds of loads; the merge of the splits is a launch of its own, 2 us.  About one row per
-// compute unit is not split: 16 wavefronts take it.  Rows of a large vocabulary between one and one and three quarters a
-// compute unit, or a little over two, would leave most compute units waiting for those with one row more.  Measured, us,
-// rows x logits, bf16 with a reference, splits as before (enough for a workgroup of 1024 threads per compute unit) / 4 / 8 / 12:
-//    16 x 32000   9.6 /  7.7 /  7.2 /  7.2     48 x 32000   9.9 /  8.2 /  8.1 /  8.4    100 x 32000  13.2 / 10.1 / 9.9 / 10.4
-//    16 x 151936 10.6 / 15.5 / 11.6 / 10.0     48 x 151936 17.7 / 17.0 / 15.0 / 14.6    100 x 151936 25.5 / 22.0 / 21.2 / 19.7
-//   192 x 32000  11.9 / 12.5 / 12.8 / 14.2    256 x 151936 33.3 / 34.9 / 35.0 / 35.4    512 x 151936 57.9 / 61.5 / 63.9 / 62.8
-//   300 x 32000  17.4 / 15.5 / 16.5 / 18.7    300 x 151936 51.9 / 41.5 / 41.4 / 41.4    400 x 151936 53.9 / 52.1 / 50.1 / 50.7
-//   400 x 32000  18.1 / 18.1 / 20.2 / 22.9    600 x 151936 78.5 / 71.4 / 70.4 / 73.7   1024 x 151936 110.6 / 113.5 / 116.8
+// Splits per row.  What bounds a call of few rows is the dependent rounds of loads of a thread (256 threads take 16 KB of a row
+// a round); the merge of the splits is a launch of its own, 2 us.  us, captured, inputs changing, rows x logits; with a
+// reference: [R].
+//   * Fewer than 64 rows: at least 12 splits, and three workgroups of 256 threads a compute unit, down to 8 KB of a row each;
+//     where 64 splits, the merge's limit, still leave more than 32 KB, workgroups of 1024 threads.  12 splits / as many as the
+//     compute units want of 1024 threads and 8192 logits and more / this:
+//       16 x 32000 bf16 [R] 7.5 / 9.7 / 7.5    16 x 151936 bf16 [R] 10.0 / 10.6 / 9.4   48 x 151936 bf16 [R] 14.4 / 17.5 / 13.4
+//       1 x 256000 bf16 [R] 10.9 / 9.1 / 7.0   8 x 151936 fp32 8.6 / 7.6 / 6.5          4 x 1000000 fp32 25.8 / 9.1 / 9.1
+//   * 64 to 191 rows: 12, down to 4096 logits each.  The same columns (the third as the first):
+//       100 x 32000 bf16 [R] 10.4 / 13.2       150 x 151936 fp32 20.3 / 25.3            191 x 256000 bf16 [R] 40.0 / 48.3
+//   * Fewer than 16384 logits, and about one row a compute unit: none, 16 wavefronts take a row (two workgroups of 256 threads
+//     / none: 48 x 9000 bf16 6.8 / 5.4, 191 x 9000 fp32 [R] 10.3 / 8.5).
+//   * A little over one or two rows a compute unit, most compute units would wait for those with one row more.  What that
+//     costs grows with a row's bytes, what splits cost with the rows; none / 4 / 8 splits:
+//       257 x 32000 bf16 [R] 16.1 / 14.4 / 14.7    257 x 32000 bf16 9.3 / 9.7 / 10.4       300 x 60000 fp32 [R] 34.0 / 29.7 / 29.8
+//       300 x 151936 bf16 [R] 51.4 / 40.2 / 40.0   352 x 65536 bf16 15.3 / 15.4 / 16.2     352 x 60000 fp32 19.8 / 20.3 / 19.1
+//       400 x 65536 bf16 16.1 / 16.9 / 18.1        448 x 151936 bf16 [R] 54.6 / 51.5 / 53.5   448 x 151936 fp32 44.9 / 46.5 / 46.8
+//       513 x 65536 bf16 [R] 36.4 / 32.3 / 34.5    576 x 151936 bf16 41.6 / 36.1 / 36.2    576 x 151936 fp32 56.0 / 59.0 / 57.2
+//       600 x 65536 fp32 [R] 55.7 / 54.3 / 53.2    640 x 65536 bf16 22.1 / 22.5 / 24.3     640 x 256000 bf16 [R] 130.5 / 108.3 / 110.9
+// The numbers of rows are those of 256 compute units; on a part of a device the calls run, with other waits.
 constexpr int64_t PER_SPLIT = 6 * sizeof(float);
+constexpr long long KB = 1024, ROUNDS = 32 * KB;             // what 256 threads read in two rounds
 int clamp_splits(long long s, long long by_size) {
   s = s < by_size ? s : by_size;
   s = s < MAX_SPLITS ? s : MAX_SPLITS;
   return s < 1 ? 1 : (int)s;
 }
+long long row_bytes(const rl_token_logprob_desc* d) { return (long long)d->vocab * (d->dtype == 0 ? 4 : 2); }
 int splits_for(const rl_token_logprob_desc* d) {
-  const long long n = d->n_rows, by_size = d->vocab / 4096;
-  if (n <= 0) return 1;
-  if (n < 192) return clamp_splits(12, by_size);
-  if (d->vocab >= 65536 && ((n > 256 && n <= 448) || (n > 512 && n <= 640))) return clamp_splits(8, by_size);
-  if (n > 256 && n <= 352) return clamp_splits(4, by_size);
+  const long long n = d->n_rows, row = row_bytes(d), all = d->ref_logits ? 2 * row : row;
+  const bool f32 = d->dtype == 0, ref = d->ref_logits != nullptr;
+  if (n <= 0 || d->vocab < 16384) return 1;
+  if (n < 64) return clamp_splits((767 + n) / n > 12 ? (767 + n) / n : 12, row / (8 * KB));
+  if (n < 192) return clamp_splits(12, d->vocab / 4096);
+  if (n > 256 && n <= 448) {
+    const bool pays = n <= 320 ? all >= (ref ? 72 : 96) * KB : n <= 352 ? all >= (f32 ? 160 : 120) * KB
+                    : n <= 376 ? all >= 256 * KB : !f32 && all >= 500 * KB;
+    const bool eight = n <= 400 && (f32 || row >= 384 * KB || (ref && row >= 128 * KB));
+    return pays ? (eight ? 8 : 4) : 1;
+  }
+  if (n > 512 && n <= 640) {
+    if (f32) return ref && row >= (n <= 600 ? 256 : 512) * KB ? 8 : 1;
+    return row >= (n <= 600 ? 128 : 192) * KB ? (row >= 384 * KB ? 8 : 4) : 1;
+  }
   return 1;
 }
-// What a caller with less workspace gets: as many splits as give every compute unit a workgroup of 1024 threads, of 8192
-// logits and more, for fewer than 192 rows; else none.
+// What a caller with less workspace gets, never more splits than the above: as many as give every compute unit a workgroup of
+// 1024 threads, of 8192 logits and more, for fewer than 192 rows; else none.
 int splits_with_less(const rl_token_logprob_desc* d) {
   if (d->n_rows <= 0 || d->n_rows >= 192) return 1;
   return clamp_splits((256 + d->n_rows - 1) / d->n_rows, d->vocab / 8192);
@@ -292,8 +314,7 @@ extern "C" {
 
 size_t rl_token_logprob_workspace_bytes(const rl_token_logprob_desc* d) {
   if (check(d) != 0) return 0;
-  const int a = splits_for(d), b = splits_with_less(d);     // room for either
-  return bytes_for(d, a > b ? a : b);
+  return bytes_for(d, splits_for(d));
 }
 
 int rl_token_logprob(const rl_token_logprob_desc* d, void* hip_stream) {
@@ -324,7 +345,8 @@ int rl_token_logprob(const rl_token_logprob_desc* d, void* hip_stream) {
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const dim3 grid((unsigned)(d->n_rows * S)), fin((unsigned)d->n_rows);
   const bool ref = d->ref_logits != nullptr;
-  const bool wide = (S == 1 || less) && d->n_rows * S <= 512;               // few workgroups: make each one 16 wavefronts
+  // few workgroups, each with more than two rounds of loads for 256 threads (or none to share a row with): 16 wavefronts
+  const bool wide = d->n_rows * S <= 512 && (S == 1 || less || row_bytes(d) / S > ROUNDS);
 #define RLTL_LAUNCH(T)                                                                                      \
   do {                                                                                                      \
     if (wide) {                                                                                             \

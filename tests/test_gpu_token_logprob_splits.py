@@ -1,6 +1,7 @@
-"""How the rows of the token statistics are cut: both sides of the lines between 12, 8, 4 splits and none (rows 192, 256, 352,
-448, 512, 640, a vocabulary of 65536), vocabularies that leave a short last split or fewer splits, and the splits that a caller
-with less workspace than asked for gets; against the fp64 oracle at the tolerances of test_gpu_token_logprob."""
+"""How the rows of the token statistics are cut: both sides of the lines between up to 64, 12, 8, 4 splits and none (rows 64, 192,
+256, 320, 352, 376, 448, 512, 600, 640, vocabularies of 16384 logits and of more than 64 splits take in two rounds), vocabularies
+that leave a short last split or fewer splits, and the splits that a caller with less workspace than asked for gets; against the
+fp64 oracle at the tolerances of test_gpu_token_logprob."""
 import numpy as np
 import pytest
 
@@ -36,14 +37,16 @@ def run(B, n, V, ref, workspace=None):
 @pytest.mark.parametrize("ref", [False, True])
 @pytest.mark.parametrize("n,V", [(1, 4095), (1, 8200), (3, 16385), (17, 50001), (191, 33000), (192, 33000), (256, 33000), (257, 33000),
                                  (352, 20003), (353, 20003), (300, 65535), (300, 65536), (448, 65536), (449, 65536), (513, 65536),
-                                 (640, 65536), (641, 65536), (5, 151936)])
+                                 (640, 65536), (641, 65536), (5, 151936), (2, 16383), (2, 16384), (1, 256001), (2, 1100003),
+                                 (63, 33000), (64, 33000), (320, 50257), (321, 33000), (376, 70001), (377, 70001), (600, 65536),
+                                 (601, 65536)])
 def test_lines_between_the_splits(B, n, V, ref):  # noqa: F811
     run(B, n, V, ref)
 
 
 @pytest.mark.parametrize("n,V", [(20, 60000), (100, 33000), (300, 70000)])
 def test_less_workspace_than_asked_for(B, n, V):  # noqa: F811
-    """20 rows of 60000: 12 splits asked for, 7 with less; 100: 8 and 3; 300 rows: 8, and none without workspace."""
+    """20 rows of 60000: 14 splits asked for, 7 with less; 100: 8 and 3; 300 rows: 8, and none without workspace."""
     import torch
     whole = run(B, n, V, True)
     old = 0 if n >= 192 else n * min(-(-256 // n), V // 8192) * 24
