@@ -18,12 +18,16 @@
 // instruction, saved that trip but took the address unit four times as long as whole rows do: 1.05 us per 64 KB and
 // compute unit.)  So the start is what counts for units of few tiles: the lengths are asked for first, then q and, where
 // the first segment's capacity has room for a whole tile, the wavefront's first K tile, before the lengths are known (a
-// tile that turns out shorter is loaded again: calls whose segments are empty pay 0.3-0.5 us for it; asking for V as well
-// gained 0.2 us more and cost those 1.0-1.7); the second tile is asked for before the first has landed; the place in the
-// grid is found without divisions; and the loop holds one copy of the arithmetic, masks under a branch.  Calls captured
-// back to back, before / after, us: 64 units x 256 keys, bf16, 64 columns 5.28 / 4.60, 128 columns 6.6 / 5.9, fp32 7.8 /
-// 7.0; x 512 keys 6.75 / 6.0, 9.6 / 9.3, 12.2 / 11.6; e4m3 of 128 columns x 512 keys 8.6 / 7.7; 448 units of up to 1864
-// keys, e4m3, 64 columns 19.0 / 17.7; 512 units x 964, bf16, 64 columns 20.4 / 19.0.
+// tile that turns out shorter is loaded again: 512 units whose first segment is empty pay 0.3-0.7 us for it; asking for V as
+// well gained 0.2 us more and cost those 1.0-1.7); the second tile is asked for before the first has landed; the place in
+// the grid is found without divisions.  From the second tile on the next K and the next V are asked for apart, each as soon
+// as its registers are free: both at once, after both had landed, cost units of many tiles up to 1.5 us of 16.  A finished
+// sequence's flag is looked at before anything of it is asked for (no measurable cost: 8 units of live sequences 5.43 / 5.38).
+// Calls captured back to back, without all of this / so, us: 64 units x 256 keys, bf16, 64 columns 5.38 / 4.48, 128 columns
+// 6.5 / 5.8, fp32 of 64 8.4 / 7.6; x 512 keys 6.4 / 5.4, 8.7 / 7.5, 11.9 / 11.2; e4m3 of 128 columns x 512 keys 8.3 / 7.3; 448
+// units of up to 1864 keys, e4m3, 64 columns 20.2 / 18.4; 512 units of 452 and up to 1024 keys, bf16, 64 columns 19.1 / 18.0, on
+// pages of 64 19.5 / 18.4, half finished 16.3 / 14.2; 512 units of 256 and up to 512, bf16, 128 columns, pages of 32, half
+// finished 14.7 / 14.0 (with K and V at once 15.5).
 // Samples of one prompt sit on one die, side by side in dispatch order, so that the prefix a group shares comes from
 // memory once and from that die's L2 for the other samples.
 //
@@ -225,6 +229,16 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     }
   };
 
+  if (act == 0) {                                      // finished: nothing of it is read
+    for (int it = tid; it < nr * (D / 4); it += 64 * NW) {
+      const int row = it / (D / 4), ch = it % (D / 4);
+      const size_t orow = (size_t)b * P.Hq + h0 + row;
+      *reinterpret_cast<f32x4*>(P.out + orow * D + 4 * ch) = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (P.lse && ch == 0) P.lse[orow] = -INFINITY;
+    }
+    return;
+  }
+
   // ---- what needs no length: q, and the wavefront's first K tile where the first segment has room for all of it
   u32x4 qr[NQ], ka[L_::NL], va[L_::NL];
   const char* qp = P.q + ((size_t)b * P.Hq + h0 + min(m16, nr - 1)) * D * QE;
@@ -242,7 +256,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   for (int s = 0; s < NSEG; ++s) {
     first[s] = T;
     if (NSEG == 2 || s < P.n_seg) {
-      len[s] = act != 0 ? clampi(len[s], 0, P.seg[s].cap) : 0;
+      len[s] = clampi(len[s], 0, P.seg[s].cap);
       T += ceil_div(len[s], TK);
     }
   }
@@ -268,7 +282,8 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   // overflow) and -inf less itself is not a number
   float m = -FLT_MAX, l = 0.f;
 
-  auto step = [&](int nvalid) {                        // the tile in LDS, its first `nvalid` keys
+  // the tile whose K is in LDS, its first `nvalid` keys; `values` brings V there, once the weights are known
+  auto step = [&](int nvalid, auto values) {
     // ---- scores of this lane's row (m16) for keys 4 g + x and 16 + 4 g + x
     // (fp32: two sums each, half as long a chain of roundings and of waits)
     f32x4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f}, s2{0.f, 0.f, 0.f, 0.f}, s3{0.f, 0.f, 0.f, 0.f};
@@ -320,6 +335,8 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
       p[x] = __builtin_amdgcn_exp2f(EXACT ? fmaf(dx, c_lo, e) : e);
     }
     l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+
+    values();
 
     // ---- O^T += V^T P^T
     if constexpr (KIND == KV_F32) {
@@ -387,18 +404,29 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     }
 #pragma unroll
     for (int i = 0; i < NQ; ++i) qr[i] = (qr[i] & qm) ^ qs;
-    int nvalid = cur.last + 1;
-    for (int t = wv;;) {
+    auto staged = [] {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      step(nvalid);
-      t += NW;
-      if (t >= T) break;
-      nvalid = nxt.last + 1;
+    };
+    staged();
+    step(cur.last + 1, [] {});
+    // The next K is asked for before the scores and the next V before the values, as soon as its registers are free.  The last
+    // tile is a copy of its own: the waits of the others then count exactly the loads that follow.
+    auto turn = [&](auto more, int t) {                // more: tile t + NW follows
+      constexpr bool MORE = decltype(more)::value;
+      const int nvalid = nxt.last + 1;
       store(kst, kr, L_::kswz);
-      store(vst, vr, L_::vswz);
-      if (t + NW < T) { nxt = tile_of(t + NW); load(nxt, nxt.k, kr); load(nxt, nxt.v, vr); }
-    }
+      if constexpr (MORE) { nxt = tile_of(t + NW); load(nxt, nxt.k, kr); }
+      staged();
+      step(nvalid, [&] {
+        store(vst, vr, L_::vswz);
+        if constexpr (MORE) load(nxt, nxt.v, vr);
+        staged();
+      });
+    };
+    int t = wv + NW;
+    for (; t + NW < T; t += NW) turn(std::true_type{}, t);
+    if (t < T) turn(std::false_type{}, t);
   }
 
   // ---- merge: every wavefront leaves its rows (O against its own maximum) in its stages, from the K stage on
