@@ -1387,7 +1387,11 @@ __device__ __forceinline__ float sum_of_row(float v) {      // over the four lan
 
 // TEAMS = 2 (few, long blocks, see launch_prefill): two teams of four wavefronts hold the same rows and take the rounds of two
 // tiles in turn, each in its own half of the LDS; the second takes its reference from the first, because its own tiles may lie in
-// a row's future, and its state is folded into the first's at the end.
+// a row's future, and its state is folded into the first's at the end.  A block of up to SOLO_TILES tiles is the first team's alone:
+// the common reference, the fold and the barriers of eight wavefronts cost 0.5 to 1 us, half a dozen tiles shared save less (1 x 20
+// tokens in a buffer of 700, 8/2 heads: 5.3 us with both teams, 4.3 so, 4.2 in workgroups of four wavefronts; up to 12 tiles, half full
+// buffers of 700 lose 6 %).
+constexpr int SOLO_TILES = 8;
 template <int NTP, int TEAMS>
 __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const PrefillParams P) {
   extern __shared__ __attribute__((aligned(16))) char lds_all[];
@@ -1406,6 +1410,8 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
   const int L = clampi(P.lens[p], 0, P.Lp_cap), a = qb * P.QB;
   if (a >= L) return;
   const int nq = min(P.QB, L - a), n_keys = a + nq, n_tiles = ceil_div(n_keys, TK), nrows = nq * P.r;
+  const bool both = TEAMS == 2 && n_tiles > SOLO_TILES;     // the workgroup's teams share its tiles
+  if (TEAMS == 2 && !both && team == 1) return;             // (the barriers are of the wavefronts that stay)
   int limit[NTP];
   bf16x8 qf[NTP][4];
 #pragma unroll
@@ -1444,7 +1450,7 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
 #pragma unroll
   for (int i = 0; i < 4; ++i) vo[i] = lrow * ROWB + ((chunk ^ (kind ? lrow << 1 ^ (i & 1) << 3 : lrow ^ i << 2)) << 4);   // V: (row & 7) << 1, K: row & 15
   auto issue = [&](int round) {
-    int t = TEAMS == 1 ? 2 * round + sub : 4 * round + 2 * team + sub;
+    int t = both ? 4 * round + 2 * team + sub : 2 * round + sub;
     if (t >= n_tiles) return;
     char* dst = lds + uni((2 * (round & 1) + sub) * STAGE_B + kind * TILE_B);
     asm volatile("" : "+s"(t));
@@ -1476,14 +1482,14 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
   bf16x8 pb[NTP], kf[4][2];
   s16x4 vf[8][2];
   // The tiles of this wavefront's team: step u is tile t = u, or with two teams the pairs of tiles in turn.
-  auto tile_at = [&](int u) { return TEAMS == 1 ? u : 4 * (u >> 1) + 2 * team + (u & 1); };
-  const int steps = TEAMS == 1 ? n_tiles : 2 * ceil_div(n_tiles, 4);        // the same for both teams: they share the barriers
+  auto tile_at = [&](int u) { return both ? 4 * (u >> 1) + 2 * team + (u & 1) : u; };
+  const int steps = both ? 2 * ceil_div(n_tiles, 4) : n_tiles;              // the same for both teams: they share the barriers
   // one step; STAGE = u % 4 is a compile-time constant of the unrolled body
   auto tile = [&](auto fixed_c, auto stage_c, int u) {
     constexpr int STAGE = decltype(stage_c)::value;
     constexpr bool FIXED = decltype(fixed_c)::value;
     const int t = tile_at(u), key0 = t * TK;
-    const bool here = TEAMS == 1 || t < n_tiles;
+    const bool here = !both || t < n_tiles;
     if (wave_has_rows && here) {
       float m_new[NTP];
       if (key0 + TK > wave_first + 1) {                     // not wholly in every row's past
@@ -1500,7 +1506,7 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
       softmax_weights<NTP, FIXED>(score, m_new, st, pb, P.c);
       wait_v_frags(vf);
     }
-    if ((STAGE & 1) || (TEAMS == 1 && t == n_tiles - 1)) {  // the round's last tile: every fragment of the round is in registers
+    if ((STAGE & 1) || (!both && t == n_tiles - 1)) {  // the round's last tile: every fragment of the round is in registers
       wait_vmem();                                          // this wavefront's loads of the next round have landed
       __builtin_amdgcn_s_barrier();
       issue((u >> 1) + 2);                                  // into the buffer the round just left
@@ -1527,7 +1533,7 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
       read_k_frags<0>(ka, kf);
       wait_k_frags(kf);
       score_products<NTP>(kf, qf, s0, s1);
-      if ((decltype(fixed)::value || TEAMS == 2) && team == 0) {            // every row sees key 0
+      if ((decltype(fixed)::value || both) && team == 0) {                  // every row sees key 0
         f32x4 t0[NTP], t1[NTP];
         float m_new[NTP];
 #pragma unroll
@@ -1536,10 +1542,10 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
         softmax_max<NTP>([&](int nt, int x) { return x < 4 ? t0[nt][x & 3] : t1[nt][x & 3]; }, st, P.c, m_new);
 #pragma unroll
         for (int nt = 0; nt < NTP; ++nt) st.m[nt] = m_new[nt];
-        if (TEAMS == 2 && g == 0) first_max[wv][m16] = m_new[0];
+        if (both && g == 0) first_max[wv][m16] = m_new[0];
       }
     }
-    if constexpr (TEAMS == 2) {                             // the other team's rows may see none of its tiles: the same reference
+    if (both) {                                             // the other team's rows may see none of its tiles: the same reference
       lds_barrier();
       if (team == 1) st.m[0] = first_max[wv][m16];
     }
@@ -1596,13 +1602,13 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
   if (lane == 0) again[WG_WAVES * team + wv] = bad;
   lds_barrier();
   int redo = again[0] | again[1] | again[2] | again[3];
-  if constexpr (TEAMS == 2) redo |= again[4] | again[5] | again[6] | again[7];
+  if (both) redo |= again[4] | again[5] | again[6] | again[7];
   if (uni(redo)) {
     pass(std::false_type{});
     lds_barrier();
   }
   // Two teams: the second leaves its state in its own part of the LDS, lane by lane, and the first folds it in.
-  if constexpr (TEAMS == 2) {
+  if (both) {
     float* const park = reinterpret_cast<float*>(lds_all + LDS_BYTES + wv * STAGE_B) + lane;
     if (team == 1) {
 #pragma unroll
@@ -1929,16 +1935,27 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   P.div_Hkv = make_fastdiv(Hkv); P.div_r = make_fastdiv(P.r); P.div_nqb = make_fastdiv(P.nqb); P.div_units = make_fastdiv(P_ * Hkv);
   typedef void (*kern_t)(const PrefillParams);
   // Workgroups that all find a place at once end with the longest one's chain of tiles; where it is long, two teams of four
-  // wavefronts share its tiles, at one workgroup per compute unit.  Measured, us, one team / two (blocks): 1 x 2048 tokens of
-  // 8/2 heads (256) 34.5 / 26.8, 2 x 2048 (512) 39.1 / 33.1, 4 x 3890 of 2/2 (488) 68.2 / 53.7, 5 x 1280 of 4/1 (400) 26.2 / 22.4,
-  // 1 x 700 of 28/4 (312) 15.8 / 14.0, 2 x 397 of 10/2 (136) 10.6 / 10.2; not 1 x 1280 of 28/4 (572) 26.5 / 30.8, 3 x 211 of
-  // 16/4 (168) 7.8 / 8.0.
+  // wavefronts share its tiles, at one workgroup per compute unit.  So the buffers have to be long, and the more so the more
+  // of the workgroups wait for a place.  Measured, us with one team, and how many times as fast with two where all prompts fill
+  // their buffers / three quarters / half of them / a quarter (blocks):
+  //   1 x  397 of  8/2 (50)   9.7  1.00 / .94 / .93 / .95      1 x 1024 of  8/2 (128) 17.9  1.12 / 1.10 / 1.04 / .94
+  //   1 x  640 of  8/2 (80)  12.6  1.06 / 1.03 / .95 / .96     1 x 2048 of  8/2 (256) 32.0  1.21 / 1.17 / 1.12 / 1.03
+  //   8 x  640 of  4/1 (320) 13.6  1.12 / 1.03 / .95 / .95     2 x 1024 of 10/2 (344) 19.1  1.13 / 1.10 / 1.03 / .92
+  //   5 x  640 of  7/1 (360) 13.8   .94 / 1.08 / .95 / .93     6 x 1024 of  4/1 (384) 19.3  1.08 / 1.14 / 1.03
+  //   3 x  640 of 16/4 (480) 14.5   .85 / .90 / .95 / .93      8 x 1024 of  4/1 (512) 20.0   .94 / .98 / 1.02 / .92
+  //   1 x  900 of 28/4 (400) 18.3  1.02 / 1.13 / 1.04          8 x  900 of  4/1 (456) 17.9   .93 / 1.01 / 1.00
+  //   6 x 1150 of  4/1 (432) 21.6  1.04 / 1.14 / 1.04          7 x 1024 of  4/1 (448) 20.2   .97 / 1.10 / 1.03
+  //   6 x 1280 of  4/1 (480) 23.4  1.01 / 1.10 / 1.06          2 x 2048 of  8/2 (512) 35.9  1.11 / 1.23 / 1.11 / 1.01
+  //   2 x 3000 of  8/2 (752) 54.0   .82 / .92 / 1.22 / 1.18    4 x 4096 of  2/2 (512) 65.5  1.18 / 1.29 / 1.20 / 1.10
+  // The host knows capacities only: in buffers a quarter full and less, 2 to 9 % (0.2 to 0.7 us) go to workgroups of eight
+  // wavefronts that have work for four or none.
   int pairs = 0;
   {
     const hipError_t e = device_pairs(pairs);
     if (e != hipSuccess) return e;
   }
-  const bool teams = !two && scale > 0.f && (int64_t)P_ * Hkv * P.nqb <= 2 * (int64_t)pairs && Lp_cap >= 640;
+  const int64_t sixths = Lp_cap >= 1280 ? 12 : Lp_cap >= 1024 ? 10 : Lp_cap >= 896 ? 9 : 8;     // of a block a compute unit
+  const bool teams = !two && scale > 0.f && Lp_cap >= 640 && 6 * (int64_t)P_ * Hkv * P.nqb <= sixths * pairs;
   const kern_t kern = two ? prefill2_kernel<2, 1> : (teams ? prefill2_kernel<1, 2> : (scale > 0.f ? prefill2_kernel<1, 1> : prefill_kernel<1>));
   {
     static std::mutex mu;

@@ -1,6 +1,7 @@
 """The prefill of few, long blocks: two teams of wavefronts share a block's tiles.  Numbers of tiles around multiples of the
-four that the teams take in turn (blocks whose second team has no tile, one, or only tiles in the future of some rows), both
-sides of the rule's lines (640 rows of capacity, two blocks a compute unit), scores that move the reference and scores that
+four that the teams take in turn (blocks whose second team has two tiles, one, none more, or only tiles in the future of some
+rows), blocks of few tiles, which the first team takes alone (up to eight), both sides of the rule's lines (640, 896, 1024 and 1280
+rows of capacity with 8, 9, 10 and 12 blocks to six compute units), scores that move the reference and scores that
 make a workgroup start over; against the fp64 oracle at the bar of the other prefill tests."""
 import math
 
@@ -15,15 +16,18 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv", [(1, 1), (7, 1), (8, 1), (6, 2)])
 @pytest.mark.parametrize("cap", [639, 640, 700])
 def test_numbers_of_tiles(B, Hq, Hkv, cap):  # noqa: F811
-    lens = [1, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 160, 193, 257, 0, cap]
+    lens = [1, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 160, 193, 225, 0, cap,
+            255, 256, 257, 288, 289, 320, 321, 352, 353, 384, 385, 416, 417, 448, 545, 608]
     for i in range(0, len(lens), 4):                               # few prompts, so that all blocks find a place at once
         x = case(cap + i + Hq, 4, cap, Hq, Hkv, lens=lens[i:i + 4])
         check(B, x, 1.0 / math.sqrt(128), (Hq, Hkv, cap, lens[i:i + 4]))
 
 
-@pytest.mark.parametrize("cap", [2048, 2056])                      # 512 and 514 blocks of eight positions
-def test_both_sides_of_two_blocks_a_compute_unit(B, cap):  # noqa: F811
-    check(B, case(cap, 2, cap, 8, 1, lens=[300, 555]), 1.0 / math.sqrt(128), cap)
+# (prompts, capacity): blocks of eight positions on either side of 8, 9, 10 and 12 to six compute units
+@pytest.mark.parametrize("P,cap", [(2, 2048), (2, 2056), (4, 680), (4, 688), (3, 888), (3, 896), (3, 1016), (3, 1024), (3, 1032), (3, 1136),
+                                   (3, 1144), (3, 1272), (3, 1280), (3, 1360), (3, 1368)])
+def test_both_sides_of_the_blocks_a_compute_unit(B, P, cap):  # noqa: F811
+    check(B, case(cap, P, cap, 8, 1, lens=[300, 555, 0, 640][:P]), 1.0 / math.sqrt(128), (P, cap))
 
 
 @pytest.mark.parametrize("gain", [6.0, 60.0])
