@@ -732,18 +732,23 @@ __device__ __forceinline__ void suffix_stream(const SharedParams& P, char* wlds,
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
   }
   bool fresh = true;
+  // Where the next tile is (its sequence's length, its page): in a short run, asked for while the present tile is on its way,
+  // which hides what a wavefront would wait for; in a long one of 16-bit tiles, which the read rate bounds, after it has landed.
+  // us, every run before the wait / after it / by this rule: 16 prompts x 8 of 28/4 heads on pages of 64, a quarter finished 45.5 /
+  // 45.9 / 45.4, 49 x 8 of 16/8 on 32 59.7 / 60.7 / 60.3, e4m3 47 x 8 of 56/8 on 128 76.0 / 77.1 / 76.2; and 32 x 8 of 28/4 on 64
+  // 119.1 / 118.4 / 118.7, 64 x 8 of 16/2 with 3000 own keys on 128 157.6 / 155.3 / 155.6, 24 x 16 of 16/4 with 4096 296 / 293 / 291.
+  const bool ahead = F8 || n <= 8;
   for (int i = 0; i < n; ++i) {
-    // where the next tile is: its sequence's length and page are on their way while the present tile still is (16 prompts x 8 of
-    // the 7B shape on pages of 64: 45.8 -> 45.1 us; 48 x 8 of 8/8 heads, e4m3, pages of 32: 67.3 -> 64.7)
     Cur nxt = cur;
     const bool has_next = i + 1 < n;
     bool next_fresh = false;
     size_t next_row = 0;
-    if (has_next) {
+    auto locate = [&] {
       cur_step(nxt, 1, len_of, P.B, P.Hkv);
       next_fresh = nxt.u != cur.u || nxt.j != cur.j;
       next_row = first_row(nxt);
-    }
+    };
+    if (has_next && ahead) locate();
     wait_vmem();
     stage_store<F8>(wlds, wlds + TILE_B, rk, rv, lrow, chunk);
     if (fresh) {
@@ -753,6 +758,7 @@ __device__ __forceinline__ void suffix_stream(const SharedParams& P, char* wlds,
       init_state(st);
     }
     if (has_next) {
+      if (!ahead) locate();
       if (next_fresh) issue_q(nxt);
       issue_tile(nxt, next_row);
     }
