@@ -348,6 +348,15 @@ int rl_decode_attn_paged_debug_route(int32_t compute_units, const rlda_paged_des
 int rl_decode_attn_tree_debug_route(int32_t compute_units, const rlda_tree_desc* desc);
 
 /*
+ * Likewise, how a call that runs on RLDA_ALGO_SHARED merges a row's partials: the number of teams of 32 lanes that share
+ * a row (1, 2, 4, 8, 16 or 32), or 0 for the form with 16 lanes a row.  RLDA_ERR_UNSUPPORTED for calls on other kernels
+ * and empty ones.
+ */
+int rl_decode_attn_debug_merge(int32_t compute_units, const rlda_desc* desc);
+int rl_decode_attn_paged_debug_merge(int32_t compute_units, const rlda_paged_desc* desc);
+int rl_decode_attn_tree_debug_merge(int32_t compute_units, const rlda_tree_desc* desc);
+
+/*
  * Testing hook, pure host code: the static work partition the shared-prefix
  * path uses for the given lengths (HOST arrays prefix_lens [P], suffix_lens
  * [P*G]; rows_per_kv_group = G * Hq / Hkv, at most 256).  A KV group with more

@@ -132,10 +132,10 @@ _lib.rl_lse_combine.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32
 
 
 RLDA_ROUTE_UNIT = 3
-for _name, _ptr in (("rl_decode_attn_debug_route", _dp), ("rl_decode_attn_paged_debug_route", _pp),
-                    ("rl_decode_attn_tree_debug_route", _tp)):
-    getattr(_lib, _name).restype = ctypes.c_int
-    getattr(_lib, _name).argtypes = [ctypes.c_int32, _ptr]
+for _form, _argtype in (("", _dp), ("_paged", _pp), ("_tree", _tp)):
+    for _name in ("route", "merge"):
+        getattr(_lib, f"rl_decode_attn{_form}_debug_{_name}").restype = ctypes.c_int
+        getattr(_lib, f"rl_decode_attn{_form}_debug_{_name}").argtypes = [ctypes.c_int32, _argtype]
 
 
 def rl_decode_attn_debug_route(desc, compute_units: int = 256) -> int:
@@ -143,6 +143,14 @@ def rl_decode_attn_debug_route(desc, compute_units: int = 256) -> int:
     RLDA_ROUTE_UNIT or a negative code."""
     fn = {rlda_desc: _lib.rl_decode_attn_debug_route, rlda_paged_desc: _lib.rl_decode_attn_paged_debug_route,
           rlda_tree_desc: _lib.rl_decode_attn_tree_debug_route}[type(desc)]
+    return fn(compute_units, ctypes.byref(desc))
+
+
+def rl_decode_attn_debug_merge(desc, compute_units: int = 256) -> int:
+    """How a call with this descriptor that runs on RLDA_ALGO_SHARED merges a row's partials: teams of 32 lanes, 0 for 16 lanes,
+    or a negative code."""
+    fn = {rlda_desc: _lib.rl_decode_attn_debug_merge, rlda_paged_desc: _lib.rl_decode_attn_paged_debug_merge,
+          rlda_tree_desc: _lib.rl_decode_attn_tree_debug_merge}[type(desc)]
     return fn(compute_units, ctypes.byref(desc))
 
 

@@ -308,6 +308,11 @@ int route_of(int rc, const Problem& pb, int planned, int32_t compute_units) {
   if (planned < 0) return planned;
   return compute_units < 1 ? RLDA_ERR_INVALID : (int)route(pb, planned, rlda::pairs_for(compute_units));
 }
+int merge_of(int r, const Problem& pb, int32_t compute_units) {
+  if (r < 0) return r;
+  if (r != RLDA_ALGO_SHARED || rlda::n_sequences(pb) == 0) return RLDA_ERR_UNSUPPORTED;
+  return rlda::shared_merge(pb, rlda::pairs_for(compute_units));
+}
 }  // namespace
 
 int rl_decode_attn_debug_route(int32_t compute_units, const rlda_desc* desc) {
@@ -325,6 +330,22 @@ int rl_decode_attn_tree_debug_route(int32_t compute_units, const rlda_tree_desc*
   const int rc = to_problem(desc, pb);
   const int rt = rc == RLDA_OK ? check_tree(pb) : rc;
   return route_of(rc, pb, rt == RLDA_OK ? (int)RLDA_ALGO_SHARED : rt, compute_units);
+}
+
+int rl_decode_attn_debug_merge(int32_t compute_units, const rlda_desc* desc) {
+  Problem pb;
+  to_problem(desc, pb);
+  return merge_of(rl_decode_attn_debug_route(compute_units, desc), pb, compute_units);
+}
+int rl_decode_attn_paged_debug_merge(int32_t compute_units, const rlda_paged_desc* desc) {
+  Problem pb;
+  to_problem(desc, pb);
+  return merge_of(rl_decode_attn_paged_debug_route(compute_units, desc), pb, compute_units);
+}
+int rl_decode_attn_tree_debug_merge(int32_t compute_units, const rlda_tree_desc* desc) {
+  Problem pb;
+  to_problem(desc, pb);
+  return merge_of(rl_decode_attn_tree_debug_route(compute_units, desc), pb, compute_units);
 }
 
 int32_t rl_decode_attn_debug_pairs(int32_t compute_units) {

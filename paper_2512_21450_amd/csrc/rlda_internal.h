@@ -63,6 +63,9 @@ bool   shared_supported(const Problem& pb);
 size_t shared_workspace_bytes(const Problem& pb);
 // workgroup pairs of the current device: pairs_for its compute-unit count, looked up once per device
 hipError_t device_pairs(int& pairs);
+// how the partials of a non-empty problem are merged on a device with `pairs` workgroup pairs (the first launch, where it takes
+// several): the teams of 32 lanes that share a row, or 0 for 16 lanes a row
+int    shared_merge(const Problem& pb, int pairs);
 // `mid`, if not null, is recorded between the partial kernel and the combine kernel
 hipError_t launch_shared(const Problem& pb, hipStream_t stream, hipEvent_t mid);
 

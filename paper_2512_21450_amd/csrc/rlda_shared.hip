@@ -1678,16 +1678,22 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
 // From 128 prefix units and 4 suffix units a pair on, rows have so few parts that their number counts: 16 lanes each
 // (32 / 16 lanes: 128 x 16 16/2 151 / 140, 128 x 8 16/2 85 / 80, 32 x 8 28/4 112.6 / 111.3; but 40 x 5 20/4 with answers
 // up to 3686 keys, half of them finished, 52 / 57).
-void launch_combine_rows(const SharedParams& P, bool tree, bool ext, int rows, int64_t prefix_units, hipStream_t stream) {
-  const int64_t suffix_units = (int64_t)P.B * P.Hkv;
-  if (!tree && prefix_units >= 128 && suffix_units >= 4 * (int64_t)P.n_cu) {
+// Returns the teams, 0 for 16 lanes; `line_units`: units of the prefix line, `prefix_units`: the same with the halves that two
+// workgroups of a pair compute side by side.
+int merge_form(bool tree, int64_t line_units, int64_t prefix_units, int64_t suffix_units, int n_cu) {
+  if (!tree && prefix_units >= 128 && suffix_units >= 4 * (int64_t)n_cu) return 0;
+  const int64_t parts = n_cu / line_units + 8 * (int64_t)n_cu / suffix_units;
+  return parts >= 700 ? 32 : parts >= 200 ? 16 : parts >= 68 ? 8 : parts >= 28 ? 4 : parts >= 12 ? 2 : 1;
+}
+void launch_combine_rows(const SharedParams& P, bool tree, bool ext, int rows, hipStream_t stream) {
+  if (rows == 0) return;
+  const int64_t line_units = (int64_t)P.P * P.HkvP;
+  const int teams = merge_form(tree, line_units, line_units * P.SM, (int64_t)P.B * P.Hkv, P.n_cu);
+  if (teams == 0) {
     if (ext) hipLaunchKernelGGL(combine16_kernel<true>, dim3((rows + 15) / 16), dim3(256), 0, stream, P);
     else     hipLaunchKernelGGL(combine16_kernel<false>, dim3((rows + 15) / 16), dim3(256), 0, stream, P);
     return;
   }
-  if (rows == 0) return;
-  const int64_t parts = P.n_cu / ((int64_t)P.P * P.HkvP) + 8 * (int64_t)P.n_cu / suffix_units;
-  const int teams = parts >= 700 ? 32 : parts >= 200 ? 16 : parts >= 68 ? 8 : parts >= 28 ? 4 : parts >= 12 ? 2 : 1;
   typedef void (*kern_t)(const SharedParams);
   static const kern_t kerns[3][6] = {
       {combine_kernel<false, false, 1>, combine_kernel<false, false, 2>, combine_kernel<false, false, 4>,
@@ -1787,6 +1793,14 @@ Problem prompt_range(const Problem& ds, int p0, int np) {
 size_t shared_workspace_bytes(const Problem& ds) {
   const int np = max_prompts_per_launch(ds);
   return layout(np < ds.P ? prompt_range(ds, 0, np) : ds).total;
+}
+
+int shared_merge(const Problem& whole, int pairs) {
+  const int np = max_prompts_per_launch(whole);
+  const Problem ds = np < whole.P ? prompt_range(whole, 0, np) : whole;
+  const int R = ds.Hq / ds.Hkv * max_group(ds);
+  const int64_t line_units = n_prefix_entries(ds) * ds.Hkv * line_parts(R, pairs);
+  return merge_form(ds.n_levels > 0, line_units, line_units * side_parts(R, pairs), n_sequences(ds) * ds.Hkv, pairs);
 }
 
 hipError_t device_pairs(int& n) {
@@ -1903,7 +1917,7 @@ hipError_t launch_shared(const Problem& whole, hipStream_t stream, hipEvent_t mi
     if (e != hipSuccess) return e;
   }
   const int rows = P.B * P.Hq;
-  launch_combine_rows(P, tree, ext, rows, (int64_t)ds.P * P.HkvP * P.SM, stream);
+  launch_combine_rows(P, tree, ext, rows, stream);
   return hipGetLastError();
 }
 

@@ -40,6 +40,8 @@ def case(seed, teams, Lp, Ls, lens):
 @pytest.mark.parametrize("teams", TEAMS)
 def test_teams(B, teams, Lp, Ls, lens):
     x, G = case(1, teams, Lp, Ls, lens)
+    P, Hkv = TEAMS[teams][0], TEAMS[teams][2]
+    assert util.merge(B.make_desc(B.RLDA_BF16, P, G, 7 * Hkv, Hkv, 128, Lp, Ls, 0.09, algo=B.RLDA_ALGO_SHARED)) == teams
     out, lse = util.gpu_run(util.to_device(x), 0.09, G, algo=B.RLDA_ALGO_SHARED)
     ro, rl = util.oracle(x, 0.09, G)
     util.compare(out, lse, ro, rl, "bf16", (teams, Lp, Ls, lens))

@@ -384,26 +384,34 @@ def test_around_the_tile_count_where_half_the_workgroup_pairs_take_over(B, tiles
     check(x, 0.09, G, "bf16", "shared", f"{tiles} tiles", B)
 
 
+@pytest.mark.parametrize("G,form", [(8, 0), (2, 1)])
 @pytest.mark.parametrize("paged", [False, True])
-def test_rows_with_many_parts_in_the_16_lane_combine(B, paged):
-    """128 prefix units select the 16-lane combine kernel; one prompt and one sequence hold nearly all
-    keys, so their rows are cut among most workgroups: more parts per row than one request (4) and than
-    one batch of lanes (16) hold, next to rows with a single part and rows with none."""
+def test_rows_with_many_parts_in_the_combine_of_many_units(B, paged, G, form):
+    """128 prefix units and 1024 suffix units select the 16-lane combine kernel, fewer suffix units the one with a team of 32
+    lanes a row; one prompt and one sequence hold nearly all keys, so their rows are cut among most workgroups: more parts per
+    row than one request (4) and than one batch of lanes (16) hold, next to rows with a single part and rows with none."""
     import torch
-    P, G, Hq, Hkv, d = 64, 2, 4, 2, 128
+    from tests.test_partition import partition
+    P, Hq, Hkv, d = 64, 4, 2, 128
     pl = np.full(P, 8, np.int32)
     pl[0], pl[9], pl[63] = 6000, 0, 700
     sl = np.full(P * G, 5, np.int32)
     sl[1], sl[18], sl[19], sl[127] = 4000, 0, 0, 900
+    assert util.merge(B.make_desc(B.RLDA_BF16, P, G, Hq, Hkv, d, 6016, 4000, 0.1)) == form
+    parts = partition(P, G, Hkv, 6016, 4000, pl, sl, R=G * Hq // Hkv)[1]
+    for kind, unit in ((0, 0), (1, 1)):                                  # two batches of 16 lanes and more from either
+        assert (parts[(parts[:, 0] == kind) & (parts[:, 1] == unit)][:, 2] == 0).sum() > 32
     x = util.random_case(77, P, G, Hq, Hkv, d, 6016, 4000, "bf16", plens=pl, slens=sl)
     if not paged:
         check(x, 0.1, G, "bf16", "auto", "many parts", B)
         return
     y = wl.to_pages(x, 64, seed=3)
     t = util.to_device(y)
-    out, lse = util.gpu_run_paged(t, 0.1, G)
+    act = np.ones(P * G, np.uint8)
+    act[[0, 2, P * G - 1]] = 0
+    out, lse = util.gpu_run_paged(t, 0.1, G, active=torch.from_numpy(act).cuda())
     torch.cuda.synchronize()
-    ro, rl = util.oracle_paged(y, 0.1, G)
+    ro, rl = util.oracle_paged(y, 0.1, G, active=act)
     util.compare(out, lse, ro, rl, "bf16", "many parts, paged")
 
 

@@ -1,4 +1,5 @@
-"""Which kernels a call runs on, by the host-side rule alone (no GPU): rl_decode_attn_debug_route."""
+"""Which kernels a call runs on, by the host-side rule alone (no GPU): rl_decode_attn_debug_route, and how its partials are merged:
+rl_decode_attn_debug_merge."""
 import pytest
 
 from paper_2512_21450_amd import binding as B
@@ -89,3 +90,21 @@ def test_units_of_hardly_any_key_in_large_numbers_stay_on_the_shared_path():
         assert B.rl_decode_attn_debug_route(desc(P=units // 8, G=1, Hq=8, Hkv=8, Lp=1, Ls=1)) == want
     for units, want in ((8192, UNIT), (16384 + 8, SHARED)):
         assert B.rl_decode_attn_debug_route(tree(units)) == want
+
+
+def test_how_the_partials_are_merged():
+    """Teams by the parts that the unit counts give (256 / (P Hkv) + 2048 / (P G Hkv) on 256 pairs, a group of up to 64 rows), 16
+    lanes from 128 prefix and 1024 suffix units on."""
+    form = lambda P, G, Hkv, r=7, cus=256, **kw: B.rl_decode_attn_debug_merge(desc(P=P, G=G, Hq=r * Hkv, Hkv=Hkv, algo=SHARED, **kw), cus)
+    assert [form(*u) for u in ((1, 1, 1), (1, 8, 1), (2, 4, 4), (4, 8, 4), (8, 8, 4), (16, 8, 4), (32, 8, 4))] == [32, 16, 8, 4, 2, 1, 0]
+    assert form(64, 2, 2) == form(64, 7, 2) == form(63, 9, 2) == 1 and form(64, 8, 2) == 0
+    assert form(64, 17, 1, 5) == 0 and form(63, 17, 1, 5) == 1              # two row halves a group: twice the prefix units
+    assert form(64, 7, 2, cus=128) == 0                                      # follows the device
+    tree = lambda n, Hkv, g: B.make_tree_desc(B.RLDA_BF16, n, 7 * Hkv, Hkv, 128, 4096, 0.1, [(None, None, None, g, 5000)])
+    assert [B.rl_decode_attn_debug_merge(tree(*a)) for a in ((256, 8, 8), (32, 4, 8), (8, 1, 8))] == [1, 4, 16]
+    assert B.rl_decode_attn_debug_merge(desc()) == B.RLDA_ERR_UNSUPPORTED    # one launch: nothing to merge
+    assert B.rl_decode_attn_debug_merge(desc(P=0, algo=SHARED)) == B.RLDA_ERR_UNSUPPORTED
+    assert B.rl_decode_attn_debug_merge(desc(d=64, algo=SHARED)) == B.RLDA_ERR_UNSUPPORTED
+    assert B.rl_decode_attn_debug_merge(desc(algo=SHARED), 0) == B.RLDA_ERR_INVALID
+    paged = B.make_paged_desc(B.RLDA_BF16, 32, 8, 28, 4, 128, 1280, 64, 40, 1000, 0.1, block_table=1 << 20)
+    assert B.rl_decode_attn_debug_merge(paged) == 0

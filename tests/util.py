@@ -42,6 +42,13 @@ def route(ds):
     return binding.rl_decode_attn_debug_route(ds, torch.cuda.get_device_properties(0).multi_processor_count)
 
 
+def merge(ds):
+    """How a call with this descriptor merges a row's partials on the GPU at hand: teams of 32 lanes, 0 for 16 lanes."""
+    import torch
+    from paper_2512_21450_amd import binding
+    return binding.rl_decode_attn_debug_merge(ds, torch.cuda.get_device_properties(0).multi_processor_count)
+
+
 def compare(out, lse, ref_out, ref_lse, dtype, what=""):
     """Element-by-element against the fp64 oracle; -inf must match exactly."""
     tol_o, tol_l = TOL[dtype]
