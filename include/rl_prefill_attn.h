@@ -57,6 +57,13 @@ typedef struct {
  */
 int rl_prefill_attn(const rl_prefill_desc* desc, void* hip_stream);
 
+/*
+ * Testing hook, pure host code: the kernel a call with this descriptor runs on, on a device with `compute_units` compute
+ * units (256: a whole MI355X): 1 (64 query rows to a workgroup), 2 (128), 3 (64, shared by two teams of wavefronts), 0 (the
+ * kernel for scales that are not positive), or the negative code of the call.
+ */
+int rl_prefill_attn_debug_form(int32_t compute_units, const rl_prefill_desc* desc);
+
 #ifdef __cplusplus
 }
 #endif

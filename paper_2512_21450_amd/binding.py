@@ -833,6 +833,8 @@ class rl_prefill_desc(ctypes.Structure):
 _PREFILL_DESC_BYTES = ctypes.sizeof(rl_prefill_desc)
 _lib.rl_prefill_attn.restype = ctypes.c_int
 _lib.rl_prefill_attn.argtypes = [ctypes.POINTER(rl_prefill_desc), ctypes.c_void_p]
+_lib.rl_prefill_attn_debug_form.restype = ctypes.c_int
+_lib.rl_prefill_attn_debug_form.argtypes = [ctypes.c_int32, ctypes.POINTER(rl_prefill_desc)]
 
 
 def make_prefill_desc(dtype, P, Hq, Hkv, d, Lp_cap, scale, **ptrs) -> rl_prefill_desc:
@@ -846,6 +848,11 @@ def make_prefill_desc(dtype, P, Hq, Hkv, d, Lp_cap, scale, **ptrs) -> rl_prefill
 
 def rl_prefill_attn_raw(desc: rl_prefill_desc, stream_handle=None) -> int:
     return _lib.rl_prefill_attn(ctypes.byref(desc), stream_handle)
+
+
+def rl_prefill_attn_debug_form(desc: rl_prefill_desc, compute_units: int = 256) -> int:
+    """The kernel a call with this descriptor runs on: 0 general, 1 64 rows a workgroup, 2 128, 3 two teams; or a negative code."""
+    return _lib.rl_prefill_attn_debug_form(compute_units, ctypes.byref(desc))
 
 
 def prefill_desc_from_tensors(q, k, v, lens, scale, out, lse=None) -> rl_prefill_desc:

@@ -458,7 +458,7 @@ int64_t rl_decode_attn_debug_partition_on(int32_t compute_units, int32_t P, int3
 
 }  // extern "C"
 
-extern "C" int rl_prefill_attn(const rl_prefill_desc* d, void* hip_stream) {
+static int check_prefill(const rl_prefill_desc* d) {
   if (!d) return RLDA_ERR_INVALID;
   if (d->struct_size != sizeof(rl_prefill_desc)) return RLDA_ERR_STRUCT_SIZE;
   if (d->P < 0 || d->Hq <= 0 || d->Hkv <= 0 || d->d <= 0 || d->Lp_cap < 0) return RLDA_ERR_INVALID;
@@ -467,11 +467,24 @@ extern "C" int rl_prefill_attn(const rl_prefill_desc* d, void* hip_stream) {
   if ((int64_t)((d->Lp_cap + qb - 1) / qb) * ((int64_t)d->P * d->Hkv + 7) > 0x7fffffffLL) return RLDA_ERR_UNSUPPORTED;
   if ((int64_t)d->Lp_cap * d->Hq * 256 >= (int64_t)1 << 40) return RLDA_ERR_UNSUPPORTED;
   if (d->Lp_cap >= 1 << 24) return RLDA_ERR_UNSUPPORTED;    // byte offsets inside one (prompt, KV head) store are 32-bit
+  return RLDA_OK;
+}
+
+extern "C" int rl_prefill_attn(const rl_prefill_desc* d, void* hip_stream) {
+  const int rc = check_prefill(d);
+  if (rc != RLDA_OK) return rc;
   if (d->P == 0 || d->Lp_cap == 0) return RLDA_OK;
   if (!d->q || !d->k || !d->v || !d->lens || !d->out) return RLDA_ERR_INVALID;
   const hipError_t e = rlda::launch_prefill(d->q, d->k, d->v, d->lens, d->out, d->lse, d->P, d->Hq, d->Hkv, d->Lp_cap,
                                             d->scale, static_cast<hipStream_t>(hip_stream));
   g_last_hip_error = e;
   return e == hipSuccess ? RLDA_OK : RLDA_ERR_LAUNCH;
+}
+
+extern "C" int rl_prefill_attn_debug_form(int32_t compute_units, const rl_prefill_desc* d) {
+  const int rc = check_prefill(d);
+  if (rc != RLDA_OK) return rc;
+  if (compute_units < 1) return RLDA_ERR_INVALID;
+  return rlda::prefill_form(d->P, d->Hkv, d->Hq / d->Hkv, d->Lp_cap, d->scale, rlda::pairs_for(compute_units));
 }
 

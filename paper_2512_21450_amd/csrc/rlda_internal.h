@@ -80,6 +80,10 @@ hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t str
 
 // ---- causal prefill attention over each prompt (bf16, d = 128, Hq/Hkv <= 16)
 bool prefill_supported(int dtype, int Hq, int Hkv, int d);
+// the kernel a prefill of P prompts runs on, r = Hq/Hkv: the general one (scales that are not positive), 64 or 128 rows to a
+// workgroup of four wavefronts, or 64 rows to two teams of four
+enum PrefillForm { PREFILL_GENERAL = 0, PREFILL_64 = 1, PREFILL_128 = 2, PREFILL_TEAMS = 3 };
+PrefillForm prefill_form(int P, int Hkv, int r, int Lp_cap, float scale, int pairs);
 hipError_t launch_prefill(const void* q, const void* k, const void* v, const int32_t* lens, float* out, float* lse,
                           int P, int Hq, int Hkv, int Lp_cap, float scale, hipStream_t stream);
 

@@ -1925,13 +1925,8 @@ bool prefill_supported(int dtype, int Hq, int Hkv, int d) {
   return dtype == RLDA_BF16 && d == D && Hkv > 0 && Hq % Hkv == 0 && Hq / Hkv <= 16;
 }
 
-hipError_t launch_prefill(const void* q, const void* k, const void* v, const int32_t* lens, float* out, float* lse,
-                          int P_, int Hq, int Hkv, int Lp_cap, float scale, hipStream_t stream) {
-  PrefillParams P;
-  P.q = static_cast<const char*>(q); P.k = static_cast<const char*>(k); P.v = static_cast<const char*>(v);
-  P.lens = lens; P.out = out; P.lse = lse;
-  P.P = P_; P.Hq = Hq; P.Hkv = Hkv; P.r = Hq / Hkv; P.Lp_cap = Lp_cap;
-  P.c = scale * 1.4426950408889634f;
+PrefillForm prefill_form(int P, int Hkv, int r, int Lp_cap, float scale, int pairs) {
+  if (!(scale > 0.f)) return PREFILL_GENERAL;
   // Two 16-row blocks per wavefront (128 rows per workgroup) amortise every LDS read, barrier and tile over
   // twice the matrix work, but halve the workgroups and are longer to start and end.  They need a full round of
   // workgroups, two per compute unit (below: 1 x 4000 tokens of 16/2 heads, 500 workgroups, 90 us with one block,
@@ -1946,14 +1941,8 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   // 92 / 74, 42.4 / 41.8.  Both bodies in one kernel that chose by the lengths cost every call 1 to 3 us.  (All before rows
   // were stored whole and past the caches, which took 2 to 15 % off either side.)
   const int rows1 = 16 * WG_WAVES;
-  const int64_t units8 = (int64_t)8 * ceil_div(P_ * Hkv, 8);              // eight XCDs, whole rounds of units
-  const int64_t wgs = (int64_t)P_ * Hkv * ceil_div(Lp_cap, (2 * rows1) / P.r);
-  const bool two = scale > 0.f && (wgs >= 4 * N_WG || (wgs >= N_WG && wgs * Lp_cap >= 600 * 1024));
-  P.QB = ((two ? 2 : 1) * rows1) / P.r;                     // query positions per workgroup
-  P.nqb = ceil_div(Lp_cap, P.QB);
-  P.spread = prefill_spread(P_ * Hkv);
-  P.div_Hkv = make_fastdiv(Hkv); P.div_r = make_fastdiv(P.r); P.div_nqb = make_fastdiv(P.nqb); P.div_units = make_fastdiv(P_ * Hkv);
-  typedef void (*kern_t)(const PrefillParams);
+  const int64_t units = (int64_t)P * Hkv, wgs = units * ceil_div(Lp_cap, (2 * rows1) / r);
+  if (wgs >= 4 * N_WG || (wgs >= N_WG && wgs * Lp_cap >= 600 * 1024)) return PREFILL_128;
   // Workgroups that all find a place at once end with the longest one's chain of tiles; where it is long, two teams of four
   // wavefronts share its tiles, at one workgroup per compute unit.  So the buffers have to be long, and the more so the more
   // of the workgroups wait for a place.  Measured, us with one team, and how many times as fast with two where all prompts fill
@@ -1969,14 +1958,32 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   //   2 x 3000 of  8/2 (752) 54.0   .82 / .92 / 1.22 / 1.18    4 x 4096 of  2/2 (512) 65.5  1.18 / 1.29 / 1.20 / 1.10
   // The host knows capacities only: in buffers a quarter full and less, 2 to 9 % (0.2 to 0.7 us) go to workgroups of eight
   // wavefronts that have work for four or none.
+  const int64_t sixths = Lp_cap >= 1280 ? 12 : Lp_cap >= 1024 ? 10 : Lp_cap >= 896 ? 9 : 8;     // of a block a compute unit
+  return Lp_cap >= 640 && 6 * units * ceil_div(Lp_cap, rows1 / r) <= sixths * pairs ? PREFILL_TEAMS : PREFILL_64;
+}
+
+hipError_t launch_prefill(const void* q, const void* k, const void* v, const int32_t* lens, float* out, float* lse,
+                          int P_, int Hq, int Hkv, int Lp_cap, float scale, hipStream_t stream) {
+  PrefillParams P;
+  P.q = static_cast<const char*>(q); P.k = static_cast<const char*>(k); P.v = static_cast<const char*>(v);
+  P.lens = lens; P.out = out; P.lse = lse;
+  P.P = P_; P.Hq = Hq; P.Hkv = Hkv; P.r = Hq / Hkv; P.Lp_cap = Lp_cap;
+  P.c = scale * 1.4426950408889634f;
   int pairs = 0;
   {
     const hipError_t e = device_pairs(pairs);
     if (e != hipSuccess) return e;
   }
-  const int64_t sixths = Lp_cap >= 1280 ? 12 : Lp_cap >= 1024 ? 10 : Lp_cap >= 896 ? 9 : 8;     // of a block a compute unit
-  const bool teams = !two && scale > 0.f && Lp_cap >= 640 && 6 * (int64_t)P_ * Hkv * P.nqb <= sixths * pairs;
-  const kern_t kern = two ? prefill2_kernel<2, 1> : (teams ? prefill2_kernel<1, 2> : (scale > 0.f ? prefill2_kernel<1, 1> : prefill_kernel<1>));
+  const PrefillForm form = prefill_form(P_, Hkv, P.r, Lp_cap, scale, pairs);
+  const bool teams = form == PREFILL_TEAMS;
+  const int64_t units8 = (int64_t)8 * ceil_div(P_ * Hkv, 8);              // eight XCDs, whole rounds of units
+  P.QB = (form == PREFILL_128 ? 2 : 1) * 16 * WG_WAVES / P.r;             // query positions per workgroup
+  P.nqb = ceil_div(Lp_cap, P.QB);
+  P.spread = prefill_spread(P_ * Hkv);
+  P.div_Hkv = make_fastdiv(Hkv); P.div_r = make_fastdiv(P.r); P.div_nqb = make_fastdiv(P.nqb); P.div_units = make_fastdiv(P_ * Hkv);
+  typedef void (*kern_t)(const PrefillParams);
+  const kern_t kern = form == PREFILL_128 ? prefill2_kernel<2, 1> : form == PREFILL_TEAMS ? prefill2_kernel<1, 2>
+                    : form == PREFILL_64 ? prefill2_kernel<1, 1> : prefill_kernel<1>;
   {
     static std::mutex mu;
     static bool done[64] = {};

@@ -1,5 +1,5 @@
-"""Which kernels a call runs on, by the host-side rule alone (no GPU): rl_decode_attn_debug_route, and how its partials are merged:
-rl_decode_attn_debug_merge."""
+"""Which kernels a call runs on, by the host-side rule alone (no GPU): rl_decode_attn_debug_route, how its partials are merged:
+rl_decode_attn_debug_merge, and the kernel of a prefill: rl_prefill_attn_debug_form."""
 import pytest
 
 from paper_2512_21450_amd import binding as B
@@ -108,3 +108,19 @@ def test_how_the_partials_are_merged():
     assert B.rl_decode_attn_debug_merge(desc(algo=SHARED), 0) == B.RLDA_ERR_INVALID
     paged = B.make_paged_desc(B.RLDA_BF16, 32, 8, 28, 4, 128, 1280, 64, 40, 1000, 0.1, block_table=1 << 20)
     assert B.rl_decode_attn_debug_merge(paged) == 0
+
+
+def test_which_kernel_a_prefill_runs_on():
+    form = lambda P, Hq, Hkv, cap, cus=256, scale=0.1, **kw: B.rl_prefill_attn_debug_form(
+        B.make_prefill_desc(kw.get("dtype", B.RLDA_BF16), P, Hq, Hkv, 128, cap, scale), cus)
+    assert form(32, 28, 4, 1280) == 2 and form(8, 16, 2, 452) == 1                # many and few blocks of 128 rows
+    assert form(8, 16, 2, 452, scale=0.0) == form(1, 8, 2, 2048, scale=-1.0) == 0
+    # two teams from 640 rows of capacity on, and up to 8, 9, 10 and 12 blocks to six compute units from 640, 896, 1024, 1280
+    assert form(1, 8, 2, 639) == 1 and form(1, 8, 2, 640) == 3
+    for P, cap, want in ((4, 680, 3), (4, 688, 1), (3, 888, 3), (3, 896, 3), (3, 1016, 3), (3, 1024, 3), (3, 1136, 3), (3, 1144, 1),
+                         (3, 1272, 1), (3, 1280, 3), (3, 1360, 3), (3, 1368, 1), (2, 2048, 3), (2, 2056, 1)):
+        assert form(P, 8, 1, cap) == want, (P, cap)
+    # what a full buffer loses by teams: 3 x 640 tokens of 16/4 heads 14.5 -> 16.9 us, 8 x 1024 of 4/1 20.0 -> 21.0
+    assert form(3, 16, 4, 640) == form(8, 4, 1, 1024) == form(5, 7, 1, 640) == 1
+    assert form(4, 8, 1, 344) == 1 and form(1, 8, 2, 2048, cus=128) == 3 and form(1, 8, 2, 2056, cus=128) == 1
+    assert form(1, 8, 2, 640, cus=0) == B.RLDA_ERR_INVALID and form(1, 8, 2, 640, dtype=B.RLDA_F32) == B.RLDA_ERR_UNSUPPORTED
