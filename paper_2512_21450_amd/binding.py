@@ -212,9 +212,18 @@ def rl_decode_attn_static_workspace_limit() -> int:
     return _lib.rl_decode_attn_static_workspace_limit()
 
 
+# the handle of torch's current stream without the stream object around it (1 us less per call); no public name, so that a
+# torch without it takes the long way
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream, like) -> int:
     """The stream a call is enqueued on: the caller's, or torch's current one on the device of tensor `like`."""
-    return stream.cuda_stream if stream is not None else torch._C._cuda_getCurrentRawStream(like.device.index)
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is not None:
+        return _current_raw_stream(like.device.index)
+    return torch.cuda.current_stream(like.device).cuda_stream
 
 
 def _ptr(t):
@@ -506,9 +515,8 @@ def rl_lse_combine(o_parts, lse_parts, out=None, lse=None, stream=None):
         out = torch.empty((n_rows, d), dtype=torch.float32, device=o_parts.device)
     if lse is None:
         lse = torch.empty((n_rows,), dtype=torch.float32, device=o_parts.device)
-    s = stream if stream is not None else torch.cuda.current_stream(o_parts.device)
     rc = _lib.rl_lse_combine(o_parts.data_ptr(), lse_parts.data_ptr(), n_parts, n_rows, d,
-                             out.data_ptr(), lse.data_ptr(), ctypes.c_void_p(s.cuda_stream))
+                             out.data_ptr(), lse.data_ptr(), _stream_handle(stream, o_parts))
     if rc != RLDA_OK:
         raise RldaError(rc)
     return out, lse
