@@ -170,17 +170,16 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
   long long n_tok, n_seq;
   if (COUNT) {
     __shared__ long long sh[2][NT / 64];
+    static_assert(COUNT_MAX % NT == 0, "a thread's sequences");
+    constexpr int U = COUNT_MAX / NT;                     // all of them, asked for at once
     long long a = 0;
-    int c = 0;
-    for (int b0 = tid; b0 < L.B; b0 += 16 * NT) {
-      int n[16];
+    int c = 0, n[U];
 #pragma unroll
-      for (int k = 0; k < 16; ++k) n[k] = b0 + k * NT < L.B ? L.lens[b0 + k * NT] : 0;
+    for (int k = 0; k < U; ++k) n[k] = tid + k * NT < L.B ? L.lens[tid + k * NT] : 0;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const int m = clamp_len(n[k], L.T);
-        a += m; c += m > 0;
-      }
+    for (int k = 0; k < U; ++k) {
+      const int m = clamp_len(n[k], L.T);
+      a += m; c += m > 0;
     }
     a = wave_sum(a); c = wave_sum(c);
     if ((tid & 63) == 0) { sh[0][tid >> 6] = a; sh[1][tid >> 6] = c; }
