@@ -191,15 +191,16 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
     n_tok = L.counts[0]; n_seq = L.counts[1];
   }
   const int b = blockIdx.x;
-  const int len = clamp_len(L.lens[b], L.T);
+  const unsigned len = clamp_len(L.lens[b], L.T);
   float w = 0.f;                                          // weight of one of this sequence's tokens in the aggregate
   if (len > 0) w = L.agg == RL_AGG_SEQ_MEAN ? (float)(1.0 / ((double)len * (double)n_seq)) : (float)(1.0 / (double)n_tok);
   const float A = L.adv[b];
   const size_t row = (size_t)b * L.stride;
   float sums[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int t = 4 * tid; t < L.T; t += 4 * NT) {
+  const unsigned T = L.T;                                 // unsigned: the last step of a row of nearly 2^31 tokens ends behind them
+  for (unsigned t = 4 * tid; t < T; t += 4 * NT) {
     f32x4 g = {0.f, 0.f, 0.f, 0.f};
-    if (t + 4 <= L.T) {                                   // the four tokens exist as memory; some may be padding
+    if (t + 4 <= T) {                                     // the four tokens exist as memory; some may be padding
       if (t < len) {
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         const f32x4 lp = *reinterpret_cast<const f32x4u*>(L.lp + row + t), old = *reinterpret_cast<const f32x4u*>(L.old + row + t);
@@ -211,7 +212,7 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
       }
       if (L.grad) *reinterpret_cast<f32x4u*>(L.grad + row + t) = g;
     } else {
-      for (int k = t; k < L.T; ++k) {
+      for (unsigned k = t; k < T; ++k) {
         float gk = 0.f;
         if (k < len)
           gk = token_term(L, L.lp[row + k], L.old[row + k], L.kl ? L.kl[row + k] : 0.f, L.ent ? L.ent[row + k] : 0.f, A, w, sums);

@@ -39,3 +39,18 @@ def test_rows_of_every_remainder(B, T, n):  # noqa: F811
     assert B.rl_policy_loss_raw(ds, torch.cuda.current_stream().cuda_stream) == 0
     torch.cuda.synchronize()
     assert torch.equal(grad, one[1]) and torch.equal(stats, one[0])
+
+
+@pytest.mark.parametrize("T", [2**31 - 1, 2**31 - 4])
+def test_the_longest_rows(B, T):  # noqa: F811
+    """Rows whose last step of 1024 tokens ends behind 2^31: eight tokens and padding, the gradient zero to the last column."""
+    import torch
+    lp, grad = torch.zeros((1, T), device="cuda"), torch.full((1, T), 7.0, device="cuda")
+    old = lp.clone()
+    stats, adv, lens = torch.empty(8, device="cuda"), torch.ones(1, device="cuda"), torch.full((1,), 8, dtype=torch.int32, device="cuda")
+    ds = B.policy_loss_desc_from_tensors(lp, old, adv, lens, 0.2, 0.28, stats, grad=grad)
+    ws = torch.empty(B.rl_policy_loss_workspace_bytes(ds), dtype=torch.uint8, device="cuda")
+    ds.workspace, ds.workspace_bytes = ws.data_ptr(), ws.numel()
+    assert B.rl_policy_loss_raw(ds, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert stats[7].item() == 8 and (grad[0, :8] == -0.125).all() and torch.count_nonzero(grad).item() == 8
