@@ -20,7 +20,7 @@ def test_rows_of_every_remainder(B, T, n):  # noqa: F811
         x["lens"][:8] = [0, 1, T - 1, max(T - 2, 0), max(T - 3, 0), max(T - 4, 0), T, 0]
     adv = np.random.default_rng(n).standard_normal(n).astype(np.float32)
     check_loss(B, x, adv, 0.2, 0.28, beta_kl=0.04, beta_ent=0.01, agg=n & 1)
-    # the same rows one element into rows of T + 3, as views: the same bits
+    # the same rows one element into rows of T + 3, as views: the same bits, and what lies around the gradient's rows stays
     def view(a):
         wide = torch.full((n, T + 3), float("nan"), device="cuda")
         wide[:, 1:T + 1] = dev(a)
@@ -30,6 +30,7 @@ def test_rows_of_every_remainder(B, T, n):  # noqa: F811
                            dev(x["entropy"]), 0.04, 0.01)
     lp, old, kl, ent = (view(x[k]) for k in names)
     grad = view(x["kl"])
+    around = grad._base
     stats = torch.empty(8, device="cuda")
     ds = B.policy_loss_desc_from_tensors(lp, old, dev(adv), dev(x["lens"]), 0.2, 0.28, stats, kl, ent, grad, 0.04, 0.01)
     ws = torch.empty(B.rl_policy_loss_workspace_bytes(ds), dtype=torch.uint8, device="cuda")
@@ -39,6 +40,7 @@ def test_rows_of_every_remainder(B, T, n):  # noqa: F811
     assert B.rl_policy_loss_raw(ds, torch.cuda.current_stream().cuda_stream) == 0
     torch.cuda.synchronize()
     assert torch.equal(grad, one[1]) and torch.equal(stats, one[0])
+    assert around.shape == (n, T + 3) and around[:, 0].isnan().all() and around[:, T + 1:].isnan().all()
 
 
 @pytest.mark.parametrize("T", [2**31 - 1, 2**31 - 4])
