@@ -732,12 +732,13 @@ __device__ __forceinline__ void suffix_stream(const SharedParams& P, char* wlds,
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
   }
   bool fresh = true;
-  // Where the next tile is (its sequence's length, its page): in a short run, asked for while the present tile is on its way,
-  // which hides what a wavefront would wait for; in a long one of 16-bit tiles, which the read rate bounds, after it has landed.
-  // us, every run before the wait / after it / by this rule: 16 prompts x 8 of 28/4 heads on pages of 64, a quarter finished 45.5 /
+  // Where the next tile is (its sequence's length, its page): asked for while the present tile is on its way, which hides what a
+  // wavefront would wait for; but in a long run over pages of 16-bit rows, which the read rate bounds, after it has landed.
+  // us, before the wait / after it / long runs after it: 16 prompts x 8 of 28/4 heads on pages of 64, a quarter finished 45.5 /
   // 45.9 / 45.4, 49 x 8 of 16/8 on 32 59.7 / 60.7 / 60.3, e4m3 47 x 8 of 56/8 on 128 76.0 / 77.1 / 76.2; and 32 x 8 of 28/4 on 64
-  // 119.1 / 118.4 / 118.7, 64 x 8 of 16/2 with 3000 own keys on 128 157.6 / 155.3 / 155.6, 24 x 16 of 16/4 with 4096 296 / 293 / 291.
-  const bool ahead = F8 || n <= 8;
+  // 119.1 / 118.4 / 118.7, 64 x 8 of 16/2 with 3000 own keys on 128 157.6 / 155.3 / 155.6 (without pages 142.4 / 144.1 / 143.6),
+  // 24 x 16 of 16/4 with 4096 296 / 293 / 291 (278.6 / 279.9).
+  const bool ahead = F8 || !EXT || !P.table || n <= 8;
   for (int i = 0; i < n; ++i) {
     Cur nxt = cur;
     const bool has_next = i + 1 < n;
