@@ -12,8 +12,9 @@
 // are numbered segment by segment (shared levels, then the own suffix), so the order of additions depends on the
 // lengths and NW only.
 //
-// What bounds it: the round trips before the first product, and the 64 bytes a clock that a compute unit loads (8 tiles of
-// 128 bf16 columns: 1 us).  A wavefront has the next tile on the way in registers while it computes on the present one,
+// What bounds it: the round trips before the first product, and the 30 or so bytes a clock that a compute unit takes in (32
+// to 128 units grow by 1.7 us per 8 tiles of 128 bf16 columns, 128 KB, and by 0.95 per 8 of 64; the units that return loaded
+// data are busy one cycle per 31 bytes).  A wavefront has the next tile on the way in registers while it computes on the present one,
 // which goes through its private part of LDS.  (K straight into the registers of the matrix operand, 16 rows to an
 // instruction, saved that trip but took the address unit four times as long as whole rows do: 1.05 us per 64 KB and
 // compute unit.)  So the start is what counts for units of few tiles: the lengths are asked for first, then q and, where
@@ -22,7 +23,7 @@
 // well gained 0.2 us more and cost those 1.0-1.7); the second tile is asked for before the first has landed; the place in
 // the grid is found without divisions.  From the second tile on the next K and the next V are asked for apart, each as soon
 // as its registers are free: both at once, after both had landed, cost units of many tiles up to 1.5 us of 16.  A finished
-// sequence's flag is looked at before anything of it is asked for (no measurable cost: 8 units of live sequences 5.43 / 5.38).
+// sequence's flag is looked at before anything of it is asked for (no measurable cost: 16 units of live sequences 5.43 / 5.38).
 // Calls captured back to back, without all of this / so, us: 64 units x 256 keys, bf16, 64 columns 5.38 / 4.48, 128 columns
 // 6.5 / 5.8, fp32 of 64 8.4 / 7.6; x 512 keys 6.4 / 5.4, 8.7 / 7.5, 11.9 / 11.2; e4m3 of 128 columns x 512 keys 8.3 / 7.3; 448
 // units of up to 1864 keys, e4m3, 64 columns 20.2 / 18.4; 512 units of 452 and up to 1024 keys, bf16, 64 columns 19.1 / 18.0, on
@@ -209,11 +210,12 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   char* const vst = kst + L_::TILE;
   const int lrow = lane / L_::CPR, chunk = lane % L_::CPR;
   u32x4 kr[L_::NL], vr[L_::NL];
-  auto load = [&](const Tile& x, const char* base, u32x4 (&r)[L_::NL]) {     // every instruction takes whole rows
+  // (inlined always: called, the registers of a tile whose rows are looked up would lie in scratch memory)
+  auto load = [&](const Tile& x, const char* base, u32x4 (&r)[L_::NL]) __attribute__((always_inline)) {   // every instruction takes whole rows
 #pragma unroll
     for (int i = 0; i < L_::NL; ++i) r[i] = *reinterpret_cast<const u32x4*>(row_at(x, base, L_::RPI * i + lrow, 16 * chunk));
   };
-  auto store = [&](char* st, const u32x4 (&r)[L_::NL], auto swz) {
+  auto store = [&](char* st, const u32x4 (&r)[L_::NL], auto swz) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < L_::NL; ++i) {
       const int row = L_::RPI * i + lrow;
