@@ -212,8 +212,8 @@ def rl_decode_attn_static_workspace_limit() -> int:
     return _lib.rl_decode_attn_static_workspace_limit()
 
 
-# the handle of torch's current stream without the stream object around it (1 us less per call); no public name, so that a
-# torch without it takes the long way
+# the handle of torch's current stream without the stream object around it (0.2 us against 2.0); no public name, so a torch
+# without it takes the long way
 _current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 

@@ -153,7 +153,7 @@ __device__ __forceinline__ float token_term(const LossParams& L, float lp, float
 // Token pass, one workgroup per sequence.  COUNT: every workgroup adds up all lengths itself before its first token, which
 // saves the launch of policy_count_kernel in front of it (1.5 us on the device and one of the host's).  That reads 4 bytes per
 // pair of sequences, so it pays up to COUNT_MAX of them only; one launch / two, advantages and loss together, captured, us:
-// 64 sequences 12.8 / 14.4, 512 13.5 / 15.0, 1024 15.6 / 17.1, 2048 19.3 / 19.7, 4096 27.1 / 24.2, 8192 48.4 / 33.7.
+// 8 sequences 10.9 / 13.2, 128 11.5 / 13.6, 1024 14.0 / 16.4; 2048 19.3 / 19.7, 4096 27.1 / 24.2, 8192 48.4 / 33.7.
 // (Workgroups that stay and take several sequences in turn read less, but longer ones hold them up: 4096 x 4096 tokens
 // 51 us against 48.)  Four tokens per thread and step: one 16-byte load per array, which the hardware wants aligned to 4
 // bytes only, so rows of any length take it (8192 x 999 tokens 35.2 -> 33.7 us, one by one before), and single elements at a

@@ -853,8 +853,8 @@ __global__ void __launch_bounds__(NTHREADS, 2) partial_kernel(const SharedParams
 // place at a time, 32 in parallel, and the places that hold one are packed in line order: lane k of the row receives
 // the k-th partial as 2 * (row index in its partial array) + [suffix], up to 32 per batch.  Every lane walking all of
 // them in turn took, of whole calls on 128-column bf16 heads: 1 x 8 sequences, 1 KV head, 1344 + 0..4096 keys 202 us
-// (35 side by side, 14.5 with
-// the teams of launch_combine_rows), 4 x 8 with 2 KV heads 60 us (36), 16 prompts x 8 of the 7B shape 42 us (40).
+// (35 side by side, 14.5 with the teams of merge_form), 4 x 8 with 2 KV heads 60 us (36), 16 prompts x 8 of the 7B
+// shape 42 us (40).
 template <bool TREE>
 struct RowParts {
   static constexpr int W = 32, NL = TREE ? MAX_LEVELS : 1;
@@ -906,7 +906,9 @@ struct RowParts {
 // weights with two 32-lane reductions; then every lane accumulates its 4 columns.  Parts are taken in line order, and the
 // teams meet in LDS in that order, so the sum has one fixed order.  The partials are read and the rows written past the
 // caches: each is touched once, and what the read of the partials and the outputs displace is what other rows still need
-// (2048 x 16 rows: 152.7 us per call before, 145 with the stores so, 140 with the loads as well; others 0 to 0.5 us).
+// (2048 x 16 rows: 152.7 us per call before, 145 with the stores so, 140 with the loads as well; others 0 to 0.5 us).  What
+// reads the rows next finds fewer of them in a cache: with a conversion to bf16 behind the call 159.0 us before, 155.7 with
+// the loads so, 154.3 with both.
 template <bool EXT, bool TREE, int TEAMS>
 __global__ void __launch_bounds__(TEAMS > 8 ? 32 * TEAMS : 256) combine_kernel(const SharedParams P) {
   const int team = (threadIdx.x >> 5) & (TEAMS - 1), rows = P.B * P.Hq;
@@ -1641,7 +1643,9 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
   // together, and what lies in the L2s as dirty lines has to leave them before the launch can end.  Rows of 64-byte pieces
   // from the accumulators / whole rows / whole rows past the caches, us: 8 ragged prompts up to 452 tokens of 16/2 heads
   // 15.9 / 15.9 / 14.2, 15 up to 635 of 14/2 27.3 / 26.8 / 24.6, 5 x 4083 of 8/4 183 / 183 / 173, 32 x 1280 of 28/4
-  // 487 / 493 / 487 (pieces past the caches 501).
+  // 487 / 493 / 487 (pieces past the caches 501).  With a conversion of the rows to bf16 behind the call, which finds fewer of
+  // them in a cache: 22.4 / 21.5 / 21.3, 46.4 / 44.4 / 45.6, 32 x 600 of 16/8 136.5 / 131.7 / 133.8, 16 up to 1344 of 28/4
+  // 221 / 217 / 211, 32 x 1280 of 28/4 629 / 624 / 607.
   char* const rows = lds + wv * STAGE_B;
 #pragma unroll
   for (int nt = 0; nt < NTP; ++nt) {

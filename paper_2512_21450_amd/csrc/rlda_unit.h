@@ -13,8 +13,7 @@
 // lengths and NW only.
 //
 // What bounds it: the round trips before the first product, and the 30 or so bytes a clock that a compute unit takes in (32
-// to 128 units grow by 1.7 us per 8 tiles of 128 bf16 columns, 128 KB, and by 0.95 per 8 of 64; the units that return loaded
-// data are busy one cycle per 31 bytes).  A wavefront has the next tile on the way in registers while it computes on the present one,
+// to 128 units grow by 1.7 us per 8 tiles of 128 bf16 columns, 128 KB, and by 0.95 per 8 of 64).  A wavefront has the next tile on the way in registers while it computes on the present one,
 // which goes through its private part of LDS.  (K straight into the registers of the matrix operand, 16 rows to an
 // instruction, saved that trip but took the address unit four times as long as whole rows do: 1.05 us per 64 KB and
 // compute unit.)  So the start is what counts for units of few tiles: the lengths are asked for first, then q and, where

@@ -76,7 +76,7 @@ def test_policy_loss_edge_cases(B):
     import torch
     x = wl.make_rollout_tokens(5, 33, 5, seed=3, lens=("uniform", 33))
     adv = np.array([1.0, -1.0, 0.0, 2.5, -0.5], np.float32)
-    # lengths outside [0, T] clamp; garbage (NaN / inf) in the padding is never read
+    # lengths outside [0, T] clamp; garbage (NaN / inf) in the padding is never used
     x["lens"] = np.array([40, -3, 33, 1, 0], np.int32)
     for k in ("logprob", "old_logprob", "kl", "entropy"):
         x[k][3, 1:] = np.nan
