@@ -1421,6 +1421,7 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
   const int nq = min(P.QB, L - a), n_keys = a + nq, n_tiles = ceil_div(n_keys, TK), nrows = nq * P.r;
   const bool both = TEAMS == 2 && n_tiles > SOLO_TILES;     // the workgroup's teams share its tiles
   if (TEAMS == 2 && !both && team == 1) return;             // (the barriers are of the wavefronts that stay)
+  const int skip = both ? ~1 : 0;                           // u + (u & skip): the rounds are every other one of the block's
   int limit[NTP];
   bf16x8 qf[NTP][4];
 #pragma unroll
@@ -1459,7 +1460,7 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
 #pragma unroll
   for (int i = 0; i < 4; ++i) vo[i] = lrow * ROWB + ((chunk ^ (kind ? lrow << 1 ^ (i & 1) << 3 : lrow ^ i << 2)) << 4);   // V: (row & 7) << 1, K: row & 15
   auto issue = [&](int round) {
-    int t = both ? 4 * round + 2 * team + sub : 2 * round + sub;
+    int t = TEAMS == 1 ? 2 * round + sub : 2 * round + (2 * round & skip) + 2 * team + sub;
     if (t >= n_tiles) return;
     char* dst = lds + uni((2 * (round & 1) + sub) * STAGE_B + kind * TILE_B);
     asm volatile("" : "+s"(t));
@@ -1490,15 +1491,17 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
   f32x4 s0[NTP], s1[NTP];
   bf16x8 pb[NTP], kf[4][2];
   s16x4 vf[8][2];
-  // The tiles of this wavefront's team: step u is tile t = u, or with two teams the pairs of tiles in turn.
-  auto tile_at = [&](int u) { return both ? 4 * (u >> 1) + 2 * team + (u & 1) : u; };
-  const int steps = both ? 2 * ceil_div(n_tiles, 4) : n_tiles;              // the same for both teams: they share the barriers
+  // The tiles of this wavefront's team: step u is tile t = u, or with two teams the pairs of tiles in turn.  One form of the
+  // index for shared and solo blocks, and whole rounds in both: branches on `both` in the loop cost 2 to 3 % (1 x 1473 tokens of
+  // 4/1 heads 20.7 us, 20.3 so; 4 x 3890 of 2/2 51.7 and 50.9).
+  auto tile_at = [&](int u) { return TEAMS == 1 ? u : u + (u & skip) + 2 * team; };
+  const int steps = TEAMS == 1 ? n_tiles : 2 * ceil_div(n_tiles, both ? 4 : 2);  // the same for both teams: they share the barriers
   // one step; STAGE = u % 4 is a compile-time constant of the unrolled body
   auto tile = [&](auto fixed_c, auto stage_c, int u) {
     constexpr int STAGE = decltype(stage_c)::value;
     constexpr bool FIXED = decltype(fixed_c)::value;
     const int t = tile_at(u), key0 = t * TK;
-    const bool here = !both || t < n_tiles;
+    const bool here = TEAMS == 1 || t < n_tiles;
     if (wave_has_rows && here) {
       float m_new[NTP];
       if (key0 + TK > wave_first + 1) {                     // not wholly in every row's past
@@ -1515,7 +1518,7 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
       softmax_weights<NTP, FIXED>(score, m_new, st, pb, P.c);
       wait_v_frags(vf);
     }
-    if ((STAGE & 1) || (!both && t == n_tiles - 1)) {  // the round's last tile: every fragment of the round is in registers
+    if ((STAGE & 1) || (TEAMS == 1 && t == n_tiles - 1)) {  // the round's last tile: every fragment of the round is in registers
       wait_vmem();                                          // this wavefront's loads of the next round have landed
       __builtin_amdgcn_s_barrier();
       issue((u >> 1) + 2);                                  // into the buffer the round just left

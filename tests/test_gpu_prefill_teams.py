@@ -36,13 +36,14 @@ def test_both_sides_of_the_blocks_a_compute_unit(B, P, cap):  # noqa: F811
 
 @pytest.mark.parametrize("gain", [6.0, 60.0])
 @pytest.mark.parametrize("first", [32, 64, 100])
-def test_growing_scores(B, gain, first):  # noqa: F811
+@pytest.mark.parametrize("L", [530, 210])                          # 17 tiles, of both teams; 7, of the first and half a round over
+def test_growing_scores(B, gain, first, L):  # noqa: F811
     """Keys past the first ones `gain` times as large: the reference follows the sums, or the workgroup starts over."""
-    x = case(int(gain) + first, 1, 700, 8, 1, lens=[530])
+    x = case(int(gain) + first, 1, 700, 8, 1, lens=[L])
     k = (x["k"].astype(np.uint32) << 16).view(np.float32).copy()
     k[:, :, first:] *= gain
     x["k"] = (k.view(np.uint32) >> 16).astype(np.uint16)
-    check(B, x, 1.0 / math.sqrt(128), (gain, first))
+    check(B, x, 1.0 / math.sqrt(128), (gain, first, L))
 
 
 def test_run_to_run(B):  # noqa: F811
