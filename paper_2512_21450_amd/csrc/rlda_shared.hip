@@ -901,7 +901,7 @@ struct RowParts {
 };
 
 // ---- combine: TEAMS teams of 32 lanes per (sequence, head) row, which take even runs of its places.  Lane k of a team first
-// owns part k: all lse values of the team's parts and the first sixteen parts' values are requested in one round trip (rows
+// owns part k: all lse values of the team's parts and up to the first sixteen parts' values are requested in one round trip (rows
 // of a small batch are cut into many parts, and every further round trip shows in its step time); the lse values become
 // weights with two 32-lane reductions; then every lane accumulates its 4 columns.  Parts are taken in line order, and the
 // teams meet in LDS in that order, so the sum has one fixed order.  The partials are read and the rows written past the
@@ -964,12 +964,24 @@ __global__ void __launch_bounds__(TEAMS > 8 ? 32 * TEAMS : 256) combine_kernel(c
     if (cnt == 0) break;
     // the first FIRST parts' values are requested together with the lse values (one round trip)
     constexpr int FIRST = 16, NEXT = 8;
+    // Few parts are asked for by few loads: sixteen a team, most of them of a part asked for already, are what short
+    // sequences in long buffers waited for.  us with sixteen / so: 128 x 2 16/2 heads 600 + 2300 keys, a twentieth filled,
+    // 17.8 / 16.4, 1 x 8 8/1 2000 + 4096 12.3 / 11.1, three tenths 12.5 / 11.3, filled 13.1 / 13.0; with four or sixteen
+    // 16.3, 11.2, 11.7, 13.0, in fours up to sixteen 16.3, 11.1, 11.4, 13.2 (2 x 4 16/4 3000 + 4096 filled 16.4 / 16.4 / 17.0).
+    // Trees, whose parts come from several levels, keep sixteen (96 of 14/2 on two levels 22.4 / 23.5).
+    const bool five = TREE || __any(cnt > 4), nine = TREE || __any(cnt > 8);
     f16x4 v8[FIRST];
+    const auto ask = [&](int from, int to) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < FIRST; ++u) {
-      const int id = __shfl(mine, min(u, cnt - 1), 32);
-      v8[u] = __builtin_nontemporal_load(reinterpret_cast<const f16x4*>(reinterpret_cast<const char*>((id & 1 ? P.so : P.po) + (size_t)(id >> 1) * D) + coff));
-    }
+      for (int u = 0; u < FIRST; ++u)
+        if (u >= from && u < to) {
+          const int id = __shfl(mine, min(u, cnt - 1), 32);
+          v8[u] = __builtin_nontemporal_load(reinterpret_cast<const f16x4*>(reinterpret_cast<const char*>((id & 1 ? P.so : P.po) + (size_t)(id >> 1) * D) + coff));
+        }
+    };
+    ask(0, 4);
+    if (five) ask(4, 8);
+    if (nine) ask(8, FIRST);
     const float2 ls = mine < 0 ? make_float2(-INFINITY, 0.f)
                                : *reinterpret_cast<const float2*>((mine & 1 ? P.sl : P.pl) + 2 * (size_t)(mine >> 1));
     const float l = ls.x;
@@ -986,12 +998,18 @@ __global__ void __launch_bounds__(TEAMS > 8 ? 32 * TEAMS : 256) combine_kernel(c
     Z = Z * resc + zs;
     M = Mn;
     acc.x *= resc; acc.y *= resc; acc.z *= resc; acc.w *= resc;
+    const auto add = [&](int from, int to) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < FIRST; ++u) {
-      const float wk = u < cnt ? __shfl(wsc, min(u, cnt - 1), 32) : 0.f;
-      acc.x = fmaf(wk, (float)v8[u][0], acc.x); acc.y = fmaf(wk, (float)v8[u][1], acc.y);
-      acc.z = fmaf(wk, (float)v8[u][2], acc.z); acc.w = fmaf(wk, (float)v8[u][3], acc.w);
-    }
+      for (int u = 0; u < FIRST; ++u)
+        if (u >= from && u < to) {
+          const float wk = u < cnt ? __shfl(wsc, min(u, cnt - 1), 32) : 0.f;
+          acc.x = fmaf(wk, (float)v8[u][0], acc.x); acc.y = fmaf(wk, (float)v8[u][1], acc.y);
+          acc.z = fmaf(wk, (float)v8[u][2], acc.z); acc.w = fmaf(wk, (float)v8[u][3], acc.w);
+        }
+    };
+    add(0, 4);
+    if (five) add(4, 8);
+    if (nine) add(8, FIRST);
     for (int k0 = FIRST; k0 < cnt; k0 += NEXT) {
       f16x4 v[NEXT];
       float wk[NEXT];

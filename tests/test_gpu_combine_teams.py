@@ -70,3 +70,19 @@ def test_teams_on_a_tree(B, seqs, Hkv):
     out, lse = B.rl_decode_attn_tree(t["q"], lv, t["k_suffix"], t["v_suffix"], t["suffix_lens"], 0.09)
     ro, rl = ref.decode_attn_tree_ref(x["q"], x["levels"], x["k_suffix"], x["v_suffix"], x["suffix_lens"], 0.09)
     util.compare(out, lse, ro, rl, "bf16", seqs)
+
+
+@pytest.mark.parametrize("a_team", [1, 3, 4, 5, 8, 9, 16, 17])
+@pytest.mark.parametrize("teams", [32, 16, 8])
+def test_numbers_of_parts_a_team(B, teams, a_team):
+    """A team asks for four, eight or sixteen parts at first: each line of them crossed, by one sequence whose tiles are a part
+    each; the others have two tiles, so that the rows of a wavefront disagree."""
+    P, G, Hkv = TEAMS[teams]
+    Ls = 32 * min(a_team * teams, 2048 // Hkv)
+    sl = np.full(P * G, min(Ls, 64))
+    sl[0] = Ls
+    x = util.random_case(a_team, P, G, 7 * Hkv, Hkv, 128, 8, Ls, plens=np.full(P, 5), slens=sl)
+    assert util.merge(B.make_desc(B.RLDA_BF16, P, G, 7 * Hkv, Hkv, 128, 8, Ls, 0.09, algo=B.RLDA_ALGO_SHARED)) == teams
+    out, lse = util.gpu_run(util.to_device(x), 0.09, G, algo=B.RLDA_ALGO_SHARED)
+    ro, rl = util.oracle(x, 0.09, G)
+    util.compare(out, lse, ro, rl, "bf16", (teams, a_team))
