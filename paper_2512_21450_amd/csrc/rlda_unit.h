@@ -22,9 +22,9 @@
 // well gained 0.2 us more and cost those 1.0-1.7); the second tile is asked for before the first has landed; the place in
 // the grid is found without divisions.  From the second tile on the next K and the next V are asked for apart, each as soon
 // as its registers are free: both at once, after both had landed, cost units of many tiles up to 1.5 us of 16.  (fp32 of 64
-// columns alone is faster with both at once, where a tile's rows lie together: 16 units of 30 and up to 3000 keys 28.7 apart /
-// 27.7, on pages of 32 29.3 / 27.8, 16 of 309 and 1905 26.5 / 25.8; its short units 0 to 1 % slower; on pages of 16 49.2 / 50.1,
-// fp32 of 128 columns 26.3 / 27.4.)  A finished
+// columns alone is faster with both at once and one copy of the step for the tiles from the second on, where a tile's rows lie
+// together: 16 units of 30 and up to 3000 keys 28.7 apart / 27.6, on pages of 32 29.3 / 27.7, 16 of 309 and 1905 26.5 / 25.6, 64
+// of 300 and 500 13.2 / 13.2; but on pages of 16 49.2 / 50.1, fp32 of 128 columns 26.3 / 27.4.)  A finished
 // sequence's flag is looked at before anything of it is asked for (no measurable cost: 16 units of live sequences 5.43 / 5.38).
 // Calls captured back to back, without all of this / so, us: 64 units x 256 keys, bf16, 64 columns 5.38 / 4.48, 128 columns
 // 6.5 / 5.8, fp32 of 64 8.4 / 7.6; x 512 keys 6.4 / 5.4, 8.7 / 7.5, 11.9 / 11.2; e4m3 of 128 columns x 512 keys 8.3 / 7.3; 448
@@ -420,13 +420,6 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
       constexpr bool MORE = decltype(more)::value;
       const int nvalid = nxt.last + 1;
       store(kst, kr, L_::kswz);
-      if constexpr (KIND == KV_F32 && D == 64 && !ROWS) {   // both at once
-        store(vst, vr, L_::vswz);
-        if constexpr (MORE) { nxt = tile_of(t + NW); load(nxt, nxt.k, kr); load(nxt, nxt.v, vr); }
-        staged();
-        step(nvalid, [] {});
-        return;
-      }
       if constexpr (MORE) { nxt = tile_of(t + NW); load(nxt, nxt.k, kr); }
       staged();
       step(nvalid, [&] {
@@ -436,8 +429,19 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
       });
     };
     int t = wv + NW;
-    for (; t + NW < T; t += NW) turn(std::true_type{}, t);
-    if (t < T) turn(std::false_type{}, t);
+    if constexpr (KIND == KV_F32 && D == 64 && !ROWS) {   // both at once, see above
+      for (; t < T; t += NW) {
+        const int nvalid = nxt.last + 1;
+        store(kst, kr, L_::kswz);
+        store(vst, vr, L_::vswz);
+        if (t + NW < T) { nxt = tile_of(t + NW); load(nxt, nxt.k, kr); load(nxt, nxt.v, vr); }
+        staged();
+        step(nvalid, [] {});
+      }
+    } else {
+      for (; t + NW < T; t += NW) turn(std::true_type{}, t);
+      if (t < T) turn(std::false_type{}, t);
+    }
   }
 
   // ---- merge: every wavefront leaves its rows (O against its own maximum) in its stages, from the K stage on
