@@ -1694,7 +1694,7 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
 // Which form merges the partials.  A row's time is the chain of its parts: with the lines cut evenly, a prefix unit is cut
 // into about 1 + pairs / units parts and a suffix unit into 1 + 8 * pairs / units, a few times that where lengths differ.
 // The more there are, the more teams of 32 lanes share a row; few rows have many parts, so that the chip has room for them.
-// Measured, us per call with 1 / 2 / 4 / 8 / 16 / 32 teams (parts by the formula below):
+// Measured, us per call with 1 / 2 / 4 / 8 / 16 / 32 teams, each asking for sixteen parts (parts by the formula below):
 //   1 x 1  32/2 heads 1500 + 4000 keys (1152)  38.2 / 28.8 / 22.8 / 18.6 / 18.0 / 14.7
 //   1 x 8   8/1   2000 + 0..4096 (512)  37.7 / 28.3 / 22.0 / 17.0 / 14.4 / 14.6      1 x 16  8/1  4000 + 500 (384)  32.9 / 30.8 / 19.8 / 15.8 / 14.7 / 15.9
 //   2 x 4  16/4   3000 + 4096    (96)   28.3 / 24.8 / 22.2 / 19.5 / 20.1             8 x 5   7/1  1600 + 4000  (83)  32.6 / 29.1 / 25.0 / 22.3 / 23.4
