@@ -75,9 +75,10 @@ typedef enum {
   RLDA_ALGO_AUTO = 0,      /* shared-prefix MFMA path when the shape allows it: bf16 q (bf16 or e4m3 K/V), d = 128,
                               Hq/Hkv <= 16, G * Hq/Hkv <= 256, scale > 0 and, for a paged store, pages of at
                               least 32 rows.  Everything else -- fp32, d = 64, other head ratios or scales,
-                              smaller pages -- is planned as SIMPLE (no sharing across sequences, no scratch);
+                              smaller pages -- is planned as SIMPLE (no sharing across sequences);
                               under AUTO most of it then runs in a one-launch form on the matrix cores, one
-                              workgroup per (sequence, KV head), with 24-bit softmax weights; few rows over few
+                              workgroup per (sequence, KV head), or several for few of them with many keys if
+                              there is a workspace, with 24-bit softmax weights; few rows over few
                               keys stay on the simple kernel, which is faster there.  The one-launch form also
                               takes batches of the shared-prefix path that are too small to fill the chip (16 or
                               24 bits of a weight); their workspace is asked for and checked all the same. */
@@ -93,7 +94,7 @@ enum {
   RLDA_OK = 0,
   RLDA_ERR_INVALID = -1,      /* NULL descriptor / required pointer NULL / negative size        */
   RLDA_ERR_UNSUPPORTED = -2,  /* d not in {64,128}, Hq % Hkv != 0, unknown dtype or algo, ...   */
-  RLDA_ERR_WORKSPACE = -3,    /* workspace NULL or smaller than rl_decode_attn_workspace_bytes  */
+  RLDA_ERR_WORKSPACE = -3,    /* workspace NULL or smaller than the RLDA_ALGO_SHARED plan needs  */
   RLDA_ERR_STRUCT_SIZE = -4,  /* struct_size != sizeof(rlda_desc) of this library version       */
   RLDA_ERR_LAUNCH = -5        /* the HIP runtime reported an error when enqueuing               */
 };
@@ -122,7 +123,8 @@ typedef struct {
   const int32_t* suffix_lens;  /* [B]  valid suffix rows per sequence; clamped to [0, Ls_cap]    */
   float*   out;                /* [B, Hq, d] fp32                                                */
   float*   lse;                /* [B, Hq]    fp32, natural log; may be NULL                      */
-  void*    workspace;          /* device scratch, 256-byte aligned, may be NULL if 0 bytes needed */
+  void*    workspace;          /* device scratch, 256-byte aligned, any contents; may be NULL if no byte is
+                                  needed (RLDA_ALGO_SIMPLE plans run without what they ask for, some slower) */
   size_t   workspace_bytes;
   const float* k_scale;        /* [Hkv] fp32 > 0, RLDA_BF16_KV8 only (else ignored); NULL = all 1 */
   const float* v_scale;        /* [Hkv] fp32, likewise                                           */
@@ -152,16 +154,18 @@ int rl_decode_attn(const rlda_desc* desc, void* hip_stream);
 int rl_decode_attn_profiled(const rlda_desc* desc, void* hip_stream, void* mid_event);
 
 /*
- * Bytes of device workspace rl_decode_attn needs for this descriptor (only the
- * shape fields, dtype and algo are read; no pointer is dereferenced, no device
- * is touched).  Returns 0 if none is needed or if the descriptor is invalid
+ * Bytes of device workspace rl_decode_attn needs (plan RLDA_ALGO_SHARED) or can
+ * use (plan RLDA_ALGO_SIMPLE under AUTO: few long units, which share it out
+ * among more workgroups; a smaller or no workspace is accepted there, the same
+ * one gives the same bits) for this descriptor (only the shape fields, dtype and
+ * algo are read; no pointer is dereferenced, no device is touched).  Returns 0 if none is needed or if the descriptor is invalid
  * (rl_decode_attn reports the reason).
  */
 size_t rl_decode_attn_workspace_bytes(const rlda_desc* desc);
 
 /*
  * How rl_decode_attn plans this descriptor: RLDA_ALGO_SHARED (the shared-prefix
- * path's shapes, with its workspace) or RLDA_ALGO_SIMPLE (no workspace), or a
+ * path's shapes, with its workspace) or RLDA_ALGO_SIMPLE (none needed), or a
  * negative RLDA_ERR_* code.  Under RLDA_ALGO_AUTO either may run in one launch
  * without that changing the plan.  Pure host function.
  */
@@ -182,7 +186,7 @@ int rl_decode_attn_plan(const rlda_desc* desc);
  * GPU's array: calls that may overlap in time there (different streams, or
  * graphs replayed concurrently) race on it and must be ordered by the caller;
  * nothing needs to be cleared between calls (the kernels write every entry
- * they later read).
+ * they later read, or tell by the number of the call that it is another's).
  */
 #define RLDA_STATIC_WORKSPACE_BYTES (64u << 20)
 int    rl_decode_attn_static(const rlda_desc* desc, void* hip_stream);

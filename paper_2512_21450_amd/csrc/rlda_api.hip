@@ -80,11 +80,17 @@ int plan_of(const Desc* desc) {
   return rc != RLDA_OK ? rc : plan(pb);
 }
 
+// what a plan needs (SHARED), or can use (SIMPLE, under AUTO)
+size_t planned_bytes(const Problem& pb, int planned) {
+  if (planned == RLDA_ALGO_SHARED) return rlda::shared_workspace_bytes(pb);
+  return planned == RLDA_ALGO_SIMPLE && pb.algo == RLDA_ALGO_AUTO ? rlda::unit_workspace_bytes(pb) : 0;
+}
+
 template <class Desc>
 size_t workspace_of(const Desc* desc) {
   Problem pb;
   if (to_problem(desc, pb) != RLDA_OK) return 0;
-  return plan(pb) == RLDA_ALGO_SHARED ? rlda::shared_workspace_bytes(pb) : 0;
+  return planned_bytes(pb, plan(pb));
 }
 
 // Tree descriptor -> Problem.  Returns RLDA_OK or the error the descriptor itself shows.
@@ -227,8 +233,8 @@ int enqueue_static(const rlda_desc* desc, void* hip_stream) {
   pb.workspace = nullptr; pb.workspace_bytes = 0;           // the descriptor's own workspace fields are not used
   const int pl = plan(pb);
   if (pl < 0) return pl;
-  if (pl == RLDA_ALGO_SHARED) {
-    const size_t need = rlda::shared_workspace_bytes(pb);
+  const size_t need = planned_bytes(pb, pl);
+  if (need > 0) {
     if (need > (size_t)RLDA_STATIC_WORKSPACE_BYTES) return RLDA_ERR_WORKSPACE;
     const int rp = check_pointers(pb);                       // before the device is asked for anything
     if (rp != RLDA_OK) return rp;

@@ -76,6 +76,9 @@ hipError_t launch_shared(const Problem& pb, hipStream_t stream, hipEvent_t mid);
 bool unit_supported(const Problem& pb, int pairs);
 bool unit_pays(const Problem& pb, int pairs);        // and runs faster here than on the simple kernel
 bool unit_preferred(const Problem& pb, int pairs);   // a problem of the shared-prefix path that runs faster here
+// workspace with which few units of many keys are shared by several workgroups each; with less they get fewer, with none one.
+// On a whole device: what a part of one wants is no more.
+size_t unit_workspace_bytes(const Problem& pb);
 hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t stream);
 
 // ---- causal prefill attention over each prompt (bf16, d = 128, Hq/Hkv <= 16)

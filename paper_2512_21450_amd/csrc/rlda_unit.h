@@ -1,5 +1,5 @@
 // Decode attention with one workgroup per unit: all keys of one (sequence, KV head) against its Hq/Hkv query rows,
-// one launch, no scratch.  Two uses:
+// one launch; few units of many keys are shared by several workgroups each (SPLIT), if there is a workspace.  Two uses:
 //   * most of what the shared-prefix kernels do not take (fp32 stores, d = 64, wider head ratios, scales that are
 //     not positive, pages under 32 rows), but for few rows over few keys, which the simple kernel runs faster
 //     (unit_pays).  Weights enter the value contraction with 24 bits (EXACT below);
@@ -34,11 +34,21 @@
 // Samples of one prompt sit on one die, side by side in dispatch order, so that the prefix a group shares comes from
 // memory once and from that die's L2 for the other samples.
 //
+// Units that are fewer than half the compute units and long are shared by up to 16 workgroups (split_rule): the wavefronts of
+// all of them take the tiles in turn, every workgroup merges its own in LDS and leaves rows, maxima and sums in the workspace, and
+// the one that arrives last (rlda_arrive.h) merges those, in order, so that the sum does not depend on who that is.  It costs about
+// a microsecond, four dependent round trips; what it saves is the rounds of tiles behind one another (2.9 us each in fp32 of 64
+// columns, 1.7 in bf16 of 128, 0.95 of 64).  How many take part follows from the lengths, on the device: short sequences in long
+// buffers stay with one workgroup, the others end at once.  One workgroup / split, us, buffers full: 32 units of 1087 keys fp32
+// 17.1 / 9.6, of 4064 46.7 / 18.4, 2 of 2048 25.0 / 7.7; bf16 of 64 columns 32 of 4000 18.4 / 11.5, 64 of 2048 11.8 / 10.7, 2 of
+// 1024 6.8 / 6.1; e4m3 of 64 64 of 4000 19.5 / 12.1; bf16 of 128 32 of 1024 11.0 / 8.2, 8 of 2000 15.6 / 7.7.
+//
 // Tile math as in the shared-prefix kernels: S^T = K Q^T, so that a lane's accumulators (one query row, 4 keys per
 // 16-key half) are the operand of O^T += V^T P^T.  A weight is split into two bf16 pieces (16 bits), EXACT: three (24),
 // each contracted with V on the matrix cores; fp32 stores use the fp32 matrix instruction.
 #pragma once
 
+#include "rlda_arrive.h"
 #include "rlda_internal.h"
 #include "rlda_sched.h"
 
@@ -60,6 +70,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int MAX_SEG = RLDA_MAX_TREE_LEVELS + 1;
+constexpr int MAX_UNIT_SPLITS = 16;
 // keys shared by `group` consecutive sequences: stores [n, Hkv, cap, d], lens [n]
 struct Segment { const char* k; const char* v; const int32_t* lens; int group, cap; FastDiv div; };   // div: by group
 
@@ -70,13 +81,20 @@ struct UnitParams {
   int n_seg;
   int B, G, Hq, Hkv, r, RB;        // r = Hq / Hkv query rows in RB blocks of 16
   FastDiv div_per, div_RB, div_Hkv;   // quotients by G * RB, RB and Hkv
-  int groups8;                     // (prompt, KV head) groups rounded up to the dies, 0: units in plain order
+  int groups8;                     // (prompt, KV head) groups (SPLIT: times splits) rounded up to the dies, 0: units in plain order
   float scale, c, c_lo;            // and |scale| * log2(e) with what its rounding left; 1 and 0 when the scale is 0
   uint32_t qsign, qmask;           // q bits: & qmask (0 when the scale is 0), ^ qsign (for a negative factor), per 16-bit half or word
   const int32_t* table;            // paged suffix: [B, max_pages] page ids, else null
   int page_shift, max_pages, n_pages;
   const uint8_t* active;
   const float* kscale; const float* vscale;
+  // units that several workgroups share (SPLIT): how many at most, from how many tiles on, what the grid counts first
+  // (groups where groups8 is set, else units), the call's number, and in the workspace a counter per unit and, per workgroup and
+  // row, the maximum with the weights' sum and the values against it
+  int splits, min_tiles, n_first;
+  FastDiv div_first;
+  uint64_t call;
+  uint64_t* arrived; uint64_t* part_ml; uint64_t* part_o;
 };
 
 enum Kind { KV_BF16, KV_F8, KV_F32 };
@@ -132,7 +150,8 @@ struct Lay {
 };
 
 // NSEG: segments per sequence (2, or MAX_SEG for a tree); ROWS: pages of fewer rows than a tile, every row is looked up
-template <int KIND, int D, bool EXACT, int NW, int NSEG, bool ROWS>
+// SPLIT: up to P.splits workgroups share a unit, wavefront for wavefront as if they were one; the last to end merges what they left
+template <int KIND, int D, bool EXACT, int NW, int NSEG, bool ROWS, bool SPLIT>
 __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) unit_kernel(const UnitParams P) {
   using L_ = Lay<KIND, D>;
   constexpr int CT = D / 16;                           // 16-column tiles of O
@@ -143,16 +162,27 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   const int tid = threadIdx.x, lane = tid & 63, wv = uni(tid >> 6), m16 = lane & 15, g = lane >> 4;
 
   // ---- which unit: sequence b, KV head j, row block rb
-  int b, j, rb;
+  int b, j, rb, split = 0;
   if (P.groups8 > 0) {
     const int xcd = blockIdx.x & 7, s = blockIdx.x >> 3, per = P.G * P.RB;
-    const int round = fast_div(s, P.div_per), grp = round * 8 + xcd, in = s - round * per;
+    const int round = fast_div(s, P.div_per), in = s - round * per;
+    int grp = round * 8 + xcd;
+    if constexpr (SPLIT) {                             // a group's samples meet in the same keys: what a die holds is one part of it
+      split = fast_div(grp, P.div_first);
+      grp -= split * P.n_first;
+      if (split >= P.splits) return;
+    }
     const int p = fast_div(grp, P.div_Hkv), own = fast_div(in, P.div_RB);
     j = grp - p * P.Hkv; b = p * P.G + own; rb = in - own * P.RB;
-    if (b >= P.B) return;                              // groups are rounded up to the eight dies
+    if (!SPLIT && b >= P.B) return;                    // groups are rounded up to the eight dies
   } else {
-    const int u = fast_div(blockIdx.x, P.div_RB);
-    rb = blockIdx.x - u * P.RB; b = fast_div(u, P.div_Hkv); j = u - b * P.Hkv;
+    int at = blockIdx.x;
+    if constexpr (SPLIT) {
+      split = fast_div(at, P.div_first);
+      at -= split * P.n_first;
+    }
+    const int u = fast_div(at, P.div_RB);
+    rb = at - u * P.RB; b = fast_div(u, P.div_Hkv); j = u - b * P.Hkv;
   }
   const int nr = min(16, P.r - 16 * rb), h0 = j * P.r + 16 * rb;
 
@@ -234,6 +264,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   };
 
   if (act == 0) {                                      // finished: nothing of it is read
+    if (SPLIT && split > 0) return;
     for (int it = tid; it < nr * (D / 4); it += 64 * NW) {
       const int row = it / (D / 4), ch = it % (D / 4);
       const size_t orow = (size_t)b * P.Hq + h0 + row;
@@ -248,9 +279,10 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   const char* qp = P.q + ((size_t)b * P.Hq + h0 + min(m16, nr - 1)) * D * QE;
 #pragma unroll
   for (int i = 0; i < NQ; ++i) qr[i] = *reinterpret_cast<const u32x4*>(qp + 64 * i + 16 * g);   // chunk 4 i + g, as K
-  const bool early = (wv + 1) * TK <= P.seg[0].cap && (NSEG == 2 || P.n_seg > 1);
+  const int w0 = SPLIT ? split * NW + wv : wv;         // the wavefront's first tile
+  const bool early = (w0 + 1) * TK <= P.seg[0].cap && (NSEG == 2 || P.n_seg > 1);
   if (early) {
-    const size_t off = at[0] + (size_t)wv * TK * L_::ROWB;
+    const size_t off = at[0] + (size_t)w0 * TK * L_::ROWB;
     const Tile guess{P.seg[0].k + off, P.seg[0].v + off, 0, TK - 1};
     load(guess, guess.k, ka);
   }
@@ -264,6 +296,15 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
       T += ceil_div(len[s], TK);
     }
   }
+  int parts = 1;                                       // workgroups that share this unit
+  if constexpr (SPLIT) {
+    if (T >= P.min_tiles) parts = min(P.splits, ceil_div(T, NW));
+    if (split >= parts) return;
+  }
+  uint64_t* const counter = SPLIT ? P.arrived + ((size_t)b * P.Hkv + j) * P.RB + rb : nullptr;
+  uint64_t seen = 0;
+  if (SPLIT && parts > 1 && tid == 0) seen = claim(counter, P.call);
+  const int stride = SPLIT ? NW * parts : NW;          // from one tile of a wavefront to its next
 
   // The factor of the exponents meets differences of products only, so that the size of the scores costs a weight
   // nothing, and is kept positive and finite (a difference of 0 or -inf times it has to stay).  EXACT: what its rounding
@@ -388,17 +429,17 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");   // LDS serves a wavefront in order: the stage may be rewritten
     __builtin_amdgcn_wave_barrier();
   };
-  if (wv < T) {
-    const Tile cur = tile_of(wv);
-    if (!(early && (wv + 1) * TK <= len[0])) load(cur, cur.k, ka);
+  if (w0 < T) {
+    const Tile cur = tile_of(w0);
+    if (!(early && (w0 + 1) * TK <= len[0])) load(cur, cur.k, ka);
     load(cur, cur.v, va);
     const uint32_t qm = m16 < nr ? P.qmask : 0u;
     const uint32_t qs = m16 < nr && (P.scale < 0.f) != (ks < 0.f) ? P.qsign : 0u;
     Tile nxt = cur;
     // the second tile is asked for before the first has landed; in branches of their own, so that the wait for the first
     // counts the loads that follow it
-    if (wv + NW < T) {
-      nxt = tile_of(wv + NW);
+    if (w0 + stride < T) {
+      nxt = tile_of(w0 + stride);
       load(nxt, nxt.k, kr); load(nxt, nxt.v, vr);
       store(kst, ka, L_::kswz);
       store(vst, va, L_::vswz);
@@ -416,11 +457,11 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     step(cur.last + 1, [] {});
     // The next K is asked for before the scores and the next V before the values, as soon as its registers are free.  The last
     // tile is a copy of its own: the waits of the others then count exactly the loads that follow.
-    auto turn = [&](auto more, int t) {                // more: tile t + NW follows
+    auto turn = [&](auto more, int t) {                // more: tile t + stride follows
       constexpr bool MORE = decltype(more)::value;
       const int nvalid = nxt.last + 1;
       store(kst, kr, L_::kswz);
-      if constexpr (MORE) { nxt = tile_of(t + NW); load(nxt, nxt.k, kr); }
+      if constexpr (MORE) { nxt = tile_of(t + stride); load(nxt, nxt.k, kr); }
       staged();
       step(nvalid, [&] {
         store(vst, vr, L_::vswz);
@@ -428,18 +469,18 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
         staged();
       });
     };
-    int t = wv + NW;
+    int t = w0 + stride;
     if constexpr (KIND == KV_F32 && D == 64 && !ROWS) {   // both at once, see above
-      for (; t < T; t += NW) {
+      for (; t < T; t += stride) {
         const int nvalid = nxt.last + 1;
         store(kst, kr, L_::kswz);
         store(vst, vr, L_::vswz);
-        if (t + NW < T) { nxt = tile_of(t + NW); load(nxt, nxt.k, kr); load(nxt, nxt.v, vr); }
+        if (t + stride < T) { nxt = tile_of(t + stride); load(nxt, nxt.k, kr); load(nxt, nxt.v, vr); }
         staged();
         step(nvalid, [] {});
       }
     } else {
-      for (; t + NW < T; t += NW) turn(std::true_type{}, t);
+      for (; t + stride < T; t += stride) turn(std::true_type{}, t);
       if (t < T) turn(std::false_type{}, t);
     }
   }
@@ -458,6 +499,19 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   if (g == 0) { wm[wv][m16] = m; wl[wv][m16] = l; }
   __syncthreads();
   bool odd = false;                                    // a column that is not finite where the row's weights are
+  // columns 4 ch .. 4 ch + 3 of a row, its values against M and their weights' sum
+  auto finish = [&](int row, int ch, float M, float L, f32x4 acc) __attribute__((always_inline)) {
+    const size_t orow = (size_t)b * P.Hq + h0 + row;
+    const float inv = T > 0 ? vfac / L : 0.f;
+    acc *= inv;
+    odd = odd || (L < INFINITY && !(fabsf(acc[0]) + fabsf(acc[1]) + fabsf(acc[2]) + fabsf(acc[3]) < INFINITY));
+    *reinterpret_cast<f32x4*>(P.out + orow * D + 4 * ch) = acc;
+    if (P.lse && ch == 0) {
+      const float f = fabsf(P.scale) * kabs, f_lo = f <= FLT_MAX ? fmaf(fabsf(P.scale), kabs, -f) : 0.f;
+      const float log_l = __builtin_amdgcn_logf(L) * 0.69314718055994531f;
+      P.lse[orow] = L > 0.f ? fmaf(M, f, fmaf(M, f_lo, log_l)) : -INFINITY;   // no key, or none that is a number
+    }
+  };
   for (int it = tid; it < nr * OC; it += 64 * NW) {
     const int row = it / OC, ch = it % OC;
     float M = wm[0][row];                              // a wavefront without a tile: the lowest maximum, and zeros
@@ -474,14 +528,57 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
       for (int x = 0; x < 4; ++x) acc[x] = fmaf(a, o[x], acc[x]);
     }
     const size_t orow = (size_t)b * P.Hq + h0 + row;
-    const float inv = T > 0 ? vfac / L : 0.f;
-    acc *= inv;
-    odd = odd || (L < INFINITY && !(fabsf(acc[0]) + fabsf(acc[1]) + fabsf(acc[2]) + fabsf(acc[3]) < INFINITY));
-    *reinterpret_cast<f32x4*>(P.out + orow * D + 4 * ch) = acc;
-    if (P.lse && ch == 0) {
-      const float f = fabsf(P.scale) * kabs, f_lo = f <= FLT_MAX ? fmaf(fabsf(P.scale), kabs, -f) : 0.f;
-      const float log_l = __builtin_amdgcn_logf(L) * 0.69314718055994531f;
-      P.lse[orow] = L > 0.f ? fmaf(M, f, fmaf(M, f_lo, log_l)) : -INFINITY;   // no key, or none that is a number
+    if (SPLIT && parts > 1) {
+      const size_t at_row = (size_t)split * P.B * P.Hq + orow;
+      put(P.part_o + at_row * (D / 2) + 2 * ch, acc[0], acc[1]);
+      put(P.part_o + at_row * (D / 2) + 2 * ch + 1, acc[2], acc[3]);
+      if (ch == 0) put(P.part_ml + at_row, M, L);
+      continue;
+    }
+    finish(row, ch, M, L, acc);
+  }
+  if constexpr (SPLIT) {
+    if (parts > 1) {
+      __shared__ bool last;
+      stores_done();
+      __syncthreads();
+      if (tid == 0) last = arrive(counter, P.call, seen, parts);
+      __syncthreads();
+      if (!last) return;
+      for (int it = tid; it < nr * OC; it += 64 * NW) {
+        const int row = it / OC, ch = it % OC;
+        const size_t orow = (size_t)b * P.Hq + h0 + row, step_ml = (size_t)P.B * P.Hq;
+        const uint64_t* const ml = P.part_ml + orow;
+        const uint64_t* const o = P.part_o + orow * (D / 2) + 2 * ch;
+        float M = -FLT_MAX, L = 0.f;
+        f32x4 acc{0.f, 0.f, 0.f, 0.f};
+        constexpr int U = 8;                           // parts asked for at once
+        for (int k0 = 0; k0 < parts; k0 += U) {
+          float2 mlv[U], oa[U], ob[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const size_t k = min(k0 + u, parts - 1) * step_ml;
+            mlv[u] = get(ml + k);
+            oa[u] = get(o + k * (D / 2));
+            ob[u] = get(o + k * (D / 2) + 1);
+          }
+          float Mn = M;
+#pragma unroll
+          for (int u = 0; u < U; ++u) Mn = fmaxf(Mn, mlv[u].x);
+          const float resc = __builtin_amdgcn_exp2f((M - Mn) * c);
+          L *= resc; acc *= resc;
+          M = Mn;
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (k0 + u < parts) {
+              const float a = __builtin_amdgcn_exp2f((mlv[u].x - M) * c);
+              L = fmaf(a, mlv[u].y, L);
+              acc[0] = fmaf(a, oa[u].x, acc[0]); acc[1] = fmaf(a, oa[u].y, acc[1]);
+              acc[2] = fmaf(a, ob[u].x, acc[2]); acc[3] = fmaf(a, ob[u].y, acc[3]);
+            }
+        }
+        finish(row, ch, M, L, acc);
+      }
     }
   }
   // An infinite value gives an infinite result; but split weights leave pieces of 0 or below zero, and rows past the
@@ -496,7 +593,11 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
     for (int it = tid; it < nr * OC; it += 64 * NW) {
       const int row = it / OC, ch = it % OC;
       float L = 0.f;
-      for (int w = 0; w < NW; ++w) L += wl[w][row];
+      if (SPLIT && parts > 1) {
+        for (int k = 0; k < parts; ++k) L += get(A->part_ml + (size_t)k * A->B * A->Hq + (size_t)b * A->Hq + h0 + row).y;
+      } else {
+        for (int w = 0; w < NW; ++w) L += wl[w][row];
+      }
       if (!(L < INFINITY)) continue;                   // a score that is not a number: the row is none
       f32x4 sum{0.f, 0.f, 0.f, 0.f};
       for (int s = 0; s < A->n_seg; ++s) {
@@ -524,7 +625,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   }
 }
 
-template <int KIND, int D, bool EXACT, int NW, int NSEG = 2, bool ROWS = false>
+template <int KIND, int D, bool EXACT, int NW, int NSEG = 2, bool ROWS = false, bool SPLIT = false>
 hipError_t launch(const UnitParams& P, int64_t blocks, hipStream_t stream) {
   constexpr int lds = NW * 2 * Lay<KIND, D>::TILE;
   // once per device: more than 64 KB of LDS in total needs an opt-in
@@ -536,13 +637,13 @@ hipError_t launch(const UnitParams& P, int64_t blocks, hipStream_t stream) {
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(mu);
     if (dev < 0 || dev >= 64 || !done[dev]) {
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(unit_kernel<KIND, D, EXACT, NW, NSEG, ROWS>),
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(unit_kernel<KIND, D, EXACT, NW, NSEG, ROWS, SPLIT>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       if (e != hipSuccess) return e;
       if (dev >= 0 && dev < 64) done[dev] = true;
     }
   }
-  hipLaunchKernelGGL((unit_kernel<KIND, D, EXACT, NW, NSEG, ROWS>), dim3((unsigned)blocks), dim3(64 * NW), lds, stream, P);
+  hipLaunchKernelGGL((unit_kernel<KIND, D, EXACT, NW, NSEG, ROWS, SPLIT>), dim3((unsigned)blocks), dim3(64 * NW), lds, stream, P);
   return hipGetLastError();
 }
 
@@ -562,7 +663,51 @@ struct UnitGrid {
   int groups8;                     // as in UnitParams
   int64_t blocks;
   int nw;                          // wavefronts of a workgroup
+  int splits, min_tiles;           // workgroups of a unit at most, and the tiles from which on it gets more than one
 };
+
+// What a unit shared by several workgroups leaves in the workspace: a counter, and per workgroup and row the values, their
+// maximum and the weights' sum.
+size_t split_counters(const Problem& pb) {             // rounded up so that what follows starts on 256 bytes
+  return ((size_t)n_sequences(pb) * pb.Hkv * ceil_div(pb.Hq / pb.Hkv, 16) + 31) & ~(size_t)31;
+}
+size_t split_bytes(const Problem& pb, int splits) {
+  return split_counters(pb) * 8 + (size_t)splits * n_sequences(pb) * pb.Hq * (8 + (size_t)pb.d * 4);
+}
+
+struct Split { int splits, nw, min_tiles; };
+// How many workgroups share a unit at most: as many as the compute units hold, up to 16, and one from `min_tiles` of the unit's real
+// tiles on.  Eight wavefronts each, as one workgroup has; but where the buffers hold 32 tiles at most and there is a compute unit for
+// every four of them, workgroups of four, so that each wavefront has one tile and more compute units share them.  Both where a round
+// of tiles costs enough: not in 16-bit stores of 64 columns.  us, one workgroup / eight wavefronts each / four each:
+//   fp32, 64 columns, 512 keys: 2 units 9.6 / 7.7 / 6.8, 64 10.9 / 9.2 / 8.3; 1024 keys: 2 14.8 / 8.3 / 6.9, 64 16.6 / 11.9 / 12.2
+//   bf16, 128 columns, 512 keys: 32 7.2 / 7.1 / 6.8, half full 6.0 / 7.1 / 6.5; 1024 keys: 2 9.9 / 7.0 / 6.4, 64 11.5 / 10.8 / 11.5
+//   bf16, 64 columns, 512 keys: 32 5.3 / 6.2 / 6.1; 1024 keys: 32 6.9 / 6.6 / 6.9
+// With two workgroups to a unit (86 to 128 of them on 256 compute units) the saving is half of that and the memory is nearly busy: from
+// more tiles on only (128 units, one / two: fp32 512 keys 11.1 / 9.8, 384 8.1 / 8.1; bf16 of 128 columns 1024 11.8 / 12.5, 1088 11.1 /
+// 10.4, 2048 18.7 / 17.4; bf16 of 64 1024 8.2 / 9.1, 2112 10.6 / 9.5), and not where the sequences' own keys are most of a call in bf16
+// of 64 columns (64 + 2048 keys 13.6 / 15.2, half full 9.4 / 10.7; e4m3 12.9 / 12.3).  More than half as many units as compute units
+// gain nothing (256 units of 1088 to 4000 keys: 2 to 15 % slower).
+Split split_rule(const Problem& pb, int pairs) {
+  const int64_t units = n_sequences(pb) * pb.Hkv * ceil_div(pb.Hq / pb.Hkv, 16);
+  const bool f32 = pb.dtype == RLDA_F32, wide = pb.d == 128;
+  Split s{1, 0, 0};
+  if (2 * units > pairs || units < 1 || (pb.paged && pb.page_shift < 5)) return s;   // (a query brings no table)
+  int tiles = ceil_div(pb.Ls_cap, TK) + ceil_div(pb.Lp_cap, TK);           // of a sequence that fills its buffers
+  for (int l = 0; l < pb.n_levels; ++l) tiles += ceil_div(pb.levels[l].cap, TK);
+  const int n = pairs / (int)units, most = n < MAX_UNIT_SPLITS ? n : MAX_UNIT_SPLITS;
+  if (tiles > (f32 ? 8 : 16) && tiles <= 32 && (f32 || wide) && ceil_div(tiles, 4) <= n) {
+    s.nw = 4;
+    s.min_tiles = 5;
+  } else {
+    s.nw = wide_waves(f32, pb.d);
+    s.min_tiles = f32 ? (n > 2 ? 9 : 14) : wide ? (n > 2 ? 17 : 41) : (n > 2 ? 25 : 57);
+    if (n == 2 && pb.dtype == RLDA_BF16 && !wide && units * pb.Ls_cap > (int64_t)512 * pairs) return s;
+  }
+  if (tiles >= s.min_tiles) s.splits = most < ceil_div(tiles, s.nw) ? most : ceil_div(tiles, s.nw);
+  return s;
+}
+
 // How many wavefronts a unit gets.  Eight while every workgroup has a compute unit to itself (128 units x 964 keys: 11.7 us,
 // 12.7 with four).  When workgroups queue, what counts is how many units are on their way at once: a workgroup holds the
 // LDS of all its wavefronts from the first length it reads to the last row it writes, so the more of them there are and
@@ -576,11 +721,21 @@ struct UnitGrid {
 //                                        256 x 1024  26 / 39 / 62 / 108  4096 x 256   223 / 134 / 134 / 117
 UnitGrid unit_grid(const Problem& pb, int pairs, bool exact) {
   const int64_t B = n_sequences(pb), G = max_group(pb), rb = ceil_div(pb.Hq / pb.Hkv, 16), keys = shared_cap(pb) + pb.Ls_cap;
-  UnitGrid u;
+  UnitGrid u{};
+  u.splits = 1;
   // fewer than two groups a die: plain order, so that neighbours spread over the dies
   const int64_t groups = B / G * pb.Hkv;
   u.groups8 = groups >= 16 && G > 1 ? (int)((groups + 7) / 8) : 0;
   u.blocks = u.groups8 > 0 ? u.groups8 * 8 * G * rb : B * pb.Hkv * rb;
+  Split sp = split_rule(pb, pairs);
+  while (sp.splits > 1 && (!pb.workspace || (reinterpret_cast<uintptr_t>(pb.workspace) & 255u) || split_bytes(pb, sp.splits) > pb.workspace_bytes))
+    --sp.splits;                                       // a caller with less workspace than asked for, or none
+  if (sp.splits > 1) {
+    u.groups8 = groups * sp.splits >= 16 && G > 1 ? (int)((groups * sp.splits + 7) / 8) : 0;
+    u.blocks = u.groups8 > 0 ? u.groups8 * 8 * G * rb : B * pb.Hkv * rb * sp.splits;
+    u.nw = sp.nw; u.splits = sp.splits; u.min_tiles = sp.min_tiles;
+    return u;
+  }
   const bool f32 = pb.dtype == RLDA_F32, many = u.blocks > 4 * (int64_t)pairs;
   // workgroups of four wavefronts that the compute units' LDS holds (tiles of 64 16-bit columns are half as large), and a
   // quarter more, which follow as soon as short units end: 528 units of up to 182 keys 9.5 us with four, 10.0 with two
@@ -606,6 +761,13 @@ UnitGrid unit_grid(const Problem& pb, int pairs, bool exact) {
 template <int KIND, int D, bool EXACT>
 hipError_t launch_form(const UnitParams& P, int nw, int64_t blocks, hipStream_t stream) {
   constexpr int WIDE = wide_waves(KIND == KV_F32, D);
+  if (P.splits > 1) {
+    if constexpr (KIND == KV_BF16 && D == 128 && !EXACT)
+      if (P.n_seg != 2) return nw == 4 ? launch<KIND, D, true, 4, MAX_SEG, false, true>(P, blocks, stream)
+                                       : launch<KIND, D, EXACT, WIDE, MAX_SEG, false, true>(P, blocks, stream);
+    return nw == 4 ? launch<KIND, D, EXACT, 4, 2, false, true>(P, blocks, stream)
+                   : launch<KIND, D, EXACT, WIDE, 2, false, true>(P, blocks, stream);
+  }
   if constexpr (EXACT)                                        // the shared-prefix path refuses small pages, so only here
     if (P.table && P.page_shift < 5) {
       if (nw == 1) return launch<KIND, D, EXACT, 1, 2, true>(P, blocks, stream);
@@ -644,7 +806,7 @@ bool unit_supported(const Problem& pb, int pairs) {
     cap += pb.Lp_cap;
   }
   if ((a & 15u) || cap > (int64_t)1 << 30) return false;
-  if (n_sequences(pb) == 0) return true;
+  if (n_sequences(pb) * pb.Hkv * ceil_div(pb.Hq / pb.Hkv, 16) < (int64_t)1 << 20) return true;   // 512 threads each, rounded up, and splits
   for (bool exact : {false, true}) {
     const UnitGrid u = unit_grid(pb, pairs, exact);
     if (u.blocks * 64 * u.nw >= (int64_t)1 << 32) return false;
@@ -707,6 +869,11 @@ bool unit_preferred(const Problem& pb, int pairs) {
          n_sequences(pb) * pb.Hkv * (shared + pb.Ls_cap) <= (int64_t)2048 * pairs && unit_supported(pb, pairs);
 }
 
+size_t unit_workspace_bytes(const Problem& pb) {
+  const int splits = split_rule(pb, N_CU).splits;
+  return splits > 1 ? split_bytes(pb, splits) : 0;
+}
+
 hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t stream) {
   UnitParams P{};
   P.q = static_cast<const char*>(pb.q); P.out = pb.out; P.lse = pb.lse;
@@ -737,6 +904,16 @@ hipError_t launch_unit(const Problem& pb, bool exact, int pairs, hipStream_t str
   if (P.B == 0) return hipSuccess;
   const UnitGrid grid = unit_grid(pb, pairs, exact);
   P.groups8 = grid.groups8;
+  P.splits = grid.splits; P.min_tiles = grid.min_tiles;
+  if (grid.splits > 1) {
+    const size_t rows = (size_t)P.B * P.Hq;
+    const int first = grid.groups8 > 0 ? P.B / P.G * P.Hkv : P.B * P.Hkv * P.RB;
+    P.n_first = first; P.div_first = make_fastdiv(first);
+    P.call = next_call();
+    P.arrived = static_cast<uint64_t*>(pb.workspace);
+    P.part_ml = P.arrived + split_counters(pb);
+    P.part_o = P.part_ml + rows * grid.splits;
+  }
   const int64_t blocks = grid.blocks;
   const int nw = grid.nw;
   if (pb.dtype == RLDA_F32)

@@ -1,0 +1,37 @@
+"""Into how many workgroups the one-launch decode cuts a unit, by the host-side rule alone (no GPU), read off the workspace query: a
+counter of 8 bytes per (sequence, KV head, 16 query rows), rounded up to 256, and 8 + 4 d bytes per workgroup and query row."""
+import pytest
+
+from paper_2512_21450_amd import binding as B
+
+F32, BF16, E4M3 = B.RLDA_F32, B.RLDA_BF16, B.RLDA_BF16_KV8
+
+
+def splits(need, units, rows, d):
+    if need == 0:
+        return 1
+    n, rest = divmod(need - (units * 8 + 255) // 256 * 256, rows * (8 + 4 * d))
+    assert rest == 0 and n > 1
+    return n
+
+
+def of(dtype, d, units, r, Lp, Ls, scale=0.1, **kw):
+    return splits(B.rl_decode_attn_workspace_bytes(B.make_desc(dtype, units, 1, r, 1, d, Lp, Ls, scale, **kw)), units * -(-r // 16), units * r, d)
+
+
+@pytest.mark.parametrize("dtype,d,units,r,Lp,Ls,want", [
+    (F32, 64, 2, 1, 128, 128, 1), (F32, 64, 2, 1, 129, 128, 3), (F32, 64, 2, 1, 512, 512, 8), (F32, 64, 2, 1, 513, 512, 5),
+    (F32, 64, 2, 1, 4000, 4000, 16), (F32, 64, 64, 7, 256, 256, 4), (F32, 64, 64, 7, 512, 512, 4), (F32, 64, 85, 4, 2048, 64, 3),
+    (F32, 64, 128, 4, 192, 224, 1), (F32, 64, 128, 4, 208, 224, 2), (F32, 64, 129, 4, 4000, 64, 1), (F32, 128, 2, 4, 1000, 1000, 16),
+    (BF16, 64, 2, 4, 384, 384, 1), (BF16, 64, 2, 4, 384, 416, 4), (BF16, 64, 32, 4, 64, 4000, 8), (BF16, 64, 86, 4, 1792, 0, 1),
+    (BF16, 64, 86, 4, 1824, 0, 2), (BF16, 64, 128, 4, 2048, 1024, 2), (BF16, 64, 128, 4, 2048, 1025, 1), (E4M3, 64, 128, 4, 2048, 1025, 2),
+    (BF16, 64, 64, 17, 2000, 0, 2), (BF16, 64, 65, 17, 2000, 0, 1), (BF16, 64, 0, 4, 2000, 2000, 1), (E4M3, 64, 4, 16, 30000, 9, 16)])
+def test_how_many_workgroups_share_a_unit(dtype, d, units, r, Lp, Ls, want):
+    assert of(dtype, d, units, r, Lp, Ls) == want
+
+
+def test_what_is_never_shared():
+    assert of(F32, 64, 2, 1, 4000, 4000, algo=B.RLDA_ALGO_SIMPLE) == 1
+    paged = lambda page, pages: B.rl_decode_attn_paged_workspace_bytes(
+        B.make_paged_desc(F32, 2, 1, 1, 1, 64, 1000, page, pages, 2 * pages, 0.1))
+    assert paged(16, 100) == 0 and splits(paged(32, 50), 2, 2, 64) == 11      # pages of fewer rows than a tile
