@@ -149,6 +149,21 @@ struct Lay {
   }
 };
 
+// Columns 4 ch .. 4 ch + 3 of a row: its values against the maximum M, L the sum of their weights; vfac 0: there is no key.  Returns
+// whether one of them is not finite where the weights are.  (As a closure of the kernel this cost fp32 of 64 columns 64 register
+// moves in the loop over the tiles and 0.1 us of 5.)
+template <int D>
+__device__ __forceinline__ bool write_row(const UnitParams& P, size_t orow, int ch, float vfac, float kabs, float M, float L, f32x4 acc) {
+  acc *= vfac != 0.f ? vfac / L : 0.f;
+  *reinterpret_cast<f32x4*>(P.out + orow * D + 4 * ch) = acc;
+  if (P.lse && ch == 0) {
+    const float f = fabsf(P.scale) * kabs, f_lo = f <= FLT_MAX ? fmaf(fabsf(P.scale), kabs, -f) : 0.f;
+    const float log_l = __builtin_amdgcn_logf(L) * 0.69314718055994531f;
+    P.lse[orow] = L > 0.f ? fmaf(M, f, fmaf(M, f_lo, log_l)) : -INFINITY;   // no key, or none that is a number
+  }
+  return L < INFINITY && !(fabsf(acc[0]) + fabsf(acc[1]) + fabsf(acc[2]) + fabsf(acc[3]) < INFINITY);
+}
+
 // NSEG: segments per sequence (2, or MAX_SEG for a tree); ROWS: pages of fewer rows than a tile, every row is looked up
 // SPLIT: up to P.splits workgroups share a unit, wavefront for wavefront as if they were one; the last to end merges what they left
 template <int KIND, int D, bool EXACT, int NW, int NSEG, bool ROWS, bool SPLIT>
@@ -499,19 +514,6 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
   if (g == 0) { wm[wv][m16] = m; wl[wv][m16] = l; }
   __syncthreads();
   bool odd = false;                                    // a column that is not finite where the row's weights are
-  // columns 4 ch .. 4 ch + 3 of a row, its values against M and their weights' sum
-  auto finish = [&](int row, int ch, float M, float L, f32x4 acc) __attribute__((always_inline)) {
-    const size_t orow = (size_t)b * P.Hq + h0 + row;
-    const float inv = T > 0 ? vfac / L : 0.f;
-    acc *= inv;
-    odd = odd || (L < INFINITY && !(fabsf(acc[0]) + fabsf(acc[1]) + fabsf(acc[2]) + fabsf(acc[3]) < INFINITY));
-    *reinterpret_cast<f32x4*>(P.out + orow * D + 4 * ch) = acc;
-    if (P.lse && ch == 0) {
-      const float f = fabsf(P.scale) * kabs, f_lo = f <= FLT_MAX ? fmaf(fabsf(P.scale), kabs, -f) : 0.f;
-      const float log_l = __builtin_amdgcn_logf(L) * 0.69314718055994531f;
-      P.lse[orow] = L > 0.f ? fmaf(M, f, fmaf(M, f_lo, log_l)) : -INFINITY;   // no key, or none that is a number
-    }
-  };
   for (int it = tid; it < nr * OC; it += 64 * NW) {
     const int row = it / OC, ch = it % OC;
     float M = wm[0][row];                              // a wavefront without a tile: the lowest maximum, and zeros
@@ -535,7 +537,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
       if (ch == 0) put(P.part_ml + at_row, M, L);
       continue;
     }
-    finish(row, ch, M, L, acc);
+    odd = write_row<D>(P, orow, ch, T > 0 ? vfac : 0.f, kabs, M, L, acc) || odd;
   }
   if constexpr (SPLIT) {
     if (parts > 1) {
@@ -577,7 +579,7 @@ __global__ void __launch_bounds__(64 * NW, KIND == KV_F32 && D == 128 ? 1 : 2) u
               acc[2] = fmaf(a, ob[u].x, acc[2]); acc[3] = fmaf(a, ob[u].y, acc[3]);
             }
         }
-        finish(row, ch, M, L, acc);
+        odd = write_row<D>(P, orow, ch, vfac, kabs, M, L, acc) || odd;
       }
     }
   }
@@ -676,12 +678,13 @@ size_t split_bytes(const Problem& pb, int splits) {
 }
 
 struct Split { int splits, nw, min_tiles; };
-// How many workgroups share a unit at most: as many as the compute units hold, up to 16, and one from `min_tiles` of the unit's real
-// tiles on.  Eight wavefronts each, as one workgroup has; but where the buffers hold 32 tiles at most and there is a compute unit for
+// How many workgroups share a unit at most: as many as the compute units hold, up to 16, and more than one from `min_tiles` of the unit's
+// real tiles on, if the buffers hold half as many again: workgroups that find nothing to do cost 0.3 to 0.7 us (80 units of e4m3, 128
+// columns, capacities 520 + 24, half full 6.9 / 7.3).  Eight wavefronts each, as one workgroup has; but where the buffers hold 32 tiles at most and there is a compute unit for
 // every four of them, workgroups of four, so that each wavefront has one tile and more compute units share them.  Both where a round
 // of tiles costs enough: not in 16-bit stores of 64 columns.  us, one workgroup / eight wavefronts each / four each:
 //   fp32, 64 columns, 512 keys: 2 units 9.6 / 7.7 / 6.8, 64 10.9 / 9.2 / 8.3; 1024 keys: 2 14.8 / 8.3 / 6.9, 64 16.6 / 11.9 / 12.2
-//   bf16, 128 columns, 512 keys: 32 7.2 / 7.1 / 6.8, half full 6.0 / 7.1 / 6.5; 1024 keys: 2 9.9 / 7.0 / 6.4, 64 11.5 / 10.8 / 11.5
+//   bf16, 128 columns, 512 keys: 32 7.2 / 7.1 / 6.8, half full 6.0 / 7.1 / 6.5 (so not below 800 keys; fp32 400); 1024 keys: 2 9.9 / 7.0 / 6.4, 64 11.5 / 10.8 / 11.5
 //   bf16, 64 columns, 512 keys: 32 5.3 / 6.2 / 6.1; 1024 keys: 32 6.9 / 6.6 / 6.9
 // With two workgroups to a unit (86 to 128 of them on 256 compute units) the saving is half of that and the memory is nearly busy: from
 // more tiles on only (128 units, one / two: fp32 512 keys 11.1 / 9.8, 384 8.1 / 8.1; bf16 of 128 columns 1024 11.8 / 12.5, 1088 11.1 /
@@ -696,7 +699,7 @@ Split split_rule(const Problem& pb, int pairs) {
   int tiles = ceil_div(pb.Ls_cap, TK) + ceil_div(pb.Lp_cap, TK);           // of a sequence that fills its buffers
   for (int l = 0; l < pb.n_levels; ++l) tiles += ceil_div(pb.levels[l].cap, TK);
   const int n = pairs / (int)units, most = n < MAX_UNIT_SPLITS ? n : MAX_UNIT_SPLITS;
-  if (tiles > (f32 ? 8 : 16) && tiles <= 32 && (f32 || wide) && ceil_div(tiles, 4) <= n) {
+  if (tiles > (f32 ? 12 : 24) && tiles <= 32 && (f32 || wide) && ceil_div(tiles, 4) <= n) {
     s.nw = 4;
     s.min_tiles = 5;
   } else {
@@ -704,7 +707,7 @@ Split split_rule(const Problem& pb, int pairs) {
     s.min_tiles = f32 ? (n > 2 ? 9 : 14) : wide ? (n > 2 ? 17 : 41) : (n > 2 ? 25 : 57);
     if (n == 2 && pb.dtype == RLDA_BF16 && !wide && units * pb.Ls_cap > (int64_t)512 * pairs) return s;
   }
-  if (tiles >= s.min_tiles) s.splits = most < ceil_div(tiles, s.nw) ? most : ceil_div(tiles, s.nw);
+  if (2 * tiles >= 3 * s.min_tiles) s.splits = most < ceil_div(tiles, s.nw) ? most : ceil_div(tiles, s.nw);
   return s;
 }
 

@@ -20,12 +20,12 @@ def of(dtype, d, units, r, Lp, Ls, scale=0.1, **kw):
 
 
 @pytest.mark.parametrize("dtype,d,units,r,Lp,Ls,want", [
-    (F32, 64, 2, 1, 128, 128, 1), (F32, 64, 2, 1, 129, 128, 3), (F32, 64, 2, 1, 512, 512, 8), (F32, 64, 2, 1, 513, 512, 5),
+    (F32, 64, 2, 1, 192, 192, 1), (F32, 64, 2, 1, 193, 192, 4), (F32, 64, 2, 1, 512, 512, 8), (F32, 64, 2, 1, 513, 512, 5),
     (F32, 64, 2, 1, 4000, 4000, 16), (F32, 64, 64, 7, 256, 256, 4), (F32, 64, 64, 7, 512, 512, 4), (F32, 64, 85, 4, 2048, 64, 3),
-    (F32, 64, 128, 4, 192, 224, 1), (F32, 64, 128, 4, 208, 224, 2), (F32, 64, 129, 4, 4000, 64, 1), (F32, 128, 2, 4, 1000, 1000, 16),
-    (BF16, 64, 2, 4, 384, 384, 1), (BF16, 64, 2, 4, 384, 416, 4), (BF16, 64, 32, 4, 64, 4000, 8), (BF16, 64, 86, 4, 1792, 0, 1),
-    (BF16, 64, 86, 4, 1824, 0, 2), (BF16, 64, 128, 4, 2048, 1024, 2), (BF16, 64, 128, 4, 2048, 1025, 1), (E4M3, 64, 128, 4, 2048, 1025, 2),
-    (BF16, 64, 64, 17, 2000, 0, 2), (BF16, 64, 65, 17, 2000, 0, 1), (BF16, 64, 0, 4, 2000, 2000, 1), (E4M3, 64, 4, 16, 30000, 9, 16)])
+    (F32, 64, 128, 4, 320, 320, 1), (F32, 64, 128, 4, 321, 320, 2), (F32, 64, 129, 4, 4000, 64, 1), (F32, 128, 2, 4, 1000, 1000, 16),
+    (BF16, 64, 2, 4, 592, 576, 1), (BF16, 64, 2, 4, 592, 608, 5), (BF16, 64, 32, 4, 64, 4000, 8), (BF16, 64, 86, 4, 2720, 0, 1),
+    (BF16, 64, 86, 4, 2752, 0, 2), (BF16, 64, 128, 4, 2048, 1024, 2), (BF16, 64, 128, 4, 2048, 1025, 1), (E4M3, 64, 128, 4, 2048, 1025, 2),
+    (BF16, 64, 64, 17, 2800, 0, 2), (BF16, 64, 65, 17, 2800, 0, 1), (BF16, 64, 0, 4, 2000, 2000, 1), (E4M3, 64, 4, 16, 30000, 9, 16)])
 def test_how_many_workgroups_share_a_unit(dtype, d, units, r, Lp, Ls, want):
     assert of(dtype, d, units, r, Lp, Ls) == want
 
