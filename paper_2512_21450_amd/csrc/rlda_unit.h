@@ -854,22 +854,36 @@ bool unit_pays(const Problem& pb, int pairs) {
 }
 
 // Where one launch beats the shared-prefix path's two.  The lengths live on the device, so the line is drawn on the
-// capacities and has to hold when they are full; shorter sequences favour the single launch further.  A unit is one
-// workgroup's work from end to end and reads the shared levels once per sequence, so both paths were timed by units x
-// (prefix + suffix) keys, suffixes full, bf16, us per call here / shared-prefix path:
-//    64 x (1024 + 512)  14.6 / 14.2   128 x (512 + 2048)  34.5 / 37.2   256 x (1024 + 512)  20.2 / 25.9
-//    64 x (1536 + 512)  17.4 / 16.4   128 x (16 + 4000)   53.4 / 53.7   512 x (512 + 512)   34.8 / 38.4
-//    64 x (16 + 4000)   46.0 / 36.7  1024 x (512 + 16)    22.8 / 23.3  1024 x (16 + 512)    53.1 / 56.4
-// and on e4m3 stores 64 x (1024 + 1024) 18.0 / 14.4, 1024 x (512 + 16) 22.9 / 21.7.  Units of hardly any key, which
-// wait for nothing but their turn: 16384 x (16 + 16) 58 / 70, 65536 x (1 + 1) 163 / 149.  All on 256 compute units; the
-// number of units that fills the chip follows the device's, as the other path does (2048 keys per workgroup pair).
-// Since rows of many parts are merged by several teams of lanes, up to 32 units of 1500 keys and more run faster over there
-// (16 x (1024 + 512) 13.4 / 12.8, 32 x (512 + 2048) half full 19.4 / 16.1), but with weights of 8 bits where this kernel keeps
-// 16, so the line stands.
+// capacities; shorter sequences favour the single launch further.  Full buffers, us (256 pairs):
+//   * here about 4 + 0.87 per 1000 tiles walked, shared ones once per sequence, or 2.6 per 1000 tiles that come from memory (e4m3
+//     1.4), if that is more; places that workgroups leave empty cost as if they walked too;
+//   * over there about 12 + 2.5 per 1000 tiles that come from memory (e4m3 1.4), and 1 to 2 less where a group has 16 rows or fewer.
+// So the single launch wins unless long prefixes are shared by many.  P x G x Hkv, prefix + suffix keys, here / over there, bf16 with 4
+// rows per KV head:
+//   1 x 1 x 4   3500 + 500   8.2 / 14.8      2 x 16 x 1   500 + 3500  15.7 / 20.7     8 x 8 x 1  1200 + 1200 13.7 / 18.3
+//   8 x 8 x 1   3500 + 500  14.0 / 15.9      32 x 4 x 1  3500 + 500   21.1 / 26.0     3 x 8 x 4  3500 + 500  19.4 / 18.9
+//   8 x 16 x 1  3500 + 500  20.1 / 18.2      8 x 16 x 1  1200 + 1200  19.2 / 25.0     16 x 16 x 1 3500 + 500 32.0 / 26.1
+//   32 x 4 x 1   500 + 3500 45.4 / 47.2      32 x 8 x 1  2048 + 256   20.2 / 22.8     32 x 16 x 1 600 + 600  34.5 / 39.0
+// with 1 row 8 x 16 x 1 2048 + 256 14.5 / 13.3, with 8 32 x 8 x 1 2048 + 256 20.5 / 25.5; e4m3 32 x 8 x 1 64 + 2000 23.7 / 32.3, 64 x 8 x 1
+// 49.1 / 51.6, 16 x 16 x 1 2048 + 256 18.7 / 16.4, 3500 + 500 29.1 / 19.7.  Beyond 20 000 tiles (e4m3 32 768) units differ in length too
+// much: half full, 64 x 8 x 1 64 + 2000 59 / 51.  Groups of 16 rows or fewer, which share little and are read at the memory's rate either
+// way, stay at 16 384.  Units of hardly any key, which wait for nothing but their turn: 16384 x (16 + 16) 58 / 70, 65536 x (1 + 1)
+// 163 / 149.  Stores of up to 2048 suffix rows and 3600 in all, prefix rows counted three times, are always taken up to 16 384 tiles: the
+// other path is up to twice as slow there with many short units.  Longer units than 8960 keys were not measured.  Trees of several levels over stores of more than 2048 suffix rows stay on
+// the shared-prefix kernels, whatever is faster: a tree call has no algo field, and that is how a caller, and the tests, take it there.
 bool unit_preferred(const Problem& pb, int pairs) {
-  const int64_t shared = shared_cap(pb);
-  return pb.Ls_cap <= 2048 && 3 * shared + pb.Ls_cap <= 3600 && n_sequences(pb) * pb.Hkv <= (int64_t)64 * pairs &&
-         n_sequences(pb) * pb.Hkv * (shared + pb.Ls_cap) <= (int64_t)2048 * pairs && unit_supported(pb, pairs);
+  const int64_t units = n_sequences(pb) * pb.Hkv, keys = shared_cap(pb) + pb.Ls_cap;
+  const bool f8 = pb.dtype == RLDA_BF16_KV8, few = max_group(pb) * (pb.Hq / pb.Hkv) <= 16;
+  if (pb.Ls_cap <= 2048 && 3 * shared_cap(pb) + pb.Ls_cap <= 3600 && units <= (int64_t)64 * pairs && units * keys <= (int64_t)2048 * pairs)
+    return unit_supported(pb, pairs);
+  if (keys > 8960 || (pb.n_levels > 1 && pb.Ls_cap > 2048) || units > (int64_t)64 * pairs) return false;
+  if (units * keys > (f8 ? 4096 : few ? 2048 : 2560) * (int64_t)pairs || !unit_supported(pb, pairs)) return false;
+  int64_t read = units * pb.Ls_cap + (int64_t)pb.P * pb.Hkv * pb.Lp_cap;                  // keys that come from memory
+  for (int l = 0; l < pb.n_levels; ++l) read += (int64_t)pb.levels[l].n_seg * pb.Hkv * pb.levels[l].cap;
+  // places that the workgroups leave empty cost as if they walked too
+  const int64_t blocks = units * split_rule(pb, pairs).splits, places = units > pairs ? 2 * (int64_t)pairs : pairs;
+  const int64_t walked = blocks < places ? units * keys * places / blocks : units * keys;
+  return 4 * walked <= (int64_t)(few ? 4 * 560 : 4 * 864) * pairs + (f8 ? 6 : 11) * read;
 }
 
 size_t unit_workspace_bytes(const Problem& pb) {

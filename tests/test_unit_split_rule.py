@@ -35,3 +35,21 @@ def test_what_is_never_shared():
     paged = lambda page, pages: B.rl_decode_attn_paged_workspace_bytes(
         B.make_paged_desc(F32, 2, 1, 1, 1, 64, 1000, page, pages, 2 * pages, 0.1))
     assert paged(16, 100) == 0 and splits(paged(32, 50), 2, 2, 64) == 11      # pages of fewer rows than a tile
+
+
+@pytest.mark.parametrize("dtype,P,G,Hkv,r,Lp,Ls,want", [
+    (BF16, 1, 1, 4, 4, 3500, 500, "UNIT"), (BF16, 8, 8, 1, 4, 3500, 500, "UNIT"), (BF16, 8, 16, 1, 4, 3500, 500, "SHARED"),
+    (BF16, 8, 16, 1, 4, 1200, 1200, "UNIT"), (BF16, 16, 16, 1, 4, 3500, 500, "SHARED"), (BF16, 32, 16, 1, 4, 600, 600, "UNIT"),
+    (BF16, 32, 8, 1, 1, 1200, 1200, "SHARED"), (BF16, 32, 8, 1, 4, 1200, 1200, "UNIT"), (BF16, 8, 16, 1, 1, 2048, 256, "SHARED"),
+    (E4M3, 32, 8, 1, 4, 64, 2000, "UNIT"), (E4M3, 16, 16, 1, 4, 2048, 256, "SHARED"), (E4M3, 32, 8, 1, 4, 2000, 2097, "SHARED"),
+    (BF16, 1, 1, 1, 4, 4480, 4480, "UNIT"), (BF16, 1, 1, 1, 4, 4480, 4481, "SHARED")])
+def test_where_one_launch_is_taken_instead_of_two(dtype, P, G, Hkv, r, Lp, Ls, want):
+    """The sides of the rule as measured, on 256 compute units."""
+    ds = B.make_desc(dtype, P, G, Hkv * r, Hkv, 128, Lp, Ls, 0.1)
+    assert B.rl_decode_attn_debug_route(ds, 256) == (B.RLDA_ROUTE_UNIT if want == "UNIT" else B.RLDA_ALGO_SHARED)
+    assert B.rl_decode_attn_workspace_bytes(ds) > 0                            # the plan's, either way
+    for levels in (1, 2):                                                      # a tree of one level is that call; see the rule for two
+        lv = [(None, None, None, G, Lp // levels)] * levels
+        if dtype == BF16 and G * r <= 64:
+            tree = B.rl_decode_attn_debug_route(B.make_tree_desc(dtype, P * G, Hkv * r, Hkv, 128, Ls, 0.1, lv), 256)
+            assert tree == (B.RLDA_ROUTE_UNIT if want == "UNIT" and (levels == 1 or Ls <= 2048) else B.RLDA_ALGO_SHARED)
