@@ -8,7 +8,7 @@
 //   m, s = sum e^(a-m), t = sum e^(a-m) a          for a = logits * inv_temperature
 //   mr, sr = sum e^(b-mr), u = sum e^(a-m) b       for b = ref_logits * inv_temperature
 // which is merged over the wavefront (xor shuffles), the workgroup (LDS) and, when S > 1, the
-// splits (second kernel, one wavefront per row).  Then
+// splits (one wavefront per row: of the row's last workgroup to end, or of a second kernel).  Then
 //   lse = m + ln s, entropy = lse - t/s, kl = (t - u)/s - lse + (mr + ln sr).
 // All merges have a fixed order, so results do not change from call to call.
 //
@@ -22,6 +22,7 @@
 #include <stdint.h>
 
 #include "../../include/rl_token_logprob.h"
+#include "rlda_arrive.h"
 
 namespace {
 
@@ -35,7 +36,9 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 struct Params {
   const char* logits; const char* ref; const int32_t* ids;
   float* logprob; float* lse; float* entropy; float* ref_logprob; float* kl;
-  float* part;                     // [n_rows][S][6]
+  float* part;                     // [n_rows][slots][6]
+  int slots;                       // per row: S, one launch: and one more
+  uint64_t call;                   // one launch: the call's number
   long long stride;                // elements
   int V, S, chunk;                 // chunk: elements per split, multiple of the vector width
   float k2;                        // inv_temperature * log2(e): logits -> base-2 exponents
@@ -152,11 +155,28 @@ __device__ __forceinline__ void finish_row(const Params& P, long long row, const
   }
 }
 
+// lane i of a wavefront has split i, merged in a fixed butterfly order
+template <typename T, bool REF>
+__device__ __forceinline__ void merge_row(const Params& P, long long row, Acc A, int lane) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) A = acc_merge<REF>(A, acc_shfl_xor<REF>(A, o));
+  if (lane == 0) {
+    const char* za = P.logits + (size_t)row * P.stride * sizeof(T);
+    const char* zb = REF ? P.ref + (size_t)row * P.stride * sizeof(T) : nullptr;
+    const int y = P.ids[row];
+    const bool ok = y >= 0 && y < P.V;
+    finish_row<REF>(P, row, A, ok ? Elem<T>::one(za, y) * P.k2 : 0.f,
+                    REF && ok ? Elem<T>::one(zb, y) * P.k2 : 0.f, y);
+  }
+}
+
+// ONE: the last of a row's workgroups to end merges what they left, its counter stands behind their states.
 // workgroup row * S + split: partial state of elements [split * chunk, min(V, (split + 1) * chunk)) of a row
-template <typename T, bool REF, int NT>
+template <typename T, bool REF, int NT, bool ONE = false>
 __global__ void __launch_bounds__(NT) token_partial_kernel(const Params P) {
   constexpr int VN = Elem<T>::VN;
   __shared__ Acc red[NT / 64];
+  __shared__ bool last;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const long long row = blockIdx.x / P.S;
   const int split = blockIdx.x % P.S;
@@ -164,6 +184,10 @@ __global__ void __launch_bounds__(NT) token_partial_kernel(const Params P) {
   const char* zb = REF ? P.ref + (size_t)row * P.stride * sizeof(T) : nullptr;
   const int c0 = split * P.chunk, c1 = min(P.V, c0 + P.chunk);
   const int v0 = c0 / VN, v1 = max(c1, c0) / VN;           // whole vectors [v0, v1)
+  uint64_t* const slots = reinterpret_cast<uint64_t*>(P.part) + (size_t)row * P.slots * 3;
+  uint64_t* const counter = slots + P.S * 3;
+  uint64_t seen = 0;
+  if (ONE && tid == 0) seen = rlda::claim(counter, P.call);
   Acc A = acc_empty();
   for (int v = v0 + tid; v < v1; v += NT * UNR) {
     u32x4 ra[UNR], rb[UNR];
@@ -205,7 +229,14 @@ __global__ void __launch_bounds__(NT) token_partial_kernel(const Params P) {
     Acc R = red[0];
 #pragma unroll
     for (int k = 1; k < NT / 64; ++k) R = acc_merge<REF>(R, red[k]);
-    if (P.S == 1) {
+    if (ONE) {
+      uint64_t* const o = slots + split * 3;
+      rlda::put(o, R.m, R.s);
+      rlda::put(o + 1, R.t, R.mr);
+      if (REF) rlda::put(o + 2, R.sr, R.u);
+      rlda::stores_done();
+      last = rlda::arrive(counter, P.call, seen, P.S);
+    } else if (P.S == 1) {
       const int y = P.ids[row];
       const bool ok = y >= 0 && y < P.V;
       finish_row<REF>(P, row, R, ok ? Elem<T>::one(za, y) * P.k2 : 0.f,
@@ -215,9 +246,20 @@ __global__ void __launch_bounds__(NT) token_partial_kernel(const Params P) {
       o[0] = R.m; o[1] = R.s; o[2] = R.t; o[3] = R.mr; o[4] = R.sr; o[5] = R.u;
     }
   }
+  if constexpr (ONE) {
+    __syncthreads();
+    if (!last || wv > 0) return;
+    Acc W = acc_empty();
+    if (lane < P.S) {
+      const uint64_t* const o = slots + lane * 3;
+      const float2 a = rlda::get(o), b = rlda::get(o + 1), c = REF ? rlda::get(o + 2) : make_float2(0.f, 0.f);
+      W = Acc{a.x, a.y, b.x, b.y, c.x, c.y};
+    }
+    merge_row<T, REF>(P, row, W, lane);
+  }
 }
 
-// one wavefront per row: lane i takes split i, merged in a fixed butterfly order
+// one wavefront per row
 template <typename T, bool REF>
 __global__ void __launch_bounds__(64) token_final_kernel(const Params P) {
   const long long row = blockIdx.x;
@@ -227,16 +269,7 @@ __global__ void __launch_bounds__(64) token_final_kernel(const Params P) {
     const float* o = P.part + ((size_t)row * P.S + lane) * 6;
     A = Acc{o[0], o[1], o[2], o[3], o[4], o[5]};
   }
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) A = acc_merge<REF>(A, acc_shfl_xor<REF>(A, o));
-  if (lane == 0) {
-    const char* za = P.logits + (size_t)row * P.stride * sizeof(T);
-    const char* zb = REF ? P.ref + (size_t)row * P.stride * sizeof(T) : nullptr;
-    const int y = P.ids[row];
-    const bool ok = y >= 0 && y < P.V;
-    finish_row<REF>(P, row, A, ok ? Elem<T>::one(za, y) * P.k2 : 0.f,
-                    REF && ok ? Elem<T>::one(zb, y) * P.k2 : 0.f, y);
-  }
+  merge_row<T, REF>(P, row, A, lane);
 }
 
 int check(const rl_token_logprob_desc* d) {
@@ -253,7 +286,7 @@ int check(const rl_token_logprob_desc* d) {
 }
 
 // Splits per row.  What bounds a call of few rows is the dependent rounds of loads of a thread (256 threads take 16 KB of a row
-// a round); the merge of the splits is a launch of its own, 2 us.  us, captured, inputs changing, rows x logits; with a
+// a round); the merge of the splits costs 1 to 2 us.  us, captured and merged by a launch of its own, inputs changing, rows x logits; with a
 // reference: [R].
 //   * Fewer than 64 rows: at least 12 splits, and three workgroups of 256 threads a compute unit, down to 8 KB of a row each;
 //     where 64 splits, the merge's limit, still leave more than 32 KB, workgroups of 1024 threads.  12 splits / as many as the
@@ -304,6 +337,13 @@ int splits_with_less(const rl_token_logprob_desc* d) {
   if (d->n_rows <= 0 || d->n_rows >= 192) return 1;
   return clamp_splits((256 + d->n_rows - 1) / d->n_rows, d->vocab / 8192);
 }
+// The last workgroup of a row merges its splits where a call is so short that the host's second launch (4.4 us) is most of what it
+// waits for; the counter takes one split's place, which long calls pay more for than the launch they save.  (By the logits alone, so that
+// what does not depend on a reference keeps its bits without one.)  us, calls one after the other from Python (captured), two launches / one:
+//   16 x 32000 bf16 16.5 (5.6) / 14.0 (5.2)      48 x 151936 bf16 [R] 18.9 (12.8) / 16.7 (12.5)   150 x 50001 fp32 [R] 19.7 (16.2) / 17.2 (15.8)
+//   257 x 32000 bf16 [R] 19.9 (13.7) / 17.2 (13.4)   100 x 151936 fp32 [R] 25.3 (24.9) / 25.9 (25.8)   448 x 151936 bf16 [R] 52.6 / 56.7
+//   1 x 151936 fp32 [R], 63 workgroups on one counter: 19.9 (6.1) / 17.5 (7.0)
+constexpr long long ONE_LAUNCH = 48 * 1000 * KB;             // bytes of logits
 size_t bytes_for(const rl_token_logprob_desc* d, int S) { return S == 1 ? 0 : (size_t)d->n_rows * S * PER_SPLIT; }
 
 thread_local hipError_t g_last = hipSuccess;
@@ -333,22 +373,32 @@ int rl_token_logprob(const rl_token_logprob_desc* d, void* hip_stream) {
   if (less) S = splits_with_less(d);
   if (!fits(S)) return -3;
   const int vn = d->dtype == 0 ? 4 : 8;
-  Params P;
+  Params P{};
   P.logits = static_cast<const char*>(d->logits); P.ref = static_cast<const char*>(d->ref_logits);
   P.ids = d->token_ids;
   P.logprob = d->logprob; P.lse = d->lse; P.entropy = d->entropy; P.ref_logprob = d->ref_logprob; P.kl = d->kl;
   P.part = static_cast<float*>(d->workspace);
-  P.stride = d->row_stride; P.V = d->vocab; P.S = S;
+  const bool ref = d->ref_logits != nullptr;
+  P.stride = d->row_stride; P.V = d->vocab; P.slots = S;
+  const bool one = S > 2 && row_bytes(d) * d->n_rows <= ONE_LAUNCH;
+  if (one) { P.call = rlda::next_call(); --S; }             // the last slot is the counter's
+  P.S = S;
   const int per = (d->vocab + S - 1) / S;
   P.chunk = (per + vn - 1) / vn * vn;
   P.k2 = d->inv_temperature * 1.4426950408889634f;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const dim3 grid((unsigned)(d->n_rows * S)), fin((unsigned)d->n_rows);
-  const bool ref = d->ref_logits != nullptr;
   // few workgroups, each with more than two rounds of loads for 256 threads (or none to share a row with): 16 wavefronts
   const bool wide = d->n_rows * S <= 512 && (S == 1 || less || row_bytes(d) / S > ROUNDS);
 #define RLTL_LAUNCH(T)                                                                                      \
   do {                                                                                                      \
+    if (one) {                                                                                              \
+      if (wide && ref) hipLaunchKernelGGL((token_partial_kernel<T, true, 1024, true>), grid, dim3(1024), 0, st, P);   \
+      else if (wide)   hipLaunchKernelGGL((token_partial_kernel<T, false, 1024, true>), grid, dim3(1024), 0, st, P);  \
+      else if (ref)    hipLaunchKernelGGL((token_partial_kernel<T, true, 256, true>), grid, dim3(256), 0, st, P);     \
+      else             hipLaunchKernelGGL((token_partial_kernel<T, false, 256, true>), grid, dim3(256), 0, st, P);    \
+      break;                                                                                                \
+    }                                                                                                       \
     if (wide) {                                                                                             \
       if (ref) hipLaunchKernelGGL((token_partial_kernel<T, true, 1024>), grid, dim3(1024), 0, st, P);       \
       else     hipLaunchKernelGGL((token_partial_kernel<T, false, 1024>), grid, dim3(1024), 0, st, P);      \
