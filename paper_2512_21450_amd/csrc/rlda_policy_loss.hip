@@ -1,7 +1,7 @@
 // Scoring, group advantage estimation and the clipped policy loss (Eq. 6 of the paper; Sec. 3.2.2
 // scoring, advantage-estimation and policy-update stages).  Element-wise work over [B] and [B, T]
 // arrays with deterministic reductions: per-thread partial sums in a fixed order, a fixed tree
-// inside the workgroup, and a further kernel that folds the per-sequence sums in fp64.
+// inside the workgroup, and a fold of the per-sequence sums in fp64 by the last workgroup to end or by a further kernel.
 //
 // rl_group_advantage: one workgroup per prompt.  The group's mean and deviations are taken in
 // fp64: with fp32 a group whose samples all earned the same reward can get a mean one ulp off and,
@@ -14,6 +14,7 @@
 #include <stdint.h>
 
 #include "../../include/rl_policy_loss.h"
+#include "rlda_arrive.h"
 
 namespace {
 
@@ -85,7 +86,9 @@ struct LossParams {
   const int32_t* lens;
   float* grad; float* stats;
   long long* counts;                                        // [2] valid tokens, sequences with tokens (first 256 workspace bytes)
-  float* part;                                              // [B][8] per-sequence sums
+  uint64_t* part;                                           // [B][4] per-sequence sums in pairs of floats; behind them a group's counter
+  uint64_t* groups_done;                                    // a counter (behind the counts)
+  uint64_t call;                                            // its number
   int B, T, form, agg;
   int64_t stride;
   float lo, hi, beta_kl, beta_ent;
@@ -131,6 +134,65 @@ __global__ void __launch_bounds__(NB) policy_count_kernel(const LossParams L) {
   }
 }
 
+// per-sequence sums -> batch statistics, in fp64 and in a fixed order: a thread's sequences in turn, the lanes of a
+// wavefront by a butterfly, the wavefronts in order.  SAME: of a launch whose other workgroups wrote them, past the caches
+template <int N, bool SAME>
+__device__ __forceinline__ void reduce_parts(const LossParams& L, long long n_tok, long long n_seq) {
+  constexpr int NW = N / 64;
+  __shared__ double sh[6][NW];
+  const int tid = threadIdx.x;
+  const double wt = n_tok > 0 ? 1.0 / (double)n_tok : 0.0;
+  double acc[6] = {0, 0, 0, 0, 0, 0};
+  constexpr int U = 4;
+  for (int b0 = tid; b0 < L.B; b0 += U * N) {
+    int len[U];
+    float4 p[U];
+    float2 q[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int b = min(b0 + k * N, L.B - 1);
+      len[k] = b0 + k * N < L.B ? L.lens[b] : 0;
+      const uint64_t* const at = L.part + (size_t)b * 4;
+      if (SAME) {
+        const float2 x = rlda::get(at), z = rlda::get(at + 1);
+        p[k] = make_float4(x.x, x.y, z.x, z.y);
+        q[k] = rlda::get(at + 2);
+      } else {
+        p[k] = *reinterpret_cast<const float4*>(at);
+        q[k] = *reinterpret_cast<const float2*>(at + 2);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int n = clamp_len(len[k], L.T);
+      if (n == 0) continue;
+      const double wa = L.agg == RL_AGG_SEQ_MEAN ? 1.0 / ((double)n * (double)n_seq) : wt;
+      acc[0] += wa * p[k].x; acc[1] += wa * p[k].y; acc[2] += wa * p[k].z;
+      acc[3] += wt * p[k].w; acc[4] += wt * q[k].x; acc[5] += wt * q[k].y;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 6; ++k) acc[k] = wave_sum(acc[k]);
+  if ((tid & 63) == 0) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) sh[k][tid >> 6] = acc[k];
+  }
+  __syncthreads();
+  if (tid < 64) {
+    double t = 0.0;
+    if (tid < 6) {
+#pragma unroll
+      for (int k = 0; k < NW; ++k) t += sh[tid][k];
+      L.stats[tid + 1] = (float)t;
+    }
+    const double kl = __shfl(t, 1, 64), ent = __shfl(t, 2, 64);
+    if (tid == 0) {
+      L.stats[0] = (float)(-t + (double)L.beta_kl * kl - (double)L.beta_ent * ent);
+      L.stats[7] = (float)n_tok;
+    }
+  }
+}
+
 // per-token arithmetic; accumulates into sums[6] = (term, kl, entropy, flat-branch count, rho, old - new)
 __device__ __forceinline__ float token_term(const LossParams& L, float lp, float old, float kl, float ent, float A,
                                             float w, float (&sums)[6]) {
@@ -160,10 +222,16 @@ __device__ __forceinline__ float token_term(const LossParams& L, float lp, float
 // row's end.  A thread adds its tokens in increasing t, the 64 lanes of a wavefront are folded by a fixed butterfly and the
 // four wavefronts in order, so the sums do not depend on anything but the data.
 constexpr int COUNT_MAX = 1024;
+// ONE: the last workgroup to end reduces, which saves the launch behind; the others meet in groups of GROUP first, so that few wait
+// for one counter.  A workgroup stays 1 to 2 us longer for it, so up to ONE_MAX sequences only, whose workgroups are all there at
+// once.  us, advantages and loss, captured (from Python), two or three launches / one or two: 8 sequences 11.8 (20.5) / 10.1 (18.2),
+// 1024 13.7 (21.9) / 12.9 (19.3), 2048 17.2 (24.9) / 16.9 (22.2); 4096 20.4 (25.0) / 22.9 (23.6), 8192 27.7 / 34.4.
+constexpr int GROUP = 64, ONE_MAX = 2048;
+static_assert(COUNT_MAX <= ONE_MAX && GROUP <= rlda::MAX_ARRIVALS && (ONE_MAX + GROUP - 1) / GROUP <= rlda::MAX_ARRIVALS, "a counter holds no more");
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4u __attribute__((aligned(4)));
 
-template <bool COUNT>
+template <bool COUNT, bool ONE>
 __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
   __shared__ float shf[NT / 64][6];
   const int tid = threadIdx.x;
@@ -191,6 +259,9 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
     n_tok = L.counts[0]; n_seq = L.counts[1];
   }
   const int b = blockIdx.x;
+  uint64_t* const group = L.part + (size_t)(b / GROUP * GROUP) * 4 + 3;
+  uint64_t seen = 0;
+  if (ONE && tid == 0) seen = rlda::claim(group, L.call);
   const unsigned len = clamp_len(L.lens[b], L.T);
   float w = 0.f;                                          // weight of one of this sequence's tokens in the aggregate
   if (len > 0) w = L.agg == RL_AGG_SEQ_MEAN ? (float)(1.0 / ((double)len * (double)n_seq)) : (float)(1.0 / (double)n_tok);
@@ -227,59 +298,27 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
     for (int k = 0; k < 6; ++k) shf[tid >> 6][k] = sums[k];
   }
   __syncthreads();
-  if (tid < 6) L.part[(size_t)b * 8 + tid] = ((shf[0][tid] + shf[1][tid]) + shf[2][tid]) + shf[3][tid];
-}
-
-// per-sequence sums -> batch statistics, in fp64 and in a fixed order: a thread's sequences in turn, the lanes of a
-// wavefront by a butterfly, the wavefronts in order
-__global__ void __launch_bounds__(NB) policy_loss_reduce_kernel(const LossParams L) {
-  __shared__ double sh[6][NBW];
-  const int tid = threadIdx.x;
-  const long long n_tok = L.counts[0], n_seq = L.counts[1];
-  const double wt = n_tok > 0 ? 1.0 / (double)n_tok : 0.0;
-  double acc[6] = {0, 0, 0, 0, 0, 0};
-  constexpr int U = 4;
-  for (int b0 = tid; b0 < L.B; b0 += U * NB) {
-    int len[U];
-    float4 p[U];
-    float2 q[U];
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int b = min(b0 + k * NB, L.B - 1);
-      len[k] = b0 + k * NB < L.B ? L.lens[b] : 0;
-      p[k] = *reinterpret_cast<const float4*>(L.part + (size_t)b * 8);
-      q[k] = *reinterpret_cast<const float2*>(L.part + (size_t)b * 8 + 4);
-    }
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int n = clamp_len(len[k], L.T);
-      if (n == 0) continue;
-      const double wa = L.agg == RL_AGG_SEQ_MEAN ? 1.0 / ((double)n * (double)n_seq) : wt;
-      acc[0] += wa * p[k].x; acc[1] += wa * p[k].y; acc[2] += wa * p[k].z;
-      acc[3] += wt * p[k].w; acc[4] += wt * q[k].x; acc[5] += wt * q[k].y;
-    }
+  if constexpr (!ONE) {
+    if (tid < 6) reinterpret_cast<float*>(L.part)[(size_t)b * 8 + tid] = ((shf[0][tid] + shf[1][tid]) + shf[2][tid]) + shf[3][tid];
+    return;
   }
-#pragma unroll
-  for (int k = 0; k < 6; ++k) acc[k] = wave_sum(acc[k]);
-  if ((tid & 63) == 0) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) sh[k][tid >> 6] = acc[k];
+  if (tid < 3) {
+    const auto sum = [&](int k) { return ((shf[0][k] + shf[1][k]) + shf[2][k]) + shf[3][k]; };
+    rlda::put(L.part + (size_t)b * 4 + tid, sum(2 * tid), sum(2 * tid + 1));
+    rlda::stores_done();
+  }
+  __shared__ bool last;
+  __syncthreads();
+  if (tid == 0) {
+    const int groups = (L.B + GROUP - 1) / GROUP;
+    last = rlda::arrive(group, L.call, seen, min(GROUP, L.B - b / GROUP * GROUP));
+    if (last) last = rlda::arrive(L.groups_done, L.call, rlda::claim(L.groups_done, L.call), groups);
   }
   __syncthreads();
-  if (tid < 64) {
-    double t = 0.0;
-    if (tid < 6) {
-#pragma unroll
-      for (int k = 0; k < NBW; ++k) t += sh[tid][k];
-      L.stats[tid + 1] = (float)t;
-    }
-    const double kl = __shfl(t, 1, 64), ent = __shfl(t, 2, 64);
-    if (tid == 0) {
-      L.stats[0] = (float)(-t + (double)L.beta_kl * kl - (double)L.beta_ent * ent);
-      L.stats[7] = (float)n_tok;
-    }
-  }
+  if (last) reduce_parts<NT, true>(L, n_tok, n_seq);
 }
+
+__global__ void __launch_bounds__(NB) policy_loss_reduce_kernel(const LossParams L) { reduce_parts<NB, false>(L, L.counts[0], L.counts[1]); }
 
 int check(const rl_policy_loss_desc* d) {
   if (!d) return -1;
@@ -328,21 +367,26 @@ int rl_policy_loss(const rl_policy_loss_desc* d, void* hip_stream) {
   L.lp = d->logprob; L.old = d->old_logprob; L.adv = d->advantages; L.kl = d->kl; L.ent = d->entropy;
   L.lens = d->lens; L.grad = d->grad_logprob; L.stats = d->stats;
   L.counts = static_cast<long long*>(d->workspace);
-  L.part = reinterpret_cast<float*>(static_cast<char*>(d->workspace) + 256);
+  L.groups_done = reinterpret_cast<uint64_t*>(L.counts + 2);
+  L.part = reinterpret_cast<uint64_t*>(static_cast<char*>(d->workspace) + 256);
   L.B = d->B; L.T = d->T; L.form = d->form; L.agg = d->agg; L.stride = d->row_stride;
   L.lo = 1.f - d->clip_low; L.hi = 1.f + d->clip_high; L.beta_kl = d->beta_kl; L.beta_ent = d->beta_ent;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const bool own = d->B > 0 && d->B <= COUNT_MAX;           // the token pass counts for itself
+  const bool one = d->B > 0 && d->B <= ONE_MAX;             // and reduces
+  L.call = one ? rlda::next_call() : 0;
   if (!own) {
     hipLaunchKernelGGL(policy_count_kernel, dim3(1), dim3(NB), 0, st, L);
     if (hipGetLastError() != hipSuccess) return -5;
   }
   if (d->B > 0) {
     const dim3 grid(d->B);
-    if (own) hipLaunchKernelGGL(policy_loss_kernel<true>, grid, dim3(NT), 0, st, L);
-    else     hipLaunchKernelGGL(policy_loss_kernel<false>, grid, dim3(NT), 0, st, L);
+    if (own)      hipLaunchKernelGGL((policy_loss_kernel<true, true>), grid, dim3(NT), 0, st, L);
+    else if (one) hipLaunchKernelGGL((policy_loss_kernel<false, true>), grid, dim3(NT), 0, st, L);
+    else          hipLaunchKernelGGL((policy_loss_kernel<false, false>), grid, dim3(NT), 0, st, L);
     if (hipGetLastError() != hipSuccess) return -5;
   }
+  if (one) return 0;
   hipLaunchKernelGGL(policy_loss_reduce_kernel, dim3(1), dim3(NB), 0, st, L);
   return hipGetLastError() == hipSuccess ? 0 : -5;
 }
