@@ -1160,40 +1160,72 @@ __global__ void __launch_bounds__(256, 8) combine16_kernel(const SharedParams P)
 // 16-row blocks, one per wavefront, and share every K/V tile through LDS exactly as the G * r rows
 // of a decode group do in prefix_stream; a lane's row sees the keys below its own limit
 // (position + 1).  No key split: a workgroup walks all tiles up to its last position, so rows are
-// normalised and written directly.  With many units all blocks of one (prompt, KV head) run on one XCD, one unit
-// after the other, from the end of the prompt (most tiles) to its start: workgroups are dealt to
-// the eight XCDs round-robin, so workgroup i belongs to XCD i % 8 and is the (i / 8)-th of its XCD;
-// with the units of an XCD laid out one after the other along that sequence, the 64 or so
-// workgroups an XCD runs at a time read the same K/V (a few hundred KB), which then stays in its
-// L2.  (Measured: spreading them over many units at a time made the pass wait on the fabric.)
+// normalised and written directly.  Workgroups are dealt to the eight XCDs round-robin: workgroup i belongs to
+// XCD i % 8 and is the (i / 8)-th of its XCD; which unit and block that is: prefill_place.
 struct PrefillParams {
   const char* q; const char* k; const char* v; const int32_t* lens;
   float* out; float* lse;
   int P, Hq, Hkv, r, Lp_cap, QB, nqb;
-  FastDiv div_Hkv, div_r, div_nqb, div_units;
-  int spread;                                               // the blocks of a unit go to all XCDs
+  FastDiv div_Hkv, div_r, div_chunk, div_units;             // div_chunk: by chunk * nqb, div_units: by chunk
+  int lg, chunk, turn, again;                               // see prefill_place
   float c;
 };
 constexpr int N_XCD = 8;
-// Whole units per XCD leave XCDs without work where their number is no multiple of eight and there
-// are few rounds of them: with the four units of a 28/4-head prompt half the chip stood still.  There
-// the blocks are dealt out one by one, the last block of every unit first, so that the long ones
-// start first and a round of short ones ends the pass.  Measured, whole units / spread, us:
-// 1 x 4096 tokens of 28/4 heads (4 units) 321 / 174, 1 x 1500 of 16/2 (2) 60.3 / 31.5, 6 x 512 of
-// 16/2 (12) 24.2 / 20.4, 3 x 2000 of 28/4 (12) 173 / 140, 7 ragged up to 4096 of 28/4 (28) 529 / 424,
-// 30 ragged up to 500 of 12/2 (60) 37.7 / 35.6; above, the working set of an XCD (every unit's K/V)
-// outgrows its L2 and the few empty places no longer cost that much: 41 x 700 of 16/2 (82) 153 / 165,
-// 50 of 12/2 (100) 54.5 / 56.1, 33 x 1500 of 28/4 (132) 358 / 375.
-inline bool prefill_spread(int units) { return units % N_XCD != 0 && units < 8 * N_XCD; }
-__device__ __forceinline__ void prefill_place(const PrefillParams& P, int b, int& pj, int& qb) {
-  if (P.spread) {
-    const int units = P.P * P.Hkv;
-    const int i = fast_div(b, P.div_units);
-    pj = b - i * units; qb = P.nqb - 1 - i;
-  } else {
-    const int xcd = b % N_XCD, seq = b / N_XCD, u = fast_div(seq, P.div_nqb);
-    pj = u * N_XCD + xcd; qb = P.nqb - 1 - (seq - u * P.nqb);
+// Where a workgroup belongs.  Groups of 1 << lg XCDs share out the units, unit u to group u % (8 >> lg); a group takes its units in
+// chunks and the blocks of a chunk one of every unit at a time, from the end of the prompts to their start: row i is block nqb - 1 - i
+// of every unit, and begins `turn` * (i + (i >> again)) units further (turn 0 or 1).  What that does, lg / chunk:
+// - 0 / 1, a unit after the other on one XCD: what is in flight there reads the K/V of one or two prompts, long and short blocks
+//   run beside each other.
+// - 0 / 8: where a unit has few blocks, its last ones no longer start beside the longest of the next.
+// - 1, 2 / 3, 4: a few ragged units per XCD leave some XCDs the long prompts.
+// The turn is for ragged prompts, whose empty workgroups are in every row at the same units: workgroups go round-robin to the XCDs
+// and, inside, to four shader engines, and an engine that got the same units in every row is left without work.  `again`: where four
+// workgroups of an XCD are several rows, turning by one unit a row brings an engine back to the same units (16 x 1500 of 7/1 heads 52.7
+// us without, 46.6; 8 x 640 of 14/1 18.5 / 17.1).
+struct PrefillOrder { int lg, chunk, turn, again; };
+// Measured (bf16, bits the same; all prompts full / ragged, us, before -> after, from 0 / 1):
+//   8 units, 2 / 4:       4 x 2744 of 16/2 heads 130 -> 130 / 95 -> 68, 8 x 2000 of 8/1 76 -> 78 / 65 -> 51, 2 x 3000 of 28/4 136 -> 137 /
+//                         82 -> 65, 8 x 640 of 14/1 28.3 -> 28.5 / 25.0 -> 17.1 (up to a round of blocks, two per compute unit, there
+//                         is nothing to win: 8 x 900 of 4/1 19.0 -> 19.6 / 17.9 -> 18.3)
+//   16, 24 units, 1 / 4 and 1 / 3:  8 x 1667 of 16/2 104 -> 102 / 62 -> 53, 16 x 1500 of 7/1 78 -> 78 / 55 -> 45, 6 x 737 of 32/4 42 ->
+//                         42 / 32 -> 25, 12 x 900 of 14/2 51 -> 50 / 38 -> 31 (up to two rounds: 8 x 512 of 16/2 20.4 -> 21.9 / 13.8 -> 14.2,
+//                         4 x 900 of 28/4 34.6 -> 37.7 / 28.2 -> 25.8: the longest blocks side by side)
+//   32 units, 0 / 8:      16 x 1500 of 2/2 40 -> 31 / 27.5 -> 26.7, 16 x 1000 of 10/2 61 -> 58 / 38 -> 33, 8 x 1500 of 20/4 116 -> 112 /
+//                         62 -> 55, 16 x 900 of 16/2 75.6 -> 74.4 / 43 -> 41
+//   more, <= 32 blocks, 0 / 8:  8 x 2048 of 8/8 110 -> 84 / 62 -> 50, 32 x 1280 of 4/4 87 -> 73 / 55 -> 44, 22 x 1100 of 12/4 118 -> 114 /
+//                         66 -> 63, 16 x 512 of 8/8 28 -> 22 / 18.5 -> 14.5, 41 x 800 of 4/2 (82 units) 50 -> 47 / 33 -> 30, 10 x 1000 of
+//                         32/8 115 -> 110 / 60 -> 61
+//   more of more blocks:  the short ones then come together, and what they wait for is not hidden by long ones: 10 x 684 of 64/8 (43
+//                         blocks a unit) 117 -> 121 / 61 -> 66, 32 x 600 of 16/2 (38) 75 -> 77 / 51 -> 49
+// A prompt whose heads go to all XCDs (Hkv a multiple of eight) is balanced as it is.
+// Not a multiple of eight and below 64 units: whole units per XCD leave XCDs without work (the four units of a 28/4-head prompt: half
+// the chip); all units to all XCDs, the last block of every unit first.  Measured, whole units / so, us: 1 x 4096 tokens of 28/4 heads
+// (4 units) 321 / 174, 1 x 1500 of 16/2 (2) 60.3 / 31.5, 6 x 512 of 16/2 (12) 24.2 / 20.4, 3 x 2000 of 28/4 (12) 173 / 140, 7 ragged
+// up to 4096 of 28/4 (28) 529 / 424, 30 ragged up to 500 of 12/2 (60) 37.7 / 35.6; above, the working set of an XCD (every unit's K/V)
+// outgrows its L2 and the few empty places no longer cost that much: 41 x 700 of 16/2 (82) 153 / 165, 50 of 12/2 (100) 54.5 / 56.1,
+// 33 x 1500 of 28/4 (132) 358 / 375.
+inline PrefillOrder prefill_order(int units, int Hkv, int64_t nqb, int64_t rounds) {
+  const int none = 31;
+  if (units % N_XCD != 0 && units < 8 * N_XCD) return {3, units, 0, none};
+  if (rounds <= 1) return {0, 1, 0, none};
+  if (Hkv % N_XCD != 0 && units == N_XCD) return {2, 4, 1, 2};
+  if (Hkv % N_XCD != 0 && units <= 3 * N_XCD) {
+    if (rounds <= 2) return {0, 1, 0, none};
+    return units == 2 * N_XCD ? PrefillOrder{1, 4, 1, 1} : PrefillOrder{1, 3, 1, none};
   }
+  return nqb <= 32 || (Hkv % N_XCD != 0 && units == 4 * N_XCD) ? PrefillOrder{0, 8, 1, none} : PrefillOrder{0, 1, 0, none};
+}
+__device__ __forceinline__ void prefill_place(const PrefillParams& P, int b, int& pj, int& qb) {
+  const int xcd = b & (N_XCD - 1), s = (b / N_XCD << P.lg) + (xcd & ((1 << P.lg) - 1));      // the s-th workgroup of its group
+  const int n = fast_div(s, P.div_chunk), in = s - n * P.chunk * P.nqb, i = fast_div(in, P.div_units);
+  int x = in - i * P.chunk;
+  if (P.turn) {
+    x += i + (i >> P.again);
+    x -= fast_div(x, P.div_units) * P.chunk;
+  }
+  const int u = n * P.chunk + x;
+  pj = u * (N_XCD >> P.lg) + (xcd >> P.lg);                 // may be none: the last chunk may not be full
+  qb = P.nqb - 1 - i;
 }
 
 template <int NTP>                                          // 16-row blocks per wavefront: the workgroup holds 64 * NTP rows
@@ -2002,11 +2034,16 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   }
   const PrefillForm form = prefill_form(P_, Hkv, P.r, Lp_cap, scale, pairs);
   const bool teams = form == PREFILL_TEAMS;
-  const int64_t units8 = (int64_t)8 * ceil_div(P_ * Hkv, 8);              // eight XCDs, whole rounds of units
   P.QB = (form == PREFILL_128 ? 2 : 1) * 16 * WG_WAVES / P.r;             // query positions per workgroup
   P.nqb = ceil_div(Lp_cap, P.QB);
-  P.spread = prefill_spread(P_ * Hkv);
-  P.div_Hkv = make_fastdiv(Hkv); P.div_r = make_fastdiv(P.r); P.div_nqb = make_fastdiv(P.nqb); P.div_units = make_fastdiv(P_ * Hkv);
+  const int units = P_ * Hkv;
+  const PrefillOrder order = prefill_order(units, Hkv, P.nqb, teams ? 1 : ((int64_t)units * P.nqb + 2 * pairs - 1) / (2 * pairs));
+  const int per = ceil_div(units, N_XCD >> order.lg), chunks = ceil_div(per, order.chunk);     // of a group of XCDs
+  P.lg = order.lg; P.chunk = ceil_div(per, chunks); P.turn = order.turn; P.again = order.again;
+  const int64_t blocks = (int64_t)P.chunk * P.nqb;          // of a chunk
+  const int64_t grid = ((chunks * blocks + (1 << P.lg) - 1) >> P.lg) * N_XCD;
+  P.div_Hkv = make_fastdiv(Hkv); P.div_r = make_fastdiv(P.r);
+  P.div_chunk = make_fastdiv((int)blocks); P.div_units = make_fastdiv(P.chunk);
   typedef void (*kern_t)(const PrefillParams);
   const kern_t kern = form == PREFILL_128 ? prefill2_kernel<2, 1> : form == PREFILL_TEAMS ? prefill2_kernel<1, 2>
                     : form == PREFILL_64 ? prefill2_kernel<1, 1> : prefill_kernel<1>;
@@ -2027,7 +2064,7 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
       if (dev >= 0 && dev < 64) done[dev] = true;
     }
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)((P.spread ? (int64_t)P_ * Hkv : units8) * P.nqb)), dim3(teams ? 2 * NTHREADS : NTHREADS),
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(teams ? 2 * NTHREADS : NTHREADS),
                      teams ? 2 * LDS_BYTES : LDS_BYTES, stream, P);
   return hipGetLastError();
 }
