@@ -144,42 +144,48 @@ __global__ void __launch_bounds__(NB) policy_count_kernel(const LossParams L) {
   }
 }
 
+// one sequence's sums into the batch's, in fp64
+__device__ __forceinline__ void add_sequence(const LossParams& L, int n, float2 x, float2 y, float2 z, double wt, long long n_seq, double (&acc)[6]) {
+  if (n == 0) return;
+  const double wa = L.agg == RL_AGG_SEQ_MEAN ? 1.0 / ((double)n * (double)n_seq) : wt;
+  acc[0] += wa * x.x; acc[1] += wa * x.y; acc[2] += wa * y.x;
+  acc[3] += wt * y.y; acc[4] += wt * z.x; acc[5] += wt * z.y;
+}
+
+// by one wavefront; t: lane k < 6 holds the k-th sum
+__device__ __forceinline__ void write_stats(const LossParams& L, double t, long long n_tok) {
+  const int lane = threadIdx.x;
+  if (lane < 6) L.stats[lane + 1] = (float)t;
+  const double kl = __shfl(t, 1, 64), ent = __shfl(t, 2, 64);
+  if (lane == 0) {
+    L.stats[0] = (float)(-t + (double)L.beta_kl * kl - (double)L.beta_ent * ent);
+    L.stats[7] = (float)n_tok;
+  }
+}
+
 // per-sequence sums -> batch statistics, in fp64 and in a fixed order: a thread's sequences in turn, the lanes of a
-// wavefront by a butterfly, the wavefronts in order.  SAME: of a launch whose other workgroups wrote them, past the caches
-template <int N, bool SAME>
-__device__ __forceinline__ void reduce_parts(const LossParams& L, long long n_tok, long long n_seq) {
-  constexpr int NW = N / 64;
-  __shared__ double sh[6][NW];
+// wavefront by a butterfly, the wavefronts in order
+__global__ void __launch_bounds__(NB) policy_loss_reduce_kernel(const LossParams L) {
+  __shared__ double sh[6][NBW];
   const int tid = threadIdx.x;
+  const long long n_tok = L.counts[0], n_seq = L.counts[1];
   const double wt = n_tok > 0 ? 1.0 / (double)n_tok : 0.0;
   double acc[6] = {0, 0, 0, 0, 0, 0};
   constexpr int U = 4;
-  for (int b0 = tid; b0 < L.B; b0 += U * N) {
+  for (int b0 = tid; b0 < L.B; b0 += U * NB) {
     int len[U];
     float4 p[U];
     float2 q[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      const int b = min(b0 + k * N, L.B - 1);
-      len[k] = b0 + k * N < L.B ? L.lens[b] : 0;
-      const uint64_t* const at = L.part + (size_t)b * 4;
-      if (SAME) {
-        const float2 x = rlda::get(at), z = rlda::get(at + 1);
-        p[k] = make_float4(x.x, x.y, z.x, z.y);
-        q[k] = rlda::get(at + 2);
-      } else {
-        p[k] = *reinterpret_cast<const float4*>(at);
-        q[k] = *reinterpret_cast<const float2*>(at + 2);
-      }
+      const int b = min(b0 + k * NB, L.B - 1);
+      len[k] = b0 + k * NB < L.B ? L.lens[b] : 0;
+      p[k] = *reinterpret_cast<const float4*>(L.part + (size_t)b * 4);
+      q[k] = *reinterpret_cast<const float2*>(L.part + (size_t)b * 4 + 2);
     }
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int n = clamp_len(len[k], L.T);
-      if (n == 0) continue;
-      const double wa = L.agg == RL_AGG_SEQ_MEAN ? 1.0 / ((double)n * (double)n_seq) : wt;
-      acc[0] += wa * p[k].x; acc[1] += wa * p[k].y; acc[2] += wa * p[k].z;
-      acc[3] += wt * p[k].w; acc[4] += wt * q[k].x; acc[5] += wt * q[k].y;
-    }
+    for (int k = 0; k < U; ++k)
+      add_sequence(L, clamp_len(len[k], L.T), make_float2(p[k].x, p[k].y), make_float2(p[k].z, p[k].w), q[k], wt, n_seq, acc);
   }
 #pragma unroll
   for (int k = 0; k < 6; ++k) acc[k] = wave_sum(acc[k]);
@@ -192,15 +198,60 @@ __device__ __forceinline__ void reduce_parts(const LossParams& L, long long n_to
     double t = 0.0;
     if (tid < 6) {
 #pragma unroll
-      for (int k = 0; k < NW; ++k) t += sh[tid][k];
-      L.stats[tid + 1] = (float)t;
+      for (int k = 0; k < NBW; ++k) t += sh[tid][k];
     }
-    const double kl = __shfl(t, 1, 64), ent = __shfl(t, 2, 64);
-    if (tid == 0) {
-      L.stats[0] = (float)(-t + (double)L.beta_kl * kl - (double)L.beta_ent * ent);
-      L.stats[7] = (float)n_tok;
-    }
+    write_stats(L, t, n_tok);
   }
+}
+
+// the k-th sum over a wavefront, in lane k
+__device__ __forceinline__ double sums_by_lane(double (&acc)[6]) {
+  double t = 0.0;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const double v = wave_sum(acc[k]);
+    if ((int)threadIdx.x == k) t = v;
+  }
+  return t;
+}
+
+// The same inside the token pass, by the first wavefront of each workgroup (the others are gone): sequences meet in groups of
+// GROUP, the last group is up to twice as large; the last of a group adds the group's, one or two to a lane, and leaves six
+// doubles where nothing else is kept; the last group's adds the groups'.  What is left for others and read of it goes past the
+// caches of one die.
+constexpr int GROUP = 64, MAX_GROUPS = 64;
+__device__ __forceinline__ int n_groups(const LossParams& L) { return max(1, L.B / GROUP); }
+__device__ __forceinline__ void reduce_groups(const LossParams& L, int g, uint64_t seen, long long n_tok, long long n_seq) {
+  const int lane = threadIdx.x, n = n_groups(L), first = g * GROUP, size = g == n - 1 ? L.B - first : GROUP;
+  const double wt = n_tok > 0 ? 1.0 / (double)n_tok : 0.0;
+  int last = 0;
+  if (lane == 0) last = rlda::arrive(L.part + (size_t)first * 4 + 3, L.call, seen, size);
+  if (!__shfl(last, 0, 64)) return;
+  double acc[6] = {0, 0, 0, 0, 0, 0};
+  for (int i = lane; i < size; i += 64) {
+    const uint64_t* const at = L.part + (size_t)(first + i) * 4;
+    const float2 x = rlda::get(at), y = rlda::get(at + 1), z = rlda::get(at + 2);
+    add_sequence(L, clamp_len(L.lens[first + i], L.T), x, y, z, wt, n_seq, acc);
+  }
+  double t = sums_by_lane(acc);
+  if (n > 1) {
+    if (lane < 6)
+      __hip_atomic_store(L.part + (size_t)(first + 1 + lane) * 4 + 3, (uint64_t)__double_as_longlong(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    rlda::stores_done();
+    last = 0;
+    if (lane == 0) last = rlda::arrive(L.groups_done, L.call, rlda::claim(L.groups_done, L.call), n);
+    if (!__shfl(last, 0, 64)) return;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) acc[k] = 0;
+    if (lane < n) {
+      const uint64_t* const at = L.part + ((size_t)lane * GROUP + 1) * 4 + 3;
+#pragma unroll
+      for (int k = 0; k < 6; ++k)
+        acc[k] = __longlong_as_double((long long)__hip_atomic_load(at + k * 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    }
+    t = sums_by_lane(acc);
+  }
+  write_stats(L, t, n_tok);
 }
 
 // per-token arithmetic; accumulates into sums[6] = (term, kl, entropy, flat-branch count, rho, old - new)
@@ -232,12 +283,14 @@ __device__ __forceinline__ float token_term(const LossParams& L, float lp, float
 // row's end.  A thread adds its tokens in increasing t, the 64 lanes of a wavefront are folded by a fixed butterfly and the
 // four wavefronts in order, so the sums do not depend on anything but the data.
 constexpr int COUNT_MAX = 1024;
-// ONE: the last workgroup to end reduces, which saves the launch behind; the others meet in groups of GROUP first, so that few wait
-// for one counter.  A workgroup stays 1 to 2 us longer for it, so up to ONE_MAX sequences only, whose workgroups are all there at
-// once.  us, advantages and loss, captured (from Python), two or three launches / one or two: 8 sequences 11.8 (20.5) / 10.1 (18.2),
-// 1024 13.7 (21.9) / 12.9 (19.3), 2048 17.2 (24.9) / 16.9 (22.2); 4096 20.4 (25.0) / 22.9 (23.6), 8192 27.7 / 34.4.
-constexpr int GROUP = 64, ONE_MAX = 2048;
-static_assert(COUNT_MAX <= ONE_MAX && GROUP <= rlda::MAX_ARRIVALS && (ONE_MAX + GROUP - 1) / GROUP <= rlda::MAX_ARRIVALS, "a counter holds no more");
+// ONE: the first wavefront of the last workgroup to end reduces (reduce_groups), which saves the launch behind.  A workgroup's other
+// wavefronts end before it waits, so that the next workgroup finds most of its place free; while all 256 threads waited and one
+// workgroup added up everything, it paid up to 2048 sequences only (4096, captured: 20.4 with a launch / 22.9).  us, advantages and
+// loss from Python, a launch / so: 512 prompts x 8 of 4096 tokens 52.7 / 50.5, of 1000 24.3 / 22.6, 200 x 16 of 3000 32.5 / 30.8; beyond
+// ONE_MAX the queue of workgroups pays for each: 350 x 16 of 2000 29.4 / 29.5, 512 x 16 of 700 29.5 / 29.4, of 80 27.9 / 28.6.
+// Few sequences, two or three launches / one or two: 8 20.5 / 18.2, 1024 21.9 / 19.3, 2048 24.9 / 22.2.
+constexpr int ONE_MAX = GROUP * MAX_GROUPS;
+static_assert(COUNT_MAX <= ONE_MAX && 2 * GROUP - 1 <= rlda::MAX_ARRIVALS && MAX_GROUPS <= 64, "a counter, and a wavefront, hold no more");
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4u __attribute__((aligned(4)));
 
@@ -269,9 +322,9 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
     n_tok = L.counts[0]; n_seq = L.counts[1];
   }
   const int b = blockIdx.x;
-  uint64_t* const group = L.part + (size_t)(b / GROUP * GROUP) * 4 + 3;
+  const int met = min(b / GROUP, n_groups(L) - 1);        // the group it meets in
   uint64_t seen = 0;
-  if (ONE && tid == 0) seen = rlda::claim(group, L.call);
+  if (ONE && tid == 0) seen = rlda::claim(L.part + (size_t)met * GROUP * 4 + 3, L.call);
   const unsigned len = clamp_len(L.lens[b], L.T);
   float w = 0.f;                                          // weight of one of this sequence's tokens in the aggregate
   if (len > 0) w = L.agg == RL_AGG_SEQ_MEAN ? (float)(1.0 / ((double)len * (double)n_seq)) : (float)(1.0 / (double)n_tok);
@@ -312,23 +365,14 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
     if (tid < 6) reinterpret_cast<float*>(L.part)[(size_t)b * 8 + tid] = ((shf[0][tid] + shf[1][tid]) + shf[2][tid]) + shf[3][tid];
     return;
   }
+  if (tid >= 64) return;
   if (tid < 3) {
     const auto sum = [&](int k) { return ((shf[0][k] + shf[1][k]) + shf[2][k]) + shf[3][k]; };
     rlda::put(L.part + (size_t)b * 4 + tid, sum(2 * tid), sum(2 * tid + 1));
-    rlda::stores_done();
   }
-  __shared__ bool last;
-  __syncthreads();
-  if (tid == 0) {
-    const int groups = (L.B + GROUP - 1) / GROUP;
-    last = rlda::arrive(group, L.call, seen, min(GROUP, L.B - b / GROUP * GROUP));
-    if (last) last = rlda::arrive(L.groups_done, L.call, rlda::claim(L.groups_done, L.call), groups);
-  }
-  __syncthreads();
-  if (last) reduce_parts<NT, true>(L, n_tok, n_seq);
+  rlda::stores_done();
+  reduce_groups(L, met, seen, n_tok, n_seq);
 }
-
-__global__ void __launch_bounds__(NB) policy_loss_reduce_kernel(const LossParams L) { reduce_parts<NB, false>(L, L.counts[0], L.counts[1]); }
 
 int check(const rl_policy_loss_desc* d) {
   if (!d) return -1;

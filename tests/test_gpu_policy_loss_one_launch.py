@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("agg", [0, 1])
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 1024, 1025, 2047, 2048, 2049])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129, 191, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097])
 def test_numbers_of_sequences(B, n, agg):  # noqa: F811
     x = wl.make_rollout_tokens(n, 300, 1, seed=n, lens=("uniform", 300))
     x["lens"][: n // 3: 5] = 0
@@ -18,7 +18,7 @@ def test_numbers_of_sequences(B, n, agg):  # noqa: F811
     check_loss(B, x, adv, 0.2, 0.28, beta_kl=0.04, beta_ent=0.01, agg=agg)
 
 
-@pytest.mark.parametrize("n", [70, 1100])
+@pytest.mark.parametrize("n", [70, 1100, 4090])
 def test_any_workspace_and_replays(B, n):  # noqa: F811
     import torch
     x = wl.make_rollout_tokens(n, 50, 1, seed=n, lens=("uniform", 50))
