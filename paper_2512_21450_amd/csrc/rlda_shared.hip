@@ -1215,7 +1215,22 @@ inline PrefillOrder prefill_order(int units, int Hkv, int64_t nqb, int64_t round
   }
   return nqb <= 32 || (Hkv % N_XCD != 0 && units == 4 * N_XCD) ? PrefillOrder{0, 8, 1, none} : PrefillOrder{0, 1, 0, none};
 }
+// Places without chunks (one unit after the other, or all units to all XCDs) by one division: three in a row, or a branch with
+// arguments of its own behind it, are 0.1 to 0.4 us of a short call (8 ragged prompts up to 452 of 16/2 heads 12.4 / 12.5, 1 x 500 of
+// 28/4 11.2 / 11.3), so the kernels of short calls have a form of each.
+inline bool prefill_plain(int lg, int chunk) { return lg == 3 || (lg == 0 && chunk == 1); }
+template <bool PLAIN>
 __device__ __forceinline__ void prefill_place(const PrefillParams& P, int b, int& pj, int& qb) {
+  if (PLAIN) {
+    if (P.lg) {                                             // chunk: all units
+      const int i = fast_div(b, P.div_units);
+      pj = b - i * P.chunk; qb = P.nqb - 1 - i;
+    } else {
+      const int xcd = b % N_XCD, seq = b / N_XCD, u = fast_div(seq, P.div_chunk);
+      pj = u * N_XCD + xcd; qb = P.nqb - 1 - (seq - u * P.nqb);
+    }
+    return;
+  }
   const int xcd = b & (N_XCD - 1), s = (b / N_XCD << P.lg) + (xcd & ((1 << P.lg) - 1));      // the s-th workgroup of its group
   const int n = fast_div(s, P.div_chunk), in = s - n * P.chunk * P.nqb, i = fast_div(in, P.div_units);
   int x = in - i * P.chunk;
@@ -1235,7 +1250,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) prefill_kernel(const PrefillParam
   constexpr int WROWS = 16 * NTP;                           // rows per wavefront
   const int units = P.P * P.Hkv;
   int pj, qb;
-  prefill_place(P, blockIdx.x, pj, qb);
+  prefill_place<false>(P, blockIdx.x, pj, qb);
   if (pj >= units) return;                                  // the last round of units may not fill all XCDs
   const int p = pj / P.Hkv, j = pj % P.Hkv;
   const int L = clampi(P.lens[p], 0, P.Lp_cap), a = qb * P.QB;
@@ -1451,7 +1466,7 @@ __device__ __forceinline__ float sum_of_row(float v) {      // over the four lan
 // tokens in a buffer of 700, 8/2 heads: 5.3 us with both teams, 4.3 so, 4.2 in workgroups of four wavefronts; up to 12 tiles, half full
 // buffers of 700 lose 6 %).
 constexpr int SOLO_TILES = 8;
-template <int NTP, int TEAMS>
+template <int NTP, int TEAMS, bool PLAIN>                   // PLAIN: see prefill_place
 __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const PrefillParams P) {
   extern __shared__ __attribute__((aligned(16))) char lds_all[];
   __shared__ int again[WG_WAVES * TEAMS];
@@ -1463,7 +1478,7 @@ __global__ void __launch_bounds__(NTHREADS * TEAMS, 2) prefill2_kernel(const Pre
   constexpr int WROWS = 16 * NTP;
   const int units = P.P * P.Hkv;
   int pj, qb;
-  prefill_place(P, blockIdx.x, pj, qb);
+  prefill_place<PLAIN>(P, blockIdx.x, pj, qb);
   if (pj >= units) return;
   const int p = fast_div(pj, P.div_Hkv), j = pj - p * P.Hkv;
   const int L = clampi(P.lens[p], 0, P.Lp_cap), a = qb * P.QB;
@@ -2041,12 +2056,14 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   const int per = ceil_div(units, N_XCD >> order.lg), chunks = ceil_div(per, order.chunk);     // of a group of XCDs
   P.lg = order.lg; P.chunk = ceil_div(per, chunks); P.turn = order.turn; P.again = order.again;
   const int64_t blocks = (int64_t)P.chunk * P.nqb;          // of a chunk
-  const int64_t grid = ((chunks * blocks + (1 << P.lg) - 1) >> P.lg) * N_XCD;
+  const bool plain = teams || (form == PREFILL_64 && prefill_plain(P.lg, P.chunk));
+  const int64_t grid = plain && P.lg ? blocks : ((chunks * blocks + (1 << P.lg) - 1) >> P.lg) * N_XCD;
   P.div_Hkv = make_fastdiv(Hkv); P.div_r = make_fastdiv(P.r);
   P.div_chunk = make_fastdiv((int)blocks); P.div_units = make_fastdiv(P.chunk);
   typedef void (*kern_t)(const PrefillParams);
-  const kern_t kern = form == PREFILL_128 ? prefill2_kernel<2, 1> : form == PREFILL_TEAMS ? prefill2_kernel<1, 2>
-                    : form == PREFILL_64 ? prefill2_kernel<1, 1> : prefill_kernel<1>;
+  const kern_t kern = form == PREFILL_128 ? prefill2_kernel<2, 1, false>
+                    : form == PREFILL_TEAMS ? prefill2_kernel<1, 2, true>                       // one round: no chunks
+                    : form == PREFILL_64 ? (plain ? prefill2_kernel<1, 1, true> : prefill2_kernel<1, 1, false>) : prefill_kernel<1>;
   {
     static std::mutex mu;
     static bool done[64] = {};
@@ -2055,10 +2072,11 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(mu);
     if (dev < 0 || dev >= 64 || !done[dev]) {
-      for (const kern_t kf : {static_cast<kern_t>(prefill_kernel<1>), static_cast<kern_t>(prefill2_kernel<2, 1>),
-                              static_cast<kern_t>(prefill2_kernel<1, 1>), static_cast<kern_t>(prefill2_kernel<1, 2>)}) {
+      for (const kern_t kf : {static_cast<kern_t>(prefill_kernel<1>), static_cast<kern_t>(prefill2_kernel<2, 1, false>),
+                              static_cast<kern_t>(prefill2_kernel<1, 1, true>), static_cast<kern_t>(prefill2_kernel<1, 1, false>),
+                              static_cast<kern_t>(prefill2_kernel<1, 2, true>)}) {
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(kf), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kf == static_cast<kern_t>(prefill2_kernel<1, 2>) ? 2 * LDS_BYTES : LDS_BYTES);
+                                kf == static_cast<kern_t>(prefill2_kernel<1, 2, true>) ? 2 * LDS_BYTES : LDS_BYTES);
         if (e != hipSuccess) return e;
       }
       if (dev >= 0 && dev < 64) done[dev] = true;
