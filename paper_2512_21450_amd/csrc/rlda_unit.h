@@ -876,6 +876,7 @@ bool unit_preferred(const Problem& pb, int pairs) {
   const bool f8 = pb.dtype == RLDA_BF16_KV8, few = max_group(pb) * (pb.Hq / pb.Hkv) <= 16;
   if (pb.Ls_cap <= 2048 && 3 * shared_cap(pb) + pb.Ls_cap <= 3600 && units <= (int64_t)64 * pairs && units * keys <= (int64_t)2048 * pairs)
     return unit_supported(pb, pairs);
+  if (units == 0) return false;                        // nothing runs; and what follows divides by units
   if (keys > 8960 || (pb.n_levels > 1 && pb.Ls_cap > 2048) || units > (int64_t)64 * pairs) return false;
   if (units * keys > (f8 ? 4096 : few ? 2048 : 2560) * (int64_t)pairs || !unit_supported(pb, pairs)) return false;
   int64_t read = units * pb.Ls_cap + (int64_t)pb.P * pb.Hkv * pb.Lp_cap;                  // keys that come from memory

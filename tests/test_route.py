@@ -92,6 +92,29 @@ def test_units_of_hardly_any_key_in_large_numbers_stay_on_the_shared_path():
         assert B.rl_decode_attn_debug_route(tree(units)) == want
 
 
+# (prefix, suffix) capacities on both sides of every line of the rule for one launch, and whether that takes an empty batch
+EMPTY = [(0, 0, UNIT), (452, 512, UNIT), (517, 2048, UNIT), (518, 2048, SHARED), (1200, 0, UNIT), (1201, 0, SHARED), (500, 2049, SHARED),
+         (4096, 4096, SHARED), (8000, 960, SHARED), (8000, 961, SHARED), (30000, 30000, SHARED)]
+
+
+@pytest.mark.parametrize("Lp,Ls,want", EMPTY)
+@pytest.mark.parametrize("dtype", [B.RLDA_BF16, B.RLDA_BF16_KV8])
+def test_queries_about_empty_batches_answer(dtype, Lp, Ls, want):
+    """A batch without a sequence has a route like any other, for every device, and nothing to merge."""
+    page = lambda P, G: B.make_paged_desc(dtype, P, G, 28, 4, 128, Lp, 64, Ls // 64, 1, 0.1, block_table=1 << 20)
+    of_pages = UNIT if 3 * Lp + Ls // 64 * 64 <= 3600 and Ls // 64 * 64 <= 2048 else SHARED
+    tree = [(B.make_tree_desc(dtype, 0, 28, 4, 128, Ls, 0.1, lv), want) for lv in
+            ([(None, None, None, 8, Lp)], [(None, None, None, 8, Lp), (None, None, None, 2, 0)])] if dtype == B.RLDA_BF16 else []
+    for ds, route in [(desc(dtype, P, G, 28, 4, Lp=Lp, Ls=Ls), want) for P, G in ((0, 8), (3, 0), (0, 0))] + \
+            [(page(P, G), of_pages) for P, G in ((0, 8), (3, 0))] + tree:
+        for cus in (256, 304, 64, 32, 1):
+            assert B.rl_decode_attn_debug_route(ds, cus) == route, (Lp, Ls, cus)
+            assert B.rl_decode_attn_debug_merge(ds, cus) == B.RLDA_ERR_UNSUPPORTED
+    for dt, d in ((B.RLDA_F32, 64), (B.RLDA_F32, 128), (dtype, 64)):      # not the shared-prefix path's
+        assert B.rl_decode_attn_debug_route(desc(dt, 0, 8, 28, 4, d, Lp, Ls)) in (UNIT, SIMPLE)
+        assert B.rl_decode_attn_debug_merge(desc(dt, 0, 8, 28, 4, d, Lp, Ls)) == B.RLDA_ERR_UNSUPPORTED
+
+
 def test_how_the_partials_are_merged():
     """Teams by the parts that the unit counts give (256 / (P Hkv) + 2048 / (P G Hkv) on 256 pairs, a group of up to 64 rows), 16
     lanes from 128 prefix and 1024 suffix units on."""
