@@ -77,8 +77,7 @@ typedef enum {
                               least 32 rows.  Everything else -- fp32, d = 64, other head ratios or scales,
                               smaller pages -- is planned as SIMPLE (no sharing across sequences);
                               under AUTO most of it then runs in a one-launch form on the matrix cores, one
-                              workgroup per (sequence, KV head), or several for few of them with many keys if
-                              there is a workspace, with 24-bit softmax weights; few rows over few
+                              workgroup per (sequence, KV head), with 24-bit softmax weights; few rows over few
                               keys stay on the simple kernel, which is faster there.  The one-launch form also
                               takes batches of the shared-prefix path that are too small to fill the chip (16 or
                               24 bits of a weight); their workspace is asked for and checked all the same. */
@@ -86,7 +85,11 @@ typedef enum {
                               plain reference on the GPU.  Under AUTO also what the one-launch form does not take:
                               few rows over few keys, stores that are not 16-byte aligned, a scale that is not
                               finite, very large capacities and grids */
-  RLDA_ALGO_SHARED = 2     /* force the shared-prefix path; RLDA_ERR_UNSUPPORTED if not possible */
+  RLDA_ALGO_SHARED = 2,    /* force the shared-prefix path; RLDA_ERR_UNSUPPORTED if not possible */
+  RLDA_ALGO_AUTO_SCRATCH = 4   /* AUTO from a caller whose workspace no other call uses until this one has run: plans of
+                              RLDA_ALGO_SIMPLE may use it too.  Few long (sequence, KV head) units are then shared by
+                              several workgroups each, up to 3 times as fast.  Under AUTO such a plan leaves the
+                              workspace alone, so calls of it that overlap in time may carry the same one. */
 } rlda_algo;
 
 /* Return codes. */
@@ -123,8 +126,9 @@ typedef struct {
   const int32_t* suffix_lens;  /* [B]  valid suffix rows per sequence; clamped to [0, Ls_cap]    */
   float*   out;                /* [B, Hq, d] fp32                                                */
   float*   lse;                /* [B, Hq]    fp32, natural log; may be NULL                      */
-  void*    workspace;          /* device scratch, 256-byte aligned, any contents; may be NULL if no byte is
-                                  needed (RLDA_ALGO_SIMPLE plans run without what they ask for, some slower) */
+  void*    workspace;          /* device scratch, 256-byte aligned, any contents; may be NULL if 0 bytes needed.
+                                  Calls that use it (plan RLDA_ALGO_SHARED; algo RLDA_ALGO_AUTO_SCRATCH) and
+                                  may overlap in time need one each */
   size_t   workspace_bytes;
   const float* k_scale;        /* [Hkv] fp32 > 0, RLDA_BF16_KV8 only (else ignored); NULL = all 1 */
   const float* v_scale;        /* [Hkv] fp32, likewise                                           */
@@ -139,7 +143,9 @@ typedef struct {
  * anything (including NaN).  Returns RLDA_OK or a negative RLDA_ERR_* code; on
  * a validation error (-1 .. -4) nothing has been enqueued; after RLDA_ERR_LAUNCH
  * part of the work may have been, and out / lse are then undefined.  Results
- * are bit-reproducible from call to call for identical inputs.
+ * are bit-reproducible from call to call for identical inputs (under
+ * RLDA_ALGO_AUTO_SCRATCH: and the same workspace_bytes, which may decide among
+ * how many workgroups a unit is shared).
  */
 int rl_decode_attn(const rlda_desc* desc, void* hip_stream);
 
@@ -154,18 +160,18 @@ int rl_decode_attn(const rlda_desc* desc, void* hip_stream);
 int rl_decode_attn_profiled(const rlda_desc* desc, void* hip_stream, void* mid_event);
 
 /*
- * Bytes of device workspace rl_decode_attn needs (plan RLDA_ALGO_SHARED) or can
- * use (plan RLDA_ALGO_SIMPLE under AUTO: few long units, which share it out
- * among more workgroups; a smaller or no workspace is accepted there, the same
- * one gives the same bits) for this descriptor (only the shape fields, dtype and
- * algo are read; no pointer is dereferenced, no device is touched).  Returns 0 if none is needed or if the descriptor is invalid
- * (rl_decode_attn reports the reason).
+ * Bytes of device workspace rl_decode_attn needs for this descriptor (only the
+ * shape fields, dtype and algo are read; no pointer is dereferenced, no device
+ * is touched), or, for a plan RLDA_ALGO_SIMPLE under RLDA_ALGO_AUTO_SCRATCH, can
+ * use: with less, or one that is misaligned, fewer workgroups share a unit, with
+ * none one has it to itself.  Returns 0 if none is needed or if the descriptor
+ * is invalid (rl_decode_attn reports the reason).
  */
 size_t rl_decode_attn_workspace_bytes(const rlda_desc* desc);
 
 /*
  * How rl_decode_attn plans this descriptor: RLDA_ALGO_SHARED (the shared-prefix
- * path's shapes, with its workspace) or RLDA_ALGO_SIMPLE (none needed), or a
+ * path's shapes, with its workspace) or RLDA_ALGO_SIMPLE (no workspace), or a
  * negative RLDA_ERR_* code.  Under RLDA_ALGO_AUTO either may run in one launch
  * without that changing the plan.  Pure host function.
  */
@@ -175,16 +181,18 @@ int rl_decode_attn_plan(const rlda_desc* desc);
  * rl_decode_attn for callers that cannot allocate or carry device memory of
  * their own for the library's scratch: code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation.  Same arguments, result
- * (bit for bit), stream and error behaviour as rl_decode_attn, except that
+ * (bit for bit; under RLDA_ALGO_AUTO_SCRATCH that of a workspace as large as
+ * rl_decode_attn_workspace_bytes), stream and error behaviour as rl_decode_attn, except that
  * desc->workspace and desc->workspace_bytes are ignored: the scan of tile
  * counts and the partial results go to an array of
  * RLDA_STATIC_WORKSPACE_BYTES that is part of the library's device image
  * (every GPU the process uses holds one copy until the process ends).  The
  * call allocates and frees nothing, on the host or on the device.  A problem
  * whose rl_decode_attn_workspace_bytes exceeds the array returns
- * RLDA_ERR_WORKSPACE and enqueues nothing.  All calls on one GPU share that
- * GPU's array: calls that may overlap in time there (different streams, or
- * graphs replayed concurrently) race on it and must be ordered by the caller;
+ * RLDA_ERR_WORKSPACE and enqueues nothing.  All calls on one GPU whose
+ * rl_decode_attn_workspace_bytes is not 0 share that GPU's array: those that may
+ * overlap in time there (different streams, or graphs replayed concurrently)
+ * race on it and must be ordered by the caller;
  * nothing needs to be cleared between calls (the kernels write every entry
  * they later read, or tell by the number of the call that it is another's).
  */

@@ -27,7 +27,7 @@ if not os.path.exists(LIB_PATH):
 _lib = ctypes.CDLL(LIB_PATH)
 
 RLDA_F32, RLDA_BF16, RLDA_BF16_KV8 = 0, 1, 2
-RLDA_ALGO_AUTO, RLDA_ALGO_SIMPLE, RLDA_ALGO_SHARED = 0, 1, 2
+RLDA_ALGO_AUTO, RLDA_ALGO_SIMPLE, RLDA_ALGO_SHARED, RLDA_ALGO_AUTO_SCRATCH = 0, 1, 2, 4
 RLDA_OK, RLDA_ERR_INVALID, RLDA_ERR_UNSUPPORTED = 0, -1, -2
 RLDA_ERR_WORKSPACE, RLDA_ERR_STRUCT_SIZE, RLDA_ERR_LAUNCH = -3, -4, -5
 
@@ -321,7 +321,8 @@ def rl_decode_attn(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, suffi
                    out=None, lse=None, workspace=None, algo=RLDA_ALGO_AUTO, stream=None, k_scale=None, v_scale=None):
     """One decode-attention step on torch device tensors; returns (out, lse).
 
-    Allocates out/lse/workspace with torch when they are not passed in.  The
+    Allocates out/lse/workspace with torch when they are not passed in; a
+    workspace of its own lets RLDA_ALGO_AUTO run as RLDA_ALGO_AUTO_SCRATCH.  The
     call is asynchronous on ``stream`` (default: torch's current stream).
     """
     if not q.is_cuda:
@@ -334,6 +335,8 @@ def rl_decode_attn(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, suffi
     ds = desc_from_tensors(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, suffix_lens, scale, G,
                            out, lse, workspace, algo, k_scale, v_scale)
     if workspace is None:
+        if algo == RLDA_ALGO_AUTO:                              # what is allocated here is this call's alone
+            ds.algo = RLDA_ALGO_AUTO_SCRATCH
         need = rl_decode_attn_workspace_bytes(ds)
         if need:
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
@@ -498,6 +501,8 @@ def rl_decode_attn_paged(q, k_prefix, v_prefix, prefix_lens, k_pages, v_pages, b
     ds = paged_desc_from_tensors(q, k_prefix, v_prefix, prefix_lens, k_pages, v_pages, block_table, suffix_lens,
                                  scale, G, out, lse, seq_active, workspace, algo, k_scale, v_scale)
     if workspace is None:
+        if algo == RLDA_ALGO_AUTO:                              # what is allocated here is this call's alone
+            ds.algo = RLDA_ALGO_AUTO_SCRATCH
         need = rl_decode_attn_paged_workspace_bytes(ds)
         if need:
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)

@@ -19,7 +19,9 @@ int to_problem(const rlda_desc* ds, Problem& pb) {
   if (!ds) return RLDA_ERR_INVALID;
   if (ds->struct_size != sizeof(rlda_desc)) return RLDA_ERR_STRUCT_SIZE;
   pb = Problem{};
-  pb.dtype = ds->dtype; pb.algo = ds->algo;
+  pb.dtype = ds->dtype;
+  pb.scratch = ds->algo == RLDA_ALGO_AUTO_SCRATCH;
+  pb.algo = pb.scratch ? (int)RLDA_ALGO_AUTO : ds->algo;
   pb.P = ds->P; pb.G = ds->G; pb.Hq = ds->Hq; pb.Hkv = ds->Hkv; pb.d = ds->d;
   pb.Lp_cap = ds->Lp_cap; pb.Ls_cap = ds->Ls_cap; pb.scale = ds->scale;
   pb.q = ds->q; pb.k_prefix = ds->k_prefix; pb.v_prefix = ds->v_prefix; pb.prefix_lens = ds->prefix_lens;
@@ -37,7 +39,9 @@ int to_problem(const rlda_paged_desc* ds, Problem& pb) {
   if ((int64_t)ds->max_pages * ds->page_size > (int64_t)1 << 30) return RLDA_ERR_UNSUPPORTED;
   if (ds->max_pages > 0 && ds->n_pages < 1) return RLDA_ERR_INVALID;
   pb = Problem{};
-  pb.dtype = ds->dtype; pb.algo = ds->algo;
+  pb.dtype = ds->dtype;
+  pb.scratch = ds->algo == RLDA_ALGO_AUTO_SCRATCH;
+  pb.algo = pb.scratch ? (int)RLDA_ALGO_AUTO : ds->algo;
   pb.P = ds->P; pb.G = ds->G; pb.Hq = ds->Hq; pb.Hkv = ds->Hkv; pb.d = ds->d;
   pb.Lp_cap = ds->Lp_cap; pb.Ls_cap = ds->max_pages * ds->page_size; pb.scale = ds->scale;
   pb.q = ds->q; pb.k_prefix = ds->k_prefix; pb.v_prefix = ds->v_prefix; pb.prefix_lens = ds->prefix_lens;
@@ -80,10 +84,10 @@ int plan_of(const Desc* desc) {
   return rc != RLDA_OK ? rc : plan(pb);
 }
 
-// what a plan needs (SHARED), or can use (SIMPLE, under AUTO)
+// what a plan needs (SHARED), or can use (SIMPLE, if the caller says that it may)
 size_t planned_bytes(const Problem& pb, int planned) {
   if (planned == RLDA_ALGO_SHARED) return rlda::shared_workspace_bytes(pb);
-  return planned == RLDA_ALGO_SIMPLE && pb.algo == RLDA_ALGO_AUTO ? rlda::unit_workspace_bytes(pb) : 0;
+  return planned == RLDA_ALGO_SIMPLE && pb.scratch ? rlda::unit_workspace_bytes(pb) : 0;
 }
 
 template <class Desc>
@@ -175,12 +179,14 @@ int check_pointers(const Problem& pb) {
   return RLDA_OK;
 }
 
-int enqueue(const Problem& pb, void* hip_stream, void* mid_event) {
+int enqueue(Problem pb, void* hip_stream, void* mid_event) {
   const int pl = plan(pb);
   if (pl < 0) return pl;
   const int rc = check_pointers(pb);
   if (rc != RLDA_OK) return rc;
   if ((int64_t)pb.P * pb.G == 0) return RLDA_OK;
+  // another call that overlaps this one may carry the same workspace: a plan that asks for none does not touch it
+  if (pl == RLDA_ALGO_SIMPLE && !pb.scratch) { pb.workspace = nullptr; pb.workspace_bytes = 0; }
   if (pl == RLDA_ALGO_SHARED) {
     const size_t need = rlda::shared_workspace_bytes(pb);
     if (need > 0 && (!pb.workspace || pb.workspace_bytes < need)) return RLDA_ERR_WORKSPACE;

@@ -28,6 +28,7 @@ struct Problem {
   const uint8_t* seq_active;      // null: every sequence is live
   float* out; float* lse;
   void* workspace; size_t workspace_bytes;
+  bool scratch;                   // algo (AUTO) was AUTO_SCRATCH: plans of RLDA_ALGO_SIMPLE may use the workspace
   const float* k_scale; const float* v_scale;   // per-KV-head factors of an e4m3 K/V store, or null
   // tree form (rl_decode_attn_tree): n_levels > 0 levels of shared segments in place of k_prefix / v_prefix /
   // prefix_lens / P / G / Lp_cap; level l has n_seg segments of `cap` rows, each shared by `group` consecutive

@@ -1,5 +1,6 @@
 // Decode attention with one workgroup per unit: all keys of one (sequence, KV head) against its Hq/Hkv query rows,
-// one launch; few units of many keys are shared by several workgroups each (SPLIT), if there is a workspace.  Two uses:
+// one launch; few units of many keys are shared by several workgroups each (SPLIT), if there is a workspace that no other call
+// uses meanwhile (plans of RLDA_ALGO_SHARED, RLDA_ALGO_AUTO_SCRATCH).  Two uses:
 //   * most of what the shared-prefix kernels do not take (fp32 stores, d = 64, wider head ratios, scales that are
 //     not positive, pages under 32 rows), but for few rows over few keys, which the simple kernel runs faster
 //     (unit_pays).  Weights enter the value contraction with 24 bits (EXACT below);
@@ -696,8 +697,9 @@ Split split_rule(const Problem& pb, int pairs) {
   const bool f32 = pb.dtype == RLDA_F32, wide = pb.d == 128;
   Split s{1, 0, 0};
   if (2 * units > pairs || units < 1 || (pb.paged && pb.page_shift < 5)) return s;   // (a query brings no table)
-  int tiles = ceil_div(pb.Ls_cap, TK) + ceil_div(pb.Lp_cap, TK);           // of a sequence that fills its buffers
-  for (int l = 0; l < pb.n_levels; ++l) tiles += ceil_div(pb.levels[l].cap, TK);
+  const auto tiles_of = [](int cap) { return cap / TK + (cap % TK != 0); };   // (capacities up to the largest int)
+  int tiles = tiles_of(pb.Ls_cap) + tiles_of(pb.Lp_cap);                   // of a sequence that fills its buffers
+  for (int l = 0; l < pb.n_levels; ++l) tiles += tiles_of(pb.levels[l].cap);
   const int n = pairs / (int)units, most = n < MAX_UNIT_SPLITS ? n : MAX_UNIT_SPLITS;
   if (tiles > (f32 ? 12 : 24) && tiles <= 32 && (f32 || wide) && ceil_div(tiles, 4) <= n) {
     s.nw = 4;

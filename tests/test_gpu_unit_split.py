@@ -27,12 +27,13 @@ def case(B, dtype, d, P, G, r, Lp, Ls, seed=1, Hkv=1):
     return wl.kv_to_e4m3(x) if dtype == "e4m3" else x
 
 
-def desc(B, t, G, workspace=None, **kw):
+def desc(B, t, G, workspace=None, algo=None):
     import torch
     n, Hq, d = t["q"].shape
     out, lse = torch.full((n, Hq, d), 7.0, device="cuda"), torch.full((n, Hq), 7.0, device="cuda")
     ds = B.desc_from_tensors(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_lens"], t["k_suffix"], t["v_suffix"], t["suffix_lens"], 0.1, G,
-                             out, lse, workspace, k_scale=t.get("k_scale"), v_scale=t.get("v_scale"), **kw)
+                             out, lse, workspace, B.RLDA_ALGO_AUTO_SCRATCH if algo is None else algo,
+                             k_scale=t.get("k_scale"), v_scale=t.get("v_scale"))
     return ds, out, lse
 
 
@@ -133,7 +134,8 @@ def test_any_workspace(B, dtype, d):  # noqa: F811
         first = first or (out.clone(), lse.clone())
         assert torch.equal(out, first[0]) and torch.equal(lse, first[1]), fill
     so, sl = torch.empty_like(out), torch.empty_like(lse)
-    B.rl_decode_attn_static(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_lens"], t["k_suffix"], t["v_suffix"], t["suffix_lens"], 0.1, 4, so, sl)
+    B.rl_decode_attn_static(t["q"], t["k_prefix"], t["v_prefix"], t["prefix_lens"], t["k_suffix"], t["v_suffix"], t["suffix_lens"], 0.1, 4, so, sl,
+                            algo=B.RLDA_ALGO_AUTO_SCRATCH)
     assert torch.equal(so, first[0]) and torch.equal(sl, first[1])
     if d == 64:                                                          # the shared-prefix plan insists on its workspace
         for less, at in ((need - 1, 0), (need // 3, 0), (256, 0), (0, 0), (need, 16)):
@@ -144,6 +146,30 @@ def test_any_workspace(B, dtype, d):  # noqa: F811
             compare(out, lse, ro, rl, EXACT, less)
             mine = 0 if at else less                                     # off 256 bytes: not used
             assert torch.equal(ws[mine:], before[mine:]), less
+
+
+def test_calls_that_asked_for_no_scratch_leave_the_workspace_alone(B):  # noqa: F811
+    """One workspace carried through calls on two streams, and the library's own array: under AUTO a plan without scratch writes to neither,
+    so nothing orders the calls and the bits are those of a call without a workspace."""
+    import torch
+    work = []
+    ws = torch.full((1 << 20,), 0x5A, dtype=torch.uint8, device="cuda")
+    for seed in (8, 9):
+        x = case(B, "f32", 64, 5, 4, 7, 400, 900, seed)
+        t = util.to_device(x)
+        alone, ao, al = desc(B, t, 4, algo=B.RLDA_ALGO_AUTO)
+        assert B.rl_decode_attn_raw(alone, torch.cuda.current_stream().cuda_stream) == 0
+        compare(ao, al, *util.oracle(x, 0.1, 4), EXACT, seed)
+        for raw in (B.rl_decode_attn_raw, B.rl_decode_attn_static_raw):
+            work.append((raw, *desc(B, t, 4, ws, B.RLDA_ALGO_AUTO), ao, al, t, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for raw, ds, _, _, _, _, _, st in work:
+            assert raw(ds, st.cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert (ws == 0x5A).all()
+    for _, _, out, lse, ao, al, _, _ in work:
+        assert torch.equal(out, ao) and torch.equal(lse, al)
 
 
 def test_replays_of_a_captured_call(B):  # noqa: F811

@@ -1,5 +1,5 @@
-"""Into how many workgroups the one-launch decode cuts a unit, by the host-side rule alone (no GPU), read off the workspace query: a
-counter of 8 bytes per (sequence, KV head, 16 query rows), rounded up to 256, and 8 + 4 d bytes per workgroup and query row."""
+"""Into how many workgroups the one-launch decode cuts a unit, by the host-side rule alone (no GPU), read off the workspace query of a
+caller who lets it use one: a counter of 8 bytes per (sequence, KV head, 16 query rows), rounded up to 256, and 8 + 4 d bytes per workgroup and query row."""
 import pytest
 
 from paper_2512_21450_amd import binding as B
@@ -15,8 +15,9 @@ def splits(need, units, rows, d):
     return n
 
 
-def of(dtype, d, units, r, Lp, Ls, scale=0.1, **kw):
-    return splits(B.rl_decode_attn_workspace_bytes(B.make_desc(dtype, units, 1, r, 1, d, Lp, Ls, scale, **kw)), units * -(-r // 16), units * r, d)
+def of(dtype, d, units, r, Lp, Ls, scale=0.1, algo=B.RLDA_ALGO_AUTO_SCRATCH):
+    need = B.rl_decode_attn_workspace_bytes(B.make_desc(dtype, units, 1, r, 1, d, Lp, Ls, scale, algo))
+    return splits(need, units * -(-r // 16), units * r, d)
 
 
 @pytest.mark.parametrize("dtype,d,units,r,Lp,Ls,want", [
@@ -32,9 +33,30 @@ def test_how_many_workgroups_share_a_unit(dtype, d, units, r, Lp, Ls, want):
 
 def test_what_is_never_shared():
     assert of(F32, 64, 2, 1, 4000, 4000, algo=B.RLDA_ALGO_SIMPLE) == 1
-    paged = lambda page, pages: B.rl_decode_attn_paged_workspace_bytes(
-        B.make_paged_desc(F32, 2, 1, 1, 1, 64, 1000, page, pages, 2 * pages, 0.1))
-    assert paged(16, 100) == 0 and splits(paged(32, 50), 2, 2, 64) == 11      # pages of fewer rows than a tile
+    paged = lambda page, pages, algo: B.rl_decode_attn_paged_workspace_bytes(
+        B.make_paged_desc(F32, 2, 1, 1, 1, 64, 1000, page, pages, 2 * pages, 0.1, algo))
+    assert paged(16, 100, B.RLDA_ALGO_AUTO_SCRATCH) == 0                      # pages of fewer rows than a tile
+    assert splits(paged(32, 50, B.RLDA_ALGO_AUTO_SCRATCH), 2, 2, 64) == 11 and paged(32, 50, B.RLDA_ALGO_AUTO) == 0
+
+
+@pytest.mark.parametrize("dtype,d,r,scale", [(F32, 64, 1, 0.1), (F32, 128, 4, 0.1), (BF16, 64, 4, 0.1), (E4M3, 64, 4, 0.1), (BF16, 128, 40, 0.1),
+                                             (BF16, 128, 4, -0.1), (E4M3, 128, 4, 0.0)])
+def test_a_plan_without_scratch_asks_for_none(dtype, d, r, scale):
+    """Programs that carry one workspace through all calls may have several of these run at a time, so none of them writes to it unless
+    the caller says that it is the call's alone."""
+    for units, Lp, Ls in ((2, 1000, 1000), (64, 2048, 2048), (128, 4000, 4000), (2, 0x7fffffff, 0x7fffffff)):
+        ds = lambda algo: B.make_desc(dtype, units, 1, r, 1, d, Lp, Ls, scale, algo)
+        assert B.rl_decode_attn_plan(ds(B.RLDA_ALGO_AUTO)) == B.rl_decode_attn_plan(ds(B.RLDA_ALGO_AUTO_SCRATCH)) == B.RLDA_ALGO_SIMPLE
+        assert B.rl_decode_attn_debug_route(ds(B.RLDA_ALGO_AUTO)) == B.rl_decode_attn_debug_route(ds(B.RLDA_ALGO_AUTO_SCRATCH))
+        assert B.rl_decode_attn_workspace_bytes(ds(B.RLDA_ALGO_AUTO)) == 0
+
+
+def test_the_plan_with_scratch_is_the_same_either_way():
+    for P, G, Hkv, Lp, Ls in ((8, 8, 2, 452, 512), (1, 1, 4, 3500, 500), (32, 8, 4, 1280, 2048)):
+        auto, own = (B.make_desc(BF16, P, G, 4 * Hkv, Hkv, 128, Lp, Ls, 0.1, a) for a in (B.RLDA_ALGO_AUTO, B.RLDA_ALGO_AUTO_SCRATCH))
+        assert B.rl_decode_attn_plan(auto) == B.rl_decode_attn_plan(own) == B.RLDA_ALGO_SHARED
+        assert B.rl_decode_attn_debug_route(auto) == B.rl_decode_attn_debug_route(own)
+        assert B.rl_decode_attn_workspace_bytes(auto) == B.rl_decode_attn_workspace_bytes(own) > 0
 
 
 @pytest.mark.parametrize("dtype,P,G,Hkv,r,Lp,Ls,want", [
