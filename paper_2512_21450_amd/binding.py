@@ -226,6 +226,18 @@ def _stream_handle(stream, like) -> int:
     return torch.cuda.current_stream(like.device).cuda_stream
 
 
+def _scratch(nbytes, like, stream):
+    """Device memory for one call.  It is freed when the function returns, before the call has run, and goes back to the
+    stream that it was allocated on: the one that the call is enqueued on, so that whatever gets it next comes after the call."""
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+    if not isinstance(stream, torch.cuda.Stream):               # any object with a handle is taken
+        stream = (torch.cuda.ExternalStream(stream.cuda_stream, device=like.device) if stream.cuda_stream
+                  else torch.cuda.default_stream(like.device))
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+
+
 def _ptr(t):
     return None if t is None or t.numel() == 0 else t.data_ptr()
 
@@ -339,7 +351,7 @@ def rl_decode_attn(q, k_prefix, v_prefix, prefix_lens, k_suffix, v_suffix, suffi
             ds.algo = RLDA_ALGO_AUTO_SCRATCH
         need = rl_decode_attn_workspace_bytes(ds)
         if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+            workspace = _scratch(need, q, stream)
             ds.workspace, ds.workspace_bytes = workspace.data_ptr(), need
     rc = _lib.rl_decode_attn(ctypes.byref(ds), _stream_handle(stream, q))
     if rc != RLDA_OK:
@@ -422,7 +434,7 @@ def rl_decode_attn_tree(q, levels, k_suffix, v_suffix, suffix_lens, scale, out=N
     ds = tree_desc_from_tensors(q, levels, k_suffix, v_suffix, suffix_lens, scale, out, lse, workspace)
     if workspace is None:
         need = rl_decode_attn_tree_workspace_bytes(ds)
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
+        workspace = _scratch(max(need, 256), q, stream)
         ds.workspace, ds.workspace_bytes = workspace.data_ptr(), workspace.numel()
     rc = _lib.rl_decode_attn_tree(ctypes.byref(ds), _stream_handle(stream, q))
     if rc != RLDA_OK:
@@ -505,7 +517,7 @@ def rl_decode_attn_paged(q, k_prefix, v_prefix, prefix_lens, k_pages, v_pages, b
             ds.algo = RLDA_ALGO_AUTO_SCRATCH
         need = rl_decode_attn_paged_workspace_bytes(ds)
         if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+            workspace = _scratch(need, q, stream)
             ds.workspace, ds.workspace_bytes = workspace.data_ptr(), need
     rc = _lib.rl_decode_attn_paged(ctypes.byref(ds), _stream_handle(stream, q), None)
     if rc != RLDA_OK:
@@ -606,7 +618,7 @@ def rl_token_logprob(logits, token_ids, inv_temperature=1.0, ref_logits=None, wa
     if workspace is None:
         need = rl_token_logprob_workspace_bytes(ds)
         if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=logits.device)
+            workspace = _scratch(need, logits, stream)
             ds.workspace, ds.workspace_bytes = workspace.data_ptr(), need
     rc = _lib.rl_token_logprob(ctypes.byref(ds), _stream_handle(stream, logits))
     if rc != RLDA_OK:
@@ -821,7 +833,7 @@ def rl_policy_loss(logprob, old_logprob, advantages, lens, clip_low, clip_high, 
                                        grad, beta_kl, beta_ent, form, agg, workspace)
     if workspace is None:
         need = rl_policy_loss_workspace_bytes(ds)
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=logprob.device)
+        workspace = _scratch(max(need, 256), logprob, stream)
         ds.workspace, ds.workspace_bytes = workspace.data_ptr(), workspace.numel()
     rc = _lib.rl_policy_loss(ctypes.byref(ds), _stream_handle(stream, logprob))
     if rc != RLDA_OK:
