@@ -93,7 +93,8 @@ def test_more_than_one_batch_of_partials_a_team_on_a_tree(B, teams, Bn, Hkv, gro
 
 
 def test_tree_rows_of_many_partials(B):
-    """Four levels and a suffix, each cut among several workgroups; one level equals the shared-prefix call."""
+    """Four levels and a suffix, each cut among several workgroups; one level equals the shared-prefix call, also with a store that
+    takes it to the same kernels."""
     import torch
     from oracle import ref
     Bn, Hq, Hkv = 8, 8, 1
@@ -101,9 +102,18 @@ def test_tree_rows_of_many_partials(B):
     x = wl.make_tree_inputs(7, Bn, Hq, Hkv, 128, levels, 2500, ("uniform", 2500))
     lv = [tuple(util.to_device({"k": k, "v": v, "n": n}).values()) + (g,) for k, v, n, g in x["levels"]]
     t = util.to_device({k: x[k] for k in ("q", "k_suffix", "v_suffix", "suffix_lens")})
+    route = lambda caps, Ls: util.route(B.make_tree_desc(B.RLDA_BF16, Bn, Hq, Hkv, 128, Ls, 0.1, [(None, None, None, g, c) for g, c in caps]))
+    assert route([lv[:2] for lv in levels], 2500) == B.RLDA_ALGO_SHARED
     out, lse = B.rl_decode_attn_tree(t["q"], lv, t["k_suffix"], t["v_suffix"], t["suffix_lens"], 0.1)
     ro, rl = ref.decode_attn_tree_ref(x["q"], x["levels"], x["k_suffix"], x["v_suffix"], x["suffix_lens"], 0.1)
     util.compare(out, lse, ro, rl, "bf16", "four levels")
-    o1, l1 = B.rl_decode_attn_tree(t["q"], lv[:1], t["k_suffix"], t["v_suffix"], t["suffix_lens"], 0.1)
-    o2, l2 = B.rl_decode_attn(t["q"], lv[0][0], lv[0][1], lv[0][2], t["k_suffix"], t["v_suffix"], t["suffix_lens"], 0.1, 8)
-    assert torch.equal(o1, o2) and torch.equal(l1, l2)
+    for Ls, want in ((2500, B.RLDA_ROUTE_UNIT), (9000, B.RLDA_ALGO_SHARED)):
+        wide = torch.full((2, Bn, Hkv, Ls, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+        wide[0, :, :, :2500], wide[1, :, :, :2500] = t["k_suffix"], t["v_suffix"]
+        ds = B.make_desc(B.RLDA_BF16, 1, 8, Hq, Hkv, 128, 1500, Ls, 0.1)
+        assert route([(8, 1500)], Ls) == util.route(ds) == want
+        o1, l1 = B.rl_decode_attn_tree(t["q"], lv[:1], wide[0], wide[1], t["suffix_lens"], 0.1)
+        o2, l2 = B.rl_decode_attn(t["q"], lv[0][0], lv[0][1], lv[0][2], wide[0], wide[1], t["suffix_lens"], 0.1, 8)
+        assert torch.equal(o1, o2) and torch.equal(l1, l2)
+        ro, rl = ref.decode_attn_tree_ref(x["q"], x["levels"][:1], x["k_suffix"], x["v_suffix"], x["suffix_lens"], 0.1)
+        util.compare(o1, l1, ro, rl, "bf16", "one level")

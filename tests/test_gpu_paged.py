@@ -53,9 +53,10 @@ def test_finished_sequences_and_finished_groups(B):
     act[0:w.G] = 0                                  # prompt 0: whole group finished, its prefix is skipped
     act[w.G:2 * w.G] = 1                            # prompt 1: all live
     act[2 * w.G] = 1; act[2 * w.G + 1:3 * w.G] = 0  # prompt 2: one survivor
-    check(y, w.dtype, w.scale, w.G, active=act, what="finished mix")
-    check(y, w.dtype, w.scale, w.G, active=np.zeros(w.B, np.uint8), what="all finished")
-    check(y, w.dtype, w.scale, w.G, active=np.ones(w.B, np.uint8), what="all live")
+    for algo in (B.RLDA_ALGO_AUTO, B.RLDA_ALGO_SHARED):   # one launch, and the kernels that walk a prefix once for its group
+        check(y, w.dtype, w.scale, w.G, active=act, algo=algo, what="finished mix")
+        check(y, w.dtype, w.scale, w.G, active=np.zeros(w.B, np.uint8), algo=algo, what="all finished")
+        check(y, w.dtype, w.scale, w.G, active=np.ones(w.B, np.uint8), algo=algo, what="all live")
     check(y, w.dtype, w.scale, w.G, active=act, algo=B.RLDA_ALGO_SIMPLE, what="finished mix, simple kernel")
 
 

@@ -196,13 +196,14 @@ def test_bitwise_determinism(algo, B):
         assert torch.equal(o1, o2) and torch.equal(l1, l2)
 
 
-def test_long_tail_load_balance_case(B):
-    """One 4096-token outlier next to short suffixes (agentic shape)."""
+@pytest.mark.parametrize("algo", ["auto", "shared"])
+def test_long_tail_load_balance_case(B, algo):
+    """One 4096-token outlier next to short suffixes (agentic shape): shared by several workgroups, and cut by the static partition."""
     w = wl.scaled(wl.WORKLOADS["agentic"], P=2)
     x = wl.make_inputs(w)
     x["suffix_lens"][:] = np.minimum(x["suffix_lens"], 300)
     x["suffix_lens"][5] = 4096
-    check(x, w.scale, w.G, "bf16", "auto", "outlier", B)
+    check(x, w.scale, w.G, "bf16", algo, "outlier", B)
 
 
 @pytest.mark.parametrize("algo", ["auto", "shared"])

@@ -3,7 +3,8 @@ shared segments with ragged (and empty) segments and suffixes, sharing widths do
 that do not nest, and the single-level case against rl_decode_attn bit for bit.
 
 The call has no algo field, and trees as small as these run in one launch.  Suffix stores of more than 2048
-rows, whatever they hold, take it to the shared-prefix kernels: every case runs on both."""
+rows, whatever they hold, take trees of several levels to the shared-prefix kernels, and so does a long level
+that is shared by many: every case runs on both."""
 import numpy as np
 import pytest
 
@@ -71,8 +72,7 @@ def test_tree_against_the_oracle(case, launches):
     scale = 1.0 / np.sqrt(128)
     ro, rl = oracle_tree(x, scale)
     y = widen(x, 2080) if launches == 2 else x
-    if launches == 2 or case[0] != "one head per KV head, long ragged segments":       # long ones take two anyway
-        assert tree_route(y, scale) == (B.RLDA_ALGO_SHARED if launches == 2 else B.RLDA_ROUTE_UNIT)
+    assert tree_route(y, scale) == (B.RLDA_ALGO_SHARED if launches == 2 else B.RLDA_ROUTE_UNIT)
     out, lse = run_tree(y, scale)
     util.compare(out, lse, ro, rl, "bf16", case[0])
 
@@ -80,10 +80,15 @@ def test_tree_against_the_oracle(case, launches):
 @pytest.mark.parametrize("launches", [1, 2])
 def test_one_level_equals_the_shared_prefix_call_bit_for_bit(launches):
     import torch
-    w = wl.scaled(wl.WORKLOADS["vlm7b"], P=3, Lp_cap=333, Ls_cap=211, prefix=("uniform", 333), suffix=("uniform", 211))
+    if launches == 1:
+        w = wl.scaled(wl.WORKLOADS["vlm7b"], P=3, Lp_cap=333, Ls_cap=211, prefix=("uniform", 333), suffix=("uniform", 211))
+    else:                                                     # long prefixes shared by many
+        w = wl.scaled(wl.WORKLOADS["vlm7b"], P=16, G=16, Hq=4, Hkv=1, Lp_cap=3500, Ls_cap=500, prefix=("uniform", 3500),
+                      suffix=("uniform", 500))
+    want = B.RLDA_ROUTE_UNIT if launches == 1 else B.RLDA_ALGO_SHARED
+    assert util.route(B.make_desc(B.RLDA_BF16, w.P, w.G, w.Hq, w.Hkv, w.d, w.Lp_cap, w.Ls_cap, w.scale)) == want
+    assert util.route(B.make_tree_desc(B.RLDA_BF16, w.B, w.Hq, w.Hkv, w.d, w.Ls_cap, w.scale, [(None, None, None, w.G, w.Lp_cap)])) == want
     x = wl.make_inputs(w)
-    if launches == 2:
-        x = widen(x, 2080)
     t = util.to_device(x)
     o1, l1 = util.gpu_run(t, w.scale, w.G)
     o2, l2 = B.rl_decode_attn_tree(t["q"], [(t["k_prefix"], t["v_prefix"], t["prefix_lens"], w.G)], t["k_suffix"],

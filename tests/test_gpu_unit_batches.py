@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
 def test_numbers_of_units(B, dtype, d, units, keys):  # noqa: F811
     if units * keys > 700_000:                                           # the oracle's time; the line lies below 512 keys
         keys = 290
-    lean = d == 128 and dtype != "f32" and 3 * (keys // 2) + keys // 2 <= 3600 and units * keys <= 1 << 19
+    code = {"f32": B.RLDA_F32, "bf16": B.RLDA_BF16, "e4m3": B.RLDA_BF16_KV8}[dtype]
+    lean = d == 128 and dtype != "f32" and util.route(B.make_desc(code, units // 4, 4, 4, 1, d, keys // 2, keys - keys // 2, 0.1)) == B.RLDA_ROUTE_UNIT
     x = case(units, units // 4, 4, 4, 1, d, keys // 2, keys - keys // 2, dtype)
     out, lse = util.gpu_run(util.to_device(x), 0.1, 4)
     ro, rl = util.oracle(x, 0.1, 4)
