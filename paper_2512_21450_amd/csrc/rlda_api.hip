@@ -1,12 +1,33 @@
 // C-ABI layer: argument validation, kernel-family selection, enqueue.
 // Validation and the workspace/plan queries are pure host code and work
 // without a GPU; only rl_decode_attn / rl_lse_combine touch the HIP runtime.
+#include "rlda_arrive.h"
 #include "rlda_internal.h"
 #include "rlda_sched.h"
 #include "../../include/rl_prefill_attn.h"
 
+#include <unistd.h>
+
+#include <atomic>
+#include <chrono>
 #include <mutex>
 #include <vector>
+
+// One counter for all operations, which may share a workspace.  It starts at the time and the process's number, mixed by the
+// finaliser of SplitMix64 (Steele, Lea and Flood, "Fast splittable pseudorandom number generators", 2014), so that numbers of
+// one process are none that another left in memory, nor look like data.
+uint64_t rlda::next_call() {
+  static std::atomic<uint64_t> n{[] {
+    uint64_t x = (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^ (uint64_t)getpid() << 40;
+    x = (x ^ x >> 30) * 0xbf58476d1ce4e5b9ull;
+    x = (x ^ x >> 27) * 0x94d049bb133111ebull;
+    return x ^ x >> 31;
+  }()};
+  uint64_t call;
+  do call = n.fetch_add(1, std::memory_order_relaxed) & (((uint64_t)1 << 56) - 1);
+  while (call == 0);
+  return call;
+}
 
 namespace {
 

@@ -1,7 +1,7 @@
 // Which of several workgroups that share a piece of work ends last, without a launch that clears a counter first.
 //
 // A counter is 64 bits in the caller's workspace, which may hold anything: the number of the call, which no other call of the
-// process has, above 8 bits that count arrivals.  At its start a workgroup puts the number there if it finds 0, and waits for
+// process has (56 bits, next_call), above 8 bits that count arrivals.  At its start a workgroup puts the number there if it finds 0, and waits for
 // nothing; when it has written what it leaves for the others it adds one.  Only where neither 0 nor the call's number stood
 // there (a workspace's first use) does it put the number there before.  An exchange that fails means that another workgroup of
 // the call was first, so none is tried twice and nothing ever waits.  The last to arrive leaves 0, which is what the next call,
@@ -16,29 +16,14 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-#include <unistd.h>
-
-#include <atomic>
-#include <chrono>
 
 namespace rlda {
+
+uint64_t next_call();                                        // a number that no other call of the process has, of any operation
+
 namespace {
 
 constexpr int MAX_ARRIVALS = 255;
-
-// a number that no other call has
-inline uint64_t next_call() {
-  static std::atomic<uint64_t> n{[] {
-    uint64_t x = (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^ (uint64_t)getpid() << 40;
-    x = (x ^ x >> 30) * 0xbf58476d1ce4e5b9ull;               // any mixing of the bits will do
-    x = (x ^ x >> 27) * 0x94d049bb133111ebull;
-    return x ^ x >> 31;
-  }()};
-  uint64_t call;
-  do call = n.fetch_add(1, std::memory_order_relaxed) & (((uint64_t)1 << 56) - 1);
-  while (call == 0);
-  return call;
-}
 
 // by one thread, at the start; the result goes to arrive()
 __device__ __forceinline__ uint64_t claim(uint64_t* counter, uint64_t call) {

@@ -296,6 +296,7 @@ typedef f32x4 f32x4u __attribute__((aligned(4)));
 
 template <bool COUNT, bool ONE>
 __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
+  static_assert(!COUNT || ONE, "the kernel behind the token pass reads the counts that policy_count_kernel leaves");
   __shared__ float shf[NT / 64][6];
   const int tid = threadIdx.x;
   long long n_tok, n_seq;
@@ -317,7 +318,6 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
     __syncthreads();
     n_tok = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
     n_seq = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
-    if (blockIdx.x == 0 && tid == 0) { L.counts[0] = n_tok; L.counts[1] = n_seq; }
   } else {
     n_tok = L.counts[0]; n_seq = L.counts[1];
   }
