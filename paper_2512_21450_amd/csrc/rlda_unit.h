@@ -678,6 +678,22 @@ size_t split_bytes(const Problem& pb, int splits) {
   return split_counters(pb) * 8 + (size_t)splits * n_sequences(pb) * pb.Hq * (8 + (size_t)pb.d * 4);
 }
 
+// (group, part) pairs that a die takes, or 0: fewer than two of them, plain order, so that neighbours spread over the dies
+int64_t die_groups(const Problem& pb, int splits) {
+  const int64_t n = n_sequences(pb) / max_group(pb) * pb.Hkv * splits;
+  return n >= 16 && max_group(pb) > 1 ? (n + 7) / 8 : 0;
+}
+int64_t unit_blocks(const Problem& pb, int splits) {
+  const int64_t rb = ceil_div(pb.Hq / pb.Hkv, 16), g8 = die_groups(pb, splits);
+  return g8 > 0 ? g8 * 8 * max_group(pb) * rb : n_sequences(pb) * pb.Hkv * rb * splits;
+}
+int full_tiles(const Problem& pb) {                    // of a sequence that fills its buffers (up to the largest int)
+  const auto of = [](int cap) { return cap / TK + (cap % TK != 0); };
+  int n = of(pb.Ls_cap) + of(pb.Lp_cap);
+  for (int l = 0; l < pb.n_levels; ++l) n += of(pb.levels[l].cap);
+  return n;
+}
+
 struct Split { int splits, nw, min_tiles; };
 // How many workgroups share a unit at most: as many as the compute units hold, up to 16, and more than one from `min_tiles` of the unit's
 // real tiles on, if the buffers hold half as many again: workgroups that find nothing to do cost 0.3 to 0.7 us (80 units of e4m3, 128
@@ -691,16 +707,15 @@ struct Split { int splits, nw, min_tiles; };
 // more tiles on only (128 units, one / two: fp32 512 keys 11.1 / 9.8, 384 8.1 / 8.1; bf16 of 128 columns 1024 11.8 / 12.5, 1088 11.1 /
 // 10.4, 2048 18.7 / 17.4; bf16 of 64 1024 8.2 / 9.1, 2112 10.6 / 9.5), and not where the sequences' own keys are most of a call in bf16
 // of 64 columns (64 + 2048 keys 13.6 / 15.2, half full 9.4 / 10.7; e4m3 12.9 / 12.3).  More than half as many units as compute units
-// gain nothing (256 units of 1088 to 4000 keys: 2 to 15 % slower).
+// gain nothing (256 units of 1088 to 4000 keys: 2 to 15 % slower).  Nor do parts that no compute unit is free for: a die takes whole
+// (group, part) pairs, and where their number is no multiple of eight some would get a second round of workgroups (e4m3, 10 prompts of
+// 5 samples, 3888 + 2760 keys: five parts, 35 workgroups on a die, 27.4, four 20.8; bf16, 3000 + 2000 keys 27.7 / 20.3).
 Split split_rule(const Problem& pb, int pairs) {
   const int64_t units = n_sequences(pb) * pb.Hkv * ceil_div(pb.Hq / pb.Hkv, 16);
   const bool f32 = pb.dtype == RLDA_F32, wide = pb.d == 128;
   Split s{1, 0, 0};
   if (2 * units > pairs || units < 1 || (pb.paged && pb.page_shift < 5)) return s;   // (a query brings no table)
-  const auto tiles_of = [](int cap) { return cap / TK + (cap % TK != 0); };   // (capacities up to the largest int)
-  int tiles = tiles_of(pb.Ls_cap) + tiles_of(pb.Lp_cap);                   // of a sequence that fills its buffers
-  for (int l = 0; l < pb.n_levels; ++l) tiles += tiles_of(pb.levels[l].cap);
-  const int n = pairs / (int)units, most = n < MAX_UNIT_SPLITS ? n : MAX_UNIT_SPLITS;
+  const int tiles = full_tiles(pb), n = pairs / (int)units, most = n < MAX_UNIT_SPLITS ? n : MAX_UNIT_SPLITS;
   if (tiles > (f32 ? 12 : 24) && tiles <= 32 && (f32 || wide) && ceil_div(tiles, 4) <= n) {
     s.nw = 4;
     s.min_tiles = 5;
@@ -710,6 +725,8 @@ Split split_rule(const Problem& pb, int pairs) {
     if (n == 2 && pb.dtype == RLDA_BF16 && !wide && units * pb.Ls_cap > (int64_t)512 * pairs) return s;
   }
   if (2 * tiles >= 3 * s.min_tiles) s.splits = most < ceil_div(tiles, s.nw) ? most : ceil_div(tiles, s.nw);
+  const int held = (160 << 10) / (s.nw * 2 * TK * pb.d * (f32 ? 4 : 2));   // workgroups in the LDS of a compute unit
+  while (s.splits > 1 && unit_blocks(pb, s.splits) > (int64_t)held * pairs) --s.splits;
   return s;
 }
 
@@ -724,21 +741,14 @@ Split split_rule(const Problem& pb, int pairs) {
 //   small batches (two bf16 pieces), 1024 x 128  19.8 / 14.8 / 12.6 / 13.1        8192 x 64    137 / 85 / 66 / 66
 //   pages of 16 rows, bf16, 128 columns  320 x 1000  38 / 44 / - / -     512 x 1000  44 / 40 / - / -   1024 x 64 34 / 21 / 13 / 14
 //                                        256 x 1024  26 / 39 / 62 / 108  4096 x 256   223 / 134 / 134 / 117
-UnitGrid unit_grid(const Problem& pb, int pairs, bool exact) {
-  const int64_t B = n_sequences(pb), G = max_group(pb), rb = ceil_div(pb.Hq / pb.Hkv, 16), keys = shared_cap(pb) + pb.Ls_cap;
+UnitGrid unit_grid(const Problem& pb, int pairs, bool exact, Split sp) {
+  const int64_t keys = shared_cap(pb) + pb.Ls_cap;
   UnitGrid u{};
-  u.splits = 1;
-  // fewer than two groups a die: plain order, so that neighbours spread over the dies
-  const int64_t groups = B / G * pb.Hkv;
-  u.groups8 = groups >= 16 && G > 1 ? (int)((groups + 7) / 8) : 0;
-  u.blocks = u.groups8 > 0 ? u.groups8 * 8 * G * rb : B * pb.Hkv * rb;
-  Split sp = split_rule(pb, pairs);
-  while (sp.splits > 1 && (!pb.workspace || (reinterpret_cast<uintptr_t>(pb.workspace) & 255u) || split_bytes(pb, sp.splits) > pb.workspace_bytes))
-    --sp.splits;                                       // a caller with less workspace than asked for, or none
+  u.splits = sp.splits;
+  u.groups8 = (int)die_groups(pb, sp.splits);
+  u.blocks = unit_blocks(pb, sp.splits);
   if (sp.splits > 1) {
-    u.groups8 = groups * sp.splits >= 16 && G > 1 ? (int)((groups * sp.splits + 7) / 8) : 0;
-    u.blocks = u.groups8 > 0 ? u.groups8 * 8 * G * rb : B * pb.Hkv * rb * sp.splits;
-    u.nw = sp.nw; u.splits = sp.splits; u.min_tiles = sp.min_tiles;
+    u.nw = sp.nw; u.min_tiles = sp.min_tiles;
     return u;
   }
   const bool f32 = pb.dtype == RLDA_F32, many = u.blocks > 4 * (int64_t)pairs;
@@ -758,6 +768,12 @@ UnitGrid unit_grid(const Problem& pb, int pairs, bool exact) {
     u.nw = u.blocks > 2 * fit && (!exact || keys <= 128) ? 1 : 2;
   }
   return u;
+}
+UnitGrid unit_grid(const Problem& pb, int pairs, bool exact) {
+  Split sp = split_rule(pb, pairs);
+  while (sp.splits > 1 && (!pb.workspace || (reinterpret_cast<uintptr_t>(pb.workspace) & 255u) || split_bytes(pb, sp.splits) > pb.workspace_bytes))
+    --sp.splits;                                       // a caller with less workspace than asked for, or none
+  return unit_grid(pb, pairs, exact, sp);
 }
 
 // The form of one store type and head dimension: pages of fewer rows than a tile, a tree, or two segments.  The fewer
@@ -869,7 +885,16 @@ bool unit_pays(const Problem& pb, int pairs) {
 // with 1 row 8 x 16 x 1 2048 + 256 14.5 / 13.3, with 8 32 x 8 x 1 2048 + 256 20.5 / 25.5; e4m3 32 x 8 x 1 64 + 2000 23.7 / 32.3, 64 x 8 x 1
 // 49.1 / 51.6, 16 x 16 x 1 2048 + 256 18.7 / 16.4, 3500 + 500 29.1 / 19.7.  Beyond 20 000 tiles (e4m3 32 768) units differ in length too
 // much: half full, 64 x 8 x 1 64 + 2000 59 / 51.  Groups of 16 rows or fewer, which share little and are read at the memory's rate either
-// way, stay at 16 384.  Units of hardly any key, which wait for nothing but their turn: 16384 x (16 + 16) 58 / 70, 65536 x (1 + 1)
+// way, stay at 16 384.
+// And a wavefront's own chain of tiles has to be short, which the other path cuts as it needs: up to 8 tiles in bf16 where units are
+// shared or a group has 16 rows or fewer, 10 else; 12 in e4m3, 14 where a group has more than 64 rows, which cost the other path row
+// parts; 7 where workgroups queue.  Beyond, lengths that differ and a queue's last round decide: 13 x 5 x 4 348 + 2030 (18.8 tiles) 78.8 /
+// 54.9, half full 38.4 / 35.3; 9 x 16 x 2 991 + 1284 55.6 / 42.4; 66 x 5 x 1 44 + 1936 half full 45.8 / 36.4; 19 x 4 x 2 2241 + 2017 39.0 /
+// 30.8; e4m3 33 x 5 x 8 386 + 330 44.4 / 35.5.  Of 1009 drawn points that the two lines above take, full and with lengths spread up to
+// that: 688 within these too are 1.25 and 1.29 times as fast here in the geometric mean, one less than 0.97 times by the sum of both (128
+// units of 1870 + 377, in two parts each, 18.3 / 16.7 full and 13.7 / 16.2 so); the 321 beyond 1.02 and 1.03, 92 of them slower.
+// Trees of several levels cost the other path more: 146 drawn ones 1.42 and 1.50, none below 0.99.
+// Units of hardly any key, which wait for nothing but their turn: 16384 x (16 + 16) 58 / 70, 65536 x (1 + 1)
 // 163 / 149.  Stores of up to 2048 suffix rows and 3600 in all, prefix rows counted three times, are always taken up to 16 384 tiles: the
 // other path is up to twice as slow there with many short units.  Longer units than 8960 keys were not measured.  Trees of several levels over stores of more than 2048 suffix rows stay on
 // the shared-prefix kernels, whatever is faster: a tree call has no algo field, and that is how a caller, and the tests, take it there.
@@ -884,9 +909,16 @@ bool unit_preferred(const Problem& pb, int pairs) {
   int64_t read = units * pb.Ls_cap + (int64_t)pb.P * pb.Hkv * pb.Lp_cap;                  // keys that come from memory
   for (int l = 0; l < pb.n_levels; ++l) read += (int64_t)pb.levels[l].n_seg * pb.Hkv * pb.levels[l].cap;
   // places that the workgroups leave empty cost as if they walked too
-  const int64_t blocks = units * split_rule(pb, pairs).splits, places = units > pairs ? 2 * (int64_t)pairs : pairs;
+  const Split sp = split_rule(pb, pairs);
+  const int64_t blocks = units * sp.splits, places = units > pairs ? 2 * (int64_t)pairs : pairs;
   const int64_t walked = blocks < places ? units * keys * places / blocks : units * keys;
-  return 4 * walked <= (int64_t)(few ? 4 * 560 : 4 * 864) * pairs + (f8 ? 6 : 11) * read;
+  if (4 * walked > (int64_t)(few ? 4 * 560 : 4 * 864) * pairs + (f8 ? 6 : 11) * read) return false;
+  if (pb.n_levels > 1) return true;
+  // the tiles that a wavefront walks one after the other
+  const UnitGrid g = unit_grid(pb, pairs, false, sp);
+  const int64_t rows = max_group(pb) * (pb.Hq / pb.Hkv);
+  const int most = g.blocks * g.nw > (int64_t)8 * pairs ? 7 : f8 ? (rows > 64 ? 14 : 12) : few || g.splits > 1 ? 8 : 10;
+  return full_tiles(pb) <= most * g.nw * g.splits;
 }
 
 size_t unit_workspace_bytes(const Problem& pb) {

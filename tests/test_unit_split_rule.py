@@ -31,6 +31,15 @@ def test_how_many_workgroups_share_a_unit(dtype, d, units, r, Lp, Ls, want):
     assert of(dtype, d, units, r, Lp, Ls) == want
 
 
+def test_no_part_waits_for_a_compute_unit():
+    """A die takes whole (group, part) pairs: five parts of ten groups are 7 pairs on most dies, 35 workgroups on 32 compute units, four are 5.
+    Two workgroups of 16-bit stores of 64 columns share a compute unit."""
+    grouped = lambda dtype, P, G, Lp, Ls: splits(B.rl_decode_attn_workspace_bytes(
+        B.make_desc(dtype, P, G, 1, 1, 64, Lp, Ls, 0.1, B.RLDA_ALGO_AUTO_SCRATCH)), P * G, P * G, 64)
+    assert grouped(F32, 10, 5, 4000, 2000) == 4 and of(F32, 64, 50, 1, 4000, 2000) == 5 and grouped(BF16, 10, 5, 4000, 2000) == 5
+    assert grouped(F32, 7, 5, 4000, 2000) == 6 and grouped(F32, 16, 4, 4000, 2000) == 4 and grouped(F32, 17, 5, 4000, 2000) == 2
+
+
 def test_what_is_never_shared():
     assert of(F32, 64, 2, 1, 4000, 4000, algo=B.RLDA_ALGO_SIMPLE) == 1
     paged = lambda page, pages, algo: B.rl_decode_attn_paged_workspace_bytes(
@@ -75,3 +84,17 @@ def test_where_one_launch_is_taken_instead_of_two(dtype, P, G, Hkv, r, Lp, Ls, w
         if dtype == BF16 and G * r <= 64:
             tree = B.rl_decode_attn_debug_route(B.make_tree_desc(dtype, P * G, Hkv * r, Hkv, 128, Ls, 0.1, lv), 256)
             assert tree == (B.RLDA_ROUTE_UNIT if want == "UNIT" and (levels == 1 or Ls <= 2048) else B.RLDA_ALGO_SHARED)
+
+
+@pytest.mark.parametrize("dtype,P,G,Hkv,r,Lp,Ls,want", [
+    # as measured: short lengths or a queue's last round decide
+    (BF16, 10, 5, 1, 4, 3000, 2000, "UNIT"), (BF16, 13, 5, 4, 4, 348, 2030, "SHARED"), (BF16, 9, 16, 2, 2, 991, 1284, "SHARED"),
+    (BF16, 19, 4, 2, 16, 2241, 2017, "SHARED"), (BF16, 66, 5, 1, 4, 44, 1936, "SHARED"), (E4M3, 33, 5, 8, 1, 386, 330, "SHARED"),
+    # either side of 8 and 10 tiles a wavefront, 8 where two workgroups share a unit, 12 and 14 in e4m3, 7 where workgroups queue
+    (BF16, 20, 8, 1, 2, 992, 1056, "UNIT"), (BF16, 20, 8, 1, 2, 992, 1057, "SHARED"), (BF16, 20, 8, 1, 4, 992, 1568, "UNIT"),
+    (BF16, 20, 8, 1, 4, 992, 1569, "SHARED"), (BF16, 16, 8, 1, 4, 992, 3104, "UNIT"), (BF16, 16, 8, 1, 4, 992, 3105, "SHARED"),
+    (E4M3, 20, 8, 1, 8, 32, 3040, "UNIT"), (E4M3, 20, 8, 1, 8, 32, 3041, "SHARED"), (E4M3, 20, 8, 1, 9, 32, 3552, "UNIT"),
+    (E4M3, 20, 8, 1, 9, 32, 3553, "SHARED"), (BF16, 41, 8, 8, 8, 32, 192, "UNIT"), (BF16, 41, 8, 8, 8, 33, 192, "SHARED")])
+def test_a_chain_of_tiles_is_short(dtype, P, G, Hkv, r, Lp, Ls, want):
+    ds = B.make_desc(dtype, P, G, Hkv * r, Hkv, 128, Lp, Ls, 0.1)
+    assert B.rl_decode_attn_debug_route(ds, 256) == (B.RLDA_ROUTE_UNIT if want == "UNIT" else B.RLDA_ALGO_SHARED)
