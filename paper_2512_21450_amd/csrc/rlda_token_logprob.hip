@@ -342,8 +342,18 @@ int splits_with_less(const rl_token_logprob_desc* d) {
 // what does not depend on a reference keeps its bits without one.)  us, calls one after the other from Python (captured), two launches / one:
 //   16 x 32000 bf16 16.5 (5.6) / 14.0 (5.2)      48 x 151936 bf16 [R] 18.9 (12.8) / 16.7 (12.5)   150 x 50001 fp32 [R] 19.7 (16.2) / 17.2 (15.8)
 //   257 x 32000 bf16 [R] 19.9 (13.7) / 17.2 (13.4)   100 x 151936 fp32 [R] 25.3 (24.9) / 25.9 (25.8)   448 x 151936 bf16 [R] 52.6 / 56.7
-//   1 x 151936 fp32 [R], 63 workgroups on one counter: 19.9 (6.1) / 17.5 (7.0)
+//   1 x 151936 fp32 [R] 18.7 / 16.3
+// Beyond MEET splits so many workgroups meet at a counter that a captured call, which waits for no host, loses: it gets the second
+// kernel.  Captured, the counter / the second kernel, 1 and 12 rows: 151936 fp32 (63 splits) 5.6 / 5.0 and 7.1 / 6.8, [R] 7.0 / 6.5 and
+// 9.6 / 9.1, 256000 bf16 (61) 5.7 / 5.4 and 7.4 / 7.1; but 151936 bf16 (36) 5.5 / 5.1 and 6.3 / 6.5, 8 rows 5.9 / 6.3.  (A split less is
+// a round of loads more for a few: 24 x 256000 bf16 captured 8.4 with 32 splits, 8.7 so.)
 constexpr long long ONE_LAUNCH = 48 * 1000 * KB;             // bytes of logits
+constexpr int MEET = 48;
+bool captured(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return s == hipStreamCaptureStatusActive;
+}
 size_t bytes_for(const rl_token_logprob_desc* d, int S) { return S == 1 ? 0 : (size_t)d->n_rows * S * PER_SPLIT; }
 
 thread_local hipError_t g_last = hipSuccess;
@@ -380,13 +390,17 @@ int rl_token_logprob(const rl_token_logprob_desc* d, void* hip_stream) {
   P.part = static_cast<float*>(d->workspace);
   const bool ref = d->ref_logits != nullptr;
   P.stride = d->row_stride; P.V = d->vocab; P.slots = S;
-  const bool one = S > 2 && row_bytes(d) * d->n_rows <= ONE_LAUNCH;
-  if (one) { P.call = rlda::next_call(); --S; }             // the last slot is the counter's
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  bool one = S > 2 && row_bytes(d) * d->n_rows <= ONE_LAUNCH;
+  if (one) {
+    P.call = rlda::next_call();
+    one = S <= MEET || !captured(st);
+    --S;                                                    // the last slot is the counter's; captured or not, the bits are the same
+  }
   P.S = S;
   const int per = (d->vocab + S - 1) / S;
   P.chunk = (per + vn - 1) / vn * vn;
   P.k2 = d->inv_temperature * 1.4426950408889634f;
-  hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const dim3 grid((unsigned)(d->n_rows * S)), fin((unsigned)d->n_rows);
   // few workgroups, each with more than two rounds of loads for 256 threads (or none to share a row with): 16 wavefronts
   const bool wide = d->n_rows * S <= 512 && (S == 1 || less || row_bytes(d) / S > ROUNDS);

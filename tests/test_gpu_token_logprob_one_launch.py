@@ -38,11 +38,13 @@ def test_either_side_of_the_line(B, n, V, dtype, ref):  # noqa: F811
     check(B.rl_token_logprob(z, ids, 1.0, w), want, (n, V, dtype, ref))
 
 
+# 8 and 63 splits: a captured call merges the latter by a second kernel, to the same bits
+@pytest.mark.parametrize("n,V,dtype", [(37, 40001, "bf16"), (2, 151936, "f32")])
 @pytest.mark.parametrize("ref", [False, True])
-def test_any_workspace_and_replays(B, ref):  # noqa: F811
+def test_any_workspace_and_replays(B, ref, n, V, dtype):  # noqa: F811
     import torch
-    z, ids, w, want = rows(37, 40001, "bf16", ref)
-    outs = {k: torch.full((37,), 7.0, device="cuda") for k in want}
+    z, ids, w, want = rows(n, V, dtype, ref)
+    outs = {k: torch.full((n,), 7.0, device="cuda") for k in want}
     ds = B.token_logprob_desc_from_tensors(z, ids, 1.0, w, outs)
     need = B.rl_token_logprob_workspace_bytes(ds)
     ws = torch.empty(need + 256, dtype=torch.uint8, device="cuda")
