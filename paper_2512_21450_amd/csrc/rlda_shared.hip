@@ -1176,25 +1176,25 @@ constexpr int N_XCD = 8;
 // of every unit, and begins `turn` * (i + (i >> again)) units further (turn 0 or 1).  What that does, lg / chunk:
 // - 0 / 1, a unit after the other on one XCD: what is in flight there reads the K/V of one or two prompts, long and short blocks
 //   run beside each other.
-// - 0 / 8: where a unit has few blocks, its last ones no longer start beside the longest of the next.
+// - 0 / 8: where a unit has few blocks, its last ones no longer start beside the longest of the next; with few heads to a KV head
+//   blocks are of many positions, and differ.
 // - 1, 2 / 3, 4: a few ragged units per XCD leave some XCDs the long prompts.
 // The turn is for ragged prompts, whose empty workgroups are in every row at the same units: workgroups go round-robin to the XCDs
 // and, inside, to four shader engines, and an engine that got the same units in every row is left without work.  `again`: where four
 // workgroups of an XCD are several rows, turning by one unit a row brings an engine back to the same units (16 x 1500 of 7/1 heads 52.7
 // us without, 46.6; 8 x 640 of 14/1 18.5 / 17.1).
 struct PrefillOrder { int lg, chunk, turn, again; };
-// Measured (bf16, bits the same; all prompts full / ragged, us, before -> after, from 0 / 1):
-//   8 units, 2 / 4:       4 x 2744 of 16/2 heads 130 -> 130 / 95 -> 68, 8 x 2000 of 8/1 76 -> 78 / 65 -> 51, 2 x 3000 of 28/4 136 -> 137 /
-//                         82 -> 65, 8 x 640 of 14/1 28.3 -> 28.5 / 25.0 -> 17.1 (up to a round of blocks, two per compute unit, there
-//                         is nothing to win: 8 x 900 of 4/1 19.0 -> 19.6 / 17.9 -> 18.3)
-//   16, 24 units, 1 / 4 and 1 / 3:  8 x 1667 of 16/2 104 -> 102 / 62 -> 53, 16 x 1500 of 7/1 78 -> 78 / 55 -> 45, 6 x 737 of 32/4 42 ->
-//                         42 / 32 -> 25, 12 x 900 of 14/2 51 -> 50 / 38 -> 31 (up to two rounds: 8 x 512 of 16/2 20.4 -> 21.9 / 13.8 -> 14.2,
-//                         4 x 900 of 28/4 34.6 -> 37.7 / 28.2 -> 25.8: the longest blocks side by side)
-//   32 units, 0 / 8:      16 x 1500 of 2/2 40 -> 31 / 27.5 -> 26.7, 16 x 1000 of 10/2 61 -> 58 / 38 -> 33, 8 x 1500 of 20/4 116 -> 112 /
-//                         62 -> 55, 16 x 900 of 16/2 75.6 -> 74.4 / 43 -> 41
-//   more, <= 32 blocks, 0 / 8:  8 x 2048 of 8/8 110 -> 84 / 62 -> 50, 32 x 1280 of 4/4 87 -> 73 / 55 -> 44, 22 x 1100 of 12/4 118 -> 114 /
-//                         66 -> 63, 16 x 512 of 8/8 28 -> 22 / 18.5 -> 14.5, 41 x 800 of 4/2 (82 units) 50 -> 47 / 33 -> 30, 10 x 1000 of
-//                         32/8 115 -> 110 / 60 -> 61
+// Measured, bf16, bits the same, as times of 0 / 1, all prompts full / ragged, geometric means over drawn shapes (n); 64 and 128 rows to a
+// workgroup; rounds: of two workgroups per compute unit.  Single shapes scatter by a tenth where they are full.
+//   8 units, 2 / 4:       from 1.5 rounds on .99 / 1.26 (48), below .99 / 1.01 (35).  4 x 2744 of 16/2 heads 132.6 -> 132.7 / 96.8 -> 66.8 us, 8 x
+//                         2000 of 8/1 78.2 -> 78.7 / 66.2 -> 51.1, 8 x 640 of 14/1 28.8 -> 29.2 / 25.4 -> 18.1, 4 x 4096 of 16/2 274 -> 276 / 196 -> 118
+//   16, 24 units, 1 / 4 and 1 / 3:  from two rounds on 1.01 / 1.13 (123).  8 x 1667 of 16/2 104 -> 102 / 62 -> 53 us, 6 x 737 of 32/4 42 -> 42 / 32 ->
+//                         25 (up to two rounds: 8 x 512 of 16/2 20.4 -> 21.9 / 13.8 -> 14.2: the longest blocks side by side)
+//   32 units of 128 rows, 0 / 8:  1.04 / 1.06 (52).  16 x 1000 of 10/2 61 -> 58 / 38 -> 33 us
+//   32 units and more, <= 32 blocks, 0 / 8, goes by r: up to 2 1.10 / 1.05 (118); 3 and 4 with 128 rows up to six rounds 1.05 / 1.07 (17), beyond
+//                         .96 / .97 (8), with 64 rows up to three where Hkv is a multiple of eight or there are 32 units 1.04 / 1.05 (14), else
+//                         .98 / 1.00 (17); from 5 on .96 / .99 (185).  8 x 2048 of 8/8 110 -> 84 / 62 -> 50 us, 16 x 1500 of 2/2 40 -> 31 / 27.5 ->
+//                         26.7, 32 x 1280 of 4/4 87 -> 73 / 55 -> 44; 50 x 558 of 40/8 285 -> 306 / 156 -> 175, 26 x 87 of 56/8 23.9 -> 26.6 / 17.4 -> 17.5
 //   more of more blocks:  the short ones then come together, and what they wait for is not hidden by long ones: 10 x 684 of 64/8 (43
 //                         blocks a unit) 117 -> 121 / 61 -> 66, 32 x 600 of 16/2 (38) 75 -> 77 / 51 -> 49
 // A prompt whose heads go to all XCDs (Hkv a multiple of eight) is balanced as it is.
@@ -1204,16 +1204,23 @@ struct PrefillOrder { int lg, chunk, turn, again; };
 // up to 4096 of 28/4 (28) 529 / 424, 30 ragged up to 500 of 12/2 (60) 37.7 / 35.6; above, the working set of an XCD (every unit's K/V)
 // outgrows its L2 and the few empty places no longer cost that much: 41 x 700 of 16/2 (82) 153 / 165, 50 of 12/2 (100) 54.5 / 56.1,
 // 33 x 1500 of 28/4 (132) 358 / 375.
-inline PrefillOrder prefill_order(int units, int Hkv, int64_t nqb, int64_t rounds) {
+inline PrefillOrder prefill_order(int units, int Hkv, int r, int64_t nqb, PrefillForm form, int pairs) {
   const int none = 31;
+  const PrefillOrder whole{0, 1, 0, none}, chunks{0, 8, 1, none};
   if (units % N_XCD != 0 && units < 8 * N_XCD) return {3, units, 0, none};
-  if (rounds <= 1) return {0, 1, 0, none};
-  if (Hkv % N_XCD != 0 && units == N_XCD) return {2, 4, 1, 2};
-  if (Hkv % N_XCD != 0 && units <= 3 * N_XCD) {
-    if (rounds <= 2) return {0, 1, 0, none};
+  const int64_t blocks = units * nqb, half = pairs;         // half a round
+  const bool two = form == PREFILL_128, balanced = Hkv % N_XCD == 0;
+  if (form == PREFILL_TEAMS || blocks <= 2 * half) return whole;
+  if (!balanced && units == N_XCD) return blocks > 3 * half ? PrefillOrder{2, 4, 1, 2} : whole;
+  if (!balanced && units <= 3 * N_XCD) {
+    if (blocks <= 4 * half) return whole;
     return units == 2 * N_XCD ? PrefillOrder{1, 4, 1, 1} : PrefillOrder{1, 3, 1, none};
   }
-  return nqb <= 32 || (Hkv % N_XCD != 0 && units == 4 * N_XCD) ? PrefillOrder{0, 8, 1, none} : PrefillOrder{0, 1, 0, none};
+  if (!balanced && units == 4 * N_XCD && two) return chunks;
+  if (nqb > 32) return whole;
+  if (r <= 2) return chunks;
+  if (r <= 4 && (two ? blocks <= 12 * half : (balanced || units == 4 * N_XCD) && blocks <= 6 * half)) return chunks;
+  return whole;
 }
 // Places without chunks (one unit after the other, or all units to all XCDs) by one division: three in a row, or a branch with
 // arguments of its own behind it, are 0.1 to 0.4 us of a short call (8 ragged prompts up to 452 of 16/2 heads 12.4 / 12.5, 1 x 500 of
@@ -2052,7 +2059,7 @@ hipError_t launch_prefill(const void* q, const void* k, const void* v, const int
   P.QB = (form == PREFILL_128 ? 2 : 1) * 16 * WG_WAVES / P.r;             // query positions per workgroup
   P.nqb = ceil_div(Lp_cap, P.QB);
   const int units = P_ * Hkv;
-  const PrefillOrder order = prefill_order(units, Hkv, P.nqb, teams ? 1 : ((int64_t)units * P.nqb + 2 * pairs - 1) / (2 * pairs));
+  const PrefillOrder order = prefill_order(units, Hkv, P.r, P.nqb, form, pairs);
   const int per = ceil_div(units, N_XCD >> order.lg), chunks = ceil_div(per, order.chunk);     // of a group of XCDs
   P.lg = order.lg; P.chunk = ceil_div(per, chunks); P.turn = order.turn; P.again = order.again;
   const int64_t blocks = (int64_t)P.chunk * P.nqb;          // of a chunk
