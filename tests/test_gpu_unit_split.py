@@ -55,6 +55,19 @@ def test_shared_units(B, dtype, d, shape):  # noqa: F811
         compare(out, lse, ro, rl, EXACT, (dtype, d, shape, seed))
 
 
+# two, three and four blocks of 16 rows a KV head, each with a counter of its own: in groups on one die, and in plain order
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("e4m3", 64), ("bf16", 128), ("e4m3", 128)])
+@pytest.mark.parametrize("P,G,Hkv,r", [(4, 4, 1, 17), (3, 5, 1, 40), (2, 2, 4, 32), (3, 1, 1, 17), (2, 1, 2, 40), (1, 1, 1, 64)])
+def test_more_than_sixteen_rows_per_kv_head(B, dtype, d, P, G, Hkv, r):  # noqa: F811
+    code = {"f32": B.RLDA_F32, "bf16": B.RLDA_BF16, "e4m3": B.RLDA_BF16_KV8}[dtype]
+    ds = B.make_desc(code, P, G, Hkv * r, Hkv, d, 1000, 1800, 0.1, B.RLDA_ALGO_AUTO_SCRATCH)
+    assert B.rl_decode_attn_workspace_bytes(ds) > 0 and util.route(ds) == B.RLDA_ROUTE_UNIT
+    x = case(B, dtype, d, P, G, r, 1000, 1800, r, Hkv=Hkv)
+    out, lse = util.gpu_run(util.to_device(x), 0.1, G)
+    ro, rl = util.oracle(x, 0.1, G)
+    compare(out, lse, ro, rl, EXACT, (dtype, d, P, G, Hkv, r))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "e4m3"])
 @pytest.mark.parametrize("shape", [(5, 4, 7, 700, 1500), (8, 8, 4, 480, 500), (10, 8, 16, 700, 90), (16, 8, 2, 500, 2000)], ids=str)
 def test_small_batches_of_long_sequences(B, dtype, shape):  # noqa: F811
@@ -103,6 +116,53 @@ def test_infinite_values_and_keys(B):  # noqa: F811
     with np.errstate(invalid="ignore"):
         assert (same | (np.abs(o - ro) <= 2e-5)).all()
     assert np.isinf(ro).any() and np.isnan(ro).any() and np.abs(lse.cpu().numpy() - rl).max() <= 1e-5
+
+
+def same_with_infinities(out, lse, ro, rl, tol):
+    o = out.cpu().numpy().astype(np.float64)
+    same = (o == ro) | (np.isnan(o) & np.isnan(ro))
+    with np.errstate(invalid="ignore"):
+        assert (same | (np.abs(o - ro) <= tol)).all()
+    assert np.isinf(ro).any() and np.isnan(ro).any() and np.abs(lse.cpu().numpy() - rl).max() <= 1e-5
+
+
+def bits(dtype, v):
+    return np.float32(v) if dtype == "f32" else wl.f32_to_bf16_bits(np.array([v], np.float32))[0]
+
+
+@pytest.mark.parametrize("page", [0, 64])
+@pytest.mark.parametrize("dtype,d,r", [("f32", 128, 3), ("bf16", 64, 3), ("bf16", 64, 20), ("bf16", 128, 3), ("bf16", 128, 20)])
+def test_infinite_values_in_shared_units(B, dtype, d, r, page):  # noqa: F811
+    """In every segment, in one column and in both directions, which gives none; rows of 24-bit and of 16-bit weights."""
+    x = util.random_case(10, 2, 2, 2 * r, 2, d, 1500, 1100, dtype, [1500, 1499], [1100, 0, 33, 1099])
+    v = lambda y: bits(dtype, y)
+    x["v_prefix"][0, :, 1499, 3], x["v_prefix"][1, :, 1040, d - 1], x["v_prefix"][1, 0, 700, 9] = v(np.inf), v(-np.inf), v(np.nan)
+    x["v_suffix"][0, 1, 1099, 3], x["v_suffix"][3, 0, 5, 2] = v(-np.inf), v(np.inf)
+    lean = d == 128 and dtype == "bf16" and r <= 16
+    code = B.RLDA_F32 if dtype == "f32" else B.RLDA_BF16
+    if page:
+        y = wl.to_pages(x, page, seed=1)
+        out, lse = util.gpu_run_paged(util.to_device(y), 0.1, 2)
+        ro, rl = util.oracle_paged(y, 0.1, 2)
+    else:
+        assert util.route(B.make_desc(code, 2, 2, 2 * r, 2, d, 1500, 1100, 0.1)) == B.RLDA_ROUTE_UNIT
+        out, lse = util.gpu_run(util.to_device(x), 0.1, 2)
+        ro, rl = util.oracle(x, 0.1, 2)
+    same_with_infinities(out, lse, ro, rl, LEAN if lean else EXACT)
+
+
+def test_infinite_values_in_a_tree(B):  # noqa: F811
+    from oracle import ref
+    x = wl.make_tree_inputs(3, 8, 10, 2, 128, [(8, 600, ("const", 600)), (2, 450, ("const", 450))], 400, ("const", 400))
+    for i, (at, y) in enumerate([((0, 0, 599, 3), np.inf), ((2, 1, 449, 77), -np.inf)]):
+        x["levels"][i][1][at] = bits("bf16", y)
+    x["v_suffix"][5, 0, 399, 3], x["v_suffix"][6, 1, 0, 9] = bits("bf16", -np.inf), bits("bf16", np.nan)
+    lv = [tuple(util.to_device({"k": k, "v": v, "n": n}).values()) + (g,) for k, v, n, g in x["levels"]]
+    t = util.to_device({k: x[k] for k in ("q", "k_suffix", "v_suffix", "suffix_lens")})
+    assert util.route(B.make_tree_desc(B.RLDA_BF16, 8, 10, 2, 128, 400, 0.1, [(None, None, None, 8, 600), (None, None, None, 2, 450)])) == B.RLDA_ROUTE_UNIT
+    out, lse = B.rl_decode_attn_tree(t["q"], lv, t["k_suffix"], t["v_suffix"], t["suffix_lens"], 0.1)
+    ro, rl = ref.decode_attn_tree_ref(x["q"], x["levels"], x["k_suffix"], x["v_suffix"], x["suffix_lens"], 0.1)
+    same_with_infinities(out, lse, ro, rl, LEAN)
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
