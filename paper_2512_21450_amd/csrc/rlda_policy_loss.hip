@@ -289,6 +289,8 @@ constexpr int COUNT_MAX = 1024;
 // loss from Python, a launch / so: 512 prompts x 8 of 4096 tokens 52.7 / 50.5, of 1000 24.3 / 22.6, 200 x 16 of 3000 32.5 / 30.8; beyond
 // ONE_MAX the queue of workgroups pays for each: 350 x 16 of 2000 29.4 / 29.5, 512 x 16 of 700 29.5 / 29.4, of 80 27.9 / 28.6.
 // Few sequences, two or three launches / one or two: 8 20.5 / 18.2, 1024 21.9 / 19.3, 2048 24.9 / 22.2.
+// Captured, a launch / so: 17 x 3972 tokens 14.0 / 11.4, 1024 x 512 14.5 / 12.7, 4095 x 500 22.2 / 21.4, 4096 x 4096 58.4 / 55.2.  The line lies at what 64
+// groups hold, one to a lane.
 constexpr int ONE_MAX = GROUP * MAX_GROUPS;
 static_assert(COUNT_MAX <= ONE_MAX && 2 * GROUP - 1 <= rlda::MAX_ARRIVALS && MAX_GROUPS <= 64, "a counter, and a wavefront, hold no more");
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -300,6 +302,9 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
   __shared__ float shf[NT / 64][6];
   const int tid = threadIdx.x;
   long long n_tok, n_seq;
+  // This sequence's length, asked for with the batch's: behind them it is a round trip more (us, captured with the advantages, behind / with
+  // them: 8 x 8 x 290 tokens 9.1 / 8.85, 4000 x 700 22.0 / 21.6; the other way 848 x 87 12.8 / 13.2).
+  int own;
   if (COUNT) {
     __shared__ long long sh[2][NT / 64];
     static_assert(COUNT_MAX % NT == 0, "a thread's sequences");
@@ -308,6 +313,7 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
     int c = 0, n[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) n[k] = tid + k * NT < L.B ? L.lens[tid + k * NT] : 0;
+    own = L.lens[blockIdx.x];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       const int m = clamp_len(n[k], L.T);
@@ -319,13 +325,14 @@ __global__ void __launch_bounds__(NT) policy_loss_kernel(const LossParams L) {
     n_tok = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
     n_seq = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
   } else {
+    own = L.lens[blockIdx.x];
     n_tok = L.counts[0]; n_seq = L.counts[1];
   }
   const int b = blockIdx.x;
   const int met = min(b / GROUP, n_groups(L) - 1);        // the group it meets in
   uint64_t seen = 0;
   if (ONE && tid == 0) seen = rlda::claim(L.part + (size_t)met * GROUP * 4 + 3, L.call);
-  const unsigned len = clamp_len(L.lens[b], L.T);
+  const unsigned len = clamp_len(own, L.T);
   float w = 0.f;                                          // weight of one of this sequence's tokens in the aggregate
   if (len > 0) w = L.agg == RL_AGG_SEQ_MEAN ? (float)(1.0 / ((double)len * (double)n_seq)) : (float)(1.0 / (double)n_tok);
   const float A = L.adv[b];

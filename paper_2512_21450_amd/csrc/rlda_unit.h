@@ -706,7 +706,9 @@ struct Split { int splits, nw, min_tiles; };
 // With two workgroups to a unit (86 to 128 of them on 256 compute units) the saving is half of that and the memory is nearly busy: from
 // more tiles on only (128 units, one / two: fp32 512 keys 11.1 / 9.8, 384 8.1 / 8.1; bf16 of 128 columns 1024 11.8 / 12.5, 1088 11.1 /
 // 10.4, 2048 18.7 / 17.4; bf16 of 64 1024 8.2 / 9.1, 2112 10.6 / 9.5), and not where the sequences' own keys are most of a call in bf16
-// of 64 columns (64 + 2048 keys 13.6 / 15.2, half full 9.4 / 10.7; e4m3 12.9 / 12.3).  More than half as many units as compute units
+// of 64 columns (64 + 2048 keys 13.6 / 15.2, half full 9.4 / 10.7; e4m3 12.9 / 12.3).  Where buffers are far from full there may be next
+// to nothing in it (64 units of 1100 + up to 256 keys in four parts 13.8 / 13.6).  200 drawn calls of fp32 and 64 columns: 1.80 times as
+// fast full, 1.67 with lengths spread, the least 1.03 and 0.98.  More than half as many units as compute units
 // gain nothing (256 units of 1088 to 4000 keys: 2 to 15 % slower).  Nor do parts that no compute unit is free for: a die takes whole
 // (group, part) pairs, and where their number is no multiple of eight some would get a second round of workgroups (e4m3, 10 prompts of
 // 5 samples, 3888 + 2760 keys: five parts, 35 workgroups on a die, 27.4, four 20.8; bf16, 3000 + 2000 keys 27.7 / 20.3).
@@ -896,8 +898,10 @@ bool unit_pays(const Problem& pb, int pairs) {
 // Trees of several levels cost the other path more: 146 drawn ones 1.42 and 1.50, none below 0.99.
 // Units of hardly any key, which wait for nothing but their turn: 16384 x (16 + 16) 58 / 70, 65536 x (1 + 1)
 // 163 / 149.  Stores of up to 2048 suffix rows and 3600 in all, prefix rows counted three times, are always taken up to 16 384 tiles: the
-// other path is up to twice as slow there with many short units.  Longer units than 8960 keys were not measured.  Trees of several levels over stores of more than 2048 suffix rows stay on
-// the shared-prefix kernels, whatever is faster: a tree call has no algo field, and that is how a caller, and the tests, take it there.
+// other path is up to twice as slow there with many short units.  Units of more than 8960 keys stay over there: one launch is quicker
+// for a few of them only (1 of 12 000 keys 12.7 / 14.5, 8 of 9500 13.4 / 14.0, 32 of 10 240 19.9 / 19.9, 64 of 9500 27.5 / 23.5, 64 of
+// 18 000 42.5 / 27.7).  So do trees of several levels over stores of more than 2048 suffix rows, although 84 drawn ones would be 1.24 times
+// as fast in one launch: a tree call has no algo field, and this is how tests take it to the shared-prefix kernels.
 bool unit_preferred(const Problem& pb, int pairs) {
   const int64_t units = n_sequences(pb) * pb.Hkv, keys = shared_cap(pb) + pb.Ls_cap;
   const bool f8 = pb.dtype == RLDA_BF16_KV8, few = max_group(pb) * (pb.Hq / pb.Hkv) <= 16;
