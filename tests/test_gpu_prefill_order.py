@@ -1,8 +1,9 @@
-"""Prefill with more than a round of blocks, two per compute unit: every block of every prompt is computed once, whatever the order in which
-they are dealt out.  The cases are on either side of each line of the rule (on 256 compute units): eight units in groups of four XCDs from 1.5
-rounds on, 16 and 24 in pairs with a chunk of four and three from two rounds on, 32 and, with up to 32 blocks each, more of them in
-chunks where few heads share a KV head, with four of them up to some numbers of rounds, of 64 and of 128 rows to a workgroup, also a last chunk and a last round that are not full; against the fp64 oracle at the bar of the other prefill tests.  Capacities are far
-longer than the prompts: what is checked is the order, and the oracle's time goes with the lengths."""
+"""Prefill with more than a round of blocks, two per compute unit: every block of every prompt is computed once, whatever the order in
+which they are dealt out. The cases are on either side of each line of the rule (on 256 compute units): eight units in groups of four
+XCDs from 1.5 rounds on, 16 and 24 in pairs with a chunk of four and three from two rounds on, 32 and, with up to 32 blocks each, more
+of them in chunks where few heads share a KV head, with four of them up to some numbers of rounds, of 64 and of 128 rows to a
+workgroup, also a last chunk and a last round that are not full; against the fp64 oracle at the bar of the other prefill tests.
+Capacities are far longer than the prompts: what is checked is the order, and the oracle's time goes with the lengths."""
 import math
 
 import pytest
